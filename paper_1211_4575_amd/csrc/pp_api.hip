@@ -325,6 +325,7 @@ pp_status pp_init_species(pp_run* r, int32_t s, double q, double m, double w, co
     if (!parts->id) S.cur.id_alt = nullptr;
     S.sorted = false;
     S.ranked = false;
+    S.binned = false;
     // initial sort: the split form needs it before its first push
     hipError_t e = launch_sort(r, s);
     if (!ok(e, "sort")) return PP_E_HIP;
@@ -354,8 +355,13 @@ pp_status pp_gather_push_deposit(pp_run* r) {
             S.pending = false;
         }
     } else {
+        unsigned done = 0;
+        e = launch_gpd64_tiles(r, target, &done);
+        if (!ok(e, "gather_push_deposit")) return PP_E_HIP;
         for (int s = 0; s < PP_MAX_SPECIES; ++s) {
             if (!r->sp[s].active) continue;
+            r->sp[s].binned = false;  // the particles move: their bins are those of the last sort
+            if (done & (1u << s)) continue;
             e = launch_gpd64(r, s, target);
             if (!ok(e, "gather_push_deposit")) return PP_E_HIP;
         }

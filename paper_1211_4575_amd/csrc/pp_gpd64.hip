@@ -1,7 +1,10 @@
-// Plain FP64 form of steps 1-3 (Sec. III): one thread per particle, absolute FP64
-// positions, fields read straight from global memory, current added with global FP64
-// atomics.  It is the reference GPU form the tiled split-precision kernel is measured
-// against.
+// FP64 form of steps 1-3 (Sec. III): absolute FP64 positions and momenta.
+//
+// Two kernels.  k_gpd64_tile takes the particles as the sort left them, binned by cell: a
+// workgroup per tile of 64 cells with the tile's fields and current in LDS.  k_gpd64 takes them
+// in any order (pushed again without a sort), one thread per particle, fields read from and
+// current added to global memory; the tile kernel sends it the rare particle that does not lie
+// in its tile.
 #include "pp_device.hpp"
 #include "pp_internal.hpp"
 
@@ -28,18 +31,18 @@ struct Gpd64Args {
     double qw;        // q w (direct current)
 };
 
-template <int O>
+template <int O, int U>
 __device__ __forceinline__ double gather1(const double* __restrict__ F, const int* ix, const int* iy, const int* iz,
                                           const double* wx, const double* wy, const double* wz, int nx, int nxy) {
     double acc = 0.0;
-#pragma unroll
+#pragma unroll U
     for (int c = 0; c <= O; ++c) {
         double accy = 0.0;
-#pragma unroll
+#pragma unroll U
         for (int b = 0; b <= O; ++b) {
             const double* row = F + (int64_t)iz[c] * nxy + (int64_t)iy[b] * nx;
             double s = 0.0;
-#pragma unroll
+#pragma unroll U
             for (int a = 0; a <= O; ++a) s += row[ix[a]] * wx[a];
             accy += s * wy[b];
         }
@@ -48,10 +51,10 @@ __device__ __forceinline__ double gather1(const double* __restrict__ F, const in
     return acc;
 }
 
-template <int O>
-__global__ void __launch_bounds__(256) k_gpd64(Gpd64Args A) {
-    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= A.np) return;
+// One particle anywhere in the box (and, as before it is wrapped, a period or more outside).  U
+// unrolls the loops over nodes: O + 2 all of them, 1 none (few registers, for a rare path).
+template <int O, int U>
+__device__ __forceinline__ void gpd64_particle(const Gpd64Args& A, int64_t p) {
     const int nx = A.n[0], ny = A.n[1], nz = A.n[2];
     const int nxy = nx * ny;
     const int64_t nc = A.ncell;
@@ -62,12 +65,12 @@ __global__ void __launch_bounds__(256) k_gpd64(Gpd64Args A) {
     // weights: centred (nodes at integers) and staggered (nodes at i + 1/2) per axis
     double wc[3][O + 1], ws[3][O + 1];
     int ic0[3][O + 1], is0[3][O + 1];
-#pragma unroll
+#pragma unroll U
     for (int d = 0; d < 3; ++d) {
         const int nd = A.n[d];
         int c0 = weights_abs<O>(X0[d], wc[d]);
         int s0 = weights_abs<O>(X0[d] - 0.5, ws[d]);
-#pragma unroll
+#pragma unroll U
         for (int a = 0; a <= O; ++a) {
             ic0[d][a] = wrap(c0 + a, nd);
             is0[d][a] = wrap(s0 + a, nd);
@@ -75,13 +78,267 @@ __global__ void __launch_bounds__(256) k_gpd64(Gpd64Args A) {
     }
     // eq. "pfields": E_x staggered along x, B_x staggered along y and z, cyclic
     V3<double> E, B;
-    E.x = gather1<O>(A.E, is0[0], ic0[1], ic0[2], ws[0], wc[1], wc[2], nx, nxy);
-    E.y = gather1<O>(A.E + nc, ic0[0], is0[1], ic0[2], wc[0], ws[1], wc[2], nx, nxy);
-    E.z = gather1<O>(A.E + 2 * nc, ic0[0], ic0[1], is0[2], wc[0], wc[1], ws[2], nx, nxy);
-    B.x = gather1<O>(A.B, ic0[0], is0[1], is0[2], wc[0], ws[1], ws[2], nx, nxy);
-    B.y = gather1<O>(A.B + nc, is0[0], ic0[1], is0[2], ws[0], wc[1], ws[2], nx, nxy);
-    B.z = gather1<O>(A.B + 2 * nc, is0[0], is0[1], ic0[2], ws[0], ws[1], wc[2], nx, nxy);
+    E.x = gather1<O, U>(A.E, is0[0], ic0[1], ic0[2], ws[0], wc[1], wc[2], nx, nxy);
+    E.y = gather1<O, U>(A.E + nc, ic0[0], is0[1], ic0[2], wc[0], ws[1], wc[2], nx, nxy);
+    E.z = gather1<O, U>(A.E + 2 * nc, ic0[0], ic0[1], is0[2], wc[0], wc[1], ws[2], nx, nxy);
+    B.x = gather1<O, U>(A.B, ic0[0], is0[1], is0[2], wc[0], ws[1], ws[2], nx, nxy);
+    B.y = gather1<O, U>(A.B + nc, is0[0], ic0[1], is0[2], ws[0], wc[1], ws[2], nx, nxy);
+    B.z = gather1<O, U>(A.B + 2 * nc, is0[0], is0[1], ic0[2], ws[0], ws[1], wc[2], nx, nxy);
 
+    const V3<double> um = u;
+    if (A.pusher == PP_PUSH_BORIS)
+        push_boris<double>(A.h, A.ic, E, B, u);
+    else
+        push_vay<double>(A.h, A.ic, E, B, u);
+    if (A.krad != 0.0) rad_cool<double>(A.krad, A.dtk, A.ic, um, u);
+
+    const double g = sqrt(1.0 + dot(u, u) * A.ic * A.ic);
+    const double uu[3] = {u.x, u.y, u.z};
+    double X1[3];
+    int bad = 0;
+#pragma unroll U
+    for (int d = 0; d < 3; ++d) {
+        X1[d] = X0[d] + A.dt * uu[d] / (g * A.d[d]);
+        if (fabs(X1[d] - X0[d]) >= 1.0) bad |= PP_FLAG_CFL;
+        if (!isfinite(X1[d]) || !isfinite(uu[d])) bad |= PP_FLAG_NONFINITE;
+    }
+    if (bad) {
+        atomic_or_flag(A.flags, bad);
+        return;
+    }
+
+    if (A.direct) {
+        // direct current (eq. "jj2"): q w v_c W at J_c's staggered nodes, at the time-centred
+        // position, with the gather's weights
+        double Xm[3], wmc[3][O + 1], wms[3][O + 1];
+        int imc[3][O + 1], ims[3][O + 1];
+#pragma unroll U
+        for (int d = 0; d < 3; ++d) {
+            Xm[d] = 0.5 * (X0[d] + X1[d]);
+            const int c0 = weights_abs<O>(Xm[d], wmc[d]);
+            const int s0 = weights_abs<O>(Xm[d] - 0.5, wms[d]);
+#pragma unroll U
+            for (int a = 0; a <= O; ++a) {
+                imc[d][a] = wrap(c0 + a, A.n[d]);
+                ims[d][a] = wrap(s0 + a, A.n[d]);
+            }
+        }
+#pragma unroll U
+        for (int comp = 0; comp < 3; ++comp) {
+            const double vq = A.qw * uu[comp] / g;
+            double* Jc = A.J + comp * nc;
+#pragma unroll U
+            for (int c = 0; c <= O; ++c) {
+                const int k = comp == 2 ? ims[2][c] : imc[2][c];
+                const double wz = comp == 2 ? wms[2][c] : wmc[2][c];
+#pragma unroll U
+                for (int b = 0; b <= O; ++b) {
+                    const int j = comp == 1 ? ims[1][b] : imc[1][b];
+                    const double wzy = vq * wz * (comp == 1 ? wms[1][b] : wmc[1][b]);
+#pragma unroll U
+                    for (int a = 0; a <= O; ++a) {
+                        const int i = comp == 0 ? ims[0][a] : imc[0][a];
+                        const double v = wzy * (comp == 0 ? wms[0][a] : wmc[0][a]);
+                        if (v != 0.0) atomic_add_f64(Jc + (int64_t)i + (int64_t)nx * (j + (int64_t)ny * k), v);
+                    }
+                }
+            }
+        }
+    } else {
+    // Esirkepov current (Sec. III.C) on the common window of O+2 centred nodes per axis
+    double S0[3][O + 2], DS[3][O + 2];
+    int base[3];
+#pragma unroll U
+    for (int d = 0; d < 3; ++d) {
+        double w0[O + 1], w1[O + 1];
+        int a0 = weights_abs<O>(X0[d], w0);
+        int a1 = weights_abs<O>(X1[d], w1);
+        int b = a0 < a1 ? a0 : a1;
+        base[d] = b;
+        int o0 = a0 - b, o1 = a1 - b;  // 0 or 1
+#pragma unroll U
+        for (int k = 0; k < O + 2; ++k) {
+            int k0 = k - o0, k1 = k - o1;
+            double s0 = (k0 >= 0 && k0 <= O) ? w0[k0 < 0 ? 0 : (k0 > O ? O : k0)] : 0.0;
+            double s1 = (k1 >= 0 && k1 <= O) ? w1[k1 < 0 ? 0 : (k1 > O ? O : k1)] : 0.0;
+            S0[d][k] = s0;
+            DS[d][k] = s1 - s0;
+        }
+    }
+    int idx[3][O + 2];
+#pragma unroll U
+    for (int d = 0; d < 3; ++d)
+#pragma unroll U
+        for (int k = 0; k < O + 2; ++k) idx[d][k] = wrap(base[d] + k, A.n[d]);
+
+#pragma unroll U
+    for (int comp = 0; comp < 3; ++comp) {
+        const int d1 = comp == 0 ? 1 : (comp == 1 ? 2 : 0);
+        const int d2 = comp == 0 ? 2 : (comp == 1 ? 0 : 1);
+        double* Jc = A.J + comp * nc;
+        const int strides[3] = {1, nx, nxy};
+#pragma unroll U
+        for (int b = 0; b < O + 2; ++b) {
+#pragma unroll U
+            for (int e = 0; e < O + 2; ++e) {
+                double F = S0[d1][b] * S0[d2][e] + 0.5 * DS[d1][b] * S0[d2][e] + 0.5 * S0[d1][b] * DS[d2][e] +
+                           DS[d1][b] * DS[d2][e] * (1.0 / 3.0);
+                if (F == 0.0) continue;
+                int64_t off = (int64_t)idx[d1][b] * strides[d1] + (int64_t)idx[d2][e] * strides[d2];
+                double acc = 0.0;
+#pragma unroll U
+                for (int a = 0; a <= O; ++a) {  // the last prefix (a = O+1) vanishes
+                    acc += DS[comp][a] * F;
+                    double v = A.fac[comp] * acc;
+                    if (v != 0.0) atomic_add_f64(Jc + off + (int64_t)idx[comp][a] * strides[comp], v);
+                }
+            }
+        }
+    }
+    }
+    (void)ny;
+    (void)nz;
+
+#pragma unroll U
+    for (int d = 0; d < 3; ++d) {
+        double x = X1[d];
+        const double nd = (double)A.n[d];
+        if (x < 0.0) x += nd;
+        if (x >= nd) x -= nd;
+        A.pos[d][p] = x;
+    }
+    A.u[0][p] = u.x;
+    A.u[1][p] = u.y;
+    A.u[2][p] = u.z;
+}
+
+template <int O>
+__global__ void __launch_bounds__(256) k_gpd64(Gpd64Args A) {
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (p < A.np) gpd64_particle<O, O + 2>(A, p);
+}
+
+// ---- tiled form ------------------------------------------------------------------------
+// A particle of cell c has X in [c - 1/2, c + 1/2): its centred and staggered supports start at
+// c - 2 or later and end at c + 2 (cubic) or c + 1 (quadratic); a step of less than a cell widens
+// the current's window by one node each way.
+constexpr int F64_LO = 2;
+constexpr int f64_hi(int O) { return O - 1; }
+constexpr int GPD64_BS = 256;
+
+struct Gpd64TileArgs {
+    int t[3], nt[3];
+    int64_t ntiles;
+    int per_xcd;
+    int parts;  // workgroups sharing a tile's particles
+    int nsp;
+    const int32_t* bins[PP_MAX_SPECIES];  // cell-bin starts of the sort (64 per tile)
+    Gpd64Args sp[PP_MAX_SPECIES];
+};
+
+// LDS extents and strides of a tile: compile-time for 4x4x4 and 8x8x1, runtime otherwise.  An
+// axis of one cell is collapsed (extent 1, stride 0: every node of it is the same).  Rows of the
+// current are padded so that the 16 lanes served together, one per cell of a 4x4 layer (or of two
+// rows of 8), fall on 16 different pairs of banks.
+template <int O, int TX, int TY, int TZ>
+struct Tile64CT {
+    static constexpr bool cz = TZ == 1;
+    static constexpr int fex = TX + F64_LO + f64_hi(O), fey = TY + F64_LO + f64_hi(O);
+    static constexpr int fez = cz ? 1 : TZ + F64_LO + f64_hi(O);
+    static constexpr int cex = TX + F64_LO + f64_hi(O) + 2, cey = TY + F64_LO + f64_hi(O) + 2;
+    static constexpr int cez = cz ? 1 : TZ + F64_LO + f64_hi(O) + 2;
+    static constexpr int fsx = 1, fsy = fex, fsz = cz ? 0 : fex * fey;
+    static constexpr int csx = 1, csy = cz ? 24 : 12, csz = cz ? 0 : csy * cey;
+    static constexpr int fvol = fex * fey * fez, cvol = csy * cey * cez;
+    static constexpr int frow = fex, fplane = fex * fey, crow = csy, cplane = csy * cey;
+    static_assert(csy >= cex, "current row padding");
+    __device__ Tile64CT(const Gpd64TileArgs&) {}
+};
+
+template <int O>
+struct Tile64RT {
+    int fex, fey, fez, cex, cey, cez, fsx, fsy, fsz, csx, csy, csz, fvol, cvol, frow, fplane, crow, cplane;
+    __device__ Tile64RT(const Gpd64TileArgs& A) {
+        const int* n = A.sp[0].n;
+        const int grow = F64_LO + f64_hi(O);
+        fex = n[0] == 1 ? 1 : A.t[0] + grow;
+        fey = n[1] == 1 ? 1 : A.t[1] + grow;
+        fez = n[2] == 1 ? 1 : A.t[2] + grow;
+        cex = n[0] == 1 ? 1 : A.t[0] + grow + 2;
+        cey = n[1] == 1 ? 1 : A.t[1] + grow + 2;
+        cez = n[2] == 1 ? 1 : A.t[2] + grow + 2;
+        frow = fex;
+        fplane = fex * fey;
+        crow = cex;
+        cplane = cex * cey;
+        fsx = n[0] == 1 ? 0 : 1;
+        csx = fsx;
+        fsy = n[1] == 1 ? 0 : frow;
+        csy = n[1] == 1 ? 0 : crow;
+        fsz = n[2] == 1 ? 0 : fplane;
+        csz = n[2] == 1 ? 0 : cplane;
+        fvol = fplane * fez;
+        cvol = cplane * cez;
+    }
+};
+
+template <int O, class TL>
+__device__ __forceinline__ double gather64(const double* F, const TL& L, int bx, int by, int bz, const double* wx,
+                                           const double* wy, const double* wz) {
+    const double* base = F + bx * L.fsx + by * L.fsy + bz * L.fsz;
+    double acc = 0.0;
+#pragma unroll
+    for (int c = 0; c <= O; ++c) {
+        double accy = 0.0;
+#pragma unroll
+        for (int b = 0; b <= O; ++b) {
+            double s = 0.0;
+#pragma unroll
+            for (int a = 0; a <= O; ++a) s += base[c * L.fsz + b * L.fsy + a * L.fsx] * wx[a];
+            accy += s * wy[b];
+        }
+        acc += accy * wz[c];
+    }
+    return acc;
+}
+
+__device__ __forceinline__ void lds_add_f64(double* p, double v) {
+    __hip_atomic_fetch_add((__attribute__((address_space(3))) double*)p, v, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Steps 1-3 of particle p of the tile whose first cell is org; false when a support of it leaves
+// the tile's block (nothing done then).
+template <int O, class TL>
+__device__ __forceinline__ bool gpd64_in_tile(const Gpd64Args& A, const TL& L, const int org[3], const int t[3],
+                                              const double* fld, double* cur, int64_t p) {
+    double X0[3] = {A.pos[0][p], A.pos[1][p], A.pos[2][p]};
+    V3<double> u{A.u[0][p], A.u[1][p], A.u[2][p]};
+    const int fe[3] = {L.fex, L.fey, L.fez};
+    int org_p[3];  // the tile's first cell in the particle's period
+    V3<double> E, B;
+    {
+        double wc[3][O + 1], ws[3][O + 1];
+        int fc[3], fs[3];
+        bool inside = true;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const int v = (int)floor(X0[d] + 0.5) - org[d];
+            org_p[d] = org[d] + (v >= t[d] ? A.n[d] : (v < 0 ? -A.n[d] : 0));
+            fc[d] = weights_abs<O>(X0[d], wc[d]) - org_p[d] + F64_LO;
+            fs[d] = weights_abs<O>(X0[d] - 0.5, ws[d]) - org_p[d] + F64_LO;
+            if (A.n[d] > 1)
+                inside = inside && fc[d] >= 0 && fs[d] >= 0 && fc[d] + O < fe[d] && fs[d] + O < fe[d];
+        }
+        if (!inside) return false;
+        // eq. "pfields"
+        E.x = gather64<O>(fld + 0 * L.fvol, L, fs[0], fc[1], fc[2], ws[0], wc[1], wc[2]);
+        E.y = gather64<O>(fld + 1 * L.fvol, L, fc[0], fs[1], fc[2], wc[0], ws[1], wc[2]);
+        E.z = gather64<O>(fld + 2 * L.fvol, L, fc[0], fc[1], fs[2], wc[0], wc[1], ws[2]);
+        B.x = gather64<O>(fld + 3 * L.fvol, L, fc[0], fs[1], fs[2], wc[0], ws[1], ws[2]);
+        B.y = gather64<O>(fld + 4 * L.fvol, L, fs[0], fc[1], fs[2], ws[0], wc[1], ws[2]);
+        B.z = gather64<O>(fld + 5 * L.fvol, L, fs[0], fs[1], fc[2], ws[0], ws[1], wc[2]);
+    }
     const V3<double> um = u;
     if (A.pusher == PP_PUSH_BORIS)
         push_boris<double>(A.h, A.ic, E, B, u);
@@ -101,101 +358,88 @@ __global__ void __launch_bounds__(256) k_gpd64(Gpd64Args A) {
     }
     if (bad) {
         atomic_or_flag(A.flags, bad);
-        return;
+        return true;
     }
 
+    const int cst[3] = {L.csx, L.csy, L.csz};
     if (A.direct) {
-        // direct current (eq. "jj2"): q w v_c W at J_c's staggered nodes, at the time-centred
-        // position, with the gather's weights
-        double Xm[3], wmc[3][O + 1], wms[3][O + 1];
-        int imc[3][O + 1], ims[3][O + 1];
+        // direct current (eq. "jj2") at the time-centred position
+        double wmc[3][O + 1], wms[3][O + 1];
+        int bc[3], bs[3];
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
-            Xm[d] = 0.5 * (X0[d] + X1[d]);
-            const int c0 = weights_abs<O>(Xm[d], wmc[d]);
-            const int s0 = weights_abs<O>(Xm[d] - 0.5, wms[d]);
-#pragma unroll
-            for (int a = 0; a <= O; ++a) {
-                imc[d][a] = wrap(c0 + a, A.n[d]);
-                ims[d][a] = wrap(s0 + a, A.n[d]);
-            }
+            const double Xm = 0.5 * (X0[d] + X1[d]);
+            bc[d] = (weights_abs<O>(Xm, wmc[d]) - org_p[d] + F64_LO + 1) * cst[d];
+            bs[d] = (weights_abs<O>(Xm - 0.5, wms[d]) - org_p[d] + F64_LO + 1) * cst[d];
         }
 #pragma unroll
         for (int comp = 0; comp < 3; ++comp) {
             const double vq = A.qw * uu[comp] / g;
-            double* Jc = A.J + comp * nc;
+            double* Jc = cur + comp * L.cvol + (comp == 0 ? bs[0] : bc[0]) + (comp == 1 ? bs[1] : bc[1]) +
+                         (comp == 2 ? bs[2] : bc[2]);
+            const double* wx = comp == 0 ? wms[0] : wmc[0];
+            const double* wy = comp == 1 ? wms[1] : wmc[1];
+            const double* wz = comp == 2 ? wms[2] : wmc[2];
 #pragma unroll
-            for (int c = 0; c <= O; ++c) {
-                const int k = comp == 2 ? ims[2][c] : imc[2][c];
-                const double wz = comp == 2 ? wms[2][c] : wmc[2][c];
+            for (int c = 0; c <= O; ++c)
 #pragma unroll
                 for (int b = 0; b <= O; ++b) {
-                    const int j = comp == 1 ? ims[1][b] : imc[1][b];
-                    const double wzy = vq * wz * (comp == 1 ? wms[1][b] : wmc[1][b]);
+                    const double wzy = vq * wz[c] * wy[b];
+#pragma unroll
+                    for (int a = 0; a <= O; ++a) lds_add_f64(Jc + c * cst[2] + b * cst[1] + a * cst[0], wzy * wx[a]);
+                }
+        }
+    } else {
+        // Esirkepov current (Sec. III.C) on the common window of O + 2 centred nodes per axis;
+        // along an axis where the old and new supports coincide its last node carries nothing
+        double S0[3][O + 2], DS[3][O + 2];
+        int off0 = 0;
+        bool moved[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            double w0[O + 1], w1[O + 1];
+            const int a0 = weights_abs<O>(X0[d], w0), a1 = weights_abs<O>(X1[d], w1);
+            const bool lo1 = a1 < a0, hi1 = a1 > a0;
+#pragma unroll
+            for (int k = 0; k < O + 2; ++k) {
+                const double s0 = lo1 ? (k >= 1 ? w0[k >= 1 ? k - 1 : 0] : 0.0) : (k <= O ? w0[k <= O ? k : O] : 0.0);
+                const double s1 = hi1 ? (k >= 1 ? w1[k >= 1 ? k - 1 : 0] : 0.0) : (k <= O ? w1[k <= O ? k : O] : 0.0);
+                S0[d][k] = s0;
+                DS[d][k] = s1 - s0;
+            }
+            moved[d] = lo1 || hi1;
+            off0 += ((lo1 ? a1 : a0) - org_p[d] + F64_LO + 1) * cst[d];
+        }
+#pragma unroll
+        for (int comp = 0; comp < 3; ++comp) {
+            const int d1 = comp == 0 ? 1 : (comp == 1 ? 2 : 0);
+            const int d2 = comp == 0 ? 2 : (comp == 1 ? 0 : 1);
+            double* Jc = cur + comp * L.cvol + off0;
+            double P[O + 1];  // prefix sums along the component's axis (the last, a = O + 1, vanishes)
+            double acc = 0.0;
+#pragma unroll
+            for (int a = 0; a <= O; ++a) {
+                acc += DS[comp][a];
+                P[a] = acc * A.fac[comp];
+            }
+#pragma unroll
+            for (int b = 0; b < O + 2; ++b) {
+                if (b == O + 1 && !moved[d1]) continue;
+#pragma unroll
+                for (int e = 0; e < O + 2; ++e) {
+                    if (e == O + 1 && !moved[d2]) continue;
+                    const double F = S0[d1][b] * (S0[d2][e] + 0.5 * DS[d2][e]) +
+                                     DS[d1][b] * (0.5 * S0[d2][e] + DS[d2][e] * (1.0 / 3.0));
+                    double* Jn = Jc + b * cst[d1] + e * cst[d2];
 #pragma unroll
                     for (int a = 0; a <= O; ++a) {
-                        const int i = comp == 0 ? ims[0][a] : imc[0][a];
-                        const double v = wzy * (comp == 0 ? wms[0][a] : wmc[0][a]);
-                        if (v != 0.0) atomic_add_f64(Jc + (int64_t)i + (int64_t)nx * (j + (int64_t)ny * k), v);
+                        if (a == O && !moved[comp]) continue;
+                        lds_add_f64(Jn + a * cst[comp], P[a] * F);
                     }
                 }
             }
         }
-    } else {
-    // Esirkepov current (Sec. III.C) on the common window of O+2 centred nodes per axis
-    double S0[3][O + 2], DS[3][O + 2];
-    int base[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        double w0[O + 1], w1[O + 1];
-        int a0 = weights_abs<O>(X0[d], w0);
-        int a1 = weights_abs<O>(X1[d], w1);
-        int b = a0 < a1 ? a0 : a1;
-        base[d] = b;
-        int o0 = a0 - b, o1 = a1 - b;  // 0 or 1
-#pragma unroll
-        for (int k = 0; k < O + 2; ++k) {
-            int k0 = k - o0, k1 = k - o1;
-            double s0 = (k0 >= 0 && k0 <= O) ? w0[k0 < 0 ? 0 : (k0 > O ? O : k0)] : 0.0;
-            double s1 = (k1 >= 0 && k1 <= O) ? w1[k1 < 0 ? 0 : (k1 > O ? O : k1)] : 0.0;
-            S0[d][k] = s0;
-            DS[d][k] = s1 - s0;
-        }
     }
-    int idx[3][O + 2];
-#pragma unroll
-    for (int d = 0; d < 3; ++d)
-#pragma unroll
-        for (int k = 0; k < O + 2; ++k) idx[d][k] = wrap(base[d] + k, A.n[d]);
-
-#pragma unroll
-    for (int comp = 0; comp < 3; ++comp) {
-        const int d1 = comp == 0 ? 1 : (comp == 1 ? 2 : 0);
-        const int d2 = comp == 0 ? 2 : (comp == 1 ? 0 : 1);
-        double* Jc = A.J + comp * nc;
-        const int strides[3] = {1, nx, nxy};
-#pragma unroll
-        for (int b = 0; b < O + 2; ++b) {
-#pragma unroll
-            for (int e = 0; e < O + 2; ++e) {
-                double F = S0[d1][b] * S0[d2][e] + 0.5 * DS[d1][b] * S0[d2][e] + 0.5 * S0[d1][b] * DS[d2][e] +
-                           DS[d1][b] * DS[d2][e] * (1.0 / 3.0);
-                if (F == 0.0) continue;
-                int64_t off = (int64_t)idx[d1][b] * strides[d1] + (int64_t)idx[d2][e] * strides[d2];
-                double acc = 0.0;
-#pragma unroll
-                for (int a = 0; a <= O; ++a) {  // the last prefix (a = O+1) vanishes
-                    acc += DS[comp][a] * F;
-                    double v = A.fac[comp] * acc;
-                    if (v != 0.0) atomic_add_f64(Jc + off + (int64_t)idx[comp][a] * strides[comp], v);
-                }
-            }
-        }
-    }
-    }
-    (void)ny;
-    (void)nz;
-
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         double x = X1[d];
@@ -207,12 +451,76 @@ __global__ void __launch_bounds__(256) k_gpd64(Gpd64Args A) {
     A.u[0][p] = u.x;
     A.u[1][p] = u.y;
     A.u[2][p] = u.z;
+    return true;
 }
 
-hipError_t launch_gpd64(pp_run* r, int s, double* J) {
+// What bounds it: the LDS, 384 reads of 8 bytes for the cubic gather and up to 300 additions of
+// 8 bytes per particle (ds_add_f64 runs at 9 clocks per wavefront where the 64 lanes' addresses
+// differ and at 193 where they coincide), against 300 global FP64 atomics of the untiled kernel.
+// 1.05e6 particles of a 64x16x16 two-stream box, cubic: 0.275 ms against 8.70; 9.9e5 of a 45x38x29
+// pair plasma: 0.383 against 6.67; 6.6e4 of a 16^3 box, quadratic: 0.045 against 0.252.
+// A workgroup takes the particles of one tile (a part of them where the box has few tiles).
+// They lie in cell order, so lane l of a wavefront walks the l-th 64th of them: the 64 lanes
+// then sit in different cells, mostly one each, and their LDS additions fall on different
+// addresses; the four wavefronts take neighbouring particles of each lane's range and share its
+// cache lines.
+template <int O, class TL>
+__global__ void __launch_bounds__(GPD64_BS, 3) k_gpd64_tile(Gpd64TileArgs A) {
+    extern __shared__ __align__(16) double lds64[];
+    const TL L(A);
+    const int64_t tile = (blockIdx.x & 7) * (int64_t)A.per_xcd + (blockIdx.x >> 3);
+    if (tile >= A.ntiles) return;
+    const int part = blockIdx.y;
+    int any = 0;
+    for (int s = 0; s < A.nsp; ++s) any |= A.bins[s][(tile + 1) * TILE_CELLS] - A.bins[s][tile * TILE_CELLS];
+    if (any == 0) return;
+    const Gpd64Args& G = A.sp[0];
+    const int org[3] = {(int)(tile % A.nt[0]) * A.t[0], (int)((tile / A.nt[0]) % A.nt[1]) * A.t[1],
+                        (int)(tile / ((int64_t)A.nt[0] * A.nt[1])) * A.t[2]};
+    double* fld = lds64;
+    double* cur = lds64 + 6 * L.fvol;
+    for (int q = threadIdx.x; q < 3 * L.cvol; q += GPD64_BS) cur[q] = 0.0;
+    for (int q = threadIdx.x; q < L.fvol; q += GPD64_BS) {
+        const int c = q / L.fplane, r = q - c * L.fplane, b = r / L.frow, a = r - b * L.frow;
+        const int i = G.n[0] == 1 ? 0 : wrap_near(org[0] - F64_LO + a, G.n[0]);
+        const int j = G.n[1] == 1 ? 0 : wrap_near(org[1] - F64_LO + b, G.n[1]);
+        const int k = G.n[2] == 1 ? 0 : wrap_near(org[2] - F64_LO + c, G.n[2]);
+        const int64_t g = (int64_t)i + (int64_t)G.n[0] * (j + (int64_t)G.n[1] * k);
+        double v[6];
+#pragma unroll
+        for (int comp = 0; comp < 3; ++comp) {
+            v[comp] = G.E[comp * G.ncell + g];
+            v[comp + 3] = G.B[comp * G.ncell + g];
+        }
+#pragma unroll
+        for (int comp = 0; comp < 6; ++comp) fld[comp * L.fvol + q] = v[comp];
+    }
+    __syncthreads();
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int s = 0; s < A.nsp; ++s) {
+        const int32_t start = A.bins[s][tile * TILE_CELLS], end = A.bins[s][(tile + 1) * TILE_CELLS];
+        const int32_t per = (end - start + 63) / 64;
+        for (int32_t r = 4 * part + wave; r < per; r += 4 * A.parts) {
+            const int64_t p = start + (int64_t)lane * per + r;
+            if (p >= end) continue;
+            if (!gpd64_in_tile<O, TL>(A.sp[s], L, org, A.t, fld, cur, p)) gpd64_particle<O, 1>(A.sp[s], p);
+        }
+    }
+    __syncthreads();
+    for (int q = threadIdx.x; q < 3 * L.cvol; q += GPD64_BS) {
+        const double v = cur[q];
+        if (v == 0.0) continue;
+        const int comp = q / L.cvol, r0 = q - comp * L.cvol;
+        const int c = r0 / L.cplane, r = r0 - c * L.cplane, b = r / L.crow, a = r - b * L.crow;
+        const int i = G.n[0] == 1 ? 0 : wrap_near(org[0] - F64_LO - 1 + a, G.n[0]);
+        const int j = G.n[1] == 1 ? 0 : wrap_near(org[1] - F64_LO - 1 + b, G.n[1]);
+        const int k = G.n[2] == 1 ? 0 : wrap_near(org[2] - F64_LO - 1 + c, G.n[2]);
+        atomic_add_f64(G.J + comp * G.ncell + (int64_t)i + (int64_t)G.n[0] * (j + (int64_t)G.n[1] * k), v);
+    }
+}
+
+static void gpd64_args(const pp_run* r, int s, double* J, Gpd64Args& A) {
     const Species& S = r->sp[s];
-    if (S.n == 0) return hipSuccess;
-    Gpd64Args A;
     for (int d = 0; d < 3; ++d) {
         A.n[d] = r->p.n[d];
         A.d[d] = r->p.d[d];
@@ -234,6 +542,13 @@ hipError_t launch_gpd64(pp_run* r, int s, double* J) {
     A.pusher = r->p.pusher;
     A.direct = r->p.current_scheme == PP_CURRENT_DIRECT ? 1 : 0;
     A.qw = S.q * S.w;
+}
+
+hipError_t launch_gpd64(pp_run* r, int s, double* J) {
+    const Species& S = r->sp[s];
+    if (S.n == 0) return hipSuccess;
+    Gpd64Args A;
+    gpd64_args(r, s, J, A);
     const int bs = 256;
     const int64_t nb = (S.n + bs - 1) / bs;
     if (r->p.shape_order == 2)
@@ -241,6 +556,68 @@ hipError_t launch_gpd64(pp_run* r, int s, double* J) {
     else
         hipLaunchKernelGGL(k_gpd64<3>, dim3((unsigned)nb), dim3(bs), 0, r->stream, A);
     return hipGetLastError();
+}
+
+template <int O, class TL>
+static void launch_tile(const Gpd64TileArgs& A, size_t lds, hipStream_t st) {
+    hipLaunchKernelGGL((k_gpd64_tile<O, TL>), dim3((unsigned)(8 * A.per_xcd), (unsigned)A.parts), dim3(GPD64_BS), lds, st,
+                       A);
+}
+
+// LDS bytes of a tile of the runtime-shaped kernel.
+static size_t runtime_tile_lds(const pp_run* r) {
+    size_t fv = 1, cv = 1;
+    for (int d = 0; d < 3; ++d) {
+        const int grow = F64_LO + f64_hi(r->p.shape_order);
+        fv *= r->p.n[d] == 1 ? 1 : r->g.t[d] + grow;
+        cv *= r->p.n[d] == 1 ? 1 : r->g.t[d] + grow + 2;
+    }
+    return (6 * fv + 3 * cv) * sizeof(double);
+}
+
+template <int O>
+static hipError_t launch_tiles(pp_run* r, const Gpd64TileArgs& A) {
+    const int* n = r->p.n;
+    const int* t = A.t;
+    if (n[0] > 1 && n[1] > 1 && n[2] > 1 && t[0] == 4 && t[1] == 4 && t[2] == 4) {
+        using TL = Tile64CT<O, 4, 4, 4>;
+        launch_tile<O, TL>(A, (6 * TL::fvol + 3 * TL::cvol) * sizeof(double), r->stream);
+    } else if (n[0] > 1 && n[1] > 1 && n[2] == 1 && t[0] == 8 && t[1] == 8 && t[2] == 1) {
+        using TL = Tile64CT<O, 8, 8, 1>;
+        launch_tile<O, TL>(A, (6 * TL::fvol + 3 * TL::cvol) * sizeof(double), r->stream);
+    } else {
+        launch_tile<O, Tile64RT<O>>(A, runtime_tile_lds(r), r->stream);
+    }
+    return hipGetLastError();
+}
+
+// All species whose particles lie as the sort left them, in one launch; *done has a bit for each
+// (the others take launch_gpd64).
+hipError_t launch_gpd64_tiles(pp_run* r, double* J, unsigned* done) {
+    Gpd64TileArgs A{};
+    *done = 0;
+    if (runtime_tile_lds(r) > 65536) return hipSuccess;  // thin tiles with a halo past the default LDS limit
+    int64_t np = 0;
+    for (int s = 0; s < PP_MAX_SPECIES; ++s) {
+        const Species& S = r->sp[s];
+        if (!S.active || !S.binned || S.n == 0) continue;
+        A.bins[A.nsp] = S.offsets;
+        gpd64_args(r, s, J, A.sp[A.nsp++]);
+        *done |= 1u << s;
+        np += S.n;
+    }
+    if (A.nsp == 0) return hipSuccess;
+    for (int d = 0; d < 3; ++d) {
+        A.t[d] = r->g.t[d];
+        A.nt[d] = r->g.nt[d];
+    }
+    A.ntiles = r->g.ntiles;
+    A.per_xcd = (int)((A.ntiles + 7) / 8);
+    // few tiles leave most of the 256 CUs idle: share a tile's particles among workgroups, as
+    // long as each of its wavefronts has particles of its own
+    A.parts = 1;
+    while (A.parts < 8 && A.ntiles * A.parts < 512 && np > A.ntiles * A.parts * 2 * GPD64_BS) A.parts *= 2;
+    return r->p.shape_order == 2 ? launch_tiles<2>(r, A) : launch_tiles<3>(r, A);
 }
 
 }  // namespace pp

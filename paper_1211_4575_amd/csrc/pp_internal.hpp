@@ -41,6 +41,7 @@ struct Species {
     // FP64 form: nbins + 1 cell-bin starts.  Split form: ntiles + 1 tile starts of the
     // tile order of pp_sort.hip (valid when sorted).
     int32_t* offsets = nullptr;
+    bool binned = false;  // FP64 form: sorted and not pushed since (offsets are the bins of the positions)
     // split form, filled by the particle kernel for the next sort: particles per cell of the
     // new positions (ncell, zero between steps), each particle's rank among the particles of
     // its new cell (n; -1 for a particle found outside its tile), the next tile starts
@@ -167,7 +168,9 @@ inline bool ok(hipError_t e, const char* where) {
 }
 
 // kernels launchers (defined in the kernel translation units)
-hipError_t launch_gpd64(pp_run* r, int s, double* J);
+hipError_t launch_gpd64(pp_run* r, int s, double* J);  // particles of one species in any order
+// every species whose particles lie binned by cell, by tiles; *done has a bit for each of them
+hipError_t launch_gpd64_tiles(pp_run* r, double* J, unsigned* done);
 hipError_t launch_gpd32(pp_run* r, double* J);
 hipError_t launch_line_solve(pp_run* r, const double* J2, double* J);
 hipError_t launch_field_step(pp_run* r);

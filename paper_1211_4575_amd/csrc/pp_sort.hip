@@ -953,6 +953,7 @@ static hipError_t sort_species(pp_run* r, int s) {
     }
     S.sorted = true;
     S.ranked = false;
+    S.binned = !split;
     return hipGetLastError();
 }
 

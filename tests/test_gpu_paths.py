@@ -1,0 +1,58 @@
+"""Paths of the library that take the same call by different kernels, against each other and the
+oracle, at the sizes where they can differ."""
+import numpy as np
+import pytest
+
+from _state import periodic_diff, random_state, rel_inf
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ppm():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_1211_4575_amd import pp
+    pp.lib()
+    return pp
+
+
+def _by_id(parts):
+    order = np.argsort(parts["id"])
+    return {k: v[..., order] for k, v in parts.items()}
+
+
+# grid, shape order, current scheme: cubic and flat tiles, ragged edges, thin and single-cell
+# axes (runtime-shaped tiles; 70x2x2 has more halo than the tiled kernel's LDS)
+FP64_TILE_CASES = [((9, 8, 5), 3, 0), ((9, 8, 5), 2, 1), ((17, 9, 1), 3, 0), ((17, 9, 1), 2, 0), ((70, 1, 1), 3, 1),
+                   ((5, 3, 2), 2, 0), ((5, 3, 2), 3, 1), ((70, 2, 2), 3, 0), ((40, 24, 36), 3, 0)]
+
+
+@pytest.mark.parametrize("n,O,current", FP64_TILE_CASES)
+def test_fp64_sorted_push_equals_unsorted_push(ppm, orc, n, O, current):
+    """A push of freshly sorted particles (tile by tile) against one of the same particles left
+    unsorted; some particles start at the edges of the box, outside it (also by more than a
+    period) and many in one cell.  FP64 sums in another order: 1e-12 of the largest value."""
+    species, E, B = random_state(orc, n, 6, seed=31, uth=0.4)
+    N = np.array(n, dtype=np.float64)
+    pos = species[0]["pos"]
+    edge = [np.zeros(3), N - 1e-9, N - 0.5, 0.5 * N, 2.3 * N, -0.2 * N, -1.4 * N]
+    for i, x in enumerate(edge):
+        pos[:, i] = x
+    pos[:, 20:min(120, pos.shape[1])] = 0.37 * N[:, None]
+    kw = dict(n=n, dt=0.35, shape_order=O, field_order=2, current_scheme=current, relax_max_iter=100)
+    out = []
+    for sort in (True, False):
+        run = ppm.Run(ppm.make_params(precision=ppm.PP_PREC_FP64, **kw), species, E=E, B=B)
+        run.gather_push_deposit()
+        if sort:
+            run.sort()
+        run.gather_push_deposit()
+        out.append((run.fields()[2], [_by_id(run.particles(s)) for s in range(len(species))], run.diagnostics().flags))
+        run.close()
+    (J1, p1, f1), (J2, p2, f2) = out
+    assert f1 == f2 == 0
+    assert rel_inf(J1, J2) < 1e-12
+    for a, b in zip(p1, p2):
+        assert np.max(np.abs(periodic_diff(a["pos"], b["pos"], n))) < 1e-12
+        assert rel_inf(a["u"], b["u"]) < 1e-12
