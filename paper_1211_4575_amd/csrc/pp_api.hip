@@ -155,8 +155,7 @@ const char* pp_last_hip_error(void) { return g_err; }
 static size_t internal_bytes(const pp_params* p, const Geom& g, int64_t nmax, int nsp) {
     const size_t nc = (size_t)g.ncell, n3 = 3 * nc, nb = (size_t)g.nbins;
     size_t b = 0;
-    if (p->field_order > 2) b += n3 * sizeof(double);                     // J2
-    b += 3 * n3 * sizeof(double);                                          // Bn, Bw, R
+    b += 4 * n3 * sizeof(double);                                          // J2, Bn, Bw, R
     b += 2 * nc * sizeof(double);                                          // rho, rho_prev
     b += nb * sizeof(int32_t) + (size_t)scan_tmp_size(g.nbins + 1) * sizeof(int32_t);
     b += sizeof(int32_t) + ((size_t)diag_acc_count() + 8) * sizeof(double);
@@ -217,8 +216,7 @@ pp_status pp_create(const pp_params* params, const pp_mesh* mesh, void* hip_stre
     }
     const size_t n3 = 3 * (size_t)g.ncell;
     bool okk = true;
-    if (params->field_order > 2) okk = okk && dmalloc(&r->J2, n3);
-    okk = okk && dmalloc(&r->Bn, n3) && dmalloc(&r->Bw, n3) && dmalloc(&r->R, n3);
+    okk = okk && dmalloc(&r->J2, n3) && dmalloc(&r->Bn, n3) && dmalloc(&r->Bw, n3) && dmalloc(&r->R, n3);
     okk = okk && dmalloc(&r->rho, (size_t)g.ncell) && dmalloc(&r->rho_prev, (size_t)g.ncell);
     okk = okk && dmalloc(&r->sort_cursor, (size_t)g.nbins) && dmalloc(&r->scan_tmp, (size_t)scan_tmp_size(g.nbins + 1));
     okk = okk && dmalloc(&r->flags, 1) && dmalloc(&r->dacc, (size_t)diag_acc_count() + 8);

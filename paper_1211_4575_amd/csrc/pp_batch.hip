@@ -175,7 +175,7 @@ pp_status batch_step(pp_batch* b, TableTarget target) {
     int64_t* fpre = (int64_t*)(H + o_fpre);
     int64_t* cpre = (int64_t*)(H + o_cpre);
     tpre[0] = fpre[0] = cpre[0] = 0;
-    int max_sweeps = 0;
+    int max_sweeps = 0, min_sweeps = 0;
     for (int i = 0; i < n; ++i) {
         pp_run* r = b->runs[i];
         double* target = uses_line_solve(r) ? r->J2 : r->mesh.J;
@@ -187,11 +187,12 @@ pp_status batch_step(pp_batch* b, TableTarget target) {
             S.pending = false;
         }
         gpd32_fixed_desc(r, target, (FixedDesc*)(H + o_fix + i * gpd32_fixed_desc_size()));
-        field_desc(r, (FieldDesc*)(H + o_field + i * field_desc_size()));
+        field_desc(r, (FieldDesc*)(H + o_field + i * field_desc_size()), n);
         tpre[i + 1] = tpre[i] + r->g.ntiles;
         fpre[i + 1] = fpre[i] + (3 * r->g.ncell + 255) / 256;
-        cpre[i + 1] = cpre[i] + field_blocks(r);
+        cpre[i + 1] = cpre[i] + field_blocks(r, n);
         max_sweeps = r->jac_sweeps > max_sweeps ? r->jac_sweeps : max_sweeps;
+        min_sweeps = i == 0 || r->jac_sweeps < min_sweeps ? r->jac_sweeps : min_sweeps;
     }
     int64_t* lpre = (int64_t*)(H + o_lpre);
     lpre[0] = 0;
@@ -237,7 +238,7 @@ pp_status batch_step(pp_batch* b, TableTarget target) {
         e = launch_sort_batch(D + o_sort[s], pre, stot[s], ns, b->stream);
         if (!ok(e, "batch sort")) return PP_E_HIP;
     }
-    e = launch_field_step_batch(D + o_field, (const int64_t*)(D + o_cpre), n, cpre[n], max_sweeps, b->stream);
+    e = launch_field_step_batch(D + o_field, (const int64_t*)(D + o_cpre), n, cpre[n], min_sweeps, max_sweeps, b->stream);
     if (!ok(e, "batch field_step")) return PP_E_HIP;
 
     // ---- host bookkeeping (tile starts and pending orders after the sort) ------------------

@@ -109,6 +109,7 @@ struct FieldDesc {
     const double* J;
     double* Bn;  // copy of B^n
     double* Bw;  // relaxation partner
+    double* Bx;  // a second one (see relax_arrays)
     double* R;   // right-hand side
     const double* omega;        // Chebyshev weights omega_k, k = 1..sweeps (device)
     const double* rho;          // charge density (Gauss-law filter)
@@ -117,63 +118,8 @@ struct FieldDesc {
     double al2s, gdiag;         // alpha^2 s, gamma / diagonal
     double al, be, c2dt, mu0;   // alpha, beta, c^2 dt, mu0
     int sweeps;
+    int zc;                     // planes a block of the tiled kernels marches over
 };
-
-__device__ __forceinline__ void copy_body(const FieldDesc& D, int q) {
-#pragma unroll
-    for (int c = 0; c < 3; ++c) D.Bn[c * D.G.nc + q] = D.B[c * D.G.nc + q];
-}
-
-// rhs = B + alpha beta s lap B - dt curl+ E + alpha c^2 mu0 dt^2 curl+ J   (B = B^n from Bn)
-__device__ __forceinline__ void rhs_body(const FieldDesc& D, int i, int j, int k) {
-    const FieldGeom& G = D.G;
-    const int q = lin(G, i, j, k);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const int d1 = (c + 1) % 3, d2 = (c + 2) % 3;
-        const double* Bc = D.Bn + c * G.nc;
-        double curlE = dup(G, D.E + d2 * G.nc, d1, i, j, k) - dup(G, D.E + d1 * G.nc, d2, i, j, k);
-        double curlJ = dup(G, D.J + d2 * G.nc, d1, i, j, k) - dup(G, D.J + d1 * G.nc, d2, i, j, k);
-        D.R[c * G.nc + q] = Bc[q] + D.cab * lap(G, Bc, i, j, k) - D.dt * curlE + D.cj * curlJ;
-    }
-}
-
-// Sweep k (1-based) of the Chebyshev-accelerated Jacobi iteration for (1 - al2s lap) x = rhs:
-//   y = x_{k-1} + gamma (rhs - A x_{k-1}) / diag,   x_k = x_{k-2} + omega_k (y - x_{k-2}),
-// x_0 = x_{-1} = B^n (Bn), omega_1 = 1.  Iterate k lives in B when sweeps - k is even and in
-// Bw otherwise, so the last one is B and x_{k-2} shares x_k's array (each cell reads its own
-// old value before writing it).
-__device__ __forceinline__ void relax_body(const FieldDesc& D, int i, int j, int kk, int k) {
-    const FieldGeom& G = D.G;
-    const int m = D.sweeps;
-    double* out = ((m - k) % 2 == 0) ? D.B : D.Bw;
-    const double* in = k == 1 ? D.Bn : (((m - k + 1) % 2 == 0) ? D.B : D.Bw);
-    const double* prev = k <= 2 ? D.Bn : out;
-    const double w = D.omega[k];
-    const int q = lin(G, i, j, kk);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const double* x = in + c * G.nc;
-        const double xq = x[q];
-        const double Ax = xq - D.al2s * lap(G, x, i, j, kk);
-        const double y = xq + (D.R[c * G.nc + q] - Ax) * D.gdiag;
-        const double p = prev[c * G.nc + q];
-        out[c * G.nc + q] = p + w * (y - p);
-    }
-}
-
-// E += c^2 dt (curl- (alpha B' + beta B) - mu0 J)
-__device__ __forceinline__ void update_E_body(const FieldDesc& D, int i, int j, int k) {
-    const FieldGeom& G = D.G;
-    const int q = lin(G, i, j, k);
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-        const int d1 = (c + 1) % 3, d2 = (c + 2) % 3;
-        double cn = ddn(G, D.B + d2 * G.nc, d1, i, j, k) - ddn(G, D.B + d1 * G.nc, d2, i, j, k);
-        double co = ddn(G, D.Bn + d2 * G.nc, d1, i, j, k) - ddn(G, D.Bn + d1 * G.nc, d2, i, j, k);
-        D.E[c * G.nc + q] += D.c2dt * (D.al * cn + D.be * co - D.mu0 * D.J[c * G.nc + q]);
-    }
-}
 
 // Gauss-law filter pass, first half: r = div- E - (rho + rho_bg)/eps0 into R
 __device__ __forceinline__ void gauss_res_body(const FieldDesc& D, int i, int j, int k) {
@@ -193,150 +139,50 @@ __device__ __forceinline__ void gauss_corr_body(const FieldDesc& D, int i, int j
     for (int c = 0; c < 3; ++c) D.E[c * G.nc + q] += D.kappa * dup(G, D.R, c, i, j, k);
 }
 
-enum FieldPhase { PH_COPY = 0, PH_RHS = 1, PH_JACOBI = 2, PH_UPDATE_E = 3, PH_GAUSS_RES = 4, PH_GAUSS_CORR = 5 };
+enum FieldPhase { PH_GAUSS_RES = 0, PH_GAUSS_CORR = 1 };
 
-__device__ __forceinline__ void field_phase(const FieldDesc& D, int64_t b, int phase, int k) {
-    int i, j, kk;
-    if (!field_cell(D.G, b, threadIdx.x, i, j, kk)) return;
-    if (phase == PH_COPY)
-        copy_body(D, lin(D.G, i, j, kk));
-    else if (phase == PH_RHS)
-        rhs_body(D, i, j, kk);
-    else if (phase == PH_JACOBI) {
-        if (k <= D.sweeps) relax_body(D, i, j, kk, k);
-    } else if (phase == PH_UPDATE_E)
-        update_E_body(D, i, j, kk);
-    else if (phase == PH_GAUSS_RES)
-        gauss_res_body(D, i, j, kk);
+__global__ void __launch_bounds__(FIELD_BS) k_field(FieldDesc D, int phase) {
+    int i, j, k;
+    if (!field_cell(D.G, blockIdx.x, threadIdx.x, i, j, k)) return;
+    if (phase == PH_GAUSS_RES)
+        gauss_res_body(D, i, j, k);
     else
-        gauss_corr_body(D, i, j, kk);
+        gauss_corr_body(D, i, j, k);
 }
 
-__global__ void __launch_bounds__(FIELD_BS) k_field(FieldDesc D, int phase, int k) {
-    field_phase(D, blockIdx.x, phase, k);
-}
-
-// batched: block b belongs to run r with prefix[r] <= b < prefix[r+1] (prefix in blocks)
-__global__ void __launch_bounds__(FIELD_BS) k_field_batch(const FieldDesc* __restrict__ T,
-                                                          const int64_t* __restrict__ prefix, int nruns, int phase,
-                                                          int k) {
-    const int64_t b = blockIdx.x;
-    const int r = find_segment(prefix, nruns, b);
-    if (r < 0) return;
-    field_phase(T[r], b - prefix[r], phase, k);
-}
-
-// Relaxation sweep, tiled (single-run path).  A block owns a 32 x 8 column of cells in x-y
-// and marches over up to RX_ZC planes in z.  Each thread keeps the 2R+1 values of its own
-// column around the current plane in registers (the z taps of the Laplacian) and the block
-// stages the current plane of the tile plus an R-wide x-y ring in LDS (the x and y taps), so
-// each value of the input comes from memory about once per plane instead of once per tap.
-// The arithmetic and the order of the sums are those of relax_body, so both give the same
-// bits (the batched path keeps relax_body).
+// ---- the field step, tiled -------------------------------------------------------------
+// A block owns a 32 x 8 column of cells in x-y of one component and marches over D.zc planes in
+// z.  Each array a stencil reads streams through the block plane by plane: a thread keeps the
+// values of its own column at the z offsets the stencil needs in registers, and where a stencil
+// runs along x or y the block stages the plane and the ring around it in LDS.  A value then
+// comes from memory about once per plane instead of once per tap.  The next plane's loads are
+// in flight while the block works on the current one.  Single and batched runs take the same
+// code, so a batched run gives the same bits as the run alone.
+//
+// A sweep is bound by memory in large boxes (256^3: 0.38 ms, 4.2 TB/s for the four arrays it
+// cannot do without) and by latency in small ones, where short marches (D.zc, down to one plane
+// with every load in flight at once) spread it over the GPU.  6th-order sweep, us, with each tap
+// read through the caches and now: 128^3 110 and 59, 128x32x32 19 and 9.5, 512x256x1 20 and 10;
+// 2nd order, 16^3 7.4 and 4.0; a batch of eight serving boxes 24 and 17.
 constexpr int RX_TX = 32, RX_TY = 8, RX_ZC = 32;
 constexpr int RX_BS = RX_TX * RX_TY;  // one thread per column of the tile
-constexpr int64_t RX_MIN_BLOCKS = 1024 * 256 / RX_BS;  // 1024 threads' columns per CU
 
-template <int R>
-__global__ void __launch_bounds__(RX_BS) k_relax_tiled(FieldDesc D, int k) {
-    constexpr int W = RX_TX + 2 * R, H = RX_TY + 2 * R;
-    constexpr int NH = (W * H + RX_BS - 1) / RX_BS;  // ring entries a thread may stage per plane
-    __shared__ double pl[W * H];
-    const FieldGeom& G = D.G;
-    const int n0 = G.n[0], n1 = G.n[1], n2 = G.n[2];
-    const int nbx = (n0 + RX_TX - 1) / RX_TX, nby = (n1 + RX_TY - 1) / RX_TY;
-    int b = blockIdx.x;
-    const int bx = b % nbx;
-    b /= nbx;
-    const int by = b % nby;
-    const int bz = b / nby;
-    const int i0 = bx * RX_TX, j0 = by * RX_TY, z0 = bz * RX_ZC;
-    const int z1 = z0 + RX_ZC < n2 ? z0 + RX_ZC : n2;
-    const int tx = threadIdx.x % RX_TX, ty = threadIdx.x / RX_TX;
-    const int i = i0 + tx, j = j0 + ty;
-    const bool valid = i < n0 && j < n1;
-    const int iw = nbw(i0, tx, n0, 1), jw = nbw(j0, ty, n1, 1);  // loads of idle threads wrap
-    const int m = D.sweeps;
-    double* out = ((m - k) % 2 == 0) ? D.B : D.Bw;
-    const double* in = k == 1 ? D.Bn : (((m - k + 1) % 2 == 0) ? D.B : D.Bw);
-    const double* prev = k <= 2 ? D.Bn : out;
-    const double w = D.omega[k];
-    const int nc = (int)G.nc;
-    const int nxy = n0 * n1;
-    // this thread's entries of the x-y ring around the tile: LDS index (-1: none) and
-    // in-plane offset (periodic), the same for every plane
-    int hl[NH], hg[NH];
-#pragma unroll
-    for (int e = 0; e < NH; ++e) {
-        const int h = threadIdx.x + RX_BS * e;
-        const int a = h % W, bb = h / W;
-        const bool ring = h < W * H && !(a >= R && a < R + RX_TX && bb >= R && bb < R + RX_TY);
-        hl[e] = ring ? h : -1;
-        hg[e] = ring ? nbw(i0, a - R, n0, 1) + n0 * nbw(j0, bb - R, n1, 1) : 0;
-    }
-    const int own = valid ? lin(G, i, j, 0) : 0;
-    for (int c = 0; c < 3; ++c) {
-        const double* x = in + c * G.nc;
-        const double* rhs = D.R + c * G.nc;
-        const double* pv = prev + c * G.nc;
-        // the loads of a plane are issued one plane ahead, so they are in flight while the
-        // block works on the current one
-        double q[2 * R + 1], hv[NH];
-#pragma unroll
-        for (int t = 0; t <= 2 * R; ++t) q[t] = x[lin(G, iw, jw, nbw(z0, t - R, n2, G.small))];
-#pragma unroll
-        for (int e = 0; e < NH; ++e) hv[e] = hl[e] >= 0 ? x[hg[e] + z0 * nxy] : 0.0;
-        double rq = valid ? rhs[own + z0 * nxy] : 0.0;
-        double pq = valid ? pv[own + z0 * nxy] : 0.0;
-        for (int kz = z0; kz < z1; ++kz) {
-            __syncthreads();  // the previous plane's LDS reads are done
-            pl[(ty + R) * W + tx + R] = q[R];
-#pragma unroll
-            for (int e = 0; e < NH; ++e)
-                if (hl[e] >= 0) pl[hl[e]] = hv[e];
-            __syncthreads();
-            const bool more = kz + 1 < z1;
-            // the next plane's loads, unconditional (the last plane reloads its own plane, a lane
-            // off the ring or the box reads the entries hg = 0 / own = 0) so that none waits at
-            // a branch: they are first used by the next plane
-            const int kn = more ? kz + 1 : kz;
-            const double qn = x[lin(G, iw, jw, nbw(kn, R, n2, G.small))];
-#pragma unroll
-            for (int e = 0; e < NH; ++e) hv[e] = x[hg[e] + kn * nxy];
-            const double rn = rhs[own + kn * nxy];
-            const double pn = pv[own + kn * nxy];
-            if (valid) {
-                double sl = 0.0;
-#pragma unroll
-                for (int o = -R; o <= R; ++o) {
-                    sl += G.L[0][o + R] * pl[(ty + R) * W + tx + R + o];
-                    sl += G.L[1][o + R] * pl[(ty + R + o) * W + tx + R];
-                    sl += G.L[2][o + R] * q[R + o];
-                }
-                const double xq = q[R];
-                const double Ax = xq - D.al2s * sl;
-                const double y = xq + (rq - Ax) * D.gdiag;
-                out[c * nc + own + kz * nxy] = pq + w * (y - pq);
-            }
-            if (more) {
-#pragma unroll
-                for (int t = 0; t < 2 * R; ++t) q[t] = q[t + 1];
-                q[2 * R] = qn;
-                rq = rn;
-                pq = pn;
-            }
-        }
-        __syncthreads();
-    }
+// Sweep k (1-based) of the Chebyshev-accelerated Jacobi iteration for (1 - al2s lap) x = rhs:
+//   y = x_{k-1} + gamma (rhs - A x_{k-1}) / diag,   x_k = x_{k-2} + omega_k (y - x_{k-2}),
+// x_0 = x_{-1} = B^n, omega_1 = 1.  The right-hand side's kernel reads B^n and its Laplacian
+// already: it keeps the copy of B^n (Bn) and takes sweep 1 as well, into Bw.  The others
+// alternate between two arrays such that the last one is B; an iterate shares the array of the
+// one before last (each cell reads its own old value before writing it):
+//   an even number of sweeps: even iterates in B, odd ones in Bw;
+//   an odd number:            x_1 in Bw, then even iterates in Bx, odd ones in B.
+__device__ __forceinline__ double* relax_array(const FieldDesc& D, int k) {
+    if ((D.sweeps & 1) == 0) return (k & 1) ? D.Bw : D.B;
+    if (D.sweeps == 1) return D.B;  // a single sweep is not taken with the right-hand side
+    return k == 1 ? D.Bw : ((k & 1) ? D.B : D.Bx);
 }
 
-// Right-hand side and E update, tiled the same way (single-run path): per component, each
-// array the component's stencils read streams through the block one z plane at a time, its
-// x-y ring staged in LDS when a stencil runs along x or y and a register window of z offsets
-// kept when one runs along z; the next plane's loads are issued before the current plane is
-// computed.  Sums are taken in the order of rhs_body and update_E_body (same bits).
 struct TileCtx {
-    int z0, z1, tx, ty, col, own, nxy, n2, small;
+    int comp, z0, z1, tx, ty, col, own, nxy, n2, small;
     bool valid;
 };
 
@@ -346,23 +192,25 @@ struct Ring {  // this thread's entries of the x-y ring of a plane: LDS index (-
     int hl[NH], hg[NH];
 };
 
+// block b of a run's launch: component, column and planes
 template <int R>
-__device__ __forceinline__ void tile_ctx(const FieldGeom& G, TileCtx& X, Ring<R>& g) {
+__device__ __forceinline__ void tile_ctx(const FieldGeom& G, int zc, int b, TileCtx& X, Ring<R>& g) {
     constexpr int W = Ring<R>::W, H = Ring<R>::H;
     const int n0 = G.n[0], n1 = G.n[1];
-    const int nbx = (n0 + RX_TX - 1) / RX_TX, nby = (n1 + RX_TY - 1) / RX_TY;
-    int b = blockIdx.x;
+    const int nbx = (n0 + RX_TX - 1) / RX_TX, nby = (n1 + RX_TY - 1) / RX_TY, nbz = (G.n[2] + zc - 1) / zc;
     const int bx = b % nbx;
     b /= nbx;
     const int by = b % nby;
-    const int bz = b / nby;
+    b /= nby;
+    const int bz = b % nbz;
+    X.comp = b / nbz;
     const int i0 = bx * RX_TX, j0 = by * RX_TY;
-    X.z0 = bz * RX_ZC;
-    X.z1 = X.z0 + RX_ZC < G.n[2] ? X.z0 + RX_ZC : G.n[2];
+    X.z0 = bz * zc;
+    X.z1 = X.z0 + zc < G.n[2] ? X.z0 + zc : G.n[2];
     X.tx = threadIdx.x % RX_TX;
     X.ty = threadIdx.x / RX_TX;
     X.valid = i0 + X.tx < n0 && j0 + X.ty < n1;
-    X.col = nbw(i0, X.tx, n0, 1) + n0 * nbw(j0, X.ty, n1, 1);  // idle threads load wrapped columns
+    X.col = wrap_near(i0 + X.tx, n0) + n0 * wrap_near(j0 + X.ty, n1);  // idle threads load wrapped columns
     X.own = X.valid ? X.col : 0;
     X.nxy = n0 * n1;
     X.n2 = G.n[2];
@@ -373,7 +221,72 @@ __device__ __forceinline__ void tile_ctx(const FieldGeom& G, TileCtx& X, Ring<R>
         const int a = h % W, bb = h / W;
         const bool ring = h < W * H && !(a >= R && a < R + RX_TX && bb >= R && bb < R + RX_TY);
         g.hl[e] = ring ? h : -1;
-        g.hg[e] = ring ? nbw(i0, a - R, n0, 1) + n0 * nbw(j0, bb - R, n1, 1) : 0;
+        g.hg[e] = ring ? wrap_near(i0 + a - R, n0) + n0 * wrap_near(j0 + bb - R, n1) : 0;
+    }
+}
+
+// Sweep k of one block: the loads are unconditional (the last plane reloads its own plane, a lane
+// off the ring or the box reads entry 0), so that none waits at a branch before the plane that is
+// computed meanwhile.
+template <int R>
+__device__ __forceinline__ void relax_tile(const FieldDesc& D, int b, int k, double* pl) {
+    constexpr int W = Ring<R>::W, NH = Ring<R>::NH;
+    const FieldGeom& G = D.G;
+    TileCtx X;
+    Ring<R> g;
+    tile_ctx<R>(G, D.zc, b, X, g);
+    const int64_t co = (int64_t)X.comp * G.nc;
+    double* out = relax_array(D, k) + co;
+    const double* x = (k == 1 ? D.Bn : relax_array(D, k - 1)) + co;
+    const double* pv = (k <= 2 ? D.Bn : relax_array(D, k - 2)) + co;
+    const double* rhs = D.R + co;
+    const double w = D.omega[k];
+    const int nxy = X.nxy, own = X.own;
+    double q[2 * R + 1], hv[NH];
+#pragma unroll
+    for (int t = 0; t <= 2 * R; ++t) q[t] = x[X.col + nxy * nbw(X.z0, t - R, X.n2, X.small)];
+#pragma unroll
+    for (int e = 0; e < NH; ++e) hv[e] = x[g.hg[e] + X.z0 * nxy];
+    double rq = rhs[own + X.z0 * nxy];
+    double pq = pv[own + X.z0 * nxy];
+    const int c0 = (X.ty + R) * W + X.tx + R;
+    for (int kz = X.z0; kz < X.z1; ++kz) {
+        if (kz > X.z0) __syncthreads();  // the previous plane's LDS reads are done
+        pl[c0] = q[R];
+#pragma unroll
+        for (int e = 0; e < NH; ++e)
+            if (g.hl[e] >= 0) pl[g.hl[e]] = hv[e];
+        __syncthreads();
+        const bool more = kz + 1 < X.z1;
+        const int kn = more ? kz + 1 : kz;
+        double qn = 0.0, rn = 0.0, pn = 0.0;
+        if (D.zc > 1) {
+            qn = x[X.col + nxy * nbw(kn, R, X.n2, X.small)];
+#pragma unroll
+            for (int e = 0; e < NH; ++e) hv[e] = x[g.hg[e] + kn * nxy];
+            rn = rhs[own + kn * nxy];
+            pn = pv[own + kn * nxy];
+        }
+        if (X.valid) {
+            double sl = 0.0;
+#pragma unroll
+            for (int o = -R; o <= R; ++o) {
+                sl += G.L[0][o + R] * pl[c0 + o];
+                sl += G.L[1][o + R] * pl[c0 + o * W];
+                sl += G.L[2][o + R] * q[R + o];
+            }
+            const double xq = q[R];
+            const double Ax = xq - D.al2s * sl;
+            const double y = xq + (rq - Ax) * D.gdiag;
+            out[own + kz * nxy] = pq + w * (y - pq);
+        }
+        if (more) {
+#pragma unroll
+            for (int t = 0; t < 2 * R; ++t) q[t] = q[t + 1];
+            q[2 * R] = qn;
+            rq = rn;
+            pq = pn;
+        }
     }
 }
 
@@ -436,6 +349,8 @@ __device__ __forceinline__ double dtile(const S& st, const double* pl, int c0, c
     return s;
 }
 
+// rhs = B + alpha beta s lap B - dt curl+ E + alpha c^2 mu0 dt^2 curl+ J   (B = B^n), B^n's copy and
+// sweep 1
 template <int M, int C>
 __device__ __forceinline__ void rhs_tiled_comp(const FieldDesc& D, const TileCtx& X, const Ring<2 * M - 1>& g,
                                                double* lds) {
@@ -446,7 +361,10 @@ __device__ __forceinline__ void rhs_tiled_comp(const FieldDesc& D, const TileCtx
     ZStream<R, -R, R, true> sB;
     ZStream<R, uz ? -M + 1 : 0, uz ? M : 0, !uz> sEu, sJu;  // E_d2, J_d2 along d1
     ZStream<R, vz ? -M + 1 : 0, vz ? M : 0, !vz> sEv, sJv;  // E_d1, J_d1 along d2
-    sB.init(D.Bn + C * G.nc, X, g);
+    double* Bn = D.Bn + C * G.nc;
+    double* x1 = D.sweeps > 1 ? D.Bw + C * G.nc : nullptr;
+    const double w1 = D.omega[1];
+    sB.init(D.B + C * G.nc, X, g);
     sEu.init(D.E + d2 * G.nc, X, g);
     sEv.init(D.E + d1 * G.nc, X, g);
     sJu.init(D.J + d2 * G.nc, X, g);
@@ -454,7 +372,7 @@ __device__ __forceinline__ void rhs_tiled_comp(const FieldDesc& D, const TileCtx
     double *pB = lds, *pEu = lds + WH, *pEv = lds + 2 * WH, *pJu = lds + 3 * WH, *pJv = lds + 4 * WH;
     const int c0 = (X.ty + R) * Ring<R>::W + X.tx + R;
     for (int kz = X.z0; kz < X.z1; ++kz) {
-        __syncthreads();  // the previous plane's LDS reads are done
+        if (kz > X.z0) __syncthreads();  // the previous plane's LDS reads are done
         sB.stage(pB, X, g);
         sEu.stage(pEu, X, g);
         sEv.stage(pEv, X, g);
@@ -479,7 +397,16 @@ __device__ __forceinline__ void rhs_tiled_comp(const FieldDesc& D, const TileCtx
             }
             double curlE = dtile<R, M, d1, 1>(sEu, pEu, c0, G.a[d1]) - dtile<R, M, d2, 1>(sEv, pEv, c0, G.a[d2]);
             double curlJ = dtile<R, M, d1, 1>(sJu, pJu, c0, G.a[d1]) - dtile<R, M, d2, 1>(sJv, pJv, c0, G.a[d2]);
-            D.R[C * G.nc + X.own + (int64_t)kz * X.nxy] = sB.at(0) + D.cab * lp - D.dt * curlE + D.cj * curlJ;
+            const double xq = sB.at(0);
+            const double rq = xq + D.cab * lp - D.dt * curlE + D.cj * curlJ;
+            const int64_t q = X.own + (int64_t)kz * X.nxy;
+            D.R[C * G.nc + q] = rq;
+            Bn[q] = xq;
+            if (x1) {  // sweep 1
+                const double Ax = xq - D.al2s * lp;
+                const double y = xq + (rq - Ax) * D.gdiag;
+                x1[q] = xq + w1 * (y - xq);
+            }
         }
         if (more) {
             sB.shift();
@@ -491,6 +418,7 @@ __device__ __forceinline__ void rhs_tiled_comp(const FieldDesc& D, const TileCtx
     }
 }
 
+// E += c^2 dt (curl- (alpha B' + beta B) - mu0 J)
 template <int M, int C>
 __device__ __forceinline__ void update_E_tiled_comp(const FieldDesc& D, const TileCtx& X, const Ring<2 * M - 1>& g,
                                                     double* lds) {
@@ -510,7 +438,7 @@ __device__ __forceinline__ void update_E_tiled_comp(const FieldDesc& D, const Ti
     double *pBu = lds, *pBv = lds + WH, *pNu = lds + 2 * WH, *pNv = lds + 3 * WH;
     const int c0 = (X.ty + R) * Ring<R>::W + X.tx + R;
     for (int kz = X.z0; kz < X.z1; ++kz) {
-        __syncthreads();
+        if (kz > X.z0) __syncthreads();
         sBu.stage(pBu, X, g);
         sBv.stage(pBv, X, g);
         sNu.stage(pNu, X, g);
@@ -542,39 +470,90 @@ __device__ __forceinline__ void update_E_tiled_comp(const FieldDesc& D, const Ti
     }
 }
 
-enum CurlKind { CK_RHS = 0, CK_UPDATE_E = 1 };
+enum FieldKind { FK_RHS = 0, FK_RELAX = 1, FK_UPDATE_E = 2 };
 
+template <int M>
+constexpr int field_lds(int kind) {
+    return (kind == FK_RELAX ? 1 : (kind == FK_RHS ? 5 : 4)) * Ring<2 * M - 1>::W * Ring<2 * M - 1>::H;
+}
+
+// block b of a run's launch of one phase (k: the sweep)
 template <int M, int KIND>
-__global__ void __launch_bounds__(RX_BS) k_curl_tiled(FieldDesc D) {
+__device__ __forceinline__ void field_tile(const FieldDesc& D, int b, int k, double* lds) {
     constexpr int R = 2 * M - 1;
-    __shared__ double lds[5 * Ring<R>::W * Ring<R>::H];
-    TileCtx X;
-    Ring<R> g;
-    tile_ctx<R>(D.G, X, g);
-    if constexpr (KIND == CK_RHS) {
-        rhs_tiled_comp<M, 0>(D, X, g, lds);
-        rhs_tiled_comp<M, 1>(D, X, g, lds);
-        rhs_tiled_comp<M, 2>(D, X, g, lds);
+    if constexpr (KIND == FK_RELAX) {
+        relax_tile<R>(D, b, k, lds);
     } else {
-        update_E_tiled_comp<M, 0>(D, X, g, lds);
-        update_E_tiled_comp<M, 1>(D, X, g, lds);
-        update_E_tiled_comp<M, 2>(D, X, g, lds);
+        TileCtx X;
+        Ring<R> g;
+        tile_ctx<R>(D.G, D.zc, b, X, g);
+        if constexpr (KIND == FK_RHS) {
+            if (X.comp == 0)
+                rhs_tiled_comp<M, 0>(D, X, g, lds);
+            else if (X.comp == 1)
+                rhs_tiled_comp<M, 1>(D, X, g, lds);
+            else
+                rhs_tiled_comp<M, 2>(D, X, g, lds);
+        } else {
+            if (X.comp == 0)
+                update_E_tiled_comp<M, 0>(D, X, g, lds);
+            else if (X.comp == 1)
+                update_E_tiled_comp<M, 1>(D, X, g, lds);
+            else
+                update_E_tiled_comp<M, 2>(D, X, g, lds);
+        }
     }
 }
 
-template <int KIND>
-static void launch_curl_tiled(const FieldDesc& D, int64_t blocks, hipStream_t st) {
-    if (D.G.M == 3)
-        hipLaunchKernelGGL((k_curl_tiled<3, KIND>), dim3((unsigned)blocks), dim3(RX_BS), 0, st, D);
-    else if (D.G.M == 2)
-        hipLaunchKernelGGL((k_curl_tiled<2, KIND>), dim3((unsigned)blocks), dim3(RX_BS), 0, st, D);
-    else
-        hipLaunchKernelGGL((k_curl_tiled<1, KIND>), dim3((unsigned)blocks), dim3(RX_BS), 0, st, D);
+template <int M, int KIND>
+__global__ void __launch_bounds__(RX_BS) k_field_tiles(FieldDesc D, int k) {
+    __shared__ double lds[field_lds<M>(KIND)];
+    field_tile<M, KIND>(D, blockIdx.x, k, lds);
 }
 
-static int64_t relax_tiled_blocks(const FieldGeom& G) {
-    return (int64_t)((G.n[0] + RX_TX - 1) / RX_TX) * ((G.n[1] + RX_TY - 1) / RX_TY) *
-           ((G.n[2] + RX_ZC - 1) / RX_ZC);
+// batched: block b belongs to run r with prefix[r] <= b < prefix[r+1] (prefix in blocks)
+template <int KIND>
+__global__ void __launch_bounds__(RX_BS) k_field_tiles_batch(const FieldDesc* __restrict__ T,
+                                                             const int64_t* __restrict__ prefix, int nruns, int k) {
+    __shared__ double lds[field_lds<3>(KIND)];
+    const int64_t b = blockIdx.x;
+    const int r = find_segment(prefix, nruns, b);
+    if (r < 0) return;
+    const FieldDesc& D = T[r];
+    if (KIND == FK_RELAX && (k > D.sweeps || (k == 1 && D.sweeps > 1))) return;
+    const int lb = (int)(b - prefix[r]);
+    if (D.G.M == 3)
+        field_tile<3, KIND>(D, lb, k, lds);
+    else if (D.G.M == 2)
+        field_tile<2, KIND>(D, lb, k, lds);
+    else
+        field_tile<1, KIND>(D, lb, k, lds);
+}
+
+template <int KIND>
+static void launch_field_tiles(const FieldDesc& D, unsigned blocks, int k, hipStream_t st) {
+    if (D.G.M == 3)
+        hipLaunchKernelGGL((k_field_tiles<3, KIND>), dim3(blocks), dim3(RX_BS), 0, st, D, k);
+    else if (D.G.M == 2)
+        hipLaunchKernelGGL((k_field_tiles<2, KIND>), dim3(blocks), dim3(RX_BS), 0, st, D, k);
+    else
+        hipLaunchKernelGGL((k_field_tiles<1, KIND>), dim3(blocks), dim3(RX_BS), 0, st, D, k);
+}
+
+// Planes per block: as many as leave the launch about 8 blocks per CU (its share of them in a
+// batch of nruns), so that small boxes fill the GPU, and at most RX_ZC, where reading the
+// stencil's planes above and below once per block costs little.
+static int planes_per_block(const int n[3], int nruns) {
+    const int64_t cols = 3 * (int64_t)((n[0] + RX_TX - 1) / RX_TX) * ((n[1] + RX_TY - 1) / RX_TY);
+    const int64_t zc = cols * n[2] * nruns / 2048;
+    return (int)(zc < 1 ? 1 : (zc > RX_ZC ? RX_ZC : zc));
+}
+
+// Blocks of one phase of a run's field step, in a batch of nruns.
+int64_t field_blocks(const pp_run* r, int nruns) {
+    const int* n = r->p.n;
+    const int zc = planes_per_block(n, nruns);
+    return 3 * (int64_t)((n[0] + RX_TX - 1) / RX_TX) * ((n[1] + RX_TY - 1) / RX_TY) * ((n[2] + zc - 1) / zc);
 }
 
 static void fd_coeffs(int order, double a[3]) {
@@ -624,8 +603,6 @@ static FieldGeom make_geom(const pp_run* r) {
 }
 
 static int64_t blocks_of(const FieldGeom& G) { return (int64_t)G.xchunks * ((G.rows + G.rpb - 1) / G.rpb); }
-
-int64_t field_blocks(const pp_run* r) { return blocks_of(make_geom(r)); }
 
 // Host set-up of the field-step constants: the composed Laplacian stencil (d- after d+,
 // identical as a stencil to d+ after d-), the true diagonal of A = 1 - alpha^2 s lap on this
@@ -753,7 +730,7 @@ void use_relax_set(pp_run* r, int k) {
     r->dt_drift = S.drift;
 }
 
-void field_desc(const pp_run* r, FieldDesc* D) {
+void field_desc(const pp_run* r, FieldDesc* D, int nruns) {
     D->G = make_geom(r);
     const double c2 = r->p.c * r->p.c, dt = r->dt_drift, s = c2 * dt * dt;
     const double al = r->p.alpha, be = 1.0 - al;
@@ -763,6 +740,7 @@ void field_desc(const pp_run* r, FieldDesc* D) {
     D->J = r->mesh.J;
     D->Bn = r->Bn;
     D->Bw = r->Bw;
+    D->Bx = r->J2;
     D->R = r->R;
     D->omega = r->omega;
     D->rho = r->rho;
@@ -779,38 +757,18 @@ void field_desc(const pp_run* r, FieldDesc* D) {
     D->c2dt = c2 * dt;
     D->mu0 = mu0;
     D->sweeps = r->jac_sweeps;
+    D->zc = planes_per_block(r->p.n, nruns);
 }
 
 size_t field_desc_size() { return sizeof(FieldDesc); }
 
 hipError_t launch_field_step(pp_run* r) {
     FieldDesc D;
-    field_desc(r, &D);
-    const int bs = FIELD_BS;
-    const dim3 grid((unsigned)blocks_of(D.G));
-    // the tiled kernels need enough columns to fill the GPU; small boxes use the per-cell
-    // ones (the same bits either way)
-    const int64_t tb = relax_tiled_blocks(D.G);
-    const dim3 rgrid((unsigned)tb);
-    hipLaunchKernelGGL(k_field, grid, dim3(bs), 0, r->stream, D, (int)PH_COPY, 0);
-    if (tb < RX_MIN_BLOCKS)
-        hipLaunchKernelGGL(k_field, grid, dim3(bs), 0, r->stream, D, (int)PH_RHS, 0);
-    else
-        launch_curl_tiled<CK_RHS>(D, tb, r->stream);
-    for (int k = 1; k <= D.sweeps; ++k) {
-        if (tb < RX_MIN_BLOCKS)
-            hipLaunchKernelGGL(k_field, grid, dim3(bs), 0, r->stream, D, (int)PH_JACOBI, k);
-        else if (D.G.R == 5)
-            hipLaunchKernelGGL(k_relax_tiled<5>, rgrid, dim3(RX_BS), 0, r->stream, D, k);
-        else if (D.G.R == 3)
-            hipLaunchKernelGGL(k_relax_tiled<3>, rgrid, dim3(RX_BS), 0, r->stream, D, k);
-        else
-            hipLaunchKernelGGL(k_relax_tiled<1>, rgrid, dim3(RX_BS), 0, r->stream, D, k);
-    }
-    if (tb < RX_MIN_BLOCKS)
-        hipLaunchKernelGGL(k_field, grid, dim3(bs), 0, r->stream, D, (int)PH_UPDATE_E, 0);
-    else
-        launch_curl_tiled<CK_UPDATE_E>(D, tb, r->stream);
+    field_desc(r, &D, 1);
+    const unsigned blocks = (unsigned)field_blocks(r, 1);
+    launch_field_tiles<FK_RHS>(D, blocks, 0, r->stream);
+    for (int k = D.sweeps > 1 ? 2 : 1; k <= D.sweeps; ++k) launch_field_tiles<FK_RELAX>(D, blocks, k, r->stream);
+    launch_field_tiles<FK_UPDATE_E>(D, blocks, 0, r->stream);
     note_relax_rhs(r);
     return hipGetLastError();
 }
@@ -876,26 +834,25 @@ hipError_t launch_gauss_filter(pp_run* r) {
     hipError_t e = deposit_rho_all(r);
     if (e != hipSuccess) return e;
     FieldDesc D;
-    field_desc(r, &D);
+    field_desc(r, &D, 1);
     const dim3 grid((unsigned)blocks_of(D.G));
     for (int it = 0; it < r->p.gauss_filter_passes; ++it) {
-        hipLaunchKernelGGL(k_field, grid, dim3(FIELD_BS), 0, r->stream, D, (int)PH_GAUSS_RES, 0);
-        hipLaunchKernelGGL(k_field, grid, dim3(FIELD_BS), 0, r->stream, D, (int)PH_GAUSS_CORR, 0);
+        hipLaunchKernelGGL(k_field, grid, dim3(FIELD_BS), 0, r->stream, D, (int)PH_GAUSS_RES);
+        hipLaunchKernelGGL(k_field, grid, dim3(FIELD_BS), 0, r->stream, D, (int)PH_GAUSS_CORR);
     }
     return hipGetLastError();
 }
 
 // Batched field step over n runs: table (device) of FieldDesc, prefix (device) of blocks.
 hipError_t launch_field_step_batch(const void* table, const int64_t* prefix, int n, int64_t total_blocks,
-                                   int max_sweeps, hipStream_t st) {
+                                   int min_sweeps, int max_sweeps, hipStream_t st) {
     if (n == 0 || total_blocks == 0) return hipSuccess;
     const FieldDesc* T = (const FieldDesc*)table;
     const dim3 grid((unsigned)total_blocks);
-    hipLaunchKernelGGL(k_field_batch, grid, dim3(FIELD_BS), 0, st, T, prefix, n, (int)PH_COPY, 0);
-    hipLaunchKernelGGL(k_field_batch, grid, dim3(FIELD_BS), 0, st, T, prefix, n, (int)PH_RHS, 0);
-    for (int k = 1; k <= max_sweeps; ++k)
-        hipLaunchKernelGGL(k_field_batch, grid, dim3(FIELD_BS), 0, st, T, prefix, n, (int)PH_JACOBI, k);
-    hipLaunchKernelGGL(k_field_batch, grid, dim3(FIELD_BS), 0, st, T, prefix, n, (int)PH_UPDATE_E, 0);
+    hipLaunchKernelGGL(k_field_tiles_batch<FK_RHS>, grid, dim3(RX_BS), 0, st, T, prefix, n, 0);
+    for (int k = min_sweeps > 1 ? 2 : 1; k <= max_sweeps; ++k)
+        hipLaunchKernelGGL(k_field_tiles_batch<FK_RELAX>, grid, dim3(RX_BS), 0, st, T, prefix, n, k);
+    hipLaunchKernelGGL(k_field_tiles_batch<FK_UPDATE_E>, grid, dim3(RX_BS), 0, st, T, prefix, n, 0);
     return hipGetLastError();
 }
 

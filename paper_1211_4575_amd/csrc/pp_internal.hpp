@@ -84,7 +84,7 @@ struct pp_run {
     pp::Geom g{};
     pp::Species sp[PP_MAX_SPECIES];
 
-    double* J2 = nullptr;      // second-order current (field order > 2)
+    double* J2 = nullptr;      // second-order current (field order > 2); relaxation scratch in the field step
     double* Bn = nullptr;      // copy of B^n during the field step
     double* Bw = nullptr;      // relaxation ping-pong partner
     double* R = nullptr;       // right-hand side of the elliptic equation
@@ -174,7 +174,8 @@ hipError_t launch_gpd64_tiles(pp_run* r, double* J, unsigned* done);
 hipError_t launch_gpd32(pp_run* r, double* J);
 hipError_t launch_line_solve(pp_run* r, const double* J2, double* J);
 hipError_t launch_field_step(pp_run* r);
-int64_t field_blocks(const pp_run* r);  // blocks of one field launch of this run
+// blocks of one launch of this run's field step, in a batch of nruns
+int64_t field_blocks(const pp_run* r, int nruns);
 // Sort species s: FP64 form, counting sort by cell; split form, the tile order (pairs of
 // ranks in chunks of 64) per tile, from the particle kernel's counts and ranks when it has
 // run since the last sort, otherwise (first sort, arbitrary order) by bucketing and a
@@ -210,9 +211,9 @@ hipError_t launch_gpd32_batch(const void* args_table, const int64_t* tile_prefix
                               const void* fixed_table, const int64_t* fixed_prefix, int64_t total_fixed_blocks, int n,
                               int shape_order, size_t lds, hipStream_t st);
 size_t field_desc_size();
-void field_desc(const pp_run* r, FieldDesc* D);
+void field_desc(const pp_run* r, FieldDesc* D, int nruns);
 hipError_t launch_field_step_batch(const void* table, const int64_t* prefix, int n, int64_t total_blocks,
-                                   int max_sweeps, hipStream_t st);
+                                   int min_sweeps, int max_sweeps, hipStream_t st);
 size_t line_desc_size();
 int64_t line_blocks(const pp_run* r);  // blocks of one line-solve launch of this run
 void line_desc(const pp_run* r, const double* J2, double* J, LineArgs* A);
