@@ -104,10 +104,11 @@ static void release(pp_run* r) {
     f(r->tile_max);
     f(r->qscale);
     for (auto& S : r->rs) f(S.omega);
-    f(r->rounds);
     for (int s = 0; s < PP_MAX_SPECIES; ++s) {
         f(r->sp[s].cell_cnt);
         f(r->sp[s].rank);
+        f(r->sp[s].rank_base);
+        f(r->sp[s].rounds);
         f(r->sp[s].perm);
         f(r->sp[s].offsets_next);
     }
@@ -163,10 +164,11 @@ static size_t internal_bytes(const pp_params* p, const Geom& g, int64_t nmax, in
     if (p->precision == PP_PREC_FP32_SPLIT) {
         b += n3 * sizeof(long long) + PP_MAX_SPECIES * sizeof(int32_t) + sizeof(double);
         b += 2 * (size_t)nmax * sizeof(int32_t);                           // sort scratch
-        b += (size_t)g.ntiles * SORT_RCAP * sizeof(RoundEntry);            // round tables
-        // per species: cell counts, particle ranks and sort permutation, next tile starts
+        // per species: cell counts, particle ranks and sort permutation, next tile starts, round
+        // tables and the ranks the particles of each tile start from
         b += (size_t)nsp * (nc * sizeof(int32_t) + 2 * (size_t)nmax * sizeof(int32_t) +
-                            ((size_t)g.ntiles + 1) * sizeof(int32_t));
+                            ((size_t)g.ntiles + 1) * sizeof(int32_t) +
+                            (size_t)g.ntiles * (SORT_RCAP * sizeof(RoundEntry) + g.dest_slots() * sizeof(int32_t)));
     }
     if (p->field_order > 2)  // line-solve coefficients: at most min(N, 127) per axis
         for (int d = 0; d < 3; ++d) b += (size_t)(p->n[d] < 127 ? p->n[d] : 127) * sizeof(double);
@@ -223,7 +225,6 @@ pp_status pp_create(const pp_params* params, const pp_mesh* mesh, void* hip_stre
     r->nrs = params->time_order == 4 ? 3 : 1;
     for (int k = 0; k < r->nrs; ++k) okk = okk && dmalloc(&r->rs[k].omega, (size_t)params->relax_max_iter + 2);
     if (params->precision == PP_PREC_FP32_SPLIT) {
-        okk = okk && dmalloc(&r->rounds, (size_t)g.ntiles * SORT_RCAP);
         okk = okk && dmalloc(&r->Jq, n3) && dmalloc(&r->tile_max, PP_MAX_SPECIES) && dmalloc(&r->qscale, 1) &&
               ok(hipMemset(r->tile_max, 0, PP_MAX_SPECIES * sizeof(int32_t)), "hipMemset");
     }
@@ -294,6 +295,8 @@ pp_status pp_init_species(pp_run* r, int32_t s, double q, double m, double w, co
     if (split) {
         if (!S.offsets_next && !dmalloc(&S.offsets_next, (size_t)r->g.ntiles + 1)) return PP_E_HIP;
         if (!S.cell_cnt && !dmalloc(&S.cell_cnt, (size_t)r->g.ncell)) return PP_E_HIP;
+        if (!S.rounds && !dmalloc(&S.rounds, (size_t)r->g.ntiles * SORT_RCAP)) return PP_E_HIP;
+        if (!S.rank_base && !dmalloc(&S.rank_base, (size_t)r->g.ntiles * r->g.dest_slots())) return PP_E_HIP;
         if (!ok(launch_fill_i32(S.cell_cnt, r->g.ncell, 0, r->stream), "fill")) return PP_E_HIP;
         if (S.rank) (void)hipFree(S.rank);
         S.rank = nullptr;
@@ -426,16 +429,8 @@ pp_status pp_step(pp_run* r) {
 
 pp_status pp_sort_particles(pp_run* r, int32_t s) {
     if (!r || s < -1 || s >= PP_MAX_SPECIES) return PP_E_ARG;
-    for (int k = 0; k < PP_MAX_SPECIES; ++k) {
-        if (s >= 0 && k != s) continue;
-        if (!r->sp[k].active) {
-            if (s >= 0) return PP_E_STATE;
-            continue;
-        }
-        hipError_t e = launch_sort(r, k);
-        if (!ok(e, "sort")) return PP_E_HIP;
-    }
-    return PP_OK;
+    if (s >= 0 && !r->sp[s].active) return PP_E_STATE;
+    return ok(launch_sort(r, s), "sort") ? PP_OK : PP_E_HIP;
 }
 
 pp_status pp_diagnostics(pp_run* r, uint32_t what, pp_diag* out) {

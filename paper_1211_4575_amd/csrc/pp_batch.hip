@@ -13,10 +13,6 @@
 
 #include "pp_internal.hpp"
 
-namespace pp {
-void sort_desc(const pp_run* r, int s, SortDesc* D);
-}  // namespace pp
-
 struct pp_batch {
     hipStream_t stream = nullptr;
     int device = 0;  // the GPU current at pp_batch_create (its static table array is used)
@@ -24,7 +20,7 @@ struct pp_batch {
     std::vector<pp_run*> runs;
     // per-step index lists, reserved for max_runs entries at creation (a step never grows them)
     std::vector<int> line_runs;
-    std::vector<int> slot_segs[PP_MAX_SPECIES];
+    std::vector<int> sort_segs;  // run * PP_MAX_SPECIES + species
     unsigned char* d_buf = nullptr;  // device copy of the step's descriptor tables
     size_t d_cap = 0;
     unsigned char* h_buf[2] = {nullptr, nullptr};  // pinned staging, used alternately
@@ -125,12 +121,12 @@ pp_status batch_step(pp_batch* b, TableTarget target) {
     for (int i = 0; i < n; ++i)
         if (uses_line_solve(b->runs[i])) line_runs.push_back(i);
     const int nl = (int)line_runs.size();
-    std::vector<int>* slot_segs = b->slot_segs;
-    for (int s = 0; s < PP_MAX_SPECIES; ++s) {
-        slot_segs[s].clear();
-        for (int i = 0; i < n; ++i)
-            if (b->runs[i]->sp[s].active) slot_segs[s].push_back(i);
-    }
+    std::vector<int>& sort_segs = b->sort_segs;
+    sort_segs.clear();
+    for (int i = 0; i < n; ++i)
+        for (int s = 0; s < PP_MAX_SPECIES; ++s)
+            if (b->runs[i]->sp[s].active) sort_segs.push_back(i * PP_MAX_SPECIES + s);
+    const int ns = (int)sort_segs.size();
 
     Layout L;
     const size_t o_gpd = L.take(n * gpd32_args_size());
@@ -139,12 +135,9 @@ pp_status batch_step(pp_batch* b, TableTarget target) {
     const size_t o_fpre = L.take((n + 1) * sizeof(int64_t));
     const size_t o_line = L.take((nl + 1) * line_desc_size());
     const size_t o_lpre = L.take((nl + 1) * sizeof(int64_t));
-    size_t o_sort[PP_MAX_SPECIES], o_spre[PP_MAX_SPECIES][SORT_BATCH_PHASES];
-    for (int s = 0; s < PP_MAX_SPECIES; ++s) {
-        const int ns = (int)slot_segs[s].size();
-        o_sort[s] = L.take((ns + 1) * sort_desc_size());
-        for (int ph = 0; ph < SORT_BATCH_PHASES; ++ph) o_spre[s][ph] = L.take((ns + 1) * sizeof(int64_t));
-    }
+    const size_t o_sort = L.take((ns + 1) * sort_desc_size());
+    size_t o_spre[SORT_BATCH_PHASES];
+    for (int ph = 0; ph < SORT_BATCH_PHASES; ++ph) o_spre[ph] = L.take((ns + 1) * sizeof(int64_t));
     const size_t o_field = L.take(n * field_desc_size());
     const size_t o_cpre = L.take((n + 1) * sizeof(int64_t));
     unsigned char* D = nullptr;
@@ -201,22 +194,20 @@ pp_status batch_step(pp_batch* b, TableTarget target) {
         line_desc(r, r->J2, r->mesh.J, (LineArgs*)(H + o_line + j * line_desc_size()));
         lpre[j + 1] = lpre[j] + line_blocks(r);
     }
-    int64_t stot[PP_MAX_SPECIES][SORT_BATCH_PHASES];
-    for (int s = 0; s < PP_MAX_SPECIES; ++s) {
-        const int ns = (int)slot_segs[s].size();
-        int64_t* pre[SORT_BATCH_PHASES];
-        for (int ph = 0; ph < SORT_BATCH_PHASES; ++ph) {
-            pre[ph] = (int64_t*)(H + o_spre[s][ph]);
-            pre[ph][0] = 0;
-        }
-        for (int j = 0; j < ns; ++j) {
-            const int i = slot_segs[s][j];
-            sort_desc(b->runs[i], s, (SortDesc*)(H + o_sort[s] + j * sort_desc_size()));
-            int64_t blocks[SORT_BATCH_PHASES];
-            sort_desc_blocks(b->runs[i], s, blocks);
-            for (int ph = 0; ph < SORT_BATCH_PHASES; ++ph) pre[ph][j + 1] = pre[ph][j] + blocks[ph];
-        }
-        for (int ph = 0; ph < SORT_BATCH_PHASES; ++ph) stot[s][ph] = pre[ph][ns];
+    int64_t* spre[SORT_BATCH_PHASES];
+    for (int ph = 0; ph < SORT_BATCH_PHASES; ++ph) {
+        spre[ph] = (int64_t*)(H + o_spre[ph]);
+        spre[ph][0] = 0;
+    }
+    size_t perm_lds = 0;
+    for (int j = 0; j < ns; ++j) {
+        const pp_run* r = b->runs[sort_segs[j] / PP_MAX_SPECIES];
+        const int s = sort_segs[j] % PP_MAX_SPECIES;
+        sort_desc(r, s, (RankedArgs*)(H + o_sort + j * sort_desc_size()));
+        int64_t blocks[SORT_BATCH_PHASES];
+        sort_desc_blocks(r, s, blocks);
+        for (int ph = 0; ph < SORT_BATCH_PHASES; ++ph) spre[ph][j + 1] = spre[ph][j] + blocks[ph];
+        perm_lds = sort_perm_lds(r) > perm_lds ? sort_perm_lds(r) : perm_lds;
     }
 
     // ---- upload and launch -------------------------------------------------------------
@@ -230,14 +221,14 @@ pp_status batch_step(pp_batch* b, TableTarget target) {
     if (!ok(e, "batch gather_push_deposit")) return PP_E_HIP;
     e = launch_line_solve_batch(D + o_line, (const int64_t*)(D + o_lpre), nl, lpre[nl], b->stream);
     if (!ok(e, "batch line_solve")) return PP_E_HIP;
-    for (int s = 0; s < PP_MAX_SPECIES; ++s) {
-        const int ns = (int)slot_segs[s].size();
-        if (ns == 0) continue;
-        const int64_t* pre[SORT_BATCH_PHASES];
-        for (int ph = 0; ph < SORT_BATCH_PHASES; ++ph) pre[ph] = (const int64_t*)(D + o_spre[s][ph]);
-        e = launch_sort_batch(D + o_sort[s], pre, stot[s], ns, b->stream);
-        if (!ok(e, "batch sort")) return PP_E_HIP;
+    const int64_t* pre[SORT_BATCH_PHASES];
+    int64_t stot[SORT_BATCH_PHASES];
+    for (int ph = 0; ph < SORT_BATCH_PHASES; ++ph) {
+        pre[ph] = (const int64_t*)(D + o_spre[ph]);
+        stot[ph] = spre[ph][ns];
     }
+    e = launch_sort_batch(D + o_sort, pre, stot, ns, perm_lds, b->stream);
+    if (!ok(e, "batch sort")) return PP_E_HIP;
     e = launch_field_step_batch(D + o_field, (const int64_t*)(D + o_cpre), n, cpre[n], min_sweeps, max_sweeps, b->stream);
     if (!ok(e, "batch field_step")) return PP_E_HIP;
 
@@ -268,7 +259,7 @@ pp_status pp_batch_create(int32_t max_runs, void* hip_stream, pp_batch** out) {
     b->max_runs = max_runs;
     b->runs.reserve(max_runs);
     b->line_runs.reserve(max_runs);
-    for (auto& v : b->slot_segs) v.reserve(max_runs);
+    b->sort_segs.reserve((size_t)max_runs * PP_MAX_SPECIES);
     pp_status st = PP_OK;
     if (!ok(hipGetDevice(&b->device), "hipGetDevice")) st = PP_E_HIP;
     for (int i = 0; i < 2 && st == PP_OK; ++i)

@@ -21,8 +21,8 @@
 //   3. flush the current block to the global accumulator with 64-bit integer atomics.
 // For the next sort each particle also gets its rank among the particles of its new cell:
 // an LDS counter per destination cell of the tile's neighbourhood hands out ranks inside
-// the tile, one global atomic per destination cell then reserves the tile's range in that
-// cell's count, and a second pass over the tile's particles adds the range start.
+// the tile, and one global atomic per destination cell then reserves the tile's range in that
+// cell's count; the sort adds the start of that range, kept per tile and cell.
 // Current accumulation is exact 64-bit fixed point.  Each contribution P_a * F * fac is
 // formed in FP64 by one fused multiply-add with the rounding constant 1.5*2^52, whose bit
 // pattern is then (constant bits + round(contribution * 2^e)); that pattern is added to the
@@ -42,7 +42,8 @@ namespace pp {
 struct Sp32 {
     const int32_t* start;  // tile starts (ntiles + 1)
     int32_t* cnt;          // particles per cell of the new positions (for the next sort)
-    int32_t* rank;         // rank of each particle in its new cell (for the next sort)
+    int32_t* rank;         // rank word of each particle (for the next sort, see pp_sort.hip)
+    int32_t* base;         // per tile and destination cell: the rank its particles start from
     // A sort leaves the new order as a permutation: slot q of the tile order holds the
     // particle at index perm[q] of the input arrays, and the kernel writes slot q of the
     // output arrays (it moves the particles as it updates them).  perm == nullptr: in place.
@@ -83,7 +84,7 @@ struct Gpd32Args {
     const double* qscale;    // 2^e (device, set by k_fixed_scale)
     int32_t* flags;
     int per_xcd;
-    int sext[3];  // destination-cell window per axis (tile + 2 below + 2 above; 1 if collapsed)
+    int sext[3];  // destination-cell window per axis (tile and DEST_HALO around it; 1 if collapsed)
     int nslots;   // sext[0] * sext[1] * sext[2]
     int direct;   // PP_CURRENT_DIRECT: eq. "jj2" instead of the Esirkepov current
 };
@@ -262,9 +263,8 @@ __device__ __forceinline__ float gather_comp(const float* __restrict__ F, const 
 
 // Rank of a particle among those bound for its destination cell: rel = destination cell
 // relative to the tile origin (unwrapped), gcell = its linear index.  Inside the tile's
-// window the rank comes from the LDS counter of that cell (slot << 20 | rank in the tile;
-// completed after the tile by the cell's range start); otherwise from the global count
-// directly (bit 31 set).
+// window the rank comes from the LDS counter of that cell (slot << 20 | rank in the tile; the
+// sort adds the cell's range start); otherwise from the global count directly (bit 31 set).
 __device__ __forceinline__ int32_t dest_rank(const Gpd32Args& A, const Sp32& S, int32_t* slots, const int rel[3],
                                              int32_t gcell) {
     int sl = 0, mul = 1;
@@ -272,7 +272,7 @@ __device__ __forceinline__ int32_t dest_rank(const Gpd32Args& A, const Sp32& S, 
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         const int e = A.sext[d];
-        const int x = e == 1 ? 0 : rel[d] + 2;
+        const int x = e == 1 ? 0 : rel[d] + DEST_HALO;
         win = win && x >= 0 && x < e;
         sl += x * mul;
         mul *= e;
@@ -280,6 +280,7 @@ __device__ __forceinline__ int32_t dest_rank(const Gpd32Args& A, const Sp32& S, 
     if (win) {
         const int32_t r = atomicAdd(&slots[sl], 1);
         if (r < (1 << 20)) return (sl << 20) | r;
+        atomicSub(&slots[sl], 1);  // past the word's range: counted below instead
     }
     return (int32_t)(0x80000000u | (uint32_t)atomicAdd(&S.cnt[gcell], 1));
 }
@@ -738,25 +739,22 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, uns
                 }
             }
         }
-        // reserve the tile's range in each destination cell's count, then complete the ranks
+        // reserve the tile's range in each destination cell's count; the sort adds its start to
+        // the particles' ranks
         __syncthreads();
         for (int q = threadIdx.x; q < A.nslots; q += GPD32_BS) {
             const int c = slots[q];
-            if (c == 0) continue;
-            const int x = q % A.sext[0], y = (q / A.sext[0]) % A.sext[1], z = q / (A.sext[0] * A.sext[1]);
-            const int gx = A.sext[0] == 1 ? 0 : wrap(org[0] + x - 2, n0);
-            const int gy = A.sext[1] == 1 ? 0 : wrap(org[1] + y - 2, n1);
-            const int gz = A.sext[2] == 1 ? 0 : wrap(org[2] + z - 2, n2);
-            slots[q] = atomicAdd(&S.cnt[gx + n0 * (gy + n1 * gz)], c);
+            slots[q] = 0;
+            int first = 0;
+            if (c != 0) {
+                const int x = q % A.sext[0], y = (q / A.sext[0]) % A.sext[1], z = q / (A.sext[0] * A.sext[1]);
+                const int gx = A.sext[0] == 1 ? 0 : wrap_near(org[0] + x - DEST_HALO, n0);
+                const int gy = A.sext[1] == 1 ? 0 : wrap_near(org[1] + y - DEST_HALO, n1);
+                const int gz = A.sext[2] == 1 ? 0 : wrap_near(org[2] + z - DEST_HALO, n2);
+                first = atomicAdd(&S.cnt[gx + n0 * (gy + n1 * gz)], c);
+            }
+            S.base[tile * A.nslots + q] = first;
         }
-        __syncthreads();
-        for (int32_t p = start + threadIdx.x; p < end; p += GPD32_BS) {
-            const int32_t v = S.rank[p];
-            if (v == -1) continue;
-            S.rank[p] = v < 0 ? (v & 0x7FFFFFFF) : slots[v >> 20] + (v & 0xFFFFF);
-        }
-        __syncthreads();
-        for (int q = threadIdx.x; q < A.nslots; q += GPD32_BS) slots[q] = 0;
         __syncthreads();
     }
     if (bad_all) atomic_or_flag(A.flags, bad_all);
@@ -896,8 +894,7 @@ size_t gpd32_lds_bytes(const pp_run* r) {
     const size_t cv = kind == TILE_444       ? (size_t)cur_plane_444(r->p.shape_order) * ce[2]
                       : kind == TILE_881_FLAT ? (size_t)cur_row_881 * ce[1]
                                               : (size_t)ce[0] * ce[1] * ce[2];
-    size_t slots = 1;
-    for (int d = 0; d < 3; ++d) slots *= r->p.n[d] == 1 ? 1 : (size_t)r->g.t[d] + 4;
+    const size_t slots = r->g.dest_slots();
     return ((6 * fv * sizeof(float) + 15) & ~(size_t)15) + 3 * cv * sizeof(unsigned long long) + slots * sizeof(int32_t);
 }
 
@@ -952,6 +949,7 @@ void gpd32_fill_args(const pp_run* r, Gpd32Args* Ap) {
         D.start = S.offsets;
         D.cnt = S.cell_cnt;
         D.rank = S.rank;
+        D.base = S.rank_base;
         D.perm = S.pending ? S.perm : nullptr;
         D.cell = S.cur.cell;
         D.cell_o = S.pending ? S.cur.cell_alt : S.cur.cell;
@@ -975,11 +973,8 @@ void gpd32_fill_args(const pp_run* r, Gpd32Args* Ap) {
     A.flags = r->flags;
     A.per_xcd = (int)((r->g.ntiles + 7) / 8);
     A.direct = r->p.current_scheme == PP_CURRENT_DIRECT ? 1 : 0;
-    A.nslots = 1;
-    for (int d = 0; d < 3; ++d) {
-        A.sext[d] = r->p.n[d] == 1 ? 1 : r->g.t[d] + 4;
-        A.nslots *= A.sext[d];
-    }
+    for (int d = 0; d < 3; ++d) A.sext[d] = r->g.dest_ext(d);
+    A.nslots = r->g.dest_slots();
 }
 
 void gpd32_fixed_desc(const pp_run* r, double* J, FixedDesc* D) {

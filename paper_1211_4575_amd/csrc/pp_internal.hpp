@@ -23,6 +23,8 @@ constexpr int fld_hi(int O) { return O == 2 ? 2 : 3; }
 constexpr int cur_lo(int) { return 2; }
 constexpr int cur_hi(int O) { return O + 1; }
 
+constexpr int DEST_HALO = 2;
+
 struct Geom {
     int n[3];       // cells
     int t[3];       // tile dims
@@ -30,30 +32,11 @@ struct Geom {
     int64_t ncell;  // n0*n1*n2
     int64_t ntiles;
     int64_t nbins;  // ntiles * 64
-};
 
-struct Species {
-    bool active = false;
-    double q = 0, m = 1, w = 0;
-    int64_t n = 0;
-    pp_particles cur{};  // buffers read by the next push
-    bool sorted = false;
-    // FP64 form: nbins + 1 cell-bin starts.  Split form: ntiles + 1 tile starts of the
-    // tile order of pp_sort.hip (valid when sorted).
-    int32_t* offsets = nullptr;
-    bool binned = false;  // FP64 form: sorted and not pushed since (offsets are the bins of the positions)
-    // split form, filled by the particle kernel for the next sort: particles per cell of the
-    // new positions (ncell, zero between steps), each particle's rank among the particles of
-    // its new cell (n; -1 for a particle found outside its tile), the next tile starts
-    int32_t* cell_cnt = nullptr;
-    int32_t* rank = nullptr;
-    int32_t* offsets_next = nullptr;
-    bool ranked = false;  // cell_cnt / rank describe the current positions
-    // split form: the last sort left its order as a permutation (slot q of the new order is
-    // particle perm[q] of the current buffers); the next particle kernel, or materialize,
-    // moves the particles
-    int32_t* perm = nullptr;
-    bool pending = false;
+    // Destination cells of a tile's particles after a step: the tile and DEST_HALO cells around it
+    // (a particle moves less than a cell and may be stored one cell lower).
+    __host__ __device__ int dest_ext(int d) const { return n[d] == 1 ? 1 : t[d] + 2 * DEST_HALO; }
+    int dest_slots() const { return dest_ext(0) * dest_ext(1) * dest_ext(2); }
 };
 
 // Round table of a tile (split-form sort), entry r for the particles of rank r in their cell
@@ -67,6 +50,34 @@ struct RoundEntry {
     int32_t sbefore;
 };
 constexpr int SORT_RCAP = 96;  // ranks per tile table (even); ranks beyond go to an overflow tail
+
+struct Species {
+    bool active = false;
+    double q = 0, m = 1, w = 0;
+    int64_t n = 0;
+    pp_particles cur{};  // buffers read by the next push
+    bool sorted = false;
+    // FP64 form: nbins + 1 cell-bin starts.  Split form: ntiles + 1 tile starts of the
+    // tile order of pp_sort.hip (valid when sorted).
+    int32_t* offsets = nullptr;
+    bool binned = false;  // FP64 form: sorted and not pushed since (offsets are the bins of the positions)
+    // split form, filled by the particle kernel for the next sort: particles per cell of the
+    // new positions (ncell, zero between steps), each particle's rank among the particles of
+    // its new cell (n; as RankedArgs in pp_sort.hip reads it), per tile and destination cell the
+    // ranks its particles start from (ntiles * dest_slots), the next tile starts; the sort's
+    // round tables (ntiles * SORT_RCAP)
+    int32_t* cell_cnt = nullptr;
+    int32_t* rank = nullptr;
+    int32_t* rank_base = nullptr;
+    int32_t* offsets_next = nullptr;
+    RoundEntry* rounds = nullptr;
+    bool ranked = false;  // cell_cnt / rank describe the current positions
+    // split form: the last sort left its order as a permutation (slot q of the new order is
+    // particle perm[q] of the current buffers); the next particle kernel, or materialize,
+    // moves the particles
+    int32_t* perm = nullptr;
+    bool pending = false;
+};
 
 // Line-solve stencil of one axis: out[i] = sum_j coef[j] * in[(i + off + j) mod n].
 struct LineStencil {
@@ -91,8 +102,7 @@ struct pp_run {
     double* rho = nullptr;     // charge density (diagnostics)
     double* rho_prev = nullptr;
     int64_t rho_prev_step = -1;
-    int32_t* sort_cursor = nullptr;   // nbins: scatter cursors (cell bins or tiles)
-    pp::RoundEntry* rounds = nullptr; // split form: ntiles * SORT_RCAP round tables
+    int32_t* sort_cursor = nullptr;   // nbins: scatter cursors (cell bins or tiles), per-tile sort state
     int32_t* scan_tmp = nullptr;      // block sums of the scan
     int32_t* sort_scratch = nullptr;  // split form: rank and permutation of the tile-order rebuild
     int64_t sort_scratch_n = 0;       // particles per half of sort_scratch
@@ -176,10 +186,10 @@ hipError_t launch_line_solve(pp_run* r, const double* J2, double* J);
 hipError_t launch_field_step(pp_run* r);
 // blocks of one launch of this run's field step, in a batch of nruns
 int64_t field_blocks(const pp_run* r, int nruns);
-// Sort species s: FP64 form, counting sort by cell; split form, the tile order (pairs of
-// ranks in chunks of 64) per tile, from the particle kernel's counts and ranks when it has
-// run since the last sort, otherwise (first sort, arbitrary order) by bucketing and a
-// per-tile rebuild.
+// Sort species s (-1: all): FP64 form, counting sort by cell; split form, the tile order (pairs
+// of ranks in chunks of 64) per tile, from the particle kernel's counts and ranks when it has
+// run since the last sort (all such species together), otherwise (first sort, arbitrary order)
+// by bucketing and a per-tile rebuild.
 hipError_t launch_sort(pp_run* r, int s);
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st);
 void sort_enqueued(pp_run* r, int s);  // host bookkeeping after a ranked sort was enqueued
@@ -204,7 +214,7 @@ struct Gpd32Args;
 struct FixedDesc;
 struct FieldDesc;
 struct LineArgs;
-struct SortDesc;
+struct RankedArgs;
 void gpd32_fill_args(const pp_run* r, Gpd32Args* A);
 void gpd32_fixed_desc(const pp_run* r, double* J, FixedDesc* D);
 hipError_t launch_gpd32_batch(const void* args_table, const int64_t* tile_prefix, int64_t total_tiles,
@@ -218,11 +228,13 @@ size_t line_desc_size();
 int64_t line_blocks(const pp_run* r);  // blocks of one line-solve launch of this run
 void line_desc(const pp_run* r, const double* J2, double* J, LineArgs* A);
 hipError_t launch_line_solve_batch(const void* table, const int64_t* prefix, int n, int64_t total_blocks, hipStream_t st);
+// ranked sort of one species of a run, as an entry of a batch's table
 size_t sort_desc_size();
-void sort_desc(const pp_run* r, int s, SortDesc* D);
-constexpr int SORT_BATCH_PHASES = 4;
+void sort_desc(const pp_run* r, int s, RankedArgs* A);
+constexpr int SORT_BATCH_PHASES = 3;
 void sort_desc_blocks(const pp_run* r, int s, int64_t blocks[SORT_BATCH_PHASES]);
+size_t sort_perm_lds(const pp_run* r);  // LDS bytes of the last phase
 hipError_t launch_sort_batch(const void* table, const int64_t* const prefixes[SORT_BATCH_PHASES],
-                             const int64_t totals[SORT_BATCH_PHASES], int nseg, hipStream_t st);
+                             const int64_t totals[SORT_BATCH_PHASES], int nseg, size_t perm_lds, hipStream_t st);
 
 }  // namespace pp

@@ -397,17 +397,28 @@ __global__ void __launch_bounds__(256) k_tile_reorder(ReorderArgs<T> A) {
 }
 
 // ---- ranked sort (split form, after a push) ---------------------------------------------
-// The particle kernel left, for species s, the number of particles of each cell at the new
-// positions (cnt) and each particle's rank among the particles of its new cell.  Round r of
-// a tile holds the rank-r particle of every cell with more than r particles, in cell order,
-// so the particle of rank r in local cell lc goes to
-//   tile start + sum over cells of min(count, r) + #{cells c < lc with count > r};
-// the first two terms come from a per-tile round table.  Ranks of SORT_RCAP and beyond go
-// to an overflow tail of the tile (order there unspecified).
+// The particle kernel left, for each species, the number of particles of each cell at the new
+// positions (cnt), and a rank word per particle:
+//   slot << 20 | r   the r-th of its tile's particles bound for destination cell `slot` of the
+//                    tile's neighbourhood; base[tile][slot] + r is its rank in that cell,
+//   bit 31 | rank    bound further away (flagged states) or past r's range: its rank itself,
+//   -1               left out (found outside its tile).
+// The ranks of a cell are 0 .. cnt - 1, each once.  Where a particle of rank r in local cell lc
+// goes inside its tile is in the tile's round table (pair_slot).  Ranks of SORT_RCAP and beyond
+// go to an overflow tail of the tile (order there unspecified).
+//
+// Three launches over every species: the round tables, a scan of the tile totals (which also
+// finds the largest tile; an atomic maximum per tile on one address had cost 20 us for 2048
+// tiles) and the permutation.  In small boxes their latency counts, in large ones the
+// permutation's bytes: a rank word read and an entry written per particle, the entries of
+// particles that change tile one by one into partial lines.  us per step, before (five to seven
+// launches a species, cell and completed rank read back, a cleared permutation) and now: 2 x
+// 4.2e6 particles in 128x32x32, 170 and 68; 2 x 6.7e7 in 128^3, 1120 and 790; 2 x 3.3e4 in 16^3,
+// 46 and 16.
 
 struct RankedArgs {
-    KeyGeom G;
-    int64_t ntiles;
+    Geom G;
+    int tsh[3];             // log2 of the tile's sides
     int32_t* cnt;           // per cell (read and cleared by the table kernel)
     RoundEntry* rounds;     // ntiles * SORT_RCAP
     int32_t* tot;           // ntiles + 1: tile totals, scanned into the next tile starts
@@ -416,28 +427,23 @@ struct RankedArgs {
     int32_t* ovf;           // ntiles: overflow cursors
     int32_t* tile_max;      // largest tile population
     const int32_t* start;   // current tile starts (source order)
-    const int32_t* rank;
+    const int32_t* rank;    // n rank words
+    const int32_t* base;    // ntiles * slots
+    int32_t* perm;          // n: perm[slot] = particle
     int64_t n;
     const int32_t* cell;
-    const float* pos[3];
-    const float* u[3];
-    const int64_t* id;
-    int32_t* cell_o;
-    float* pos_o[3];
-    float* u_o[3];
-    int64_t* id_o;
 };
 
 // one wavefront per tile: lane = local cell
 __device__ __forceinline__ void round_table_tile(const RankedArgs& A, int64_t t) {
     const int lane = threadIdx.x & 63;
-    if (t >= A.ntiles) return;
-    const KeyGeom& G = A.G;
+    const Geom& G = A.G;
+    if (t >= G.ntiles) return;
     const int ti = (int)(t % G.nt[0]), tj = (int)((t / G.nt[0]) % G.nt[1]), tk = (int)(t / ((int64_t)G.nt[0] * G.nt[1]));
-    const int li = lane % G.t[0], lj = (lane / G.t[0]) % G.t[1], lk = lane / (G.t[0] * G.t[1]);
+    const int li = lane & (G.t[0] - 1), lj = (lane >> A.tsh[0]) & (G.t[1] - 1), lk = lane >> (A.tsh[0] + A.tsh[1]);
     const int i = ti * G.t[0] + li, j = tj * G.t[1] + lj, k = tk * G.t[2] + lk;
     int c = 0;
-    if (i < G.n[0] && j < G.n[1] && k < G.n[2]) {
+    if (lk < G.t[2] && i < G.n[0] && j < G.n[1] && k < G.n[2]) {
         const int64_t g = (int64_t)i + (int64_t)G.n[0] * (j + (int64_t)G.n[1] * k);
         c = A.cnt[g];
         A.cnt[g] = 0;
@@ -458,122 +464,215 @@ __device__ __forceinline__ void round_table_tile(const RankedArgs& A, int64_t t)
         A.rtot[t] = intable;
         A.nchunk[t] = nchunk;
         A.ovf[t] = 0;
-        // one address for every tile: read first (the value only grows, so a stale read
-        // can only cause an unneeded atomic), so that few of the atomics are issued
-        if (tot > *(volatile int32_t*)A.tile_max) atomicMax(A.tile_max, tot);
-        if (t == A.ntiles - 1) A.tot[A.ntiles] = 0;
     }
 }
 
-__global__ void __launch_bounds__(256) k_round_tables(RankedArgs A) {
-    round_table_tile(A, (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6));
+// Exclusive scan of data[0..n) in place by one workgroup of SCAN1_BS threads: four entries a
+// thread at a time, the next ones in flight meanwhile.  Returns the total and the largest entry
+// (to every thread).
+constexpr int SCAN1_BS = 1024;
+
+__device__ __forceinline__ void scan_workgroup(int32_t* data, int64_t n, int32_t& total, int32_t& largest) {
+    __shared__ int32_t wsum[2][SCAN1_BS / 64];
+    __shared__ int32_t wmax[SCAN1_BS / 64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int32_t carry = 0, mx = 0;
+    int32_t v[4], nx[4];
+    auto load = [&](int64_t base, int32_t* x) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int64_t q = base + 4 * (int64_t)threadIdx.x + e;
+            x[e] = q < n ? data[q] : 0;
+        }
+    };
+    load(0, v);
+    int buf = 0;
+    for (int64_t base = 0; base < n; base += 4 * SCAN1_BS, buf ^= 1) {
+        load(base + 4 * SCAN1_BS, nx);
+        const int32_t sum = v[0] + v[1] + v[2] + v[3];
+        int32_t incl = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int32_t y = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += y;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) mx = v[e] > mx ? v[e] : mx;
+        if (lane == 63) wsum[buf][wave] = incl;
+        __syncthreads();  // two buffers: the next round writes the other one
+        int32_t before = 0, all = 0;
+#pragma unroll
+        for (int w = 0; w < SCAN1_BS / 64; ++w) {
+            const int32_t s = wsum[buf][w];
+            before += w < wave ? s : 0;
+            all += s;
+        }
+        int32_t run = carry + before + incl - sum;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int64_t q = base + 4 * (int64_t)threadIdx.x + e;
+            if (q < n) data[q] = run;
+            run += v[e];
+            v[e] = nx[e];
+        }
+        carry += all;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const int32_t y = __shfl_xor(mx, o, 64);
+        mx = y > mx ? y : mx;
+    }
+    if (lane == 0) wmax[wave] = mx;
+    __syncthreads();
+    for (int w = 0; w < SCAN1_BS / 64; ++w) mx = wmax[w] > mx ? wmax[w] : mx;
+    total = carry;
+    largest = mx;
 }
 
-// Destination slots of PERM_PER particles per thread, p = p0 + 256 k below pend: the table
-// position of rank r in the new cell's tile (tot holds the next tile starts), or -1 for a
-// flagged particle (negative rank) and for inconsistent counts (flagged state: never past the
-// tile).  Every load of every particle is issued before any result is used, so the
-// dependent loads of several particles are in flight together.  Ranks past the round table
-// take slots at the end of their tile with one atomic per wavefront and tile, lanes in lane
-// order (bunched plasmas put hundreds of particles in one cell).  Called by whole wavefronts.
+// Next tile starts and the largest tile population.  The ranks fill every slot below the total;
+// the slots past it (particles left out) hold no particle.
+__device__ __forceinline__ void ranked_scan(const RankedArgs& A) {
+    int32_t total, largest;
+    scan_workgroup(A.tot, A.G.ntiles, total, largest);
+    if (threadIdx.x == 0) {
+        A.tot[A.G.ntiles] = total;
+        *A.tile_max = largest;
+    }
+    for (int64_t q = total + (int64_t)threadIdx.x; q < A.n; q += SCAN1_BS) A.perm[q] = -1;
+}
+
+// What a particle bound for one destination cell needs: the cell's tile and place in it, the
+// tile's next range, whole chunks and table total, and the rank the source tile starts from.
+struct DestCell {
+    int32_t tile_lc;  // tile << 6 | local cell
+    int32_t d0, nd;
+    int32_t nchunk, rtot;
+    int32_t base;
+};
+
+__device__ __forceinline__ DestCell dest_cell(const RankedArgs& A, int gx, int gy, int gz, int32_t base) {
+    const Geom& G = A.G;
+    const int tx = gx >> A.tsh[0], ty = gy >> A.tsh[1], tz = gz >> A.tsh[2];
+    const int32_t t = tx + G.nt[0] * (ty + G.nt[1] * tz);
+    const int lc = (gx & (G.t[0] - 1)) + ((gy & (G.t[1] - 1)) << A.tsh[0]) + ((gz & (G.t[2] - 1)) << (A.tsh[0] + A.tsh[1]));
+    DestCell c;
+    c.tile_lc = (t << 6) | lc;
+    c.d0 = A.tot[t];
+    c.nd = A.tot[t + 1] - c.d0;
+    c.nchunk = A.nchunk[t];
+    c.rtot = A.rtot[t];
+    c.base = base;
+    return c;
+}
+
+// perm[slot] = particle for the particles of source tile T (one workgroup per tile).  The tile's
+// destination cells -- a few hundred, against thousands of particles -- are looked up once, in
+// LDS; a particle then takes one load of its rank word and one of its round-table entry.  Most
+// particles stay in the tile: their entries are collected in an LDS image of T's next range and
+// written out in order (entries that particles from neighbouring tiles fill are written by those
+// tiles' workgroups, directly); the rest, and every entry of a range larger than the image, are
+// written directly.  Each thread issues the loads of PERM_PER particles before it uses any.
+// Ranks past the round table take slots at the end of their tile with one atomic per wavefront
+// and tile, lanes in lane order (bunched plasmas put hundreds of particles in one cell).
 constexpr int PERM_PER = 4;
 constexpr int PERM_BLOCK = 256 * PERM_PER;
-
-__device__ __forceinline__ void ranked_slots(const RankedArgs& A, int64_t p0, int64_t pend, int32_t pos[PERM_PER]) {
-    int32_t r[PERM_PER], c[PERM_PER], t[PERM_PER], lim[PERM_PER];
-#pragma unroll
-    for (int k = 0; k < PERM_PER; ++k) {
-        const int64_t p = p0 + k * 256;
-        const bool v = p < pend;
-        r[k] = v ? A.rank[p] : -1;
-        c[k] = v ? A.cell[p] : 0;
-    }
-    // the table reads of every particle, issued together and unconditionally (a particle
-    // without a slot reads its tile's first entries and ignores them), then the slots
-    int32_t lc[PERM_PER], base[PERM_PER], nch[PERM_PER], rt[PERM_PER];
-    RoundEntry e[PERM_PER];
-#pragma unroll
-    for (int k = 0; k < PERM_PER; ++k) {
-        const int32_t key = key_cell(A.G, r[k] < 0 ? 0 : c[k]);
-        t[k] = key / TILE_CELLS;
-        lc[k] = key % TILE_CELLS;
-    }
-#pragma unroll
-    for (int k = 0; k < PERM_PER; ++k) {
-        base[k] = A.tot[t[k]];
-        lim[k] = A.tot[t[k] + 1];
-        nch[k] = A.nchunk[t[k]];
-        rt[k] = A.rtot[t[k]];
-        e[k] = A.rounds[(int64_t)t[k] * SORT_RCAP + (r[k] >= 0 && r[k] < SORT_RCAP ? r[k] : 0)];
-    }
-#pragma unroll
-    for (int k = 0; k < PERM_PER; ++k) {
-        // computed for every particle and selected (no branch the table reads could sink into)
-        const bool in_table = r[k] >= 0 && r[k] < SORT_RCAP;
-        const int32_t ps = pair_slot(e[k], nch[k], in_table ? r[k] : 0, lc[k]);
-        pos[k] = r[k] < 0 ? -1 : base[k] + (in_table ? ps : rt[k]);
-    }
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int k = 0; k < PERM_PER; ++k) {
-        const bool over = r[k] >= SORT_RCAP;
-        uint64_t todo = __ballot(over);
-        while (todo) {
-            const int leader = __ffsll((unsigned long long)todo) - 1;
-            const int32_t lt = __shfl(t[k], leader, 64);
-            const uint64_t grp = __ballot(over && t[k] == lt) & todo;
-            int32_t base = 0;
-            if (lane == leader) base = atomicAdd(&A.ovf[lt], (int32_t)__popcll(grp));
-            base = __shfl(base, leader, 64);
-            if (over && t[k] == lt) pos[k] += base + (int32_t)__popcll(grp & ((1ull << lane) - 1ull));
-            todo &= ~grp;
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < PERM_PER; ++k)
-        if (r[k] < 0 || pos[k] >= lim[k]) pos[k] = -1;
-}
-
-// perm[slot] = particle for the particles of source tile T (one workgroup per tile).  Most
-// of them stay in the tile: their entries are collected in an LDS image of T's destination
-// range and written out in order (entries that particles from neighbouring tiles fill are
-// written by those tiles' workgroups, directly); the rest, and every entry of a destination
-// range larger than the image, are written directly.
 constexpr int PERM_IMG = 4096;
 
-__device__ __forceinline__ void ranked_perm_tile(const RankedArgs& A, int32_t* perm, int64_t T, int32_t* img) {
-    if (T >= A.ntiles) return;
+__device__ __forceinline__ void ranked_perm_tile(const RankedArgs& A, int64_t T, int32_t* lds) {
+    const Geom& G = A.G;
+    if (T >= G.ntiles) return;
     const int32_t ss = A.start[T], se = A.start[T + 1];
-    const int32_t d0 = A.tot[T];
-    const int32_t nd = A.tot[T + 1] - d0;
+    const int32_t d0 = A.tot[T], nd = A.tot[T + 1] - d0;
     const bool staged = nd <= PERM_IMG;
+    int32_t* img = lds;
+    DestCell* dest = (DestCell*)(lds + PERM_IMG);
     if (staged)
         for (int32_t q = threadIdx.x; q < nd; q += blockDim.x) img[q] = -1;
+    const int e0 = G.dest_ext(0), e1 = G.dest_ext(1), slots = e0 * e1 * G.dest_ext(2);
+    const int ox = (int)(T % G.nt[0]) * G.t[0], oy = (int)((T / G.nt[0]) % G.nt[1]) * G.t[1],
+              oz = (int)(T / ((int64_t)G.nt[0] * G.nt[1])) * G.t[2];
+    if (se > ss)
+        for (int q = threadIdx.x; q < slots; q += blockDim.x) {
+            const int z = q / (e0 * e1), r = q - z * e0 * e1, y = r / e0, x = r - y * e0;
+            dest[q] = dest_cell(A, e0 == 1 ? 0 : wrap_near(ox + x - DEST_HALO, G.n[0]),
+                                e1 == 1 ? 0 : wrap_near(oy + y - DEST_HALO, G.n[1]),
+                                G.n[2] == 1 ? 0 : wrap_near(oz + z - DEST_HALO, G.n[2]), A.base[T * slots + q]);
+        }
     __syncthreads();
+    const int lane = threadIdx.x & 63;
     for (int64_t b = ss; b < se; b += PERM_BLOCK) {
-        int32_t pos[PERM_PER];
-        ranked_slots(A, b + threadIdx.x, se, pos);
+        int32_t w[PERM_PER], r[PERM_PER];
+        DestCell c[PERM_PER];
+        RoundEntry e[PERM_PER];
 #pragma unroll
         for (int k = 0; k < PERM_PER; ++k) {
-            if (pos[k] < 0) continue;
+            const int64_t p = b + threadIdx.x + k * 256;
+            w[k] = p < se ? A.rank[p] : -1;
+        }
+#pragma unroll
+        for (int k = 0; k < PERM_PER; ++k) {
+            c[k] = dest[w[k] >= 0 ? w[k] >> 20 : 0];
+            r[k] = w[k] >= 0 ? c[k].base + (w[k] & 0xFFFFF) : -1;
+            if (w[k] < -1) {  // its rank itself, in a cell that may lie anywhere
+                const int32_t g = A.cell[b + threadIdx.x + k * 256];
+                const bool in = g >= 0 && g < G.ncell;
+                const int gx = in ? g % G.n[0] : 0, gr = in ? g / G.n[0] : 0;
+                c[k] = dest_cell(A, gx, gr % G.n[1], gr / G.n[1], 0);
+                r[k] = w[k] & 0x7FFFFFFF;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < PERM_PER; ++k)
+            e[k] = A.rounds[(int64_t)(c[k].tile_lc >> 6) * SORT_RCAP + (r[k] >= 0 && r[k] < SORT_RCAP ? r[k] : 0)];
+        int32_t pos[PERM_PER];
+#pragma unroll
+        for (int k = 0; k < PERM_PER; ++k) {
+            // computed for every particle and selected (no branch the table reads could sink into)
+            const bool in_table = r[k] >= 0 && r[k] < SORT_RCAP;
+            const int32_t ps = pair_slot(e[k], c[k].nchunk, in_table ? r[k] : 0, c[k].tile_lc & 63);
+            pos[k] = in_table ? ps : c[k].rtot;
+        }
+#pragma unroll
+        for (int k = 0; k < PERM_PER; ++k) {
+            const bool over = r[k] >= SORT_RCAP;
+            const int32_t t = c[k].tile_lc >> 6;
+            uint64_t todo = __ballot(over);
+            while (todo) {
+                const int leader = __ffsll((unsigned long long)todo) - 1;
+                const int32_t lt = __shfl(t, leader, 64);
+                const uint64_t grp = __ballot(over && t == lt) & todo;
+                int32_t first = 0;
+                if (lane == leader) first = atomicAdd(&A.ovf[lt], (int32_t)__popcll(grp));
+                first = __shfl(first, leader, 64);
+                if (over && t == lt) pos[k] += first + (int32_t)__popcll(grp & ((1ull << lane) - 1ull));
+                todo &= ~grp;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < PERM_PER; ++k) {
+            if (r[k] < 0 || pos[k] >= c[k].nd) continue;
             const int32_t p = (int32_t)(b + threadIdx.x + k * 256);
-            const int32_t q = pos[k] - d0;
-            if (staged && q >= 0 && q < nd)
-                img[q] = p;
+            if (staged && (c[k].tile_lc >> 6) == (int32_t)T)
+                img[pos[k]] = p;
             else
-                perm[pos[k]] = p;
+                A.perm[c[k].d0 + pos[k]] = p;
         }
     }
     __syncthreads();
     if (staged)
         for (int32_t q = threadIdx.x; q < nd; q += blockDim.x) {
             const int32_t v = img[q];
-            if (v >= 0) perm[d0 + q] = v;
+            if (v >= 0) A.perm[d0 + q] = v;
         }
+}
+
+size_t sort_perm_lds(const pp_run* r) {
+    return PERM_IMG * sizeof(int32_t) + (size_t)r->g.dest_slots() * sizeof(DestCell);
 }
 
 // ---- exclusive scan of int32, in place ------------------------------------------------
 constexpr int SCAN_BS = 256, SCAN_PER = 8, SCAN_CHUNK = SCAN_BS * SCAN_PER;
+constexpr int64_t SCAN_ONE_MAX = 32768;  // longest scan that one workgroup does
 
 __global__ void __launch_bounds__(SCAN_BS) k_scan_chunks(int32_t* data, int64_t n, int32_t* sums) {
     __shared__ int32_t sh[2][SCAN_BS];
@@ -616,6 +715,11 @@ __global__ void __launch_bounds__(SCAN_BS) k_scan_add(int32_t* data, int64_t n, 
     }
 }
 
+__global__ void __launch_bounds__(SCAN1_BS) k_scan_one(int32_t* data, int64_t n) {
+    int32_t total, largest;
+    scan_workgroup(data, n, total, largest);
+}
+
 int64_t scan_tmp_size(int64_t n) {
     int64_t tot = 0;
     while (n > 1) {
@@ -626,6 +730,10 @@ int64_t scan_tmp_size(int64_t n) {
 }
 
 static void scan_inplace(int32_t* data, int64_t n, int32_t* tmp, hipStream_t st) {
+    if (n <= SCAN_ONE_MAX) {  // one launch instead of three
+        hipLaunchKernelGGL(k_scan_one, dim3(1), dim3(SCAN1_BS), 0, st, data, n);
+        return;
+    }
     const int64_t nb = (n + SCAN_CHUNK - 1) / SCAN_CHUNK;
     hipLaunchKernelGGL(k_scan_chunks, dim3((unsigned)nb), dim3(SCAN_BS), 0, st, data, n, tmp);
     if (nb > 1) {
@@ -651,109 +759,69 @@ static KeyGeom key_geom(const pp_run* r) {
     return G;
 }
 
-// ---- batched ranked sort of one species slot over several runs -----------------------------
-struct SortDesc {
-    RankedArgs A;
-    int32_t* perm;  // n slots: the destination order, perm[slot] = particle
-};
+// ---- launches of the ranked sort: all species of a run, or of all runs of a batch ----------
+enum SortPhase { SP_TABLES = 0, SP_SCAN = 1, SP_PERM = 2 };
 
-// reset: tile maximum and perm = -1; tables: round tables; scan: next tile starts;
-// perm: every particle's slot
-enum SortPhase { SP_RESET = 0, SP_TABLES = 1, SP_SCAN = 2, SP_PERM = 3 };
-
-// whole-segment exclusive scan by one workgroup (segments are short: one entry per tile)
-__device__ __forceinline__ void scan_segment(int32_t* data, int64_t n) {
-    __shared__ int32_t sh[256];
-    __shared__ int32_t carry;
-    if (threadIdx.x == 0) carry = 0;
-    __syncthreads();
-    for (int64_t base = 0; base < n; base += 256) {
-        const int64_t q = base + threadIdx.x;
-        const int32_t v = q < n ? data[q] : 0;
-        sh[threadIdx.x] = v;
-        __syncthreads();
-        for (int off = 1; off < 256; off <<= 1) {
-            const int32_t x = (int)threadIdx.x >= off ? sh[threadIdx.x - off] : 0;
-            __syncthreads();
-            sh[threadIdx.x] += x;
-            __syncthreads();
-        }
-        const int32_t incl = sh[threadIdx.x];
-        if (q < n) data[q] = carry + incl - v;
-        __syncthreads();
-        if (threadIdx.x == 255) carry += incl;
-        __syncthreads();
-    }
+template <int PHASE>
+__device__ __forceinline__ void sort_phase(const RankedArgs& A, int64_t blk, int32_t* lds) {
+    if constexpr (PHASE == SP_TABLES)
+        round_table_tile(A, blk * 4 + (threadIdx.x >> 6));
+    else if constexpr (PHASE == SP_SCAN)
+        ranked_scan(A);
+    else
+        ranked_perm_tile(A, blk, lds);
 }
 
-__global__ void __launch_bounds__(256) k_sort_batch(const SortDesc* __restrict__ T, const int64_t* __restrict__ prefix,
-                                                    int nseg, int phase) {
+constexpr int sort_threads(int phase) { return phase == SP_SCAN ? SCAN1_BS : 256; }
+
+struct SortArgs {
+    RankedArgs sp[PP_MAX_SPECIES];
+};
+
+template <int PHASE>
+__global__ void __launch_bounds__(sort_threads(PHASE)) k_sort(SortArgs S) {
+    extern __shared__ int32_t lds_sort[];
+    sort_phase<PHASE>(S.sp[blockIdx.y], blockIdx.x, lds_sort);
+}
+
+template <int PHASE>
+__global__ void __launch_bounds__(sort_threads(PHASE)) k_sort_batch(const RankedArgs* __restrict__ T,
+                                                                    const int64_t* __restrict__ prefix, int nseg) {
+    extern __shared__ int32_t lds_sort[];
     const int64_t b = blockIdx.x;
     const int r = find_segment(prefix, nseg, b);
     if (r < 0) return;
-    const RankedArgs& A = T[r].A;
-    const int64_t blk = b - prefix[r];
-    const int64_t p = blk * 256 + threadIdx.x;
-    switch (phase) {
-    case SP_RESET:
-        if (p == 0) *A.tile_max = 0;
-        if (p < A.n) T[r].perm[p] = -1;
-        break;
-    case SP_TABLES:
-        round_table_tile(A, blk * 4 + (threadIdx.x >> 6));
-        break;
-    case SP_SCAN:
-        scan_segment(A.tot, A.ntiles + 1);
-        break;
-    case SP_PERM: {
-        __shared__ int32_t img[PERM_IMG];
-        ranked_perm_tile(A, T[r].perm, blk, img);
-        break;
-    }
-    default:
-        break;
-    }
+    sort_phase<PHASE>(T[r], b - prefix[r], lds_sort);
 }
 
-static void ranked_args(const pp_run* r, int s, RankedArgs* A) {
+void sort_desc(const pp_run* r, int s, RankedArgs* A) {
     const Species& S = r->sp[s];
     const int64_t nt = r->g.ntiles;
-    A->G = key_geom(r);
-    A->ntiles = nt;
+    A->G = r->g;
+    for (int d = 0; d < 3; ++d) {
+        A->tsh[d] = 0;
+        while ((1 << A->tsh[d]) < r->g.t[d]) ++A->tsh[d];
+    }
     A->cnt = S.cell_cnt;
-    A->rounds = r->rounds;
+    A->rounds = S.rounds;
     A->tot = S.offsets_next;
-    A->rtot = r->sort_cursor;
-    A->ovf = r->sort_cursor + nt;
-    A->nchunk = r->sort_cursor + 2 * nt;
+    A->rtot = r->sort_cursor + 3 * nt * s;  // 64 entries per tile, 3 used by each of 8 species
+    A->ovf = A->rtot + nt;
+    A->nchunk = A->rtot + 2 * nt;
     A->tile_max = r->tile_max + s;
     A->start = S.offsets;
     A->rank = S.rank;
+    A->base = S.rank_base;
+    A->perm = S.perm;
     A->n = S.n;
     A->cell = S.cur.cell;
-    A->id = S.cur.id;
-    A->cell_o = S.cur.cell_alt;
-    A->id_o = S.cur.id ? S.cur.id_alt : nullptr;
-    for (int d = 0; d < 3; ++d) {
-        A->pos[d] = (const float*)S.cur.pos[d];
-        A->u[d] = (const float*)S.cur.u[d];
-        A->pos_o[d] = (float*)S.cur.pos_alt[d];
-        A->u_o[d] = (float*)S.cur.u_alt[d];
-    }
 }
 
-void sort_desc(const pp_run* r, int s, SortDesc* D) {
-    ranked_args(r, s, &D->A);
-    D->perm = r->sp[s].perm;
-}
-
-size_t sort_desc_size() { return sizeof(SortDesc); }
+size_t sort_desc_size() { return sizeof(RankedArgs); }
 
 // Blocks each phase needs for one descriptor.
 void sort_desc_blocks(const pp_run* r, int s, int64_t blocks[SORT_BATCH_PHASES]) {
     const int64_t nt = r->g.ntiles;
-    const int64_t pb = (r->sp[s].n + 255) / 256;
-    blocks[SP_RESET] = pb > 0 ? pb : 1;
     blocks[SP_TABLES] = (nt + 3) / 4;
     blocks[SP_SCAN] = 1;
     blocks[SP_PERM] = r->sp[s].n > 0 ? nt : 0;
@@ -761,13 +829,16 @@ void sort_desc_blocks(const pp_run* r, int s, int64_t blocks[SORT_BATCH_PHASES])
 
 // prefixes: one array of nseg + 1 block prefixes (device) per phase, totals: blocks per phase
 hipError_t launch_sort_batch(const void* table, const int64_t* const prefixes[SORT_BATCH_PHASES],
-                             const int64_t totals[SORT_BATCH_PHASES], int nseg, hipStream_t st) {
+                             const int64_t totals[SORT_BATCH_PHASES], int nseg, size_t perm_lds, hipStream_t st) {
     if (nseg == 0) return hipSuccess;
-    const SortDesc* T = (const SortDesc*)table;
-    for (int ph = 0; ph < SORT_BATCH_PHASES; ++ph) {
-        if (totals[ph] == 0) continue;
-        hipLaunchKernelGGL(k_sort_batch, dim3((unsigned)totals[ph]), dim3(256), 0, st, T, prefixes[ph], nseg, ph);
-    }
+    const RankedArgs* T = (const RankedArgs*)table;
+    hipLaunchKernelGGL(k_sort_batch<SP_TABLES>, dim3((unsigned)totals[SP_TABLES]), dim3(sort_threads(SP_TABLES)), 0, st, T,
+                       prefixes[SP_TABLES], nseg);
+    hipLaunchKernelGGL(k_sort_batch<SP_SCAN>, dim3((unsigned)totals[SP_SCAN]), dim3(sort_threads(SP_SCAN)), 0, st, T,
+                       prefixes[SP_SCAN], nseg);
+    if (totals[SP_PERM] > 0)
+        hipLaunchKernelGGL(k_sort_batch<SP_PERM>, dim3((unsigned)totals[SP_PERM]), dim3(sort_threads(SP_PERM)), perm_lds,
+                           st, T, prefixes[SP_PERM], nseg);
     return hipGetLastError();
 }
 
@@ -798,14 +869,6 @@ void sort_enqueued(pp_run* r, int s) {
     S.ranked = false;
     S.sorted = true;
     S.pending = S.n > 0;
-}
-
-// Destination slot of every particle, as a permutation: perm[slot] = particle (slots no
-// particle goes to keep -1).  The particle kernel then reads through it and writes the
-// new order, so the particles move once per step, together with their update.
-__global__ void __launch_bounds__(256) k_ranked_perm(RankedArgs A, int32_t* perm) {
-    __shared__ int32_t img[PERM_IMG];
-    ranked_perm_tile(A, perm, blockIdx.x, img);
 }
 
 // out[q] = in[perm[q]] for every attribute (the move a pending permutation stands for)
@@ -865,20 +928,26 @@ hipError_t materialize(pp_run* r, int s) {
     return hipSuccess;
 }
 
-static hipError_t sort_ranked(pp_run* r, int s) {
-    RankedArgs A;
-    ranked_args(r, s, &A);
-    Species& S = r->sp[s];
-    const int64_t nt = r->g.ntiles;
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(1), 0, r->stream, r->tile_max + s, (int64_t)1, 0);
-    hipLaunchKernelGGL(k_round_tables, dim3((unsigned)((nt + 3) / 4)), dim3(256), 0, r->stream, A);
-    scan_inplace(A.tot, nt + 1, r->scan_tmp, r->stream);
-    if (S.n > 0) {
-        hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(S.n, 256)), dim3(256), 0, r->stream, S.perm, S.n, -1);
-        hipLaunchKernelGGL(k_ranked_perm, dim3((unsigned)nt), dim3(256), 0, r->stream, A, S.perm);
+// The ranked sort of the species in mask, together.
+static hipError_t sort_ranked(pp_run* r, unsigned mask) {
+    SortArgs A;
+    unsigned ns = 0;
+    bool any = false;
+    for (int s = 0; s < PP_MAX_SPECIES; ++s) {
+        if (!(mask & (1u << s))) continue;
+        sort_desc(r, s, &A.sp[ns++]);
+        any = any || r->sp[s].n > 0;
     }
+    if (ns == 0) return hipSuccess;
+    const int64_t nt = r->g.ntiles;
+    hipLaunchKernelGGL(k_sort<SP_TABLES>, dim3((unsigned)((nt + 3) / 4), ns), dim3(sort_threads(SP_TABLES)), 0, r->stream, A);
+    hipLaunchKernelGGL(k_sort<SP_SCAN>, dim3(1, ns), dim3(sort_threads(SP_SCAN)), 0, r->stream, A);
+    if (any)
+        hipLaunchKernelGGL(k_sort<SP_PERM>, dim3((unsigned)nt, ns), dim3(sort_threads(SP_PERM)), sort_perm_lds(r),
+                           r->stream, A);
     hipError_t e = hipGetLastError();
-    sort_enqueued(r, s);
+    for (int s = 0; s < PP_MAX_SPECIES; ++s)
+        if (mask & (1u << s)) sort_enqueued(r, s);
     return e;
 }
 
@@ -958,12 +1027,22 @@ static hipError_t sort_species(pp_run* r, int s) {
 }
 
 hipError_t launch_sort(pp_run* r, int s) {
-    if (r->p.precision == PP_PREC_FP32_SPLIT) {
+    const bool split = r->p.precision == PP_PREC_FP32_SPLIT;
+    if (split) {
         hipError_t e = materialize(r, s);  // a sort of a sort: apply the pending order first
         if (e != hipSuccess) return e;
-        return r->sp[s].ranked ? sort_ranked(r, s) : sort_species<float>(r, s);
     }
-    return sort_species<double>(r, s);
+    unsigned ranked = 0;
+    for (int k = 0; k < PP_MAX_SPECIES; ++k) {
+        if ((s >= 0 && k != s) || !r->sp[k].active) continue;
+        if (split && r->sp[k].ranked) {
+            ranked |= 1u << k;
+            continue;
+        }
+        hipError_t e = split ? sort_species<float>(r, k) : sort_species<double>(r, k);
+        if (e != hipSuccess) return e;
+    }
+    return sort_ranked(r, ranked);
 }
 
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st) {

@@ -79,3 +79,35 @@ def test_field_step_matches_oracle_for_any_sweep_count(ppm, orc, n, order):
         assert rel_inf(Eg, ref.E) < 1e-12 and rel_inf(Bg, ref.B) < 1e-12, (dt, sweeps)
         run.close()
     assert seen == {1, 2, 3} or max(n) == 1
+
+
+@pytest.mark.parametrize("n,O", [((9, 8, 5), 3), ((17, 9, 1), 2), ((64, 1, 1), 3), ((18, 2, 2), 2), ((3, 5, 8), 3)])
+def test_species_sorted_one_by_one_and_together(ppm, orc, n, O):
+    """Three species, one of them empty and one with 700 particles in a cell, sorted together, one
+    by one, and one of them twice: the current of the next push is an exact sum over the same
+    particles, so it has to come out bit for bit the same."""
+    species, E, B = random_state(orc, n, 5, seed=3, uth=0.4, nspecies=3, pair=False)
+    species[1] = dict(species[1], pos=np.zeros((3, 0)), u=np.zeros((3, 0)))
+    many = 0.4 * np.array(n)[:, None] + np.random.default_rng(1).uniform(0, 0.3, (3, 700))
+    species[2] = dict(species[2], pos=np.concatenate([species[2]["pos"], many], 1),
+                      u=np.concatenate([species[2]["u"], np.full((3, 700), 0.1)], 1))
+    from paper_1211_4575_amd import inputs as I
+    split = []
+    for s in species:
+        cell, off = I.to_split(s["pos"], n, origin=I.split_origin(O))
+        split.append(dict(q=s["q"], m=s["m"], w=s["w"], cell=cell, off=off, u=s["u"].astype(np.float32)))
+    kw = dict(n=n, dt=0.35, shape_order=O, field_order=4, relax_max_iter=100, precision=ppm.PP_PREC_FP32_SPLIT)
+    out = []
+    for order in ((-1,), (2, 0, 1), (2, -1), (0, 0, -1)):
+        run = ppm.Run(ppm.make_params(**kw), split, E=E, B=B)
+        for _ in range(3):
+            run.gather_push_deposit()
+            for s in order:
+                run.sort(s)
+        run.gather_push_deposit()
+        assert run.diagnostics().flags == 0
+        assert [len(np.unique(run.particles(s)["id"])) for s in range(3)] == [s["u"].shape[1] for s in split]
+        out.append(run.fields()[2])
+        run.close()
+    for J in out[1:]:
+        assert np.array_equal(J, out[0])
