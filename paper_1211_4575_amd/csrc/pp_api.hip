@@ -102,7 +102,6 @@ static void release(pp_run* r) {
     f(r->dacc);
     f(r->Jq);
     f(r->tile_max);
-    f(r->qscale);
     for (auto& S : r->rs) f(S.omega);
     for (int s = 0; s < PP_MAX_SPECIES; ++s) {
         f(r->sp[s].cell_cnt);
@@ -162,7 +161,7 @@ static size_t internal_bytes(const pp_params* p, const Geom& g, int64_t nmax, in
     b += sizeof(int32_t) + ((size_t)diag_acc_count() + 8) * sizeof(double);
     b += (p->time_order == 4 ? 3 : 1) * ((size_t)p->relax_max_iter + 2) * sizeof(double);  // relaxation weights
     if (p->precision == PP_PREC_FP32_SPLIT) {
-        b += n3 * sizeof(long long) + PP_MAX_SPECIES * sizeof(int32_t) + sizeof(double);
+        b += n3 * sizeof(long long) + PP_MAX_SPECIES * sizeof(int32_t);
         b += 2 * (size_t)nmax * sizeof(int32_t);                           // sort scratch
         // per species: cell counts, particle ranks and sort permutation, next tile starts, round
         // tables and the ranks the particles of each tile start from
@@ -225,7 +224,8 @@ pp_status pp_create(const pp_params* params, const pp_mesh* mesh, void* hip_stre
     r->nrs = params->time_order == 4 ? 3 : 1;
     for (int k = 0; k < r->nrs; ++k) okk = okk && dmalloc(&r->rs[k].omega, (size_t)params->relax_max_iter + 2);
     if (params->precision == PP_PREC_FP32_SPLIT) {
-        okk = okk && dmalloc(&r->Jq, n3) && dmalloc(&r->tile_max, PP_MAX_SPECIES) && dmalloc(&r->qscale, 1) &&
+        okk = okk && dmalloc(&r->Jq, n3) && dmalloc(&r->tile_max, PP_MAX_SPECIES) &&
+              ok(launch_fill((double*)r->Jq, (int64_t)n3, 0.0, r->stream), "fill") &&
               ok(hipMemset(r->tile_max, 0, PP_MAX_SPECIES * sizeof(int32_t)), "hipMemset");
     }
     if (okk && params->field_order > 2) {
@@ -339,15 +339,15 @@ pp_status pp_gather_push_deposit(pp_run* r) {
     for (int s = 0; s < PP_MAX_SPECIES; ++s)
         if (split && r->sp[s].active && !r->sp[s].sorted) return PP_E_STATE;
     if (flush_timing(r) != PP_OK) return PP_E_HIP;
-    double* target = uses_line_solve(r) ? r->J2 : r->mesh.J;
+    double* target = uses_line_solve(r) ? r->J2 : r->mesh.J;  // FP64 form
     hipError_t e = hipSuccess;
-    if (!split) {  // the split kernel overwrites its target
+    if (!split) {
         e = launch_fill(target, 3 * r->g.ncell, 0.0, r->stream);
         if (!ok(e, "fill")) return PP_E_HIP;
     }
     if (r->timing && !ok(hipEventRecord(r->ev0, r->stream), "hipEventRecord")) return PP_E_HIP;
     if (split) {
-        e = launch_gpd32(r, target);
+        e = launch_gpd32(r);
         if (!ok(e, "gather_push_deposit")) return PP_E_HIP;
         for (int s = 0; s < PP_MAX_SPECIES; ++s) {  // the kernel wrote the pending order
             Species& S = r->sp[s];
@@ -377,7 +377,7 @@ pp_status pp_gather_push_deposit(pp_run* r) {
             r->sp[s].ranked = true;  // the kernel counted the new cells for the next sort
         }
     if (uses_line_solve(r)) {
-        e = launch_line_solve(r, r->J2, r->mesh.J);
+        e = launch_line_solve(r);
         if (!ok(e, "line_solve")) return PP_E_HIP;
     }
     r->step += 1;

@@ -171,7 +171,6 @@ pp_status batch_step(pp_batch* b, TableTarget target) {
     int max_sweeps = 0, min_sweeps = 0;
     for (int i = 0; i < n; ++i) {
         pp_run* r = b->runs[i];
-        double* target = uses_line_solve(r) ? r->J2 : r->mesh.J;
         gpd32_fill_args(r, (Gpd32Args*)(H + o_gpd + i * gpd32_args_size()));
         for (int s = 0; s < PP_MAX_SPECIES; ++s) {  // the kernel writes the pending order
             Species& S = r->sp[s];
@@ -179,10 +178,10 @@ pp_status batch_step(pp_batch* b, TableTarget target) {
             swap_buffers(S.cur);
             S.pending = false;
         }
-        gpd32_fixed_desc(r, target, (FixedDesc*)(H + o_fix + i * gpd32_fixed_desc_size()));
+        gpd32_fixed_desc(r, (FixedDesc*)(H + o_fix + i * gpd32_fixed_desc_size()));
         field_desc(r, (FieldDesc*)(H + o_field + i * field_desc_size()), n);
         tpre[i + 1] = tpre[i] + r->g.ntiles;
-        fpre[i + 1] = fpre[i] + (3 * r->g.ncell + 255) / 256;
+        fpre[i + 1] = fpre[i] + gpd32_fixed_blocks(r);
         cpre[i + 1] = cpre[i] + field_blocks(r, n);
         max_sweeps = r->jac_sweeps > max_sweeps ? r->jac_sweeps : max_sweeps;
         min_sweeps = i == 0 || r->jac_sweeps < min_sweeps ? r->jac_sweeps : min_sweeps;
@@ -191,8 +190,8 @@ pp_status batch_step(pp_batch* b, TableTarget target) {
     lpre[0] = 0;
     for (int j = 0; j < nl; ++j) {
         pp_run* r = b->runs[line_runs[j]];
-        line_desc(r, r->J2, r->mesh.J, (LineArgs*)(H + o_line + j * line_desc_size()));
-        lpre[j + 1] = lpre[j] + line_blocks(r);
+        line_desc(r, (LineArgs*)(H + o_line + j * line_desc_size()), nl);
+        lpre[j + 1] = lpre[j] + line_blocks(r, nl);
     }
     int64_t* spre[SORT_BATCH_PHASES];
     for (int ph = 0; ph < SORT_BATCH_PHASES; ++ph) {

@@ -320,11 +320,13 @@ __global__ void __launch_bounds__(256) k_rho32(Rho32Args A) {
     }
 }
 
-__global__ void __launch_bounds__(256) k_rho_from_fixed(const unsigned long long* __restrict__ acc, int64_t nc,
+__global__ void __launch_bounds__(256) k_rho_from_fixed(unsigned long long* __restrict__ acc, int64_t nc,
                                                         const double* __restrict__ scale, double* rho) {
     const double inv = 1.0 / *scale;  // exact: a power of two
-    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < nc; q += (int64_t)gridDim.x * blockDim.x)
+    for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < nc; q += (int64_t)gridDim.x * blockDim.x) {
         rho[q] = (double)(long long)acc[q] * inv;
+        acc[q] = 0ull;
+    }
 }
 
 struct DivGeom {
@@ -457,26 +459,24 @@ static hipError_t launch_rho32(pp_run* r, unsigned mask) {
         vol *= A.ext[d];
     }
     A.nc = r->g.ncell;
-    A.acc = (unsigned long long*)r->Jq;  // free between steps: the particle kernel clears it
+    A.acc = (unsigned long long*)r->Jq;  // free and zero between steps, and left so
     A.scale = r->dacc + ACC_RHO_SCALE;
     // every contribution is at most |q w| (the weights of a node are at most 1)
     int e0 = 50 - (int)ceil(log2(qwmax));
     if (e0 > 1000) e0 = 1000;
     hipLaunchKernelGGL(k_rho_scale, dim3(1), dim3(64), 0, r->stream, (const int32_t*)r->tile_max, mask, e0,
                        pending ? 1 : 0, r->dacc + ACC_RHO_SCALE);
-    hipError_t e = launch_fill((double*)r->Jq, A.nc, 0.0, r->stream);  // all-zero bits
-    if (e != hipSuccess) return e;
     const size_t lds = (size_t)vol * sizeof(unsigned long long);
     if (O == 2)
         hipLaunchKernelGGL(k_rho32<2>, dim3((unsigned)r->g.ntiles), dim3(256), lds, r->stream, A);
     else
         hipLaunchKernelGGL(k_rho32<3>, dim3((unsigned)r->g.ntiles), dim3(256), lds, r->stream, A);
-    e = hipGetLastError();
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     int64_t g = (A.nc + 255) / 256;
     if (g > 8192) g = 8192;
     hipLaunchKernelGGL(k_rho_from_fixed, dim3((unsigned)g), dim3(256), 0, r->stream,
-                       (const unsigned long long*)r->Jq, A.nc, (const double*)(r->dacc + ACC_RHO_SCALE), r->rho);
+                       (unsigned long long*)r->Jq, A.nc, (const double*)(r->dacc + ACC_RHO_SCALE), r->rho);
     return hipGetLastError();
 }
 

@@ -2,6 +2,7 @@
 // "enplus1", "EllipticB") and the high-order current line solve (Sec. III.C, eqs.
 // "jj6d", "penta").  Mesh arrays are FP64, x fastest, periodic.
 #include "pp_device.hpp"
+#include "pp_fixed.hpp"
 #include "pp_internal.hpp"
 
 namespace pp {
@@ -872,6 +873,10 @@ struct LineArgs {
     int W[3];
     int64_t nb[3];
     const double* J2;
+    // LDS form of a split run: the fixed-point current, read in J2's place and cleared for the
+    // next step (nullptr: J2)
+    FixedScale scale;
+    unsigned long long* Jq;
     double* J;
 };
 
@@ -905,9 +910,55 @@ __device__ __forceinline__ void line_body(const LineArgs& A, int64_t b) {
 // offset off), into LDS with coalesced loads, then writes J[j] = sum_t coef[t] ext[j + t].
 // x lines are rows (stored line by line, j fastest); y and z lines are taken W consecutive
 // x at a time (stored with the W lines interleaved, x fastest), so loads and stores move
-// whole rows or W-wide row segments.
+// whole rows or W-wide row segments.  A thread takes LINE_OUT consecutive outputs of a line, so
+// an LDS value is read once per LINE_OUT outputs it enters; LINE_OUT is odd, so that the lanes of
+// an x line, LINE_OUT values apart, fall on different banks.  256^3, 25 taps: 0.26 ms for the
+// three components with the fixed-point current read and cleared (0.74 ms for the lines alone
+// with one output per thread, and 0.19 for the passes that converted and cleared the current);
+// 128x32x32: 12 us (23, and 12 for those passes and the scale's own launch).
 constexpr int LINE_LDS_DOUBLES = 4608;  // 36 KiB: 16 lines of 256 cells plus the wrap-around
 constexpr int LINE_BATCH = 8;           // loads per thread in flight while a block fills its lines
+constexpr int LINE_OUT = 5;
+
+typedef const __attribute__((address_space(4))) double const_f64;
+typedef const __attribute__((address_space(1))) double glob_f64;
+typedef __attribute__((address_space(1))) unsigned long long glob_u64;
+
+// LINE_OUT outputs from x[0], x[step], ...; each sum in the order of the taps
+__device__ __forceinline__ void line_taps(const double* x, int step, const_f64* cf, int len, double acc[LINE_OUT]) {
+#pragma unroll
+    for (int o = 0; o < LINE_OUT; ++o) acc[o] = 0.0;
+    if (len < LINE_OUT) {
+        for (int t = 0; t < len; ++t)
+#pragma unroll
+            for (int o = 0; o < LINE_OUT; ++o) acc[o] += cf[t] * x[(t + o) * step];
+        return;
+    }
+#pragma unroll
+    for (int t = 0; t < LINE_OUT - 1; ++t) {
+        const double v = x[t * step];
+#pragma unroll
+        for (int o = 0; o <= t; ++o) acc[o] += cf[t - o] * v;
+    }
+    for (int t = LINE_OUT - 1; t < len; ++t) {
+        const double v = x[t * step];
+#pragma unroll
+        for (int o = 0; o < LINE_OUT; ++o) acc[o] += cf[t - o] * v;
+    }
+#pragma unroll
+    for (int t = 0; t < LINE_OUT - 1; ++t) {
+        const double v = x[(len + t) * step];
+#pragma unroll
+        for (int o = t + 1; o < LINE_OUT; ++o) acc[o] += cf[len + t - o] * v;
+    }
+}
+
+// element c of a kernel argument's array, without an address of it (which would move the
+// arguments to scratch memory)
+template <typename T>
+__device__ __forceinline__ T arg3(const T a[3], int c) {
+    return c == 0 ? a[0] : (c == 1 ? a[1] : a[2]);
+}
 
 __device__ __forceinline__ void line_lds_body(const LineArgs& A, int64_t b, double* e) {
     const FieldGeom& G = A.G;
@@ -922,10 +973,9 @@ __device__ __forceinline__ void line_lds_body(const LineArgs& A, int64_t b, doub
     }
     if (c == 2 && b >= A.nb[2]) return;
     const int n0 = G.n[0], n1 = G.n[1];
-    const int N = G.n[c], W = A.W[c], len = A.len[c], off = A.off[c];
+    const int N = arg3(G.n, c), W = arg3(A.W, c), len = arg3(A.len, c), off = arg3(A.off, c);
     const int ext = N + len - 1;
     const int64_t nc = G.nc;
-    const double* src = A.J2 + (int64_t)c * nc;
     double* dst = A.J + (int64_t)c * nc;
     // first line of the block and the line count / axis stride
     int64_t base0;
@@ -945,60 +995,59 @@ __device__ __forceinline__ void line_lds_body(const LineArgs& A, int64_t b, doub
         stride = c == 1 ? n0 : n0 * n1;
         nlines = n0 - i0 < W ? n0 - i0 : W;
     }
-    // line w starts at base0 + w * (x lines: n0, else 1)
+    // line w starts at base0 + w * (x lines: n0, else 1); in LDS at w * ws, its values js apart
     const int64_t lstep = c == 0 ? n0 : 1;
-    const int total = ext * W;
-    // global memory (not generic) loads, which the LDS stores need not wait behind
-    const __attribute__((address_space(1))) double* gsrc = (const __attribute__((address_space(1))) double*)src;
-    // LINE_BATCH loads per thread in flight before the first is stored; every lane loads (an
-    // entry past the end or of a line past the last reads the block's first value and stores
-    // nothing or zero), so that no load waits at a branch
-    for (int q0 = threadIdx.x; q0 < total; q0 += LINE_BATCH * FIELD_BS) {
+    const int ws = c == 0 ? ext : 1, js = c == 0 ? 1 : W;
+    // a thread stays on one line: 256 / W threads a line, neighbours along the memory order
+    const int per_line = FIELD_BS / W;
+    const int w = c == 0 ? (int)threadIdx.x / per_line : (int)threadIdx.x % W;
+    const int j0 = c == 0 ? (int)threadIdx.x % per_line : (int)threadIdx.x / W;
+    const bool live = w < nlines;
+    const int64_t line = (int64_t)c * nc + base0 + (live ? w : 0) * lstep;
+    // global memory (not generic) accesses, which the LDS stores need not wait behind
+    glob_f64* gsrc = A.Jq ? (glob_f64*)A.Jq + line : (glob_f64*)A.J2 + line;
+    const double inv = A.Jq ? 1.0 / fixed_scale(A.scale) : 1.0;  // exact: a power of two
+    // LINE_BATCH loads per thread in flight before the first is stored; every lane loads (past the
+    // end, its line's first value), so that no load waits at a branch
+    for (int q0 = j0; q0 < ext; q0 += LINE_BATCH * per_line) {
         double v[LINE_BATCH];
-        int dst[LINE_BATCH];  // LDS entry, or -1 past the end
-        bool live[LINE_BATCH];
 #pragma unroll
         for (int t = 0; t < LINE_BATCH; ++t) {
-            const int q = q0 + t * FIELD_BS;
-            const int qc = q < total ? q : 0;
-            int w, jj;
-            if (c == 0) {
-                w = qc / ext;
-                jj = qc - w * ext;
-            } else {
-                jj = qc / W;
-                w = qc - jj * W;
-            }
-            const int sidx = wrap_near(off + jj, N);
-            live[t] = w < nlines;
-            v[t] = gsrc[base0 + (live[t] ? w : 0) * lstep + (int64_t)sidx * stride];
-            dst[t] = q < total ? q : -1;
+            const int jj = q0 + t * per_line;
+            v[t] = gsrc[(int64_t)wrap_near(off + (jj < ext ? jj : 0), N) * stride];
         }
 #pragma unroll
-        for (int t = 0; t < LINE_BATCH; ++t)
-            if (dst[t] >= 0) e[dst[t]] = live[t] ? v[t] : 0.0;
+        for (int t = 0; t < LINE_BATCH; ++t) {
+            const int jj = q0 + t * per_line;
+            if (jj < ext) e[w * ws + jj * js] = A.Jq ? (double)__double_as_longlong(v[t]) * inv : v[t];
+        }
     }
     __syncthreads();
-    const int outs = N * W;
-    for (int q = threadIdx.x; q < outs; q += FIELD_BS) {
-        int w, j, es, eb;
-        if (c == 0) {
-            w = q / N;
-            j = q - w * N;
-            eb = w * ext + j;
-            es = 1;
+    if (A.Jq && live) {
+        glob_u64* gq = (glob_u64*)A.Jq + line;
+        for (int j = j0; j < N; j += per_line) gq[(int64_t)j * stride] = 0ull;
+    }
+    // the coefficients are the same for the whole block: read-only, uniform (scalar) loads
+    const_f64* cf = (const_f64*)arg3(A.coef, c);
+    const int chunks = (N + LINE_OUT - 1) / LINE_OUT;
+    for (int k = j0; k < chunks; k += per_line) {
+        // the last chunk starts earlier instead of running past the line
+        const int j = k * LINE_OUT + LINE_OUT <= N ? k * LINE_OUT : (N > LINE_OUT ? N - LINE_OUT : 0);
+        double acc[LINE_OUT];
+        if (N >= LINE_OUT) {
+            line_taps(e + w * ws + j * js, js, cf, len, acc);
         } else {
-            j = q / W;
-            w = q - j * W;
-            eb = j * W + w;
-            es = W;
+#pragma unroll
+            for (int o = 0; o < LINE_OUT; ++o) {
+                acc[o] = 0.0;
+                if (o < N)
+                    for (int t = 0; t < len; ++t) acc[o] += cf[t] * e[w * ws + (o + t) * js];
+            }
         }
-        if (w >= nlines) continue;
-        // the coefficients are the same for the whole block: read-only, uniform (scalar) loads
-        const __attribute__((address_space(4))) double* cf = (const __attribute__((address_space(4))) double*)A.coef[c];
-        double s = 0.0;
-        for (int t = 0; t < len; ++t) s += cf[t] * e[eb + t * es];
-        dst[base0 + w * lstep + (int64_t)j * stride] = s;
+        if (!live) continue;
+#pragma unroll
+        for (int o = 0; o < LINE_OUT; ++o)
+            if (j + o < N) dst[base0 + w * lstep + (int64_t)(j + o) * stride] = acc[o];
     }
 }
 
@@ -1061,46 +1110,64 @@ int line_setup_axis(int order, int N, double* coef_host, int* off) {
     return 2 * Rr + 1;
 }
 
-void line_desc(const pp_run* r, const double* J2, double* J, LineArgs* A) {
+// Lines per block of each axis: as many as the LDS copy holds, fewer (down to 8, whole cache
+// lines of the y and z rows) while a component has not two blocks per CU (its share of them in a
+// batch of nruns).
+static bool line_blocks_of(const pp_run* r, int nruns, int W[3], int64_t nb[3]) {
+    const int64_t n0 = r->p.n[0];
+    for (int d = 0; d < 3; ++d) {
+        const int ext = r->p.n[d] + r->line[d].len - 1;
+        W[d] = 64;
+        while (W[d] > 1 && (int64_t)W[d] * ext > LINE_LDS_DOUBLES) W[d] >>= 1;
+        if ((int64_t)W[d] * ext > LINE_LDS_DOUBLES) return false;
+        auto blocks = [&] {
+            return d == 0 ? ((int64_t)r->p.n[1] * r->p.n[2] + W[d] - 1) / W[d]
+                          : ((n0 + W[d] - 1) / W[d]) * (d == 1 ? r->p.n[2] : r->p.n[1]);
+        };
+        while (W[d] > 8 && blocks() * nruns < 512) W[d] >>= 1;
+        nb[d] = blocks();
+    }
+    return true;
+}
+
+bool line_reads_fixed(const pp_run* r) {
+    int W[3];
+    int64_t nb[3];
+    return uses_line_solve(r) && r->Jq && line_blocks_of(r, 1, W, nb);
+}
+
+void line_desc(const pp_run* r, LineArgs* A, int nruns) {
     A->G = make_geom(r);
-    bool fits = true;
     for (int d = 0; d < 3; ++d) {
         A->coef[d] = r->line[d].coef;
         A->len[d] = r->line[d].len;
         A->off[d] = r->line[d].off;
-        const int ext = r->p.n[d] + r->line[d].len - 1;
-        int W = 64;
-        while (W > 1 && (int64_t)W * ext > LINE_LDS_DOUBLES) W >>= 1;
-        if ((int64_t)W * ext > LINE_LDS_DOUBLES) fits = false;
-        A->W[d] = W;
-        const int64_t n0 = r->p.n[0];
-        if (d == 0)
-            A->nb[d] = ((int64_t)r->p.n[1] * r->p.n[2] + W - 1) / W;
-        else
-            A->nb[d] = ((n0 + W - 1) / W) * (d == 1 ? r->p.n[2] : r->p.n[1]);
     }
-    if (!fits) {
+    A->Jq = nullptr;
+    if (!line_blocks_of(r, nruns, A->W, A->nb)) {
         A->W[0] = 0;
         A->nb[0] = blocks_of(A->G);
         A->nb[1] = A->nb[2] = 0;
+    } else if (r->Jq) {
+        A->Jq = (unsigned long long*)r->Jq;
+        A->scale = gpd32_scale(r);
     }
-    A->J2 = J2;
-    A->J = J;
+    A->J2 = r->J2;
+    A->J = r->mesh.J;
 }
 
 size_t line_desc_size() { return sizeof(LineArgs); }
 
-int64_t line_blocks(const pp_run* r) {
-    LineArgs A;
-    line_desc(r, nullptr, nullptr, &A);
-    return A.nb[0] + A.nb[1] + A.nb[2];
+int64_t line_blocks(const pp_run* r, int nruns) {
+    int W[3];
+    int64_t nb[3];
+    return line_blocks_of(r, nruns, W, nb) ? nb[0] + nb[1] + nb[2] : blocks_of(make_geom(r));
 }
 
-hipError_t launch_line_solve(pp_run* r, const double* J2, double* J) {
+hipError_t launch_line_solve(pp_run* r) {
     LineArgs A;
-    line_desc(r, J2, J, &A);
-    hipLaunchKernelGGL(k_line_solve, dim3((unsigned)(A.nb[0] + A.nb[1] + A.nb[2])), dim3(FIELD_BS), 0, r->stream,
-                       A);
+    line_desc(r, &A, 1);
+    hipLaunchKernelGGL(k_line_solve, dim3((unsigned)line_blocks(r, 1)), dim3(FIELD_BS), 0, r->stream, A);
     return hipGetLastError();
 }
 

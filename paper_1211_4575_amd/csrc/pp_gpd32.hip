@@ -35,6 +35,7 @@
 // independent of summation order (bitwise deterministic).  All species are processed by the
 // same workgroup.
 #include "pp_device.hpp"
+#include "pp_fixed.hpp"
 #include "pp_internal.hpp"
 
 namespace pp {
@@ -80,8 +81,8 @@ struct Gpd32Args {
     Sp32 sp[PP_MAX_SPECIES];
     const double* E;
     const double* B;
-    unsigned long long* Jq;  // fixed-point current accumulator (3 * nc)
-    const double* qscale;    // 2^e (device, set by k_fixed_scale)
+    unsigned long long* Jq;  // fixed-point current accumulator (3 * nc, zero on entry)
+    FixedScale scale;
     int32_t* flags;
     int per_xcd;
     int sext[3];  // destination-cell window per axis (tile and DEST_HALO around it; 1 if collapsed)
@@ -341,8 +342,7 @@ struct TileCtx {
     const float* fld;
     unsigned long long* cur;
     int32_t* slots;
-    double facq[3];  // -q w d_c / dt, times the fixed-point scale
-    double qwq;      // q w times the fixed-point scale (direct current)
+    double* facq;  // LDS: -q w d_c / dt per axis and q w (direct current), times the fixed-point scale
 };
 
 // The particle step of slot q (gather, push, move, renormalise, store, rank for the next sort;
@@ -472,7 +472,7 @@ __device__ __forceinline__ void step_particle(const Gpd32Args& A, const Sp32& S,
 #pragma unroll
         for (int comp = 0; comp < 3; ++comp) {
             unsigned long long* Jc = C.cur + comp * L.cvol;
-            const double vq = C.qwq * (double)(uu[comp] * ig);
+            const double vq = C.facq[3] * (double)(uu[comp] * ig);
             const int n0x = comp == 0 ? nsm[0] : ncm[0];
             const int n0y = comp == 1 ? nsm[1] : ncm[1];
             const int n0z = comp == 2 ? nsm[2] : ncm[2];
@@ -643,6 +643,7 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, uns
     const int tk = (int)(tile / ((int64_t)A.nt[0] * A.nt[1]));
     const int org[3] = {ti * L.tx, tj * L.ty, tk * L.tz};
     const int n0 = A.n[0], n1 = A.n[1], n2 = A.n[2];
+    const double qs = fixed_scale(A.scale);
 
     // fields first: the gather's LDS reads then use small immediate offsets
     float* fld = (float*)lds_raw;  // 6 * fvol
@@ -678,7 +679,8 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, uns
             if (dst[k] >= 0) fld[dst[k]] = (float)v[k];
     }
     for (int q = threadIdx.x; q < 3 * L.cvol; q += GPD32_BS) cur[q] = 0ull;
-    int32_t* slots = (int32_t*)(cur + 3 * L.cvol);  // A.nslots destination-cell counters
+    double* facq = (double*)(cur + 3 * L.cvol);
+    int32_t* slots = (int32_t*)(facq + 4);  // A.nslots destination-cell counters
     for (int q = threadIdx.x; q < A.nslots; q += GPD32_BS) slots[q] = 0;
     __syncthreads();
 
@@ -689,7 +691,8 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, uns
     C.fld = fld;
     C.cur = cur;
     C.slots = slots;
-    const double qs = *A.qscale;
+    C.facq = facq;
+
     int bad_all = 0;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 
@@ -697,8 +700,8 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, uns
         const Sp32& S = A.sp[s];
         const int32_t start = S.start[tile];
         const int32_t end = S.start[tile + 1];
-        for (int d = 0; d < 3; ++d) C.facq[d] = S.fac[d] * qs;
-        C.qwq = S.qw * qs;
+        if (threadIdx.x < 4) facq[threadIdx.x] = (threadIdx.x < 3 ? S.fac[threadIdx.x] : S.qw) * qs;
+        __syncthreads();
         if constexpr (!TL::pairs) {
             for (int32_t q = start + threadIdx.x; q < end; q += GPD32_BS) {
                 Win<O> W;
@@ -811,58 +814,33 @@ __global__ void __launch_bounds__(GPD32_BS, TL::pairs ? 3 : 1) k_gpd32_batch(con
     gpd32_tile<O, TL>(table[r], b - prefix[r], lds_raw);
 }
 
-// Fixed-point current bookkeeping of one run: scale, accumulator, FP64 target.
+// Fixed-point current of a run to FP64, clearing the accumulator for the next step (runs without
+// the line solve, whose kernel does both as it reads the current).
 struct FixedDesc {
-    const int32_t* tile_max;  // largest tile population per species slot
-    int e0;                   // host part of the exponent
-    double* scale;            // 2^e (device)
-    unsigned long long* Jq;   // accumulator, 3 * nc
-    double* J;                // FP64 current written from the accumulator
+    FixedScale scale;
+    unsigned long long* Jq;  // accumulator, 3 * nc
+    double* J;
     int64_t n3;
 };
 
-// 2^e with e = e0 - ceil(log2(N)), N the sum over species of the largest particle count of
-// any tile: then |one contribution| <= 2^(50 - ceil log2 N) and |a node's LDS sum| <= 2^50.
-__device__ __forceinline__ void fixed_scale_body(const FixedDesc& D) {
-    long long nb = 0;
-    for (int s = 0; s < PP_MAX_SPECIES; ++s) nb += D.tile_max[s];
-    int lg = 0;
-    while ((1ll << lg) < nb) ++lg;
-    *D.scale = ldexp(1.0, D.e0 - lg);
-}
-
-enum FixedPhase { FX_ZERO = 0, FX_TO_F64 = 1 };
-
-__device__ __forceinline__ void fixed_body(const FixedDesc& D, int64_t q, int phase) {
+__device__ __forceinline__ void fixed_body(const FixedDesc& D, int64_t q, double inv) {
     if (q >= D.n3) return;
-    if (phase == FX_ZERO) {
-        D.Jq[q] = 0ull;
-    } else {
-        const double inv = 1.0 / *D.scale;  // exact: a power of two
-        D.J[q] = (double)(long long)D.Jq[q] * inv;
-    }
+    D.J[q] = (double)(long long)D.Jq[q] * inv;
+    D.Jq[q] = 0ull;
 }
 
-__global__ void k_fixed_scale(FixedDesc D) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) fixed_scale_body(D);
-}
-
-__global__ void __launch_bounds__(256) k_fixed(FixedDesc D, int phase) {
+__global__ void __launch_bounds__(256) k_fixed(FixedDesc D) {
+    const double inv = 1.0 / fixed_scale(D.scale);  // exact: a power of two
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < D.n3; q += (int64_t)gridDim.x * blockDim.x)
-        fixed_body(D, q, phase);
-}
-
-__global__ void k_fixed_scale_batch(const FixedDesc* __restrict__ T, int n) {
-    const int r = blockIdx.x * blockDim.x + threadIdx.x;
-    if (r < n) fixed_scale_body(T[r]);
+        fixed_body(D, q, inv);
 }
 
 __global__ void __launch_bounds__(256) k_fixed_batch(const FixedDesc* __restrict__ T, const int64_t* __restrict__ prefix,
-                                                     int n, int phase) {
+                                                     int n) {
     const int64_t b = blockIdx.x;
     const int r = find_segment(prefix, n, b);
     if (r < 0) return;
-    fixed_body(T[r], (b - prefix[r]) * blockDim.x + threadIdx.x, phase);
+    fixed_body(T[r], (b - prefix[r]) * blockDim.x + threadIdx.x, 1.0 / fixed_scale(T[r].scale));
 }
 
 enum TileKind { TILE_444 = 0, TILE_881_FLAT = 1, TILE_RT = 2 };
@@ -895,7 +873,7 @@ size_t gpd32_lds_bytes(const pp_run* r) {
                       : kind == TILE_881_FLAT ? (size_t)cur_row_881 * ce[1]
                                               : (size_t)ce[0] * ce[1] * ce[2];
     const size_t slots = r->g.dest_slots();
-    return ((6 * fv * sizeof(float) + 15) & ~(size_t)15) + 3 * cv * sizeof(unsigned long long) + slots * sizeof(int32_t);
+    return ((6 * fv * sizeof(float) + 15) & ~(size_t)15) + 3 * cv * sizeof(unsigned long long) + 4 * sizeof(double) + slots * sizeof(int32_t);
 }
 
 // Host part of the fixed-point exponent: e0 = 50 - ceil(log2(max |fac|)), every contribution
@@ -969,7 +947,7 @@ void gpd32_fill_args(const pp_run* r, Gpd32Args* Ap) {
     A.E = r->mesh.E;
     A.B = r->mesh.B;
     A.Jq = (unsigned long long*)r->Jq;
-    A.qscale = r->qscale;
+    A.scale = gpd32_scale(r);
     A.flags = r->flags;
     A.per_xcd = (int)((r->g.ntiles + 7) / 8);
     A.direct = r->p.current_scheme == PP_CURRENT_DIRECT ? 1 : 0;
@@ -977,14 +955,17 @@ void gpd32_fill_args(const pp_run* r, Gpd32Args* Ap) {
     A.nslots = r->g.dest_slots();
 }
 
-void gpd32_fixed_desc(const pp_run* r, double* J, FixedDesc* D) {
-    D->tile_max = r->tile_max;
-    D->e0 = gpd32_scale_e0(r);
-    D->scale = r->qscale;
+FixedScale gpd32_scale(const pp_run* r) { return FixedScale{r->tile_max, gpd32_scale_e0(r)}; }
+
+void gpd32_fixed_desc(const pp_run* r, FixedDesc* D) {
+    D->scale = gpd32_scale(r);
     D->Jq = (unsigned long long*)r->Jq;
-    D->J = J;
+    D->J = uses_line_solve(r) ? r->J2 : r->mesh.J;
     D->n3 = 3 * r->g.ncell;
 }
+
+// blocks of the batched conversion (none where the line solve reads the fixed-point current)
+int64_t gpd32_fixed_blocks(const pp_run* r) { return line_reads_fixed(r) ? 0 : (3 * r->g.ncell + 255) / 256; }
 
 size_t gpd32_args_size() { return sizeof(Gpd32Args); }
 size_t gpd32_fixed_desc_size() { return sizeof(FixedDesc); }
@@ -996,13 +977,9 @@ static unsigned fixed_grid(int64_t n3) {
     return (unsigned)(g < 1 ? 1 : g);
 }
 
-hipError_t launch_gpd32(pp_run* r, double* J) {
+hipError_t launch_gpd32(pp_run* r) {
     Gpd32Args A;
     gpd32_fill_args(r, &A);
-    FixedDesc F;
-    gpd32_fixed_desc(r, J, &F);
-    hipLaunchKernelGGL(k_fixed_scale, dim3(1), dim3(64), 0, r->stream, F);
-    hipLaunchKernelGGL(k_fixed, dim3(fixed_grid(F.n3)), dim3(256), 0, r->stream, F, (int)FX_ZERO);
     const size_t lds = gpd32_lds_bytes(r);
     const unsigned grid = (unsigned)(8 * (int64_t)A.per_xcd);
     const int kind = tile_kind(r);
@@ -1023,20 +1000,20 @@ hipError_t launch_gpd32(pp_run* r, double* J) {
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    if (J) hipLaunchKernelGGL(k_fixed, dim3(fixed_grid(F.n3)), dim3(256), 0, r->stream, F, (int)FX_TO_F64);
+    if (!line_reads_fixed(r)) {
+        FixedDesc F;
+        gpd32_fixed_desc(r, &F);
+        hipLaunchKernelGGL(k_fixed, dim3(fixed_grid(F.n3)), dim3(256), 0, r->stream, F);
+    }
     return hipGetLastError();
 }
 
 // Batched particle step of n runs that all use 4x4x4 tiles and the same weight order:
-// fixed-point scales, accumulator clear, the tiled kernel, conversion to FP64.
+// the tiled kernel, and the conversion to FP64 of the runs that need it.
 hipError_t launch_gpd32_batch(const void* args_table, const int64_t* tile_prefix, int64_t total_tiles,
                               const void* fixed_table, const int64_t* fixed_prefix, int64_t total_fixed_blocks, int n,
                               int shape_order, size_t lds, hipStream_t st) {
     if (n == 0) return hipSuccess;
-    const FixedDesc* F = (const FixedDesc*)fixed_table;
-    hipLaunchKernelGGL(k_fixed_scale_batch, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, st, F, n);
-    hipLaunchKernelGGL(k_fixed_batch, dim3((unsigned)total_fixed_blocks), dim3(256), 0, st, F, fixed_prefix, n,
-                       (int)FX_ZERO);
     const Gpd32Args* T = (const Gpd32Args*)args_table;
     if (shape_order == 2)
         hipLaunchKernelGGL((k_gpd32_batch<2, TileCT<2, 4, 4, 4, false>>), dim3((unsigned)total_tiles), dim3(GPD32_BS), lds,
@@ -1044,8 +1021,9 @@ hipError_t launch_gpd32_batch(const void* args_table, const int64_t* tile_prefix
     else
         hipLaunchKernelGGL((k_gpd32_batch<3, TileCT<3, 4, 4, 4, false>>), dim3((unsigned)total_tiles), dim3(GPD32_BS), lds,
                            st, T, tile_prefix, n);
-    hipLaunchKernelGGL(k_fixed_batch, dim3((unsigned)total_fixed_blocks), dim3(256), 0, st, F, fixed_prefix, n,
-                       (int)FX_TO_F64);
+    if (total_fixed_blocks > 0)
+        hipLaunchKernelGGL(k_fixed_batch, dim3((unsigned)total_fixed_blocks), dim3(256), 0, st,
+                           (const FixedDesc*)fixed_table, fixed_prefix, n);
     return hipGetLastError();
 }
 

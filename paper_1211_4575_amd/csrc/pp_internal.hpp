@@ -106,9 +106,9 @@ struct pp_run {
     int32_t* scan_tmp = nullptr;      // block sums of the scan
     int32_t* sort_scratch = nullptr;  // split form: rank and permutation of the tile-order rebuild
     int64_t sort_scratch_n = 0;       // particles per half of sort_scratch
-    long long* Jq = nullptr;          // split form: current in 64-bit fixed point (3*ncell)
+    long long* Jq = nullptr;          // split form: current in 64-bit fixed point (3*ncell), zero
+                                      // between calls
     int32_t* tile_max = nullptr;      // split form: largest particle count of a tile, per species
-    double* qscale = nullptr;         // split form: 2^e of the fixed-point current (device)
     int32_t* flags = nullptr;        // device error flags
     double* dacc = nullptr;          // device accumulators for diagnostics
     pp::LineStencil line[3];
@@ -181,8 +181,9 @@ inline bool ok(hipError_t e, const char* where) {
 hipError_t launch_gpd64(pp_run* r, int s, double* J);  // particles of one species in any order
 // every species whose particles lie binned by cell, by tiles; *done has a bit for each of them
 hipError_t launch_gpd64_tiles(pp_run* r, double* J, unsigned* done);
-hipError_t launch_gpd32(pp_run* r, double* J);
-hipError_t launch_line_solve(pp_run* r, const double* J2, double* J);
+hipError_t launch_gpd32(pp_run* r);       // J (or J2, or Jq where line_reads_fixed) of all species
+hipError_t launch_line_solve(pp_run* r);  // J from J2 or Jq
+bool line_reads_fixed(const pp_run* r);   // the line solve takes the fixed-point current itself
 hipError_t launch_field_step(pp_run* r);
 // blocks of one launch of this run's field step, in a batch of nruns
 int64_t field_blocks(const pp_run* r, int nruns);
@@ -216,7 +217,8 @@ struct FieldDesc;
 struct LineArgs;
 struct RankedArgs;
 void gpd32_fill_args(const pp_run* r, Gpd32Args* A);
-void gpd32_fixed_desc(const pp_run* r, double* J, FixedDesc* D);
+void gpd32_fixed_desc(const pp_run* r, FixedDesc* D);
+int64_t gpd32_fixed_blocks(const pp_run* r);
 hipError_t launch_gpd32_batch(const void* args_table, const int64_t* tile_prefix, int64_t total_tiles,
                               const void* fixed_table, const int64_t* fixed_prefix, int64_t total_fixed_blocks, int n,
                               int shape_order, size_t lds, hipStream_t st);
@@ -225,8 +227,8 @@ void field_desc(const pp_run* r, FieldDesc* D, int nruns);
 hipError_t launch_field_step_batch(const void* table, const int64_t* prefix, int n, int64_t total_blocks,
                                    int min_sweeps, int max_sweeps, hipStream_t st);
 size_t line_desc_size();
-int64_t line_blocks(const pp_run* r);  // blocks of one line-solve launch of this run
-void line_desc(const pp_run* r, const double* J2, double* J, LineArgs* A);
+int64_t line_blocks(const pp_run* r, int nruns);  // blocks of this run's line solve in a batch of nruns
+void line_desc(const pp_run* r, LineArgs* A, int nruns);
 hipError_t launch_line_solve_batch(const void* table, const int64_t* prefix, int n, int64_t total_blocks, hipStream_t st);
 // ranked sort of one species of a run, as an entry of a batch's table
 size_t sort_desc_size();
