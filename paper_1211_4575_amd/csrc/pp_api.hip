@@ -27,6 +27,7 @@ hipError_t field_setup(pp_run* r);
 int line_setup_axis(int order, int N, double* coef_host, int* off);
 int64_t scan_tmp_size(int64_t n);
 int diag_acc_count();
+int64_t diag_buffer_count();
 size_t gpd32_lds_bytes(const pp_run* r);
 
 static bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
@@ -158,7 +159,7 @@ static size_t internal_bytes(const pp_params* p, const Geom& g, int64_t nmax, in
     b += 4 * n3 * sizeof(double);                                          // J2, Bn, Bw, R
     b += 2 * nc * sizeof(double);                                          // rho, rho_prev
     b += nb * sizeof(int32_t) + (size_t)scan_tmp_size(g.nbins + 1) * sizeof(int32_t);
-    b += sizeof(int32_t) + ((size_t)diag_acc_count() + 8) * sizeof(double);
+    b += sizeof(int32_t) + (size_t)diag_buffer_count() * sizeof(double);
     b += (p->time_order == 4 ? 3 : 1) * ((size_t)p->relax_max_iter + 2) * sizeof(double);  // relaxation weights
     if (p->precision == PP_PREC_FP32_SPLIT) {
         b += n3 * sizeof(long long) + PP_MAX_SPECIES * sizeof(int32_t);
@@ -220,7 +221,7 @@ pp_status pp_create(const pp_params* params, const pp_mesh* mesh, void* hip_stre
     okk = okk && dmalloc(&r->J2, n3) && dmalloc(&r->Bn, n3) && dmalloc(&r->Bw, n3) && dmalloc(&r->R, n3);
     okk = okk && dmalloc(&r->rho, (size_t)g.ncell) && dmalloc(&r->rho_prev, (size_t)g.ncell);
     okk = okk && dmalloc(&r->sort_cursor, (size_t)g.nbins) && dmalloc(&r->scan_tmp, (size_t)scan_tmp_size(g.nbins + 1));
-    okk = okk && dmalloc(&r->flags, 1) && dmalloc(&r->dacc, (size_t)diag_acc_count() + 8);
+    okk = okk && dmalloc(&r->flags, 1) && dmalloc(&r->dacc, (size_t)diag_buffer_count());
     r->nrs = params->time_order == 4 ? 3 : 1;
     for (int k = 0; k < r->nrs; ++k) okk = okk && dmalloc(&r->rs[k].omega, (size_t)params->relax_max_iter + 2);
     if (params->precision == PP_PREC_FP32_SPLIT) {

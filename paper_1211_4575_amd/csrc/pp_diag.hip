@@ -31,24 +31,11 @@ enum {
     ACC_RELAX_RHS,  // max |rhs|
     ACC_COUNT
 };
-// device-only slot after the copied accumulators: 2^e of the fixed-point charge density
-constexpr int ACC_RHO_SCALE = ACC_COUNT;
-
-__device__ __forceinline__ void atomic_max_nonneg(double* p, double v) {
-    atomicMax((unsigned long long*)p, (unsigned long long)__double_as_longlong(v));
-}
-
-__device__ __forceinline__ void block_max(double v, double* dst) {
-    __shared__ double sh[256];
-    __syncthreads();  // the array is reused by consecutive calls
-    sh[threadIdx.x] = v;
-    __syncthreads();
-    for (int off = blockDim.x / 2; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off) sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + off]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) atomic_max_nonneg(dst, sh[0]);
-}
+// after the accumulators: the flag word (copied with them) and, device-only, 2^e of the
+// fixed-point charge density and the partials
+constexpr int ACC_FLAGS = ACC_COUNT;
+constexpr int ACC_RHO_SCALE = ACC_COUNT + 1;
+constexpr int ACC_PART = ACC_COUNT + 8;  // partials of the sums (ROW_COUNT rows)
 
 __global__ void k_fill_f64(double* p, int64_t n, double v) {
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += (int64_t)gridDim.x * blockDim.x)
@@ -64,42 +51,93 @@ hipError_t launch_fill(double* p, int64_t n, double v, hipStream_t st) {
     return hipGetLastError();
 }
 
-// kinetic energy w V m u^2/(gamma + 1) (= w V m c^2 (gamma - 1)) and momentum w V m u
-template <typename T>
-__global__ void __launch_bounds__(256) k_moments(const T* __restrict__ ux, const T* __restrict__ uy,
-                                                 const T* __restrict__ uz, int64_t n, double ic, double wVm, double* acc_kin,
-                                                 double* acc_mom) {
-    double v[4] = {0, 0, 0, 0};
-    for (int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; p < n; p += (int64_t)gridDim.x * blockDim.x) {
-        double a = (double)ux[p], b = (double)uy[p], c = (double)uz[p];
-        double u2 = a * a + b * b + c * c;
-        double g = sqrt(1.0 + u2 * ic * ic);
-        v[0] += u2 / (g + 1.0);
-        v[1] += a;
-        v[2] += b;
-        v[3] += c;
-    }
+// Sums and maxima over particles or cells: each workgroup writes its value of every row to the
+// row's partials, and k_finish combines them in a fixed order (atomics on one address are served
+// one after another, about 13 ns each: 5.2e6 particles' moments took 2 x 160 us that way).
+constexpr int PART_MAX = 512;  // partials of a row: workgroups of a launch
+enum { ROW_SPECIES = 0, ROW_FIELD = 4 * PP_MAX_SPECIES, ROW_RESID = ROW_FIELD + 3, ROW_COUNT = ROW_RESID + 3 };
+
+template <bool MAX>
+__device__ __forceinline__ double join(double a, double b) {
+    return MAX ? fmax(a, b) : a + b;
+}
+
+template <int NV, bool MAX>
+__device__ __forceinline__ void write_partials(double v[NV], double* part) {
+    __shared__ double sh[NV][4];
 #pragma unroll
-    for (int a = 0; a < 4; ++a) v[a] *= wVm;
-    __shared__ double sh[4][256];
+    for (int a = 0; a < NV; ++a)
+        for (int o = 32; o > 0; o >>= 1) v[a] = join<MAX>(v[a], __shfl_xor(v[a], o, 64));
+    if ((threadIdx.x & 63) == 0)
 #pragma unroll
-    for (int a = 0; a < 4; ++a) sh[a][threadIdx.x] = v[a];
+        for (int a = 0; a < NV; ++a) sh[a][threadIdx.x >> 6] = v[a];
     __syncthreads();
-    for (int off = blockDim.x / 2; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off)
+    if (threadIdx.x == 0)
 #pragma unroll
-            for (int a = 0; a < 4; ++a) sh[a][threadIdx.x] += sh[a][threadIdx.x + off];
-        __syncthreads();
+        for (int a = 0; a < NV; ++a)
+            part[(int64_t)a * PART_MAX + blockIdx.x] =
+                join<MAX>(join<MAX>(sh[a][0], sh[a][1]), join<MAX>(sh[a][2], sh[a][3]));
+}
+
+constexpr int DIAG_UNROLL = 4;
+
+// workgroups of 256 threads for a sum over n entries: each has a few rounds of work
+static unsigned sum_grid(int64_t n) {
+    const int64_t g = (n + 256 * DIAG_UNROLL - 1) / (256 * DIAG_UNROLL);
+    return (unsigned)(g < 1 ? 1 : (g > PART_MAX ? PART_MAX : g));
+}
+
+// kinetic energy w V m u^2/(gamma + 1) (= w V m c^2 (gamma - 1)) and momentum w V m u of every
+// species in one launch
+struct MomentArgs {
+    const void* u[PP_MAX_SPECIES][3];
+    int64_t n[PP_MAX_SPECIES];
+    double wVm[PP_MAX_SPECIES];
+    int slot[PP_MAX_SPECIES];
+    double ic;
+    double* part;
+};
+
+template <typename T>
+__global__ void __launch_bounds__(256) k_moments(MomentArgs A) {
+    const int s = blockIdx.y;
+    const T* ux = (const T*)A.u[s][0];
+    const T* uy = (const T*)A.u[s][1];
+    const T* uz = (const T*)A.u[s][2];
+    const int64_t n = A.n[s];
+    const double ic = A.ic;
+    double v[4] = {0, 0, 0, 0};
+    const int64_t step = (int64_t)gridDim.x * 256;
+    for (int64_t p0 = (int64_t)blockIdx.x * 256 + threadIdx.x; p0 < n; p0 += DIAG_UNROLL * step) {
+        T x[DIAG_UNROLL], y[DIAG_UNROLL], z[DIAG_UNROLL];
+#pragma unroll
+        for (int k = 0; k < DIAG_UNROLL; ++k) {
+            const int64_t p = p0 + k * step < n ? p0 + k * step : p0;
+            x[k] = ux[p];
+            y[k] = uy[p];
+            z[k] = uz[p];
+        }
+#pragma unroll
+        for (int k = 0; k < DIAG_UNROLL; ++k) {
+            if (p0 + k * step >= n) break;
+            const double a = (double)x[k], b = (double)y[k], c = (double)z[k];
+            const double u2 = a * a + b * b + c * c;
+            const double g = sqrt(1.0 + u2 * ic * ic);
+            v[0] += u2 / (g + 1.0);
+            v[1] += a;
+            v[2] += b;
+            v[3] += c;
+        }
     }
-    if (threadIdx.x == 0) {
-        atomic_add_f64(acc_kin, sh[0][0]);
-        for (int a = 0; a < 3; ++a) atomic_add_f64(acc_mom + a, sh[a + 1][0]);
-    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a) v[a] *= A.wVm[s];
+    write_partials<4, false>(v, A.part + (int64_t)(ROW_SPECIES + 4 * A.slot[s]) * PART_MAX);
 }
 
 __global__ void __launch_bounds__(256) k_field_energy(const double* __restrict__ E, const double* __restrict__ B,
-                                                      int64_t nc, double hV_eps0, double hV_imu0, double* acc) {
+                                                      int64_t nc, double hV_eps0, double hV_imu0, double* part) {
     double v[3] = {0, 0, 0};
+#pragma unroll 2
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < nc; q += (int64_t)gridDim.x * blockDim.x) {
         double ex = E[q], ey = E[nc + q], ez = E[2 * nc + q];
         double bx = B[q], by = B[nc + q], bz = B[2 * nc + q];
@@ -110,21 +148,7 @@ __global__ void __launch_bounds__(256) k_field_energy(const double* __restrict__
     v[0] *= hV_eps0;
     v[1] *= hV_imu0;
     v[2] *= hV_eps0;
-    __shared__ double sh[3][256];
-#pragma unroll
-    for (int a = 0; a < 3; ++a) sh[a][threadIdx.x] = v[a];
-    __syncthreads();
-    for (int off = blockDim.x / 2; off > 0; off >>= 1) {
-        if ((int)threadIdx.x < off)
-#pragma unroll
-            for (int a = 0; a < 3; ++a) sh[a][threadIdx.x] += sh[a][threadIdx.x + off];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        atomic_add_f64(acc + 0, sh[0][0]);
-        atomic_add_f64(acc + 1, sh[1][0]);
-        atomic_add_f64(acc + 2, sh[2][0]);
-    }
+    write_partials<3, false>(v, part + (int64_t)ROW_FIELD * PART_MAX);
 }
 
 // rho(node) += q w W(X - node), FP64, for either particle form
@@ -189,6 +213,7 @@ struct Rho32Args {
     int lo[3];    // nodes below the tile: RHO_HALO + 1 (0 on a single-cell axis)
     int halo[3];  // cells around the tile deposited in the block: RHO_HALO (0 on a single-cell axis)
     int64_t nc;
+    double inv_n0, inv_n1;  // 1 / n[0], 1 / n[1]: a cell's row and plane without integer divisions
     int nsp;
     Rho32Sp sp[PP_MAX_SPECIES];
     unsigned long long* acc;  // nc, zero on entry
@@ -237,7 +262,6 @@ __global__ void __launch_bounds__(256) k_rho32(Rho32Args A) {
     __syncthreads();
     const double sc = *A.scale;
     const float flo = O == 2 ? -0.5f : 0.0f;
-    const int nxy = A.n[0] * A.n[1];
     for (int s = 0; s < A.nsp; ++s) {
         const Rho32Sp& S = A.sp[s];
         const double v = S.qw * sc;
@@ -245,7 +269,9 @@ __global__ void __launch_bounds__(256) k_rho32(Rho32Args A) {
         for (int32_t p = S.start[tile] + threadIdx.x; p < end; p += blockDim.x) {
             const int32_t cell = S.cell[p];
             if (cell < 0 || (int64_t)cell >= A.nc) continue;  // reported by the error flags
-            const int g[3] = {cell % A.n[0], (cell / A.n[0]) % A.n[1], cell / nxy};
+            // exact: (cell + 1/2) / n is at least 1/(2n) from an integer, and below 2^30
+            const int row = (int)(((double)cell + 0.5) * A.inv_n0), gz = (int)(((double)row + 0.5) * A.inv_n1);
+            const int g[3] = {cell - row * A.n[0], row - gz * A.n[1], gz};
             const float f[3] = {S.pos[0][p], S.pos[1][p], S.pos[2][p]};
             bool finite = true, in_block = true;
             int ll[3];
@@ -334,6 +360,7 @@ struct DivGeom {
     int64_t nc;
     int M;
     double a[3][3];  // a_m / d
+    double inv_n0, inv_n1;  // 1 / n[0], 1 / n[1]
 };
 
 __device__ __forceinline__ int nbw(int i, int o, int n) {
@@ -381,21 +408,19 @@ __device__ __forceinline__ double div_up(const DivGeom& G, const double* F, int 
 __global__ void __launch_bounds__(256) k_residuals(DivGeom G, const double* __restrict__ E, const double* __restrict__ J,
                                                    const double* __restrict__ B, const double* __restrict__ rho,
                                                    const double* __restrict__ rho_prev, double rho_bg, double ieps0,
-                                                   double dt, int want_rho, int have_prev, int want_divb, double* acc) {
+                                                   double dt, int want_rho, int have_prev, int want_divb, double* part) {
     double g = 0.0, cc = 0.0, db = 0.0;
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < G.nc; q += (int64_t)gridDim.x * blockDim.x) {
-        const int i = (int)(q % G.n[0]);
-        const int j = (int)((q / G.n[0]) % G.n[1]);
-        const int k = (int)(q / ((int64_t)G.n[0] * G.n[1]));
+        const int row = (int)(((double)q + 0.5) * G.inv_n0), k = (int)(((double)row + 0.5) * G.inv_n1);
+        const int i = (int)q - row * G.n[0], j = row - k * G.n[1];
         if (want_rho) {
             g = fmax(g, fabs(div_dn(G, E, i, j, k) - (rho[q] + rho_bg) * ieps0));
             if (have_prev) cc = fmax(cc, fabs(rho[q] - rho_prev[q] + dt * div_dn(G, J, i, j, k)));
         }
         if (want_divb) db = fmax(db, fabs(div_up(G, B, i, j, k)));
     }
-    block_max(g, acc + 0);
-    block_max(cc, acc + 1);
-    block_max(db, acc + 2);
+    double v[3] = {g, cc, db};
+    write_partials<3, true>(v, part + (int64_t)ROW_RESID * PART_MAX);
 }
 
 static void fd_coeffs(int order, double a[3]) {
@@ -459,6 +484,8 @@ static hipError_t launch_rho32(pp_run* r, unsigned mask) {
         vol *= A.ext[d];
     }
     A.nc = r->g.ncell;
+    A.inv_n0 = 1.0 / A.n[0];
+    A.inv_n1 = 1.0 / A.n[1];
     A.acc = (unsigned long long*)r->Jq;  // free and zero between steps, and left so
     A.scale = r->dacc + ACC_RHO_SCALE;
     // every contribution is at most |q w| (the weights of a node are at most 1)
@@ -505,40 +532,88 @@ hipError_t deposit_rho_all(pp_run* r) {
     return hipGetLastError();
 }
 
+// The partials of every row into the accumulators (zero rows whose partials were not written), and
+// beside them the flag word (a double holds it exactly), cleared for the next call: one copy to
+// the host takes all.
+struct FinishArgs {
+    const double* part;
+    double* dacc;
+    int32_t* flags;
+    int count[ROW_COUNT];  // partials of each row
+};
+
+__global__ void __launch_bounds__(1024) k_finish(FinishArgs A) {
+    const int lane = threadIdx.x & 63;
+    for (int row = threadIdx.x >> 6; row < ROW_COUNT; row += 16) {
+        const bool mx = row >= ROW_RESID;
+        double v = 0.0;
+        for (int i = lane; i < A.count[row]; i += 64) {
+            const double x = A.part[(int64_t)row * PART_MAX + i];
+            v = mx ? fmax(v, x) : v + x;
+        }
+        for (int o = 32; o > 0; o >>= 1) {
+            const double x = __shfl_xor(v, o, 64);
+            v = mx ? fmax(v, x) : v + x;
+        }
+        int to;
+        if (row < ROW_FIELD)
+            to = row % 4 == 0 ? ACC_KIN + row / 4 : ACC_MOM + 3 * (row / 4) + row % 4 - 1;
+        else
+            to = row < ROW_RESID ? ACC_UE + row - ROW_FIELD : ACC_GAUSS + row - ROW_RESID;
+        if (lane == 0) A.dacc[to] = v;
+    }
+    if (threadIdx.x == 0) {
+        A.dacc[ACC_FLAGS] = (double)*A.flags;
+        *A.flags = 0;
+    }
+}
+
 // Fills host_out[0..ACC_COUNT) with the accumulators and [ACC_COUNT] with the flag word.
 hipError_t launch_diag(pp_run* r, uint32_t what, double* host_out) {
     const int bs = 256;
     const int64_t nc = r->g.ncell;
     // a pending sort order needs no move here: the moments are sums over every particle and
     // the charge deposit follows the tile starts of the buffers as they are
-    hipError_t e = launch_fill(r->dacc, ACC_COUNT, 0.0, r->stream);
-    if (e != hipSuccess) return e;
+    hipError_t e = hipSuccess;
+    FinishArgs F{};
+    F.part = r->dacc + ACC_PART;
+    F.dacc = r->dacc;
+    F.flags = r->flags;
+    double* part = r->dacc + ACC_PART;
     const bool split = r->p.precision == PP_PREC_FP32_SPLIT;
     const double V = r->p.d[0] * r->p.d[1] * r->p.d[2];
     const double ic = 1.0 / r->p.c;
     if (what & PP_DIAG_MOMENTS) {
+        MomentArgs A;
+        unsigned ns = 0;
+        int64_t nmax = 0;
         for (int s = 0; s < PP_MAX_SPECIES; ++s) {
             const Species& S = r->sp[s];
             if (!S.active || S.n == 0) continue;
-            int64_t g = (S.n + bs - 1) / bs;
-            if (g > 4096) g = 4096;
-            const double wVm = S.w * V * S.m;
+            for (int d = 0; d < 3; ++d) A.u[ns][d] = S.cur.u[d];
+            A.n[ns] = S.n;
+            A.wVm[ns] = S.w * V * S.m;
+            A.slot[ns] = s;
+            nmax = S.n > nmax ? S.n : nmax;
+            ++ns;
+        }
+        A.ic = ic;
+        A.part = part;
+        if (ns > 0) {
+            const dim3 grid(sum_grid(nmax), ns);
+            for (unsigned k = 0; k < ns; ++k)
+                for (int a = 0; a < 4; ++a) F.count[ROW_SPECIES + 4 * A.slot[k] + a] = (int)grid.x;
             if (split)
-                hipLaunchKernelGGL(k_moments<float>, dim3((unsigned)g), dim3(bs), 0, r->stream, (const float*)S.cur.u[0],
-                                   (const float*)S.cur.u[1], (const float*)S.cur.u[2], S.n, ic, wVm, r->dacc + ACC_KIN + s,
-                                   r->dacc + ACC_MOM + 3 * s);
+                hipLaunchKernelGGL(k_moments<float>, grid, dim3(bs), 0, r->stream, A);
             else
-                hipLaunchKernelGGL(k_moments<double>, dim3((unsigned)g), dim3(bs), 0, r->stream,
-                                   (const double*)S.cur.u[0], (const double*)S.cur.u[1], (const double*)S.cur.u[2], S.n,
-                                   ic, wVm, r->dacc + ACC_KIN + s, r->dacc + ACC_MOM + 3 * s);
+                hipLaunchKernelGGL(k_moments<double>, grid, dim3(bs), 0, r->stream, A);
         }
     }
     if (what & PP_DIAG_FIELDS) {
-        int64_t g = (nc + bs - 1) / bs;
-        if (g > 4096) g = 4096;
         const double mu0 = 1.0 / (r->p.eps0 * r->p.c * r->p.c);
-        hipLaunchKernelGGL(k_field_energy, dim3((unsigned)g), dim3(bs), 0, r->stream, (const double*)r->mesh.E,
-                           (const double*)r->mesh.B, nc, 0.5 * r->p.eps0 * V, 0.5 * V / mu0, r->dacc + ACC_UE);
+        hipLaunchKernelGGL(k_field_energy, dim3(sum_grid(nc)), dim3(bs), 0, r->stream, (const double*)r->mesh.E,
+                           (const double*)r->mesh.B, nc, 0.5 * r->p.eps0 * V, 0.5 * V / mu0, part);
+        for (int a = 0; a < 3; ++a) F.count[ROW_FIELD + a] = (int)sum_grid(nc);
     }
     const bool want_rho = (what & PP_DIAG_RHO) != 0;
     const bool want_divb = (what & PP_DIAG_DIVB) != 0;
@@ -553,37 +628,36 @@ hipError_t launch_diag(pp_run* r, uint32_t what, double* host_out) {
         for (int d = 0; d < 3; ++d) G.n[d] = r->p.n[d];
         G.nc = nc;
         G.M = r->p.field_order / 2;
+        G.inv_n0 = 1.0 / G.n[0];
+        G.inv_n1 = 1.0 / G.n[1];
         double a[3];
         fd_coeffs(r->p.field_order, a);
         for (int d = 0; d < 3; ++d)
             for (int m = 0; m < 3; ++m) G.a[d][m] = a[m] / r->p.d[d];
         int64_t g = (nc + bs - 1) / bs;
-        if (g > 4096) g = 4096;
+        if (g > PART_MAX) g = PART_MAX;
+        for (int a = 0; a < 3; ++a) F.count[ROW_RESID + a] = (int)g;
         hipLaunchKernelGGL(k_residuals, dim3((unsigned)g), dim3(bs), 0, r->stream, G, (const double*)r->mesh.E,
                            (const double*)r->mesh.J, (const double*)r->mesh.B, (const double*)r->rho,
                            (const double*)r->rho_prev, r->p.rho_background, 1.0 / r->p.eps0, r->dt_drift, want_rho ? 1 : 0,
-                           have_prev ? 1 : 0, want_divb ? 1 : 0, r->dacc + ACC_GAUSS);
+                           have_prev ? 1 : 0, want_divb ? 1 : 0, part);
     }
     const bool want_relax = (what & PP_DIAG_RELAX) != 0 && r->rhs_valid;
     if (want_relax) {
+        e = launch_fill(r->dacc + ACC_RELAX, 2, 0.0, r->stream);
+        if (e != hipSuccess) return e;
         e = launch_relax_resid(r, r->dacc + ACC_RELAX);
         if (e != hipSuccess) return e;
     }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = hipMemcpyAsync(host_out, r->dacc, ACC_COUNT * sizeof(double), hipMemcpyDeviceToHost, r->stream);
-    if (e != hipSuccess) return e;
-    int32_t flags = 0;
-    e = hipMemcpyAsync(&flags, r->flags, sizeof(int32_t), hipMemcpyDeviceToHost, r->stream);
+    hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, r->stream, F);
+    e = hipMemcpyAsync(host_out, r->dacc, (ACC_COUNT + 1) * sizeof(double), hipMemcpyDeviceToHost, r->stream);
     if (e != hipSuccess) return e;
     e = hipStreamSynchronize(r->stream);
     if (e != hipSuccess) return e;
-    host_out[ACC_COUNT] = (double)flags;
     host_out[ACC_COUNT + 1] = have_prev ? 1.0 : 0.0;
     host_out[ACC_COUNT + 2] = want_relax ? 1.0 : 0.0;
-    // clear the flags and keep rho for the next continuity check
-    e = hipMemsetAsync(r->flags, 0, sizeof(int32_t), r->stream);
-    if (e != hipSuccess) return e;
     if (want_rho) {
         double* t = r->rho_prev;
         r->rho_prev = r->rho;
@@ -594,5 +668,6 @@ hipError_t launch_diag(pp_run* r, uint32_t what, double* host_out) {
 }
 
 int diag_acc_count() { return ACC_COUNT; }
+int64_t diag_buffer_count() { return ACC_PART + (int64_t)ROW_COUNT * PART_MAX; }
 
 }  // namespace pp
