@@ -109,6 +109,8 @@ static void release(pp_run* r) {
         f(r->sp[s].rank);
         f(r->sp[s].rank_base);
         f(r->sp[s].rounds);
+        f(r->sp[s].bin_pre);
+        f(r->sp[s].tile_tot);
         f(r->sp[s].perm);
         f(r->sp[s].offsets_next);
     }
@@ -170,6 +172,8 @@ static size_t internal_bytes(const pp_params* p, const Geom& g, int64_t nmax, in
                             ((size_t)g.ntiles + 1) * sizeof(int32_t) +
                             (size_t)g.ntiles * (SORT_RCAP * sizeof(RoundEntry) + g.dest_slots() * sizeof(int32_t)));
     }
+    else  // per species: bin counts, next bin starts, cell starts, ranks and permutation, tile totals
+        b += (size_t)nsp * ((3 * nb + 1 + 2 * (size_t)nmax + (size_t)g.ntiles + 1) * sizeof(int32_t));
     if (p->field_order > 2)  // line-solve coefficients: at most min(N, 127) per axis
         for (int d = 0; d < 3; ++d) b += (size_t)(p->n[d] < 127 ? p->n[d] : 127) * sizeof(double);
     b += (size_t)nsp * (nb + 1) * sizeof(int32_t);                        // per-species offsets
@@ -293,19 +297,24 @@ pp_status pp_init_species(pp_run* r, int32_t s, double q, double m, double w, co
     }
     Species& S = r->sp[s];
     if (!S.offsets && !dmalloc(&S.offsets, (size_t)r->g.nbins + 1)) return PP_E_HIP;
+    const size_t nt = (size_t)r->g.ntiles, nbins = (size_t)r->g.nbins;
+    const int64_t ncnt = split ? r->g.ncell : r->g.nbins;
+    if (!S.offsets_next && !dmalloc(&S.offsets_next, (split ? nt : nbins) + 1)) return PP_E_HIP;
+    if (!S.cell_cnt && !dmalloc(&S.cell_cnt, (size_t)ncnt)) return PP_E_HIP;
     if (split) {
-        if (!S.offsets_next && !dmalloc(&S.offsets_next, (size_t)r->g.ntiles + 1)) return PP_E_HIP;
-        if (!S.cell_cnt && !dmalloc(&S.cell_cnt, (size_t)r->g.ncell)) return PP_E_HIP;
-        if (!S.rounds && !dmalloc(&S.rounds, (size_t)r->g.ntiles * SORT_RCAP)) return PP_E_HIP;
-        if (!S.rank_base && !dmalloc(&S.rank_base, (size_t)r->g.ntiles * r->g.dest_slots())) return PP_E_HIP;
-        if (!ok(launch_fill_i32(S.cell_cnt, r->g.ncell, 0, r->stream), "fill")) return PP_E_HIP;
-        if (S.rank) (void)hipFree(S.rank);
-        S.rank = nullptr;
-        if (!dmalloc(&S.rank, (size_t)parts->n)) return PP_E_HIP;
-        if (S.perm) (void)hipFree(S.perm);
-        S.perm = nullptr;
-        if (!dmalloc(&S.perm, (size_t)parts->n)) return PP_E_HIP;
+        if (!S.rounds && !dmalloc(&S.rounds, nt * SORT_RCAP)) return PP_E_HIP;
+        if (!S.rank_base && !dmalloc(&S.rank_base, nt * r->g.dest_slots())) return PP_E_HIP;
+    } else {
+        if (!S.bin_pre && !dmalloc(&S.bin_pre, nbins)) return PP_E_HIP;
+        if (!S.tile_tot && !dmalloc(&S.tile_tot, nt + 1)) return PP_E_HIP;
     }
+    if (!ok(launch_fill_i32(S.cell_cnt, ncnt, 0, r->stream), "fill")) return PP_E_HIP;
+    if (S.rank) (void)hipFree(S.rank);
+    S.rank = nullptr;
+    if (!dmalloc(&S.rank, (size_t)parts->n)) return PP_E_HIP;
+    if (S.perm) (void)hipFree(S.perm);
+    S.perm = nullptr;
+    if (!dmalloc(&S.perm, (size_t)parts->n)) return PP_E_HIP;
     S.pending = false;
     if (split && parts->n > r->sort_scratch_n) {
         if (r->sort_scratch) (void)hipFree(r->sort_scratch);
@@ -362,8 +371,17 @@ pp_status pp_gather_push_deposit(pp_run* r) {
         if (!ok(e, "gather_push_deposit")) return PP_E_HIP;
         for (int s = 0; s < PP_MAX_SPECIES; ++s) {
             if (!r->sp[s].active) continue;
-            r->sp[s].binned = false;  // the particles move: their bins are those of the last sort
-            if (done & (1u << s)) continue;
+            Species& S = r->sp[s];
+            S.binned = false;  // the particles move: their bins are those of the last sort
+            const bool counts_left = S.ranked;  // by an earlier push that no sort has followed
+            S.ranked = (done & (1u << s)) != 0;
+            if (S.ranked) {
+                if (S.pending) swap_buffers(S.cur);  // the kernel wrote the pending order
+                S.pending = false;
+                continue;
+            }
+            if (!ok(materialize(r, s), "materialize")) return PP_E_HIP;
+            if (counts_left && !ok(launch_fill_i32(S.cell_cnt, r->g.nbins, 0, r->stream), "fill")) return PP_E_HIP;
             e = launch_gpd64(r, s, target);
             if (!ok(e, "gather_push_deposit")) return PP_E_HIP;
         }

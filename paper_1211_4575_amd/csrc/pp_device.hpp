@@ -22,6 +22,15 @@ __device__ __forceinline__ int wrap_near(int i, int n) {
     return (j >= 0 && j < n) ? j : wrap(i, n);
 }
 
+// Nearest cell of an FP64 position on an axis of n cells: positions outside the box by a period
+// or more (not produced by the push) are binned into cell 0, keeping every index in range.
+__device__ __forceinline__ int nearest_cell(double x, int n) {
+    int v = (int)floor(x + 0.5);
+    if (v >= n) v -= n;
+    if (v < 0) v += n;
+    return v < 0 || v >= n ? 0 : v;
+}
+
 // Weights of order O (Sec. II: TSC for O = 2, PCS for O = 3) of the O+1 nodes
 // i0, i0+1, ..., i0+O nearest to coordinate y (node positions are integers).
 //   O = 2: c = floor(y + 1/2), t = y - c in [-1/2, 1/2), i0 = c - 1,

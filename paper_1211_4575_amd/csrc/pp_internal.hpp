@@ -61,18 +61,21 @@ struct Species {
     // tile order of pp_sort.hip (valid when sorted).
     int32_t* offsets = nullptr;
     bool binned = false;  // FP64 form: sorted and not pushed since (offsets are the bins of the positions)
-    // split form, filled by the particle kernel for the next sort: particles per cell of the
-    // new positions (ncell, zero between steps), each particle's rank among the particles of
-    // its new cell (n; as RankedArgs in pp_sort.hip reads it), per tile and destination cell the
-    // ranks its particles start from (ntiles * dest_slots), the next tile starts; the sort's
-    // round tables (ntiles * SORT_RCAP)
+    // FP64 form: starts of a tile's cells inside the tile (nbins), tile totals and starts (ntiles + 1)
+    int32_t* bin_pre = nullptr;
+    int32_t* tile_tot = nullptr;
+    // filled by the (tiled) particle kernel for the next sort: particles per cell of the
+    // new positions (ncell, FP64 form per bin; zero between steps), each particle's rank among the
+    // particles of its new cell (n; as pp_sort.hip reads it), per tile and destination cell the
+    // ranks its particles start from (split form: ntiles * dest_slots), the next tile starts
+    // (FP64 form: bin starts); the sort's round tables (split form: ntiles * SORT_RCAP)
     int32_t* cell_cnt = nullptr;
     int32_t* rank = nullptr;
     int32_t* rank_base = nullptr;
     int32_t* offsets_next = nullptr;
     RoundEntry* rounds = nullptr;
     bool ranked = false;  // cell_cnt / rank describe the current positions
-    // split form: the last sort left its order as a permutation (slot q of the new order is
+    // the last sort left its order as a permutation (slot q of the new order is
     // particle perm[q] of the current buffers); the next particle kernel, or materialize,
     // moves the particles
     int32_t* perm = nullptr;

@@ -1,8 +1,10 @@
 // Per-cell particle sort (Sec. III: between the particle and field updates the particle
 // arrays are sorted by cell for cache locality).
 //
-// FP64 form: counting sort by tile-major cell key (histogram -> exclusive scan -> scatter
-// with atomic cursors; order inside a cell unspecified).
+// FP64 form: particles in cell order, the cells tile by tile (order inside a cell unspecified).
+// After a push by tiles the particle kernel has counted and ranked the particles of every new
+// cell (ranked sort, as for the split form); otherwise a counting sort by tile-major cell key
+// (histogram -> exclusive scan -> scatter with atomic cursors).
 //
 // Split form: particles are laid out tile by tile (64 cells).  Every particle has a rank r
 // inside its cell; a tile's particles are laid out in pairs of ranks (see pair_table below):
@@ -42,19 +44,7 @@ __device__ __forceinline__ int32_t tile_key(const KeyGeom& G, int i, int j, int 
 
 // key of an FP64 particle: nearest cell centre
 __device__ __forceinline__ int32_t key_f64(const KeyGeom& G, double x, double y, double z) {
-    int c[3];
-    const double X[3] = {x, y, z};
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        int v = (int)floor(X[d] + 0.5);
-        if (v >= G.n[d]) v -= G.n[d];
-        if (v < 0) v += G.n[d];
-        // positions outside [0, n) (not produced by the push) are binned into cell 0,
-        // keeping every bin index in range; the particle kernel checks positions itself
-        if (v < 0 || v >= G.n[d]) v = 0;
-        c[d] = v;
-    }
-    return tile_key(G, c[0], c[1], c[2]);
+    return tile_key(G, nearest_cell(x, G.n[0]), nearest_cell(y, G.n[1]), nearest_cell(z, G.n[2]));
 }
 
 __device__ __forceinline__ int32_t key_cell(const KeyGeom& G, int32_t cell) {
@@ -432,7 +422,28 @@ struct RankedArgs {
     int32_t* perm;          // n: perm[slot] = particle
     int64_t n;
     const int32_t* cell;
+    // FP64 form: cnt by bin (64 per tile), start and next_bins bin starts, pre the starts of a
+    // tile's cells inside it; no round table, rank base or overflow
+    int32_t* pre;
+    int32_t* next_bins;
+    const double* pos[3];
 };
+
+// FP64 form, one wavefront per tile: the cells' starts inside the tile and its total
+__device__ __forceinline__ void bin_prefix_tile(const RankedArgs& A, int64_t t) {
+    const int lane = threadIdx.x & 63;
+    if (t >= A.G.ntiles) return;
+    const int32_t c = A.cnt[t * TILE_CELLS + lane];
+    A.cnt[t * TILE_CELLS + lane] = 0;
+    int32_t incl = c;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const int32_t y = __shfl_up(incl, o, 64);
+        if (lane >= o) incl += y;
+    }
+    A.pre[t * TILE_CELLS + lane] = incl - c;
+    if (lane == 63) A.tot[t] = incl;
+}
 
 // one wavefront per tile: lane = local cell
 __device__ __forceinline__ void round_table_tile(const RankedArgs& A, int64_t t) {
@@ -536,7 +547,7 @@ __device__ __forceinline__ void ranked_scan(const RankedArgs& A) {
     scan_workgroup(A.tot, A.G.ntiles, total, largest);
     if (threadIdx.x == 0) {
         A.tot[A.G.ntiles] = total;
-        *A.tile_max = largest;
+        if (A.tile_max) *A.tile_max = largest;
     }
     for (int64_t q = total + (int64_t)threadIdx.x; q < A.n; q += SCAN1_BS) A.perm[q] = -1;
 }
@@ -666,6 +677,70 @@ __device__ __forceinline__ void ranked_perm_tile(const RankedArgs& A, int64_t T,
         }
 }
 
+// FP64 form: perm[slot] = particle for the particles of source tile T, and T's next bin starts.  A
+// rank word holds the destination cell and the rank in it (slot << 20 | rank, or bit 31 | rank
+// with the cell taken from the position), so a particle's slot is one LDS lookup away.
+__device__ __forceinline__ void bin_perm_tile(const RankedArgs& A, int64_t T, int32_t* lds) {
+    const Geom& G = A.G;
+    if (T >= G.ntiles) return;
+    const int32_t ss = A.start[T * TILE_CELLS], se = A.start[(T + 1) * TILE_CELLS];
+    const int32_t d0 = A.tot[T], nd = A.tot[T + 1] - d0;
+    const bool staged = nd <= PERM_IMG;
+    int32_t* img = lds;
+    int32_t* first = lds + PERM_IMG;  // first slot of each destination cell
+    if (threadIdx.x < TILE_CELLS) {
+        A.next_bins[T * TILE_CELLS + threadIdx.x] = d0 + A.pre[T * TILE_CELLS + threadIdx.x];
+        if (T == G.ntiles - 1 && threadIdx.x == 0) A.next_bins[G.nbins] = A.tot[G.ntiles];
+    }
+    if (staged)
+        for (int32_t q = threadIdx.x; q < nd; q += blockDim.x) img[q] = -1;
+    auto cell_first = [&](int gx, int gy, int gz) {
+        const int32_t t = (gx >> A.tsh[0]) + G.nt[0] * ((gy >> A.tsh[1]) + G.nt[1] * (gz >> A.tsh[2]));
+        const int lc = (gx & (G.t[0] - 1)) + ((gy & (G.t[1] - 1)) << A.tsh[0]) + ((gz & (G.t[2] - 1)) << (A.tsh[0] + A.tsh[1]));
+        return A.tot[t] + A.pre[t * TILE_CELLS + lc];
+    };
+    const int e0 = G.dest_ext(0), e1 = G.dest_ext(1), slots = e0 * e1 * G.dest_ext(2);
+    const int ox = (int)(T % G.nt[0]) * G.t[0], oy = (int)((T / G.nt[0]) % G.nt[1]) * G.t[1],
+              oz = (int)(T / ((int64_t)G.nt[0] * G.nt[1])) * G.t[2];
+    if (se > ss)
+        for (int q = threadIdx.x; q < slots; q += blockDim.x) {
+            const int z = q / (e0 * e1), r = q - z * e0 * e1, y = r / e0, x = r - y * e0;
+            first[q] = cell_first(e0 == 1 ? 0 : wrap_near(ox + x - DEST_HALO, G.n[0]),
+                                  e1 == 1 ? 0 : wrap_near(oy + y - DEST_HALO, G.n[1]),
+                                  G.n[2] == 1 ? 0 : wrap_near(oz + z - DEST_HALO, G.n[2]));
+        }
+    __syncthreads();
+    for (int64_t b = ss; b < se; b += PERM_BLOCK) {
+        int32_t w[PERM_PER];
+#pragma unroll
+        for (int k = 0; k < PERM_PER; ++k) {
+            const int64_t p = b + threadIdx.x + k * 256;
+            w[k] = p < se ? A.rank[p] : 0;
+        }
+#pragma unroll
+        for (int k = 0; k < PERM_PER; ++k) {
+            const int64_t p = b + threadIdx.x + k * 256;
+            if (p >= se) continue;
+            int32_t q;
+            if (w[k] >= 0)
+                q = first[w[k] >> 20] + (w[k] & 0xFFFFF);
+            else
+                q = cell_first(nearest_cell(A.pos[0][p], G.n[0]), nearest_cell(A.pos[1][p], G.n[1]),
+                               nearest_cell(A.pos[2][p], G.n[2])) + (w[k] & 0x7FFFFFFF);
+            if (staged && q >= d0 && q < d0 + nd)
+                img[q - d0] = (int32_t)p;
+            else
+                A.perm[q] = (int32_t)p;
+        }
+    }
+    __syncthreads();
+    if (staged)
+        for (int32_t q = threadIdx.x; q < nd; q += blockDim.x) {
+            const int32_t v = img[q];
+            if (v >= 0) A.perm[d0 + q] = v;
+        }
+}
+
 size_t sort_perm_lds(const pp_run* r) {
     return PERM_IMG * sizeof(int32_t) + (size_t)r->g.dest_slots() * sizeof(DestCell);
 }
@@ -762,14 +837,23 @@ static KeyGeom key_geom(const pp_run* r) {
 // ---- launches of the ranked sort: all species of a run, or of all runs of a batch ----------
 enum SortPhase { SP_TABLES = 0, SP_SCAN = 1, SP_PERM = 2 };
 
-template <int PHASE>
+enum SortForm { SF_SPLIT = 0, SF_FP64 = 1 };
+
+template <int PHASE, int FORM>
 __device__ __forceinline__ void sort_phase(const RankedArgs& A, int64_t blk, int32_t* lds) {
-    if constexpr (PHASE == SP_TABLES)
-        round_table_tile(A, blk * 4 + (threadIdx.x >> 6));
-    else if constexpr (PHASE == SP_SCAN)
+    if constexpr (PHASE == SP_TABLES) {
+        const int64_t t = blk * 4 + (threadIdx.x >> 6);
+        if constexpr (FORM == SF_SPLIT)
+            round_table_tile(A, t);
+        else
+            bin_prefix_tile(A, t);
+    } else if constexpr (PHASE == SP_SCAN) {
         ranked_scan(A);
-    else
+    } else if constexpr (FORM == SF_SPLIT) {
         ranked_perm_tile(A, blk, lds);
+    } else {
+        bin_perm_tile(A, blk, lds);
+    }
 }
 
 constexpr int sort_threads(int phase) { return phase == SP_SCAN ? SCAN1_BS : 256; }
@@ -778,10 +862,10 @@ struct SortArgs {
     RankedArgs sp[PP_MAX_SPECIES];
 };
 
-template <int PHASE>
+template <int PHASE, int FORM>
 __global__ void __launch_bounds__(sort_threads(PHASE)) k_sort(SortArgs S) {
     extern __shared__ int32_t lds_sort[];
-    sort_phase<PHASE>(S.sp[blockIdx.y], blockIdx.x, lds_sort);
+    sort_phase<PHASE, FORM>(S.sp[blockIdx.y], blockIdx.x, lds_sort);
 }
 
 template <int PHASE>
@@ -791,7 +875,7 @@ __global__ void __launch_bounds__(sort_threads(PHASE)) k_sort_batch(const Ranked
     const int64_t b = blockIdx.x;
     const int r = find_segment(prefix, nseg, b);
     if (r < 0) return;
-    sort_phase<PHASE>(T[r], b - prefix[r], lds_sort);
+    sort_phase<PHASE, SF_SPLIT>(T[r], b - prefix[r], lds_sort);
 }
 
 void sort_desc(const pp_run* r, int s, RankedArgs* A) {
@@ -804,17 +888,21 @@ void sort_desc(const pp_run* r, int s, RankedArgs* A) {
     }
     A->cnt = S.cell_cnt;
     A->rounds = S.rounds;
-    A->tot = S.offsets_next;
+    const bool split = r->p.precision == PP_PREC_FP32_SPLIT;
+    A->tot = split ? S.offsets_next : S.tile_tot;
     A->rtot = r->sort_cursor + 3 * nt * s;  // 64 entries per tile, 3 used by each of 8 species
     A->ovf = A->rtot + nt;
     A->nchunk = A->rtot + 2 * nt;
-    A->tile_max = r->tile_max + s;
+    A->tile_max = split ? r->tile_max + s : nullptr;
     A->start = S.offsets;
     A->rank = S.rank;
     A->base = S.rank_base;
     A->perm = S.perm;
     A->n = S.n;
     A->cell = S.cur.cell;
+    A->pre = S.bin_pre;
+    A->next_bins = S.offsets_next;
+    for (int d = 0; d < 3; ++d) A->pos[d] = split ? nullptr : (const double*)S.cur.pos[d];
 }
 
 size_t sort_desc_size() { return sizeof(RankedArgs); }
@@ -868,29 +956,32 @@ void sort_enqueued(pp_run* r, int s) {
     S.offsets_next = t;
     S.ranked = false;
     S.sorted = true;
+    S.binned = r->p.precision == PP_PREC_FP64;
     S.pending = S.n > 0;
 }
 
 // out[q] = in[perm[q]] for every attribute (the move a pending permutation stands for)
+template <typename T>
 struct ApplyArgs {
     int64_t n;
     const int32_t* perm;
     const int32_t* cell;
-    const float* pos[3];
-    const float* u[3];
+    const T* pos[3];
+    const T* u[3];
     const int64_t* id;
     int32_t* cell_o;
-    float* pos_o[3];
-    float* u_o[3];
+    T* pos_o[3];
+    T* u_o[3];
     int64_t* id_o;
 };
 
-__global__ void __launch_bounds__(256) k_apply_perm(ApplyArgs A) {
+template <typename T>
+__global__ void __launch_bounds__(256) k_apply_perm(ApplyArgs<T> A) {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= A.n) return;
     const int32_t p = A.perm[q];
     if (p < 0) return;
-    A.cell_o[q] = A.cell[p];
+    if (A.cell) A.cell_o[q] = A.cell[p];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         A.pos_o[d][q] = A.pos[d][p];
@@ -899,26 +990,34 @@ __global__ void __launch_bounds__(256) k_apply_perm(ApplyArgs A) {
     if (A.id) A.id_o[q] = A.id[p];
 }
 
+template <typename T>
+static void apply_perm(pp_run* r, const Species& S) {
+    ApplyArgs<T> A;
+    A.n = S.n;
+    A.perm = S.perm;
+    A.cell = S.cur.cell;
+    A.cell_o = S.cur.cell_alt;
+    A.id = S.cur.id;
+    A.id_o = S.cur.id ? S.cur.id_alt : nullptr;
+    for (int d = 0; d < 3; ++d) {
+        A.pos[d] = (const T*)S.cur.pos[d];
+        A.u[d] = (const T*)S.cur.u[d];
+        A.pos_o[d] = (T*)S.cur.pos_alt[d];
+        A.u_o[d] = (T*)S.cur.u_alt[d];
+    }
+    hipLaunchKernelGGL(k_apply_perm<T>, dim3((unsigned)((S.n + 255) / 256)), dim3(256), 0, r->stream, A);
+}
+
 hipError_t materialize(pp_run* r, int s) {
     for (int k = 0; k < PP_MAX_SPECIES; ++k) {
         if (s >= 0 && k != s) continue;
         Species& S = r->sp[k];
         if (!S.active || !S.pending) continue;
         if (S.n > 0) {
-            ApplyArgs A;
-            A.n = S.n;
-            A.perm = S.perm;
-            A.cell = S.cur.cell;
-            A.cell_o = S.cur.cell_alt;
-            A.id = S.cur.id;
-            A.id_o = S.cur.id ? S.cur.id_alt : nullptr;
-            for (int d = 0; d < 3; ++d) {
-                A.pos[d] = (const float*)S.cur.pos[d];
-                A.u[d] = (const float*)S.cur.u[d];
-                A.pos_o[d] = (float*)S.cur.pos_alt[d];
-                A.u_o[d] = (float*)S.cur.u_alt[d];
-            }
-            hipLaunchKernelGGL(k_apply_perm, dim3((unsigned)((S.n + 255) / 256)), dim3(256), 0, r->stream, A);
+            if (r->p.precision == PP_PREC_FP32_SPLIT)
+                apply_perm<float>(r, S);
+            else
+                apply_perm<double>(r, S);
             hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
             swap_buffers(S.cur);
@@ -926,6 +1025,17 @@ hipError_t materialize(pp_run* r, int s) {
         S.pending = false;
     }
     return hipSuccess;
+}
+
+template <int FORM>
+static void launch_ranked(pp_run* r, const SortArgs& A, unsigned ns, bool any, size_t perm_lds) {
+    const int64_t nt = r->g.ntiles;
+    hipLaunchKernelGGL((k_sort<SP_TABLES, FORM>), dim3((unsigned)((nt + 3) / 4), ns), dim3(sort_threads(SP_TABLES)), 0,
+                       r->stream, A);
+    hipLaunchKernelGGL((k_sort<SP_SCAN, FORM>), dim3(1, ns), dim3(sort_threads(SP_SCAN)), 0, r->stream, A);
+    if (any)
+        hipLaunchKernelGGL((k_sort<SP_PERM, FORM>), dim3((unsigned)nt, ns), dim3(sort_threads(SP_PERM)), perm_lds,
+                           r->stream, A);
 }
 
 // The ranked sort of the species in mask, together.
@@ -939,12 +1049,10 @@ static hipError_t sort_ranked(pp_run* r, unsigned mask) {
         any = any || r->sp[s].n > 0;
     }
     if (ns == 0) return hipSuccess;
-    const int64_t nt = r->g.ntiles;
-    hipLaunchKernelGGL(k_sort<SP_TABLES>, dim3((unsigned)((nt + 3) / 4), ns), dim3(sort_threads(SP_TABLES)), 0, r->stream, A);
-    hipLaunchKernelGGL(k_sort<SP_SCAN>, dim3(1, ns), dim3(sort_threads(SP_SCAN)), 0, r->stream, A);
-    if (any)
-        hipLaunchKernelGGL(k_sort<SP_PERM>, dim3((unsigned)nt, ns), dim3(sort_threads(SP_PERM)), sort_perm_lds(r),
-                           r->stream, A);
+    if (r->p.precision == PP_PREC_FP32_SPLIT)
+        launch_ranked<SF_SPLIT>(r, A, ns, any, sort_perm_lds(r));
+    else
+        launch_ranked<SF_FP64>(r, A, ns, any, (PERM_IMG + (size_t)r->g.dest_slots()) * sizeof(int32_t));
     hipError_t e = hipGetLastError();
     for (int s = 0; s < PP_MAX_SPECIES; ++s)
         if (mask & (1u << s)) sort_enqueued(r, s);
@@ -1028,18 +1136,16 @@ static hipError_t sort_species(pp_run* r, int s) {
 
 hipError_t launch_sort(pp_run* r, int s) {
     const bool split = r->p.precision == PP_PREC_FP32_SPLIT;
-    if (split) {
-        hipError_t e = materialize(r, s);  // a sort of a sort: apply the pending order first
-        if (e != hipSuccess) return e;
-    }
+    hipError_t e = materialize(r, s);  // a sort of a sort: apply the pending order first
+    if (e != hipSuccess) return e;
     unsigned ranked = 0;
     for (int k = 0; k < PP_MAX_SPECIES; ++k) {
         if ((s >= 0 && k != s) || !r->sp[k].active) continue;
-        if (split && r->sp[k].ranked) {
+        if (r->sp[k].ranked) {
             ranked |= 1u << k;
             continue;
         }
-        hipError_t e = split ? sort_species<float>(r, k) : sort_species<double>(r, k);
+        e = split ? sort_species<float>(r, k) : sort_species<double>(r, k);
         if (e != hipSuccess) return e;
     }
     return sort_ranked(r, ranked);

@@ -111,3 +111,48 @@ def test_species_sorted_one_by_one_and_together(ppm, orc, n, O):
         run.close()
     for J in out[1:]:
         assert np.array_equal(J, out[0])
+
+
+@pytest.mark.parametrize("n,O", [((9, 8, 5), 3), ((17, 9, 1), 2), ((64, 1, 1), 3), ((70, 2, 2), 3), ((3, 5, 8), 2)])
+def test_fp64_sort_orders(ppm, orc, n, O):
+    """Pushes with and without sorts between them, in several orders (the sort after a tiled push
+    takes its counts and ranks, the others count again): the same particles, J and cell order as
+    sorting every time; each sum is FP64 in another order, 1e-12 of the largest value."""
+    species, E, B = random_state(orc, n, 5, seed=8, uth=0.4, nspecies=2, pair=False)
+    many = 0.4 * np.array(n)[:, None] + np.random.default_rng(1).uniform(0, 0.3, (3, 5000))
+    species[1] = dict(species[1], pos=np.concatenate([species[1]["pos"], many], 1),
+                      u=np.concatenate([species[1]["u"], np.full((3, 5000), 0.1)], 1))
+    species[0]["pos"][:, 0] = 1.7 * np.array(n)  # a period outside
+    species[0]["u"][:, 1] = np.nan  # flagged and left as it is
+    kw = dict(n=n, dt=0.35, shape_order=O, field_order=4, relax_max_iter=100, precision=ppm.PP_PREC_FP64)
+    out = []
+    for sorts in ((-1,), (0, 1), (1, -1), (), (0,), "every second step"):
+        run = ppm.Run(ppm.make_params(**kw), species, E=E, B=B)
+        for i in range(4):
+            run.gather_push_deposit()
+            for s in (sorts if sorts != "every second step" else ((-1, -1) if i % 2 else ())):
+                run.sort(s)
+        run.gather_push_deposit()
+        flags = run.diagnostics().flags
+        run.sort()
+        parts = [run.particles(s) for s in range(2)]
+        out.append((run.fields()[2], [_by_id(p) for p in parts], flags))
+        # in cell order, the cells tile by tile (sides of a tile: powers of two, 64 cells)
+        t = [1, 1, 1]
+        while np.prod(t) < 64 and any(t[d] < n[d] for d in range(3)):
+            t[min((d for d in range(3) if t[d] < n[d]), key=lambda d: t[d])] *= 2
+        nt = [-(-n[d] // t[d]) for d in range(3)]
+        for p in parts:
+            c = np.floor(p["pos"] + 0.5).astype(int)
+            c = np.where(c >= np.array(n)[:, None], c - np.array(n)[:, None], c)
+            tile = c[0] // t[0] + nt[0] * (c[1] // t[1] + nt[1] * (c[2] // t[2]))
+            key = tile * 64 + c[0] % t[0] + t[0] * (c[1] % t[1] + t[1] * (c[2] % t[2]))
+            assert np.all(np.diff(key) >= 0)
+        run.close()
+    for J, parts, flags in out[1:]:
+        assert flags == out[0][2] == ppm.PP_FLAG_NONFINITE
+        assert rel_inf(J, out[0][0]) < 1e-12
+        for a, b in zip(parts, out[0][1]):
+            assert np.max(np.abs(periodic_diff(a["pos"], b["pos"], n))) < 1e-12
+            assert np.array_equal(np.isnan(a["u"]), np.isnan(b["u"]))
+            assert np.nanmax(np.abs(a["u"] - b["u"])) < 1e-12
