@@ -23,7 +23,7 @@ void set_error_text(const char* msg) {
 }
 
 // defined in the kernel translation units
-hipError_t field_setup(pp_run* r);
+void field_setup(pp_run* r, double* consts);  // consts: host copy of the run's constants
 int line_setup_axis(int order, int N, double* coef_host, int* off);
 int64_t scan_tmp_size(int64_t n);
 int diag_acc_count();
@@ -79,43 +79,75 @@ static void choose_tiles(const int n[3], int t[3]) {
     }
 }
 
-template <typename T>
-static bool dmalloc(T** p, size_t count) {
-    *p = nullptr;
-    if (count == 0) count = 1;
-    return ok(hipMalloc((void**)p, count * sizeof(T)), "hipMalloc");
+// The arrays of a run, or of a species, as parts of one device allocation (every hipMalloc and
+// hipFree costs tens of microseconds, and a served request creates a run).  The same list gives
+// the size alone.
+struct Arena {
+    static constexpr int MAX = 24;
+    void** ptr[MAX];
+    size_t off[MAX];
+    int count = 0;
+    size_t size = 0;
+
+    template <typename T>
+    void add(T** p, size_t n) {
+        ptr[count] = (void**)p;
+        off[count++] = size;
+        size += ((n > 0 ? n : 1) * sizeof(T) + 255) & ~(size_t)255;
+    }
+    bool allocate(void** base) {
+        *base = nullptr;
+        if (!ok(hipMalloc(base, size), "hipMalloc")) {
+            *base = nullptr;
+            return false;
+        }
+        for (int i = 0; i < count; ++i) *ptr[i] = (char*)*base + off[i];
+        return true;
+    }
+};
+
+// values of the run's constants: relaxation weights of each drift, line-solve taps of each axis
+static size_t omega_count(const pp_params* p) { return (size_t)p->relax_max_iter + 2; }
+
+static void run_arrays(const pp_params* p, const Geom& g, pp_run* r, Arena& A) {
+    const size_t nc = (size_t)g.ncell, n3 = 3 * nc;
+    A.add(&r->J2, n3);
+    A.add(&r->Bn, n3);
+    A.add(&r->Bw, n3);
+    A.add(&r->R, n3);
+    A.add(&r->rho, nc);
+    A.add(&r->rho_prev, nc);
+    A.add(&r->sort_cursor, (size_t)g.nbins);
+    A.add(&r->scan_tmp, (size_t)scan_tmp_size(g.nbins + 1));
+    A.add(&r->dacc, (size_t)diag_buffer_count());
+    A.add(&r->consts, 3 * omega_count(p) + 3 * 127);
+    // cleared at the start, together: the flag word, the largest tiles, the fixed-point current
+    A.add(&r->flags, 1);
+    A.add(&r->tile_max, PP_MAX_SPECIES);
+    A.add(&r->Jq, p->precision == PP_PREC_FP32_SPLIT ? n3 : 0);
+}
+
+static void species_arrays(const pp_params* p, const Geom& g, int64_t n, Species& S, Arena& A) {
+    const bool split = p->precision == PP_PREC_FP32_SPLIT;
+    const size_t nt = (size_t)g.ntiles, nb = (size_t)g.nbins;
+    A.add(&S.offsets, nb + 1);
+    A.add(&S.offsets_next, (split ? nt : nb) + 1);
+    A.add(&S.cell_cnt, split ? (size_t)g.ncell : nb);
+    A.add(&S.rank, (size_t)n);
+    A.add(&S.perm, (size_t)n);
+    if (split) {
+        A.add(&S.rounds, nt * SORT_RCAP);
+        A.add(&S.rank_base, nt * (size_t)g.dest_slots());
+    } else {
+        A.add(&S.bin_pre, nb);
+        A.add(&S.tile_tot, nt + 1);
+    }
 }
 
 static void release(pp_run* r) {
-    auto f = [](void* p) {
-        if (p) (void)hipFree(p);
-    };
-    f(r->J2);
-    f(r->Bn);
-    f(r->Bw);
-    f(r->R);
-    f(r->rho);
-    f(r->rho_prev);
-    f(r->sort_cursor);
-    f(r->sort_scratch);
-    f(r->scan_tmp);
-    f(r->flags);
-    f(r->dacc);
-    f(r->Jq);
-    f(r->tile_max);
-    for (auto& S : r->rs) f(S.omega);
-    for (int s = 0; s < PP_MAX_SPECIES; ++s) {
-        f(r->sp[s].cell_cnt);
-        f(r->sp[s].rank);
-        f(r->sp[s].rank_base);
-        f(r->sp[s].rounds);
-        f(r->sp[s].bin_pre);
-        f(r->sp[s].tile_tot);
-        f(r->sp[s].perm);
-        f(r->sp[s].offsets_next);
-    }
-    for (int d = 0; d < 3; ++d) f(r->line[d].coef);
-    for (int s = 0; s < PP_MAX_SPECIES; ++s) f(r->sp[s].offsets);
+    if (r->arena) (void)hipFree(r->arena);
+    for (Species& S : r->sp)
+        if (S.arena) (void)hipFree(S.arena);
     if (r->ev0) (void)hipEventDestroy(r->ev0);
     if (r->ev1) (void)hipEventDestroy(r->ev1);
 }
@@ -153,31 +185,17 @@ const char* pp_status_str(pp_status st) {
 
 const char* pp_last_hip_error(void) { return g_err; }
 
-// Device bytes pp_create and pp_init_species allocate for a run (the caller-owned mesh and
-// particle arrays not included); mirrors the allocations below.
+// Device bytes pp_create and pp_init_species allocate for a run at most (the caller-owned mesh
+// and particle arrays not included): the arrays without particles, the rank and permutation of
+// every species' particles and, in the split form, as much again for the largest species (the
+// first sort's scratch, which those two arrays serve as today).
 static size_t internal_bytes(const pp_params* p, const Geom& g, int64_t nmax, int nsp) {
-    const size_t nc = (size_t)g.ncell, n3 = 3 * nc, nb = (size_t)g.nbins;
-    size_t b = 0;
-    b += 4 * n3 * sizeof(double);                                          // J2, Bn, Bw, R
-    b += 2 * nc * sizeof(double);                                          // rho, rho_prev
-    b += nb * sizeof(int32_t) + (size_t)scan_tmp_size(g.nbins + 1) * sizeof(int32_t);
-    b += sizeof(int32_t) + (size_t)diag_buffer_count() * sizeof(double);
-    b += (p->time_order == 4 ? 3 : 1) * ((size_t)p->relax_max_iter + 2) * sizeof(double);  // relaxation weights
-    if (p->precision == PP_PREC_FP32_SPLIT) {
-        b += n3 * sizeof(long long) + PP_MAX_SPECIES * sizeof(int32_t);
-        b += 2 * (size_t)nmax * sizeof(int32_t);                           // sort scratch
-        // per species: cell counts, particle ranks and sort permutation, next tile starts, round
-        // tables and the ranks the particles of each tile start from
-        b += (size_t)nsp * (nc * sizeof(int32_t) + 2 * (size_t)nmax * sizeof(int32_t) +
-                            ((size_t)g.ntiles + 1) * sizeof(int32_t) +
-                            (size_t)g.ntiles * (SORT_RCAP * sizeof(RoundEntry) + g.dest_slots() * sizeof(int32_t)));
-    }
-    else  // per species: bin counts, next bin starts, cell starts, ranks and permutation, tile totals
-        b += (size_t)nsp * ((3 * nb + 1 + 2 * (size_t)nmax + (size_t)g.ntiles + 1) * sizeof(int32_t));
-    if (p->field_order > 2)  // line-solve coefficients: at most min(N, 127) per axis
-        for (int d = 0; d < 3; ++d) b += (size_t)(p->n[d] < 127 ? p->n[d] : 127) * sizeof(double);
-    b += (size_t)nsp * (nb + 1) * sizeof(int32_t);                        // per-species offsets
-    return b;
+    pp_run r;
+    Arena A, B;
+    run_arrays(p, g, &r, A);
+    species_arrays(p, g, 0, r.sp[0], B);
+    const size_t pair = 2 * (size_t)nmax * sizeof(int32_t);
+    return A.size + (size_t)nsp * (B.size + pair) + (p->precision == PP_PREC_FP32_SPLIT ? pair : 0);
 }
 
 static void make_geom_host(const pp_params* p, Geom& g) {
@@ -220,61 +238,57 @@ pp_status pp_create(const pp_params* params, const pp_mesh* mesh, void* hip_stre
         delete r;
         return PP_E_CAPACITY;
     }
-    const size_t n3 = 3 * (size_t)g.ncell;
-    bool okk = true;
-    okk = okk && dmalloc(&r->J2, n3) && dmalloc(&r->Bn, n3) && dmalloc(&r->Bw, n3) && dmalloc(&r->R, n3);
-    okk = okk && dmalloc(&r->rho, (size_t)g.ncell) && dmalloc(&r->rho_prev, (size_t)g.ncell);
-    okk = okk && dmalloc(&r->sort_cursor, (size_t)g.nbins) && dmalloc(&r->scan_tmp, (size_t)scan_tmp_size(g.nbins + 1));
-    okk = okk && dmalloc(&r->flags, 1) && dmalloc(&r->dacc, (size_t)diag_buffer_count());
-    r->nrs = params->time_order == 4 ? 3 : 1;
-    for (int k = 0; k < r->nrs; ++k) okk = okk && dmalloc(&r->rs[k].omega, (size_t)params->relax_max_iter + 2);
-    if (params->precision == PP_PREC_FP32_SPLIT) {
-        okk = okk && dmalloc(&r->Jq, n3) && dmalloc(&r->tile_max, PP_MAX_SPECIES) &&
-              ok(launch_fill((double*)r->Jq, (int64_t)n3, 0.0, r->stream), "fill") &&
-              ok(hipMemset(r->tile_max, 0, PP_MAX_SPECIES * sizeof(int32_t)), "hipMemset");
-    }
-    if (okk && params->field_order > 2) {
-        for (int d = 0; d < 3; ++d) {
-            double host[1024 + 128];
-            int off = 0;
-            const int N = g.n[d];
-            // the full circulant is used on short lines; long lines use a truncated stencil
-            double* buf = host;
-            double* heap = nullptr;
-            if (N > 1024) {
-                heap = new (std::nothrow) double[N];
-                if (!heap) {
-                    okk = false;
-                    break;
-                }
-                buf = heap;
-            }
-            int len = line_setup_axis(params->field_order, N, buf, &off);
-            r->line[d].len = len;
-            r->line[d].off = off;
-            okk = okk && dmalloc(&r->line[d].coef, (size_t)len) &&
-                  ok(hipMemcpy(r->line[d].coef, buf, len * sizeof(double), hipMemcpyHostToDevice), "hipMemcpy");
-            delete[] heap;
+    const bool split = params->precision == PP_PREC_FP32_SPLIT;
+    if (split) {
+        int dev = 0, lds = 0;
+        if (!ok(hipGetDevice(&dev), "hipGetDevice") ||
+            !ok(hipDeviceGetAttribute(&lds, hipDeviceAttributeMaxSharedMemoryPerBlock, dev), "hipDeviceGetAttribute")) {
+            delete r;
+            return PP_E_HIP;
         }
-    }
-    okk = okk && ok(hipMemset(r->flags, 0, sizeof(int32_t)), "hipMemset");
-    okk = okk && ok(hipEventCreate(&r->ev0), "hipEventCreate") && ok(hipEventCreate(&r->ev1), "hipEventCreate");
-    if (okk && params->precision == PP_PREC_FP32_SPLIT) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        okk = ok(hipGetDevice(&dev), "hipGetDevice") && ok(hipGetDeviceProperties(&prop, dev), "hipGetDeviceProperties");
-        if (okk && gpd32_lds_bytes(r) > (size_t)prop.sharedMemPerBlock) {
-            release(r);
+        if (gpd32_lds_bytes(r) > (size_t)lds) {
             delete r;
             return PP_E_CAPACITY;
         }
     }
-    if (!okk) {
-        release(r);
+    Arena A;
+    run_arrays(params, g, r, A);
+    r->nrs = params->time_order == 4 ? 3 : 1;
+    // the constants are worked out on the host and copied once
+    const size_t no = omega_count(params), nconst = 3 * no + 3 * 127;
+    double* host = new (std::nothrow) double[nconst]();
+    if (!host) {
         delete r;
-        return PP_E_HIP;
+        return PP_E_CAPACITY;
     }
-    if (!ok(field_setup(r), "field_setup")) {
+    bool okk = A.allocate(&r->arena);
+    if (!split) r->Jq = nullptr;
+    for (int k = 0; k < r->nrs; ++k) r->rs[k].omega = r->consts + k * no;
+    if (okk && params->field_order > 2)
+        for (int d = 0; d < 3; ++d) {
+            LineStencil& L = r->line[d];
+            const size_t at = 3 * no + (size_t)d * 127;
+            L.coef = r->consts + at;
+            int same = -1;  // an axis of the same length before: the same taps
+            for (int e = 0; e < d; ++e)
+                if (g.n[e] == g.n[d]) same = e;
+            if (same >= 0) {
+                L.len = r->line[same].len;
+                L.off = r->line[same].off;
+                std::memcpy(host + at, host + 3 * no + (size_t)same * 127, 127 * sizeof(double));
+            } else {
+                L.len = line_setup_axis(params->field_order, g.n[d], host + at, &L.off);
+                okk = okk && L.len > 0;
+            }
+        }
+    if (okk) field_setup(r, host);
+    okk = okk && ok(hipMemcpy(r->consts, host, nconst * sizeof(double), hipMemcpyHostToDevice), "hipMemcpy");
+    delete[] host;
+    if (okk) {  // flags .. the end of the arena, all-zero bits
+        const size_t bytes = (size_t)((char*)r->arena + A.size - (char*)r->flags);
+        okk = ok(launch_fill((double*)r->flags, (int64_t)(bytes / sizeof(double)), 0.0, r->stream), "fill");
+    }
+    if (!okk) {
         release(r);
         delete r;
         return PP_E_HIP;
@@ -296,33 +310,16 @@ pp_status pp_init_species(pp_run* r, int32_t s, double q, double m, double w, co
         if (parts->id && !parts->id_alt) return PP_E_ARG;
     }
     Species& S = r->sp[s];
-    if (!S.offsets && !dmalloc(&S.offsets, (size_t)r->g.nbins + 1)) return PP_E_HIP;
-    const size_t nt = (size_t)r->g.ntiles, nbins = (size_t)r->g.nbins;
-    const int64_t ncnt = split ? r->g.ncell : r->g.nbins;
-    if (!S.offsets_next && !dmalloc(&S.offsets_next, (split ? nt : nbins) + 1)) return PP_E_HIP;
-    if (!S.cell_cnt && !dmalloc(&S.cell_cnt, (size_t)ncnt)) return PP_E_HIP;
-    if (split) {
-        if (!S.rounds && !dmalloc(&S.rounds, nt * SORT_RCAP)) return PP_E_HIP;
-        if (!S.rank_base && !dmalloc(&S.rank_base, nt * r->g.dest_slots())) return PP_E_HIP;
-    } else {
-        if (!S.bin_pre && !dmalloc(&S.bin_pre, nbins)) return PP_E_HIP;
-        if (!S.tile_tot && !dmalloc(&S.tile_tot, nt + 1)) return PP_E_HIP;
+    if (!S.arena || S.arena_n < parts->n) {
+        if (S.arena) (void)hipFree(S.arena);
+        S.active = false;  // until the new arrays are there
+        Arena A;
+        species_arrays(&r->p, r->g, parts->n, S, A);
+        if (!A.allocate(&S.arena)) return PP_E_HIP;
+        S.arena_n = parts->n;
     }
-    if (!ok(launch_fill_i32(S.cell_cnt, ncnt, 0, r->stream), "fill")) return PP_E_HIP;
-    if (S.rank) (void)hipFree(S.rank);
-    S.rank = nullptr;
-    if (!dmalloc(&S.rank, (size_t)parts->n)) return PP_E_HIP;
-    if (S.perm) (void)hipFree(S.perm);
-    S.perm = nullptr;
-    if (!dmalloc(&S.perm, (size_t)parts->n)) return PP_E_HIP;
+    if (!ok(launch_fill_i32(S.cell_cnt, split ? r->g.ncell : r->g.nbins, 0, r->stream), "fill")) return PP_E_HIP;
     S.pending = false;
-    if (split && parts->n > r->sort_scratch_n) {
-        if (r->sort_scratch) (void)hipFree(r->sort_scratch);
-        r->sort_scratch = nullptr;
-        r->sort_scratch_n = 0;
-        if (!dmalloc(&r->sort_scratch, 2 * (size_t)parts->n)) return PP_E_HIP;
-        r->sort_scratch_n = parts->n;
-    }
     S.active = true;
     S.q = q;
     S.m = m;
@@ -503,6 +500,8 @@ pp_status pp_get_particles(pp_run* r, int32_t s, pp_particles* out) {
 pp_status pp_timing_enable(pp_run* r, int32_t enable) {
     if (!r) return PP_E_ARG;
     if (flush_timing(r) != PP_OK) return PP_E_HIP;
+    if (enable && !r->ev0 && !ok(hipEventCreate(&r->ev0), "hipEventCreate")) return PP_E_HIP;
+    if (enable && !r->ev1 && !ok(hipEventCreate(&r->ev1), "hipEventCreate")) return PP_E_HIP;
     r->timing = enable != 0;
     return PP_OK;
 }

@@ -1,6 +1,8 @@
 // Field kernels: the implicit B / explicit E step (Sec. III.B, eqs. "bnplus1",
 // "enplus1", "EllipticB") and the high-order current line solve (Sec. III.C, eqs.
 // "jj6d", "penta").  Mesh arrays are FP64, x fastest, periodic.
+#include <new>
+
 #include "pp_device.hpp"
 #include "pp_fixed.hpp"
 #include "pp_internal.hpp"
@@ -615,9 +617,9 @@ static int64_t blocks_of(const FieldGeom& G) { return (int64_t)G.xchunks * ((G.r
 // Varga 1961): after m sweeps the error is multiplied by at most 1 / T_m(1/r) (T_m the
 // Chebyshev polynomial) and the residual by at most amax / T_m(1/r); m is the smallest
 // count for which that is <= relax_tol.
-static hipError_t relax_setup(pp_run* r, double dt, pp_run::RelaxSet& S);
+static void relax_setup(pp_run* r, double dt, pp_run::RelaxSet& S, double* om);
 
-hipError_t field_setup(pp_run* r) {
+void field_setup(pp_run* r, double* consts) {
     double a[3];
     fd_coeffs(r->p.field_order, a);
     const int M = r->p.field_order / 2;
@@ -653,21 +655,17 @@ hipError_t field_setup(pp_run* r) {
     r->gauss_kappa = kmax2 > 0.0 ? 1.0 / kmax2 : 0.0;
     // relaxation constants for each drift size the run steps with
     const double drifts[3] = {r->p.dt, FR_DRIFT[0] * r->p.dt, FR_DRIFT[2] * r->p.dt};
-    for (int k = 0; k < r->nrs; ++k) {
-        hipError_t e = relax_setup(r, drifts[k], r->rs[k]);
-        if (e != hipSuccess) return e;
-    }
+    for (int k = 0; k < r->nrs; ++k) relax_setup(r, drifts[k], r->rs[k], consts + (r->rs[k].omega - r->consts));
     use_relax_set(r, 0);
     r->dt_kick = r->dt_drift = r->p.dt;
-    return hipSuccess;
 }
 
-// Relaxation constants of one drift size dt (the operator depends on dt^2 only).
-static hipError_t relax_setup(pp_run* r, double dt, pp_run::RelaxSet& S) {
+// Relaxation constants of one drift size dt (the operator depends on dt^2 only); om: its weights.
+static void relax_setup(pp_run* r, double dt, pp_run::RelaxSet& S, double* om) {
     const int R = r->lap_r;
     const double s = r->p.c * r->p.c * dt * dt;
     const double al2s = r->p.alpha * r->p.alpha * s;
-    double diag = 1.0, amax = 1.0;
+    double diag = 1.0, amax = 1.0, min_sym[3];
     for (int d = 0; d < 3; ++d) {
         const int N = r->p.n[d];
         double fold0 = 0.0;
@@ -675,11 +673,16 @@ static hipError_t relax_setup(pp_run* r, double dt, pp_run::RelaxSet& S) {
             if (((o % N) + N) % N == 0) fold0 += r->lap[d][o + R];
         diag -= al2s * fold0;
         double mn = 0.0;
-        for (int mm = 0; mm < N; ++mm) {
-            double k = 2.0 * M_PI * mm / N, sym = 0.0;
-            for (int o = -R; o <= R; ++o) sym += r->lap[d][o + R] * cos(o * k);
+        int same = -1;  // an axis before with the same stencil and length: the same minimum
+        for (int e = 0; e < d; ++e)
+            if (r->p.n[e] == N && r->p.d[e] == r->p.d[d]) same = e;
+        for (int mm = 0; same < 0 && mm < N; ++mm) {
+            double k = 2.0 * M_PI * mm / N, sym = 0.0, cs[16];
+            for (int o = 0; o <= R; ++o) cs[o] = cos(o * k);  // cos(-o k) is the same value
+            for (int o = -R; o <= R; ++o) sym += r->lap[d][o + R] * cs[o < 0 ? -o : o];
             if (sym < mn) mn = sym;
         }
+        min_sym[d] = mn = same < 0 ? mn : min_sym[same];
         amax -= al2s * mn;
     }
     S.drift = dt;
@@ -708,14 +711,9 @@ static hipError_t relax_setup(pp_run* r, double dt, pp_run::RelaxSet& S) {
     S.converged = bound <= r->p.relax_tol;
     // omega_1 = 1, omega_2 = 1 / (1 - r^2/2), omega_{k+1} = 1 / (1 - r^2 omega_k / 4)
     const int n_om = r->p.relax_max_iter + 2;
-    double* om = new (std::nothrow) double[n_om];
-    if (!om) return hipErrorOutOfMemory;
     om[0] = 0.0;
     om[1] = 1.0;
     for (int k = 2; k < n_om; ++k) om[k] = k == 2 ? 1.0 / (1.0 - 0.5 * rr * rr) : 1.0 / (1.0 - 0.25 * rr * rr * om[k - 1]);
-    hipError_t e = hipMemcpy(S.omega, om, n_om * sizeof(double), hipMemcpyHostToDevice);
-    delete[] om;
-    return e;
 }
 
 void use_relax_set(pp_run* r, int k) {
@@ -1073,7 +1071,8 @@ __global__ void __launch_bounds__(FIELD_BS) k_line_solve_batch(const LineArgs* _
 }
 
 // Host: coefficients of T^{-1} on a periodic line of N cells, by the discrete Fourier
-// transform of 1 / T(k); truncated where they fall below 1e-18 of the centre value.
+// transform of 1 / T(k); truncated where they fall below 1e-16 of the centre value.  At most 127
+// of them; 0 if there is no memory.
 int line_setup_axis(int order, int N, double* coef_host, int* off) {
     double a[3];
     fd_coeffs(order, a);
@@ -1081,16 +1080,23 @@ int line_setup_axis(int order, int N, double* coef_host, int* off) {
     double T[3] = {0, 0, 0};
     for (int l = 0; l < M; ++l)
         for (int m = l + 1; m <= M; ++m) T[l] += a[m - 1];
-    // g(m) = 1/N sum_k cos(2 pi k m / N) / T(k)
+    double* symbol = new (std::nothrow) double[N];  // T(k)
+    if (!symbol) return 0;
+    for (int kk = 0; kk < N; ++kk) {
+        double k = 2.0 * M_PI * kk / N;
+        symbol[kk] = T[0];
+        for (int l = 1; l < M; ++l) symbol[kk] += 2.0 * T[l] * cos(l * k);
+    }
+    // g(m) = 1/N sum_k cos(2 pi k m / N) / T(k), each worked out once
+    double known[130];
+    int nknown = 0;
     auto g = [&](int m) {
-        double s = 0.0;
-        for (int kk = 0; kk < N; ++kk) {
-            double k = 2.0 * M_PI * kk / N;
-            double sym = T[0];
-            for (int l = 1; l < M; ++l) sym += 2.0 * T[l] * cos(l * k);
-            s += cos(k * m) / sym;
+        for (; nknown <= m; ++nknown) {
+            double s = 0.0;
+            for (int kk = 0; kk < N; ++kk) s += cos(2.0 * M_PI * kk / N * nknown) / symbol[kk];
+            known[nknown] = s / N;
         }
-        return s / N;
+        return known[m];
     };
     // the coefficients decay geometrically down to the rounding noise of the sum (~1e-17);
     // keep them while two consecutive ones stand above 1e-16 of the centre value
@@ -1102,10 +1108,12 @@ int line_setup_axis(int order, int N, double* coef_host, int* off) {
     }
     if (2 * Rr + 1 >= N) {  // full circulant: offsets 0..N-1
         for (int m = 0; m < N; ++m) coef_host[m] = g(m);
+        delete[] symbol;
         *off = 0;
         return N;
     }
     for (int m = -Rr; m <= Rr; ++m) coef_host[m + Rr] = g(m < 0 ? -m : m);
+    delete[] symbol;
     *off = -Rr;
     return 2 * Rr + 1;
 }

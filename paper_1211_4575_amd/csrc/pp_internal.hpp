@@ -52,6 +52,8 @@ struct RoundEntry {
 constexpr int SORT_RCAP = 96;  // ranks per tile table (even); ranks beyond go to an overflow tail
 
 struct Species {
+    void* arena = nullptr;   // one device allocation: every array below
+    int64_t arena_n = 0;     // particles it holds room for
     bool active = false;
     double q = 0, m = 1, w = 0;
     int64_t n = 0;
@@ -98,6 +100,7 @@ struct pp_run {
     pp::Geom g{};
     pp::Species sp[PP_MAX_SPECIES];
 
+    void* arena = nullptr;     // one device allocation: every array of the run but its species'
     double* J2 = nullptr;      // second-order current (field order > 2); relaxation scratch in the field step
     double* Bn = nullptr;      // copy of B^n during the field step
     double* Bw = nullptr;      // relaxation ping-pong partner
@@ -107,8 +110,6 @@ struct pp_run {
     int64_t rho_prev_step = -1;
     int32_t* sort_cursor = nullptr;   // nbins: scatter cursors (cell bins or tiles), per-tile sort state
     int32_t* scan_tmp = nullptr;      // block sums of the scan
-    int32_t* sort_scratch = nullptr;  // split form: rank and permutation of the tile-order rebuild
-    int64_t sort_scratch_n = 0;       // particles per half of sort_scratch
     long long* Jq = nullptr;          // split form: current in 64-bit fixed point (3*ncell), zero
                                       // between calls
     int32_t* tile_max = nullptr;      // split form: largest particle count of a tile, per species
@@ -130,6 +131,7 @@ struct pp_run {
     // with the alpha^2 c^2 dt^2 of that step
     bool rhs_valid = false;
     double rhs_al2s = 0.0;
+    double* consts = nullptr;  // device copy of the relaxation weights and line-solve taps
     double* omega = nullptr; // Chebyshev weights (device, relax_max_iter + 2)
     double gauss_kappa = 0.0; // damping of the Gauss-law filter: 1 / max |K|^2
     // time step of the particle and field kernels: kick (momentum update) and drift

@@ -1122,8 +1122,8 @@ static hipError_t sort_species(pp_run* r, int s) {
                 B.pos_o[d] = (T*)S.cur.pos_alt[d];
                 B.u_o[d] = (T*)S.cur.u_alt[d];
             }
-            B.rank = r->sort_scratch;
-            B.perm = r->sort_scratch + r->sort_scratch_n;
+            B.rank = S.rank;  // free here: no push since the last sort, no order pending
+            B.perm = S.perm;
             hipLaunchKernelGGL(k_tile_reorder<T>, dim3((unsigned)ntiles), dim3(256), 0, r->stream, B);
             swap_buffers(S.cur);
         }
