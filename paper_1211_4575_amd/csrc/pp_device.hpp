@@ -170,6 +170,15 @@ __device__ __forceinline__ void rad_cool(T k, T dt, T ic, const V3<T>& um, V3<T>
 
 __device__ __forceinline__ void atomic_add_f64(double* p, double v) { unsafeAtomicAdd(p, v); }
 
+// Workgroups go round-robin over the 8 XCDs, each with its own L2: this block's number when every
+// XCD takes a contiguous eighth of n blocks (-1: none left), so that neighbours share an L2.  The
+// launch has xcd_grid(n) blocks.
+__device__ __forceinline__ int64_t xcd_block(int64_t b, int64_t n) {
+    const int64_t per = (n + 7) / 8, c = (b & 7) * per + (b >> 3);
+    return c < n ? c : -1;
+}
+inline unsigned xcd_grid(int64_t n) { return (unsigned)(8 * ((n + 7) / 8)); }
+
 // Segment of a batched launch: the largest r in [0, n) with prefix[r] <= b < prefix[r + 1]
 // (prefix has n + 1 non-decreasing entries), or -1 when b is beyond the last segment.
 __device__ __forceinline__ int find_segment(const int64_t* __restrict__ prefix, int n, int64_t b) {

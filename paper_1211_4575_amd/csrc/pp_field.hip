@@ -164,9 +164,10 @@ __global__ void __launch_bounds__(FIELD_BS) k_field(FieldDesc D, int phase) {
 //
 // A sweep is bound by memory in large boxes (256^3: 0.38 ms, 4.2 TB/s for the four arrays it
 // cannot do without) and by latency in small ones, where short marches (D.zc, down to one plane
-// with every load in flight at once) spread it over the GPU.  6th-order sweep, us, with each tap
-// read through the caches and now: 128^3 110 and 59, 128x32x32 19 and 9.5, 512x256x1 20 and 10;
-// 2nd order, 16^3 7.4 and 4.0; a batch of eight serving boxes 24 and 17.
+// with every load in flight at once) spread it over the GPU.  Tiles of 64x8, 32x16, 64x4 and 64x16
+// took 0 to 14 % longer.  Whole field step, us, with each tap of the boxes below 1024 columns read
+// through the caches and now: 256^3 5750 and 4890, 128^3 1520 and 629, 128x32x32 260 and 99,
+// 512x256x1 243 and 108, 64x32x32 222 and 70.
 constexpr int RX_TX = 32, RX_TY = 8, RX_ZC = 32;
 constexpr int RX_BS = RX_TX * RX_TY;  // one thread per column of the tile
 
@@ -185,20 +186,42 @@ __device__ __forceinline__ double* relax_array(const FieldDesc& D, int k) {
 }
 
 struct TileCtx {
-    int comp, z0, z1, tx, ty, col, own, nxy, n2, small;
+    int comp, i0, j0, z0, z1, tx, ty, col, own, nxy, n2, small;
     bool valid;
 };
 
-template <int R>
-struct Ring {  // this thread's entries of the x-y ring of a plane: LDS index (-1: none), offset
-    static constexpr int W = RX_TX + 2 * R, H = RX_TY + 2 * R, NH = (W * H + RX_BS - 1) / RX_BS;
+// The entries around a tile that its x and y taps reach: H deep on each side, no corners.  A
+// thread's share of them: LDS index (-1: none) and in-plane offset (periodic), the same for every
+// plane.  HX or HY 0: no taps along that axis.
+template <int HX, int HY>
+struct Ring {
+    static constexpr int W = RX_TX + 2 * HX, H = RX_TY + 2 * HY;
+    static constexpr int NX = 2 * HX * RX_TY, NY = 2 * HY * RX_TX, NH = (NX + NY + RX_BS - 1) / RX_BS;
     int hl[NH], hg[NH];
+    __device__ __forceinline__ void init(int i0, int j0, int n0, int n1) {
+#pragma unroll
+        for (int e = 0; e < NH; ++e) {
+            const int h = threadIdx.x + RX_BS * e;
+            int a, b;  // column and row, 0 at the first of the entries' rows and columns
+            if (h < NX) {
+                b = HY + h / (HX > 0 ? 2 * HX : 1);
+                a = h % (HX > 0 ? 2 * HX : 1);
+                a += a < HX ? 0 : RX_TX;
+            } else {
+                b = (h - NX) / RX_TX;
+                b += b < HY ? 0 : RX_TY;
+                a = HX + (h - NX) % RX_TX;
+            }
+            const bool ring = h < NX + NY;
+            hl[e] = ring ? a + W * b : -1;
+            hg[e] = ring ? wrap_near(i0 + a - HX, n0) + n0 * wrap_near(j0 + b - HY, n1) : 0;
+        }
+    }
+    static __device__ __forceinline__ int own(int tx, int ty) { return (ty + HY) * W + tx + HX; }
 };
 
 // block b of a run's launch: component, column and planes
-template <int R>
-__device__ __forceinline__ void tile_ctx(const FieldGeom& G, int zc, int b, TileCtx& X, Ring<R>& g) {
-    constexpr int W = Ring<R>::W, H = Ring<R>::H;
+__device__ __forceinline__ void tile_ctx(const FieldGeom& G, int zc, int b, TileCtx& X) {
     const int n0 = G.n[0], n1 = G.n[1];
     const int nbx = (n0 + RX_TX - 1) / RX_TX, nby = (n1 + RX_TY - 1) / RX_TY, nbz = (G.n[2] + zc - 1) / zc;
     const int bx = b % nbx;
@@ -207,25 +230,18 @@ __device__ __forceinline__ void tile_ctx(const FieldGeom& G, int zc, int b, Tile
     b /= nby;
     const int bz = b % nbz;
     X.comp = b / nbz;
-    const int i0 = bx * RX_TX, j0 = by * RX_TY;
+    X.i0 = bx * RX_TX;
+    X.j0 = by * RX_TY;
     X.z0 = bz * zc;
     X.z1 = X.z0 + zc < G.n[2] ? X.z0 + zc : G.n[2];
     X.tx = threadIdx.x % RX_TX;
     X.ty = threadIdx.x / RX_TX;
-    X.valid = i0 + X.tx < n0 && j0 + X.ty < n1;
-    X.col = wrap_near(i0 + X.tx, n0) + n0 * wrap_near(j0 + X.ty, n1);  // idle threads load wrapped columns
+    X.valid = X.i0 + X.tx < n0 && X.j0 + X.ty < n1;
+    X.col = wrap_near(X.i0 + X.tx, n0) + n0 * wrap_near(X.j0 + X.ty, n1);  // idle threads load wrapped columns
     X.own = X.valid ? X.col : 0;
     X.nxy = n0 * n1;
     X.n2 = G.n[2];
     X.small = G.small;
-#pragma unroll
-    for (int e = 0; e < Ring<R>::NH; ++e) {
-        const int h = threadIdx.x + RX_BS * e;
-        const int a = h % W, bb = h / W;
-        const bool ring = h < W * H && !(a >= R && a < R + RX_TX && bb >= R && bb < R + RX_TY);
-        g.hl[e] = ring ? h : -1;
-        g.hg[e] = ring ? wrap_near(i0 + a - R, n0) + n0 * wrap_near(j0 + bb - R, n1) : 0;
-    }
 }
 
 // Sweep k of one block: the loads are unconditional (the last plane reloads its own plane, a lane
@@ -233,11 +249,12 @@ __device__ __forceinline__ void tile_ctx(const FieldGeom& G, int zc, int b, Tile
 // computed meanwhile.
 template <int R>
 __device__ __forceinline__ void relax_tile(const FieldDesc& D, int b, int k, double* pl) {
-    constexpr int W = Ring<R>::W, NH = Ring<R>::NH;
+    constexpr int W = Ring<R, R>::W, NH = Ring<R, R>::NH;
     const FieldGeom& G = D.G;
     TileCtx X;
-    Ring<R> g;
-    tile_ctx<R>(G, D.zc, b, X, g);
+    Ring<R, R> g;
+    tile_ctx(G, D.zc, b, X);
+    g.init(X.i0, X.j0, G.n[0], G.n[1]);
     const int64_t co = (int64_t)X.comp * G.nc;
     double* out = relax_array(D, k) + co;
     const double* x = (k == 1 ? D.Bn : relax_array(D, k - 1)) + co;
@@ -252,7 +269,7 @@ __device__ __forceinline__ void relax_tile(const FieldDesc& D, int b, int k, dou
     for (int e = 0; e < NH; ++e) hv[e] = x[g.hg[e] + X.z0 * nxy];
     double rq = rhs[own + X.z0 * nxy];
     double pq = pv[own + X.z0 * nxy];
-    const int c0 = (X.ty + R) * W + X.tx + R;
+    const int c0 = g.own(X.tx, X.ty);
     for (int kz = X.z0; kz < X.z1; ++kz) {
         if (kz > X.z0) __syncthreads();  // the previous plane's LDS reads are done
         pl[c0] = q[R];
@@ -294,37 +311,48 @@ __device__ __forceinline__ void relax_tile(const FieldDesc& D, int b, int k, dou
 }
 
 // One array streamed through the planes: values at z offsets WLO..WHI of the thread's column
-// around the current plane and, with PLANE, the current plane's ring for the LDS stage.
-template <int R, int WLO, int WHI, bool PLANE>
+// around the current plane and, where the array has taps along x (HX deep) or y (HY), the plane
+// and its ring staged in LDS.
+template <int HX, int HY, int WLO, int WHI>
 struct ZStream {
-    static constexpr int NW = WHI - WLO + 1, NH = Ring<R>::NH;
+    static constexpr bool PLANE = HX > 0 || HY > 0;
+    static constexpr int NW = WHI - WLO + 1;
+    using G = Ring<HX, HY>;
+    static constexpr int NH = PLANE ? G::NH : 1, LDS = PLANE ? G::W * G::H : 0;
     const double* f;
+    double* pl;
+    int c0;
+    G g;
     double w[NW];
-    double hv[PLANE ? NH : 1];
+    double hv[NH];
     double wn;
-    __device__ __forceinline__ void init(const double* src, const TileCtx& X, const Ring<R>& g) {
+    // lds: the next free part of the block's LDS
+    __device__ __forceinline__ void init(const double* src, const TileCtx& X, const FieldGeom& F, double*& lds) {
         f = src;
 #pragma unroll
         for (int t = 0; t < NW; ++t) w[t] = f[X.col + X.nxy * nbw(X.z0, WLO + t, X.n2, X.small)];
         if constexpr (PLANE) {
+            pl = lds;
+            lds += LDS;
+            c0 = G::own(X.tx, X.ty);
+            g.init(X.i0, X.j0, F.n[0], F.n[1]);
 #pragma unroll
-            for (int e = 0; e < NH; ++e) hv[e] = g.hl[e] >= 0 ? f[g.hg[e] + X.z0 * X.nxy] : 0.0;
+            for (int e = 0; e < NH; ++e) hv[e] = f[g.hg[e] + X.z0 * X.nxy];
         }
     }
-    __device__ __forceinline__ void stage(double* pl, const TileCtx& X, const Ring<R>& g) const {
+    __device__ __forceinline__ void stage() const {
         if constexpr (PLANE) {
-            pl[(X.ty + R) * Ring<R>::W + X.tx + R] = w[-WLO];
+            pl[c0] = w[-WLO];
 #pragma unroll
             for (int e = 0; e < NH; ++e)
                 if (g.hl[e] >= 0) pl[g.hl[e]] = hv[e];
         }
     }
-    __device__ __forceinline__ void prefetch(int kz1, const TileCtx& X, const Ring<R>& g) {
+    __device__ __forceinline__ void prefetch(int kz1, const TileCtx& X) {
         wn = f[X.col + X.nxy * nbw(kz1, WHI, X.n2, X.small)];
         if constexpr (PLANE) {
 #pragma unroll
-            for (int e = 0; e < NH; ++e)
-                if (g.hl[e] >= 0) hv[e] = f[g.hg[e] + kz1 * X.nxy];
+            for (int e = 0; e < NH; ++e) hv[e] = f[g.hg[e] + kz1 * X.nxy];
         }
     }
     __device__ __forceinline__ void shift() {
@@ -333,21 +361,28 @@ struct ZStream {
         w[NW - 1] = wn;
     }
     __device__ __forceinline__ double at(int o) const { return w[o - WLO]; }
+    __device__ __forceinline__ double x(int o) const { return pl[c0 + o]; }
+    __device__ __forceinline__ double y(int o) const { return pl[c0 + o * G::W]; }
 };
+
+// A stream for first differences along AX only (UP: as dtile)
+template <int M, int AX, int UP>
+using DStream = ZStream<AX == 0 ? M : 0, AX == 1 ? M : 0, AX == 2 ? UP - M : 0, AX == 2 ? M - 1 + UP : 0>;
 
 // sum_m a_m (f[+m-1+UP] - f[-m+UP]) along axis AX (UP = 1: dup, UP = 0: ddn), from the staged
 // plane (x, y) or the z window
-template <int R, int M, int AX, int UP, class S>
-__device__ __forceinline__ double dtile(const S& st, const double* pl, int c0, const double* a) {
-    constexpr int step = AX == 0 ? 1 : Ring<R>::W;
+template <int M, int AX, int UP>
+__device__ __forceinline__ double dtile(const DStream<M, AX, UP>& st, const double* a) {
     double s = 0.0;
 #pragma unroll
     for (int m = 1; m <= M; ++m) {
         const int hi = m - 1 + UP, lo = -m + UP;
         if constexpr (AX == 2)
             s += a[m - 1] * (st.at(hi) - st.at(lo));
+        else if constexpr (AX == 1)
+            s += a[m - 1] * (st.y(hi) - st.y(lo));
         else
-            s += a[m - 1] * (pl[c0 + hi * step] - pl[c0 + lo * step]);
+            s += a[m - 1] * (st.x(hi) - st.x(lo));
     }
     return s;
 }
@@ -355,51 +390,47 @@ __device__ __forceinline__ double dtile(const S& st, const double* pl, int c0, c
 // rhs = B + alpha beta s lap B - dt curl+ E + alpha c^2 mu0 dt^2 curl+ J   (B = B^n), B^n's copy and
 // sweep 1
 template <int M, int C>
-__device__ __forceinline__ void rhs_tiled_comp(const FieldDesc& D, const TileCtx& X, const Ring<2 * M - 1>& g,
-                                               double* lds) {
-    constexpr int R = 2 * M - 1, WH = Ring<R>::W * Ring<R>::H;
+__device__ __forceinline__ void rhs_tiled_comp(const FieldDesc& D, const TileCtx& X, double* lds) {
+    constexpr int R = 2 * M - 1;
     constexpr int d1 = (C + 1) % 3, d2 = (C + 2) % 3;
-    constexpr bool uz = d1 == 2, vz = d2 == 2;  // which curl term differentiates along z
     const FieldGeom& G = D.G;
-    ZStream<R, -R, R, true> sB;
-    ZStream<R, uz ? -M + 1 : 0, uz ? M : 0, !uz> sEu, sJu;  // E_d2, J_d2 along d1
-    ZStream<R, vz ? -M + 1 : 0, vz ? M : 0, !vz> sEv, sJv;  // E_d1, J_d1 along d2
+    ZStream<R, R, -R, R> sB;
+    DStream<M, d1, 1> sEu, sJu;  // E_d2, J_d2 along d1
+    DStream<M, d2, 1> sEv, sJv;  // E_d1, J_d1 along d2
     double* Bn = D.Bn + C * G.nc;
     double* x1 = D.sweeps > 1 ? D.Bw + C * G.nc : nullptr;
     const double w1 = D.omega[1];
-    sB.init(D.B + C * G.nc, X, g);
-    sEu.init(D.E + d2 * G.nc, X, g);
-    sEv.init(D.E + d1 * G.nc, X, g);
-    sJu.init(D.J + d2 * G.nc, X, g);
-    sJv.init(D.J + d1 * G.nc, X, g);
-    double *pB = lds, *pEu = lds + WH, *pEv = lds + 2 * WH, *pJu = lds + 3 * WH, *pJv = lds + 4 * WH;
-    const int c0 = (X.ty + R) * Ring<R>::W + X.tx + R;
+    sB.init(D.B + C * G.nc, X, G, lds);
+    sEu.init(D.E + d2 * G.nc, X, G, lds);
+    sEv.init(D.E + d1 * G.nc, X, G, lds);
+    sJu.init(D.J + d2 * G.nc, X, G, lds);
+    sJv.init(D.J + d1 * G.nc, X, G, lds);
     for (int kz = X.z0; kz < X.z1; ++kz) {
         if (kz > X.z0) __syncthreads();  // the previous plane's LDS reads are done
-        sB.stage(pB, X, g);
-        sEu.stage(pEu, X, g);
-        sEv.stage(pEv, X, g);
-        sJu.stage(pJu, X, g);
-        sJv.stage(pJv, X, g);
+        sB.stage();
+        sEu.stage();
+        sEv.stage();
+        sJu.stage();
+        sJv.stage();
         __syncthreads();
         const bool more = kz + 1 < X.z1;
         if (more) {
-            sB.prefetch(kz + 1, X, g);
-            sEu.prefetch(kz + 1, X, g);
-            sEv.prefetch(kz + 1, X, g);
-            sJu.prefetch(kz + 1, X, g);
-            sJv.prefetch(kz + 1, X, g);
+            sB.prefetch(kz + 1, X);
+            sEu.prefetch(kz + 1, X);
+            sEv.prefetch(kz + 1, X);
+            sJu.prefetch(kz + 1, X);
+            sJv.prefetch(kz + 1, X);
         }
         if (X.valid) {
             double lp = 0.0;
 #pragma unroll
             for (int o = -R; o <= R; ++o) {
-                lp += G.L[0][o + R] * pB[c0 + o];
-                lp += G.L[1][o + R] * pB[c0 + o * Ring<R>::W];
+                lp += G.L[0][o + R] * sB.x(o);
+                lp += G.L[1][o + R] * sB.y(o);
                 lp += G.L[2][o + R] * sB.at(o);
             }
-            double curlE = dtile<R, M, d1, 1>(sEu, pEu, c0, G.a[d1]) - dtile<R, M, d2, 1>(sEv, pEv, c0, G.a[d2]);
-            double curlJ = dtile<R, M, d1, 1>(sJu, pJu, c0, G.a[d1]) - dtile<R, M, d2, 1>(sJv, pJv, c0, G.a[d2]);
+            const double curlE = dtile<M, d1, 1>(sEu, G.a[d1]) - dtile<M, d2, 1>(sEv, G.a[d2]);
+            const double curlJ = dtile<M, d1, 1>(sJu, G.a[d1]) - dtile<M, d2, 1>(sJv, G.a[d2]);
             const double xq = sB.at(0);
             const double rq = xq + D.cab * lp - D.dt * curlE + D.cj * curlJ;
             const int64_t q = X.own + (int64_t)kz * X.nxy;
@@ -423,42 +454,37 @@ __device__ __forceinline__ void rhs_tiled_comp(const FieldDesc& D, const TileCtx
 
 // E += c^2 dt (curl- (alpha B' + beta B) - mu0 J)
 template <int M, int C>
-__device__ __forceinline__ void update_E_tiled_comp(const FieldDesc& D, const TileCtx& X, const Ring<2 * M - 1>& g,
-                                                    double* lds) {
-    constexpr int R = 2 * M - 1, WH = Ring<R>::W * Ring<R>::H;
+__device__ __forceinline__ void update_E_tiled_comp(const FieldDesc& D, const TileCtx& X, double* lds) {
     constexpr int d1 = (C + 1) % 3, d2 = (C + 2) % 3;
-    constexpr bool uz = d1 == 2, vz = d2 == 2;
     const FieldGeom& G = D.G;
-    ZStream<R, uz ? -M : 0, uz ? M - 1 : 0, !uz> sBu, sNu;  // B_d2, Bn_d2 along d1
-    ZStream<R, vz ? -M : 0, vz ? M - 1 : 0, !vz> sBv, sNv;  // B_d1, Bn_d1 along d2
-    ZStream<R, 0, 0, false> sE, sJ;
-    sBu.init(D.B + d2 * G.nc, X, g);
-    sBv.init(D.B + d1 * G.nc, X, g);
-    sNu.init(D.Bn + d2 * G.nc, X, g);
-    sNv.init(D.Bn + d1 * G.nc, X, g);
-    sE.init(D.E + C * G.nc, X, g);
-    sJ.init(D.J + C * G.nc, X, g);
-    double *pBu = lds, *pBv = lds + WH, *pNu = lds + 2 * WH, *pNv = lds + 3 * WH;
-    const int c0 = (X.ty + R) * Ring<R>::W + X.tx + R;
+    DStream<M, d1, 0> sBu, sNu;  // B_d2, Bn_d2 along d1
+    DStream<M, d2, 0> sBv, sNv;  // B_d1, Bn_d1 along d2
+    ZStream<0, 0, 0, 0> sE, sJ;
+    sBu.init(D.B + d2 * G.nc, X, G, lds);
+    sBv.init(D.B + d1 * G.nc, X, G, lds);
+    sNu.init(D.Bn + d2 * G.nc, X, G, lds);
+    sNv.init(D.Bn + d1 * G.nc, X, G, lds);
+    sE.init(D.E + C * G.nc, X, G, lds);
+    sJ.init(D.J + C * G.nc, X, G, lds);
     for (int kz = X.z0; kz < X.z1; ++kz) {
         if (kz > X.z0) __syncthreads();
-        sBu.stage(pBu, X, g);
-        sBv.stage(pBv, X, g);
-        sNu.stage(pNu, X, g);
-        sNv.stage(pNv, X, g);
+        sBu.stage();
+        sBv.stage();
+        sNu.stage();
+        sNv.stage();
         __syncthreads();
         const bool more = kz + 1 < X.z1;
         if (more) {
-            sBu.prefetch(kz + 1, X, g);
-            sBv.prefetch(kz + 1, X, g);
-            sNu.prefetch(kz + 1, X, g);
-            sNv.prefetch(kz + 1, X, g);
-            sE.prefetch(kz + 1, X, g);
-            sJ.prefetch(kz + 1, X, g);
+            sBu.prefetch(kz + 1, X);
+            sBv.prefetch(kz + 1, X);
+            sNu.prefetch(kz + 1, X);
+            sNv.prefetch(kz + 1, X);
+            sE.prefetch(kz + 1, X);
+            sJ.prefetch(kz + 1, X);
         }
         if (X.valid) {
-            double cn = dtile<R, M, d1, 0>(sBu, pBu, c0, G.a[d1]) - dtile<R, M, d2, 0>(sBv, pBv, c0, G.a[d2]);
-            double co = dtile<R, M, d1, 0>(sNu, pNu, c0, G.a[d1]) - dtile<R, M, d2, 0>(sNv, pNv, c0, G.a[d2]);
+            const double cn = dtile<M, d1, 0>(sBu, G.a[d1]) - dtile<M, d2, 0>(sBv, G.a[d2]);
+            const double co = dtile<M, d1, 0>(sNu, G.a[d1]) - dtile<M, d2, 0>(sNv, G.a[d2]);
             D.E[C * G.nc + X.own + (int64_t)kz * X.nxy] =
                 sE.at(0) + D.c2dt * (D.al * cn + D.be * co - D.mu0 * sJ.at(0));
         }
@@ -475,43 +501,49 @@ __device__ __forceinline__ void update_E_tiled_comp(const FieldDesc& D, const Ti
 
 enum FieldKind { FK_RHS = 0, FK_RELAX = 1, FK_UPDATE_E = 2 };
 
+// LDS of a phase (doubles): the Laplacian's plane, and the curl's planes of the component with the
+// most (the one whose curl runs along x and y)
 template <int M>
 constexpr int field_lds(int kind) {
-    return (kind == FK_RELAX ? 1 : (kind == FK_RHS ? 5 : 4)) * Ring<2 * M - 1>::W * Ring<2 * M - 1>::H;
+    constexpr int R = 2 * M - 1;
+    constexpr int lap = Ring<R, R>::W * Ring<R, R>::H;
+    constexpr int dx = DStream<M, 0, 1>::LDS, dy = DStream<M, 1, 1>::LDS;
+    return kind == FK_RELAX ? lap : (kind == FK_RHS ? lap : 0) + 2 * (dx + dy);
 }
 
 // block b of a run's launch of one phase (k: the sweep)
 template <int M, int KIND>
 __device__ __forceinline__ void field_tile(const FieldDesc& D, int b, int k, double* lds) {
-    constexpr int R = 2 * M - 1;
     if constexpr (KIND == FK_RELAX) {
-        relax_tile<R>(D, b, k, lds);
+        relax_tile<2 * M - 1>(D, b, k, lds);
     } else {
         TileCtx X;
-        Ring<R> g;
-        tile_ctx<R>(D.G, D.zc, b, X, g);
+        tile_ctx(D.G, D.zc, b, X);
         if constexpr (KIND == FK_RHS) {
             if (X.comp == 0)
-                rhs_tiled_comp<M, 0>(D, X, g, lds);
+                rhs_tiled_comp<M, 0>(D, X, lds);
             else if (X.comp == 1)
-                rhs_tiled_comp<M, 1>(D, X, g, lds);
+                rhs_tiled_comp<M, 1>(D, X, lds);
             else
-                rhs_tiled_comp<M, 2>(D, X, g, lds);
+                rhs_tiled_comp<M, 2>(D, X, lds);
         } else {
             if (X.comp == 0)
-                update_E_tiled_comp<M, 0>(D, X, g, lds);
+                update_E_tiled_comp<M, 0>(D, X, lds);
             else if (X.comp == 1)
-                update_E_tiled_comp<M, 1>(D, X, g, lds);
+                update_E_tiled_comp<M, 1>(D, X, lds);
             else
-                update_E_tiled_comp<M, 2>(D, X, g, lds);
+                update_E_tiled_comp<M, 2>(D, X, lds);
         }
     }
 }
 
 template <int M, int KIND>
-__global__ void __launch_bounds__(RX_BS) k_field_tiles(FieldDesc D, int k) {
+__global__ void __launch_bounds__(RX_BS) k_field_tiles(FieldDesc D, int k, int blocks) {
     __shared__ double lds[field_lds<M>(KIND)];
-    field_tile<M, KIND>(D, blockIdx.x, k, lds);
+    // a sweep's blocks side by side on an XCD share the planes around them in its L2 (128^3: 47 us
+    // against 59); the other two phases are slower that way in large boxes (256^3: 1.07 against 0.97)
+    const int b = KIND == FK_RELAX ? (int)xcd_block(blockIdx.x, blocks) : (int)blockIdx.x;
+    if (b >= 0) field_tile<M, KIND>(D, b, k, lds);
 }
 
 // batched: block b belongs to run r with prefix[r] <= b < prefix[r+1] (prefix in blocks)
@@ -533,14 +565,81 @@ __global__ void __launch_bounds__(RX_BS) k_field_tiles_batch(const FieldDesc* __
         field_tile<1, KIND>(D, lb, k, lds);
 }
 
+// The whole relaxation of a small box, a workgroup per component: the current iterate in LDS
+// (two buffers, so one barrier a sweep), the one before last and the right-hand side in registers.
+// A sweep by launch costs 3.4 us at least; here 4096 cells of the 2nd-order stencil take 1.3, but
+// on one CU the work of a wider stencil or a larger box soon costs more than the launch it saves.
+constexpr int RS_BS = 1024, RS_CELLS = 4 * RS_BS;
+
+static bool relax_in_lds(const FieldGeom& G) { return G.nc * G.R <= RS_CELLS; }
+
+template <int R>
+__global__ void __launch_bounds__(RS_BS) k_relax_small(FieldDesc D) {
+    constexpr int PER = (RS_CELLS / R + RS_BS - 1) / RS_BS;
+    __shared__ double buf[2][PER * RS_BS];
+    const FieldGeom& G = D.G;
+    const int nc = (int)G.nc, n0 = G.n[0], n1 = G.n[1], n2 = G.n[2], nxy = n0 * n1;
+    const int64_t co = (int64_t)blockIdx.x * G.nc;
+    int k = D.sweeps > 1 ? 2 : 1;
+    const double* x = (k == 1 ? D.Bn : relax_array(D, k - 1)) + co;
+    double p[PER], rq[PER];
+    int nb[PER][3][2 * R];  // LDS entries of the taps, the same in every sweep
+#pragma unroll
+    for (int c = 0; c < PER; ++c) {
+        const int q = threadIdx.x + c * RS_BS, qc = q < nc ? q : 0;
+        buf[0][q] = x[qc];
+        p[c] = D.Bn[co + qc];
+        rq[c] = D.R[co + qc];
+        const int kz = qc / nxy, r = qc - kz * nxy, j = r / n0, i = r - j * n0;
+#pragma unroll
+        for (int t = 0; t < 2 * R; ++t) {
+            const int o = t < R ? t - R : t - R + 1;
+            nb[c][0][t] = qc - i + nbw(i, o, n0, G.small);
+            nb[c][1][t] = qc + (nbw(j, o, n1, G.small) - j) * n0;
+            nb[c][2][t] = qc + (nbw(kz, o, n2, G.small) - kz) * nxy;
+        }
+    }
+    for (int cur = 0; k <= D.sweeps; ++k, cur ^= 1) {
+        const double w = D.omega[k];
+        __syncthreads();
+        const double* b = buf[cur];
+#pragma unroll
+        for (int c = 0; c < PER; ++c) {
+            const int q = threadIdx.x + c * RS_BS;  // entries past the box take part and are not kept
+            const double xq = b[q];
+            double sl = 0.0;
+#pragma unroll
+            for (int t = 0; t <= 2 * R; ++t)
+#pragma unroll
+                for (int ax = 0; ax < 3; ++ax)
+                    sl += G.L[ax][t] * (t == R ? xq : b[nb[c][ax][t < R ? t : (t == R ? 0 : t - 1)]]);
+            const double Ax = xq - D.al2s * sl;
+            const double y = xq + (rq[c] - Ax) * D.gdiag;
+            const double xn = p[c] + w * (y - p[c]);
+            buf[cur ^ 1][q] = xn;
+            p[c] = xq;
+            if (k == D.sweeps && q < nc) D.B[co + q] = xn;
+        }
+    }
+}
+
+static void launch_relax_small(const FieldDesc& D, hipStream_t st) {
+    if (D.G.R == 5)
+        hipLaunchKernelGGL(k_relax_small<5>, dim3(3), dim3(RS_BS), 0, st, D);
+    else if (D.G.R == 3)
+        hipLaunchKernelGGL(k_relax_small<3>, dim3(3), dim3(RS_BS), 0, st, D);
+    else
+        hipLaunchKernelGGL(k_relax_small<1>, dim3(3), dim3(RS_BS), 0, st, D);
+}
+
 template <int KIND>
 static void launch_field_tiles(const FieldDesc& D, unsigned blocks, int k, hipStream_t st) {
     if (D.G.M == 3)
-        hipLaunchKernelGGL((k_field_tiles<3, KIND>), dim3(blocks), dim3(RX_BS), 0, st, D, k);
+        hipLaunchKernelGGL((k_field_tiles<3, KIND>), dim3(KIND == FK_RELAX ? xcd_grid(blocks) : blocks), dim3(RX_BS), 0, st, D, k, (int)blocks);
     else if (D.G.M == 2)
-        hipLaunchKernelGGL((k_field_tiles<2, KIND>), dim3(blocks), dim3(RX_BS), 0, st, D, k);
+        hipLaunchKernelGGL((k_field_tiles<2, KIND>), dim3(KIND == FK_RELAX ? xcd_grid(blocks) : blocks), dim3(RX_BS), 0, st, D, k, (int)blocks);
     else
-        hipLaunchKernelGGL((k_field_tiles<1, KIND>), dim3(blocks), dim3(RX_BS), 0, st, D, k);
+        hipLaunchKernelGGL((k_field_tiles<1, KIND>), dim3(KIND == FK_RELAX ? xcd_grid(blocks) : blocks), dim3(RX_BS), 0, st, D, k, (int)blocks);
 }
 
 // Planes per block: as many as leave the launch about 8 blocks per CU (its share of them in a
@@ -766,7 +865,10 @@ hipError_t launch_field_step(pp_run* r) {
     field_desc(r, &D, 1);
     const unsigned blocks = (unsigned)field_blocks(r, 1);
     launch_field_tiles<FK_RHS>(D, blocks, 0, r->stream);
-    for (int k = D.sweeps > 1 ? 2 : 1; k <= D.sweeps; ++k) launch_field_tiles<FK_RELAX>(D, blocks, k, r->stream);
+    if (relax_in_lds(D.G))
+        launch_relax_small(D, r->stream);
+    else
+        for (int k = D.sweeps > 1 ? 2 : 1; k <= D.sweeps; ++k) launch_field_tiles<FK_RELAX>(D, blocks, k, r->stream);
     launch_field_tiles<FK_UPDATE_E>(D, blocks, 0, r->stream);
     note_relax_rhs(r);
     return hipGetLastError();
