@@ -625,8 +625,9 @@ __device__ __forceinline__ void deposit_cc(const TL& L, unsigned long long* cur,
     }
 }
 
-// One tile of one run: the whole particle step of the tile's particles (the body shared by
-// the single-run kernel and the batched kernel, so both do identical arithmetic).
+// One tile of one run: the whole particle step of the tile's particles of species slots s0 to s1
+// (the body shared by the single-run kernel and the batched kernel, so both do identical
+// arithmetic).
 // Each wavefront takes 128 consecutive slots at a time, lane l the slots l and 64 + l.  In
 // the chunks of pairs of the tile order both are a particle of the same cell, whose current
 // windows start at the same node unless one of the particles crossed a face the storage did
@@ -636,7 +637,7 @@ __device__ __forceinline__ void deposit_cc(const TL& L, unsigned long long* cur,
 // alone.  Flat (8x8x1) and runtime-shaped tiles take one particle per lane and slot (64
 // consecutive slots per wavefront).
 template <int O, class TL>
-__device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, unsigned char* lds_raw) {
+__device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, int s0, int s1, unsigned char* lds_raw) {
     const TL L(A);
     const int ti = (int)(tile % A.nt[0]);
     const int tj = (int)((tile / A.nt[0]) % A.nt[1]);
@@ -696,7 +697,7 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, uns
     int bad_all = 0;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 
-    for (int s = 0; s < A.nsp; ++s) {
+    for (int s = s0; s < s1; ++s) {
         const Sp32& S = A.sp[s];
         const int32_t start = S.start[tile];
         const int32_t end = S.start[tile + 1];
@@ -800,7 +801,9 @@ __global__ void __launch_bounds__(GPD32_BS, TL::pairs ? 3 : 1) k_gpd32(Gpd32Args
     const int64_t b = blockIdx.x;
     const int64_t tile = (b & 7) * (int64_t)A.per_xcd + (b >> 3);
     if (tile >= A.ntiles) return;
-    gpd32_tile<O, TL>(A, tile, lds_raw);
+    // a small box has a workgroup per tile and species (the current's integer sum is the same)
+    const int s0 = gridDim.y > 1 ? (int)blockIdx.y : 0, s1 = gridDim.y > 1 ? s0 + 1 : A.nsp;
+    gpd32_tile<O, TL>(A, tile, s0, s1, lds_raw);
 }
 
 // Batched: block b of the launch is tile b - prefix[r] of run r (prefix = running tile counts).
@@ -811,7 +814,7 @@ __global__ void __launch_bounds__(GPD32_BS, TL::pairs ? 3 : 1) k_gpd32_batch(con
     const int64_t b = blockIdx.x;
     const int r = find_segment(prefix, nruns, b);
     if (r < 0) return;
-    gpd32_tile<O, TL>(table[r], b - prefix[r], lds_raw);
+    gpd32_tile<O, TL>(table[r], b - prefix[r], 0, table[r].nsp, lds_raw);
 }
 
 // Fixed-point current of a run to FP64, clearing the accumulator for the next step (runs without
@@ -981,22 +984,26 @@ hipError_t launch_gpd32(pp_run* r) {
     Gpd32Args A;
     gpd32_fill_args(r, &A);
     const size_t lds = gpd32_lds_bytes(r);
-    const unsigned grid = (unsigned)(8 * (int64_t)A.per_xcd);
+    // with three workgroups a CU (of 256), a species of its own each halves the time of two
+    // species as long as all are resident at once (16^3, quadratic, 2 x 3.3e4 particles: 36 us
+    // against 58); beyond that it only stages the fields twice
+    const unsigned split = A.ntiles * A.nsp <= 768 ? (unsigned)(A.nsp > 0 ? A.nsp : 1) : 1u;
+    const dim3 grid((unsigned)(8 * (int64_t)A.per_xcd), split);
     const int kind = tile_kind(r);
     if (r->p.shape_order == 2) {
         if (kind == TILE_444)
-            hipLaunchKernelGGL((k_gpd32<2, TileCT<2, 4, 4, 4, false>>), dim3(grid), dim3(GPD32_BS), lds, r->stream, A);
+            hipLaunchKernelGGL((k_gpd32<2, TileCT<2, 4, 4, 4, false>>), grid, dim3(GPD32_BS), lds, r->stream, A);
         else if (kind == TILE_881_FLAT)
-            hipLaunchKernelGGL((k_gpd32<2, TileCT<2, 8, 8, 1, true>>), dim3(grid), dim3(GPD32_BS), lds, r->stream, A);
+            hipLaunchKernelGGL((k_gpd32<2, TileCT<2, 8, 8, 1, true>>), grid, dim3(GPD32_BS), lds, r->stream, A);
         else
-            hipLaunchKernelGGL((k_gpd32<2, TileRT>), dim3(grid), dim3(GPD32_BS), lds, r->stream, A);
+            hipLaunchKernelGGL((k_gpd32<2, TileRT>), grid, dim3(GPD32_BS), lds, r->stream, A);
     } else {
         if (kind == TILE_444)
-            hipLaunchKernelGGL((k_gpd32<3, TileCT<3, 4, 4, 4, false>>), dim3(grid), dim3(GPD32_BS), lds, r->stream, A);
+            hipLaunchKernelGGL((k_gpd32<3, TileCT<3, 4, 4, 4, false>>), grid, dim3(GPD32_BS), lds, r->stream, A);
         else if (kind == TILE_881_FLAT)
-            hipLaunchKernelGGL((k_gpd32<3, TileCT<3, 8, 8, 1, true>>), dim3(grid), dim3(GPD32_BS), lds, r->stream, A);
+            hipLaunchKernelGGL((k_gpd32<3, TileCT<3, 8, 8, 1, true>>), grid, dim3(GPD32_BS), lds, r->stream, A);
         else
-            hipLaunchKernelGGL((k_gpd32<3, TileRT>), dim3(grid), dim3(GPD32_BS), lds, r->stream, A);
+            hipLaunchKernelGGL((k_gpd32<3, TileRT>), grid, dim3(GPD32_BS), lds, r->stream, A);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -511,8 +511,10 @@ __global__ void __launch_bounds__(GPD64_BS, 3) k_gpd64_tile(Gpd64TileArgs A) {
     const int64_t tile = (blockIdx.x & 7) * (int64_t)A.per_xcd + (blockIdx.x >> 3);
     if (tile >= A.ntiles) return;
     const int part = blockIdx.y;
+    // a small box has a workgroup per tile, part and species
+    const int s0 = gridDim.z > 1 ? (int)blockIdx.z : 0, s1 = gridDim.z > 1 ? s0 + 1 : A.nsp;
     int any = 0;
-    for (int s = 0; s < A.nsp; ++s) any |= A.bins[s][(tile + 1) * TILE_CELLS] - A.bins[s][tile * TILE_CELLS];
+    for (int s = s0; s < s1; ++s) any |= A.bins[s][(tile + 1) * TILE_CELLS] - A.bins[s][tile * TILE_CELLS];
     if (any == 0) return;
     const Gpd64Args& G = A.sp[0];
     const int org[3] = {(int)(tile % A.nt[0]) * A.t[0], (int)((tile / A.nt[0]) % A.nt[1]) * A.t[1],
@@ -540,7 +542,7 @@ __global__ void __launch_bounds__(GPD64_BS, 3) k_gpd64_tile(Gpd64TileArgs A) {
     }
     __syncthreads();
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int s = 0; s < A.nsp; ++s) {
+    for (int s = s0; s < s1; ++s) {
         const Gpd64Args& S = A.sp[s];
         const int32_t start = A.bins[s][tile * TILE_CELLS], end = A.bins[s][(tile + 1) * TILE_CELLS];
         const int32_t per = (end - start + 63) / 64;
@@ -660,8 +662,9 @@ hipError_t launch_gpd64(pp_run* r, int s, double* J) {
 
 template <int O, class TL>
 static void launch_tile(const Gpd64TileArgs& A, size_t lds, hipStream_t st) {
-    hipLaunchKernelGGL((k_gpd64_tile<O, TL>), dim3((unsigned)(8 * A.per_xcd), (unsigned)A.parts), dim3(GPD64_BS), lds, st,
-                       A);
+    const unsigned split = A.ntiles * A.parts * A.nsp <= 768 ? (unsigned)A.nsp : 1u;  // all resident at once: 31 us against 50 (16^3)
+    hipLaunchKernelGGL((k_gpd64_tile<O, TL>), dim3((unsigned)(8 * A.per_xcd), (unsigned)A.parts, split), dim3(GPD64_BS),
+                       lds, st, A);
 }
 
 // LDS bytes of a tile of the runtime-shaped kernel.
