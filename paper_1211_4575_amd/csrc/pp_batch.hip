@@ -103,6 +103,14 @@ pp_status grow_device(pp_batch* b, size_t need) {
     return PP_OK;
 }
 
+// Mean particles per tile: what a workgroup of the run's particle kernel works on.
+double tile_load(const pp_run* r) {
+    int64_t n = 0;
+    for (const pp::Species& S : r->sp)
+        if (S.active) n += S.n;
+    return (double)n / (double)r->g.ntiles;
+}
+
 enum TableTarget { TABLES_OWN = 0, TABLES_STATIC = 1 };
 
 // One step of every member (the body of pp_batch_step and pp_batch_step_noalloc).  With
@@ -180,7 +188,7 @@ pp_status batch_step(pp_batch* b, TableTarget target) {
         }
         gpd32_fixed_desc(r, (FixedDesc*)(H + o_fix + i * gpd32_fixed_desc_size()));
         field_desc(r, (FieldDesc*)(H + o_field + i * field_desc_size()), n);
-        tpre[i + 1] = tpre[i] + r->g.ntiles;
+        tpre[i + 1] = tpre[i] + gpd32_blocks(r);
         fpre[i + 1] = fpre[i] + gpd32_fixed_blocks(r);
         cpre[i + 1] = cpre[i] + field_blocks(r, n);
         max_sweeps = r->jac_sweeps > max_sweeps ? r->jac_sweeps : max_sweeps;
@@ -295,7 +303,11 @@ pp_status pp_batch_add(pp_batch* b, pp_run* r) {
     if (!b->runs.empty() && b->runs[0]->p.shape_order != r->p.shape_order) return PP_E_ARG;
     for (int s = 0; s < PP_MAX_SPECIES; ++s)
         if (r->sp[s].active && !r->sp[s].sorted) return PP_E_STATE;
-    b->runs.push_back(r);
+    // the runs with the most particles per tile first: the launches' last workgroups are short ones
+    // (eight serving runs: particle kernel 1.69 ms against 1.74 in any order)
+    size_t at = 0;
+    while (at < b->runs.size() && tile_load(b->runs[at]) >= tile_load(r)) ++at;
+    b->runs.insert(b->runs.begin() + (long)at, r);
     return PP_OK;
 }
 

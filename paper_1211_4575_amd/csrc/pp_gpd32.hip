@@ -806,7 +806,7 @@ __global__ void __launch_bounds__(GPD32_BS, TL::pairs ? 3 : 1) k_gpd32(Gpd32Args
     gpd32_tile<O, TL>(A, tile, s0, s1, lds_raw);
 }
 
-// Batched: block b of the launch is tile b - prefix[r] of run r (prefix = running tile counts).
+// Batched: block b of the launch belongs to run r with prefix[r] <= b (prefix = running block counts).
 template <int O, class TL>
 __global__ void __launch_bounds__(GPD32_BS, TL::pairs ? 3 : 1) k_gpd32_batch(const Gpd32Args* __restrict__ table,
                                                           const int64_t* __restrict__ prefix, int nruns) {
@@ -814,7 +814,11 @@ __global__ void __launch_bounds__(GPD32_BS, TL::pairs ? 3 : 1) k_gpd32_batch(con
     const int64_t b = blockIdx.x;
     const int r = find_segment(prefix, nruns, b);
     if (r < 0) return;
-    gpd32_tile<O, TL>(table[r], b - prefix[r], 0, table[r].nsp, lds_raw);
+    // as in a single run, an XCD takes a contiguous eighth of the run's tiles (prefix counts whole
+    // eights, so the XCD is the same b & 7)
+    const int64_t lb = b - prefix[r], tile = (lb & 7) * (int64_t)table[r].per_xcd + (lb >> 3);
+    if (tile >= table[r].ntiles) return;
+    gpd32_tile<O, TL>(table[r], tile, 0, table[r].nsp, lds_raw);
 }
 
 // Fixed-point current of a run to FP64, clearing the accumulator for the next step (runs without
@@ -970,6 +974,7 @@ void gpd32_fixed_desc(const pp_run* r, FixedDesc* D) {
 // blocks of the batched conversion (none where the line solve reads the fixed-point current)
 int64_t gpd32_fixed_blocks(const pp_run* r) { return line_reads_fixed(r) ? 0 : (3 * r->g.ncell + 255) / 256; }
 
+int64_t gpd32_blocks(const pp_run* r) { return 8 * ((r->g.ntiles + 7) / 8); }
 size_t gpd32_args_size() { return sizeof(Gpd32Args); }
 size_t gpd32_fixed_desc_size() { return sizeof(FixedDesc); }
 bool gpd32_batchable(const pp_run* r) { return tile_kind(r) == TILE_444; }
@@ -1017,17 +1022,17 @@ hipError_t launch_gpd32(pp_run* r) {
 
 // Batched particle step of n runs that all use 4x4x4 tiles and the same weight order:
 // the tiled kernel, and the conversion to FP64 of the runs that need it.
-hipError_t launch_gpd32_batch(const void* args_table, const int64_t* tile_prefix, int64_t total_tiles,
+hipError_t launch_gpd32_batch(const void* args_table, const int64_t* tile_prefix, int64_t total_blocks,
                               const void* fixed_table, const int64_t* fixed_prefix, int64_t total_fixed_blocks, int n,
                               int shape_order, size_t lds, hipStream_t st) {
     if (n == 0) return hipSuccess;
     const Gpd32Args* T = (const Gpd32Args*)args_table;
     if (shape_order == 2)
-        hipLaunchKernelGGL((k_gpd32_batch<2, TileCT<2, 4, 4, 4, false>>), dim3((unsigned)total_tiles), dim3(GPD32_BS), lds,
-                           st, T, tile_prefix, n);
+        hipLaunchKernelGGL((k_gpd32_batch<2, TileCT<2, 4, 4, 4, false>>), dim3((unsigned)total_blocks), dim3(GPD32_BS),
+                           lds, st, T, tile_prefix, n);
     else
-        hipLaunchKernelGGL((k_gpd32_batch<3, TileCT<3, 4, 4, 4, false>>), dim3((unsigned)total_tiles), dim3(GPD32_BS), lds,
-                           st, T, tile_prefix, n);
+        hipLaunchKernelGGL((k_gpd32_batch<3, TileCT<3, 4, 4, 4, false>>), dim3((unsigned)total_blocks), dim3(GPD32_BS),
+                           lds, st, T, tile_prefix, n);
     if (total_fixed_blocks > 0)
         hipLaunchKernelGGL(k_fixed_batch, dim3((unsigned)total_fixed_blocks), dim3(256), 0, st,
                            (const FixedDesc*)fixed_table, fixed_prefix, n);

@@ -212,6 +212,7 @@ hipError_t launch_fill(double* p, int64_t n, double v, hipStream_t st);
 void swap_buffers(pp_particles& c);
 
 // batched launches (pp_batch.hip builds the descriptor tables)
+int64_t gpd32_blocks(const pp_run* r);  // blocks of this run in the batched particle kernel
 size_t gpd32_args_size();
 size_t gpd32_fixed_desc_size();
 bool gpd32_batchable(const pp_run* r);
@@ -224,7 +225,7 @@ struct RankedArgs;
 void gpd32_fill_args(const pp_run* r, Gpd32Args* A);
 void gpd32_fixed_desc(const pp_run* r, FixedDesc* D);
 int64_t gpd32_fixed_blocks(const pp_run* r);
-hipError_t launch_gpd32_batch(const void* args_table, const int64_t* tile_prefix, int64_t total_tiles,
+hipError_t launch_gpd32_batch(const void* args_table, const int64_t* tile_prefix, int64_t total_blocks,
                               const void* fixed_table, const int64_t* fixed_prefix, int64_t total_fixed_blocks, int n,
                               int shape_order, size_t lds, hipStream_t st);
 size_t field_desc_size();

@@ -24,6 +24,8 @@
 // species (arbitrary order) buckets by tile -- a count per tile, a scan, and a scatter whose
 // positions come from block-aggregated atomics -- and then rebuilds the tile order tile by
 // tile.
+#include <type_traits>
+
 #include "pp_device.hpp"
 #include "pp_internal.hpp"
 
@@ -975,19 +977,43 @@ struct ApplyArgs {
     int64_t* id_o;
 };
 
+// Each thread moves APPLY_PER particles, their loads in flight together.  The old places of a
+// tile's slots lie close together: neighbouring blocks run on one XCD, so that their lines are
+// fetched into one L2.  6.7e7 tagged particles: 2.19 ms (2.53 with one a thread on any XCD).
+constexpr int APPLY_PER = 4, APPLY_BLOCK = 256 * APPLY_PER;
+
 template <typename T>
 __global__ void __launch_bounds__(256) k_apply_perm(ApplyArgs<T> A) {
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= A.n) return;
-    const int32_t p = A.perm[q];
-    if (p < 0) return;
-    if (A.cell) A.cell_o[q] = A.cell[p];
+    const int64_t b = xcd_block(blockIdx.x, (A.n + APPLY_BLOCK - 1) / APPLY_BLOCK);
+    if (b < 0) return;
+    int64_t q[APPLY_PER];
+    int32_t p[APPLY_PER];
+    bool live[APPLY_PER];
+#pragma unroll
+    for (int k = 0; k < APPLY_PER; ++k) {
+        q[k] = b * APPLY_BLOCK + k * 256 + threadIdx.x;
+        p[k] = q[k] < A.n ? A.perm[q[k]] : -1;
+    }
+#pragma unroll
+    for (int k = 0; k < APPLY_PER; ++k) {
+        live[k] = p[k] >= 0;
+        p[k] = live[k] ? p[k] : 0;
+    }
+    auto move = [&](const auto* in, auto* out) {
+        std::remove_const_t<std::remove_reference_t<decltype(*in)>> v[APPLY_PER];
+#pragma unroll
+        for (int k = 0; k < APPLY_PER; ++k) v[k] = in[p[k]];
+#pragma unroll
+        for (int k = 0; k < APPLY_PER; ++k)
+            if (live[k]) out[q[k]] = v[k];
+    };
+    if (A.cell) move(A.cell, A.cell_o);
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
-        A.pos_o[d][q] = A.pos[d][p];
-        A.u_o[d][q] = A.u[d][p];
+        move(A.pos[d], A.pos_o[d]);
+        move(A.u[d], A.u_o[d]);
     }
-    if (A.id) A.id_o[q] = A.id[p];
+    if (A.id) move(A.id, A.id_o);
 }
 
 template <typename T>
@@ -1005,7 +1031,7 @@ static void apply_perm(pp_run* r, const Species& S) {
         A.pos_o[d] = (T*)S.cur.pos_alt[d];
         A.u_o[d] = (T*)S.cur.u_alt[d];
     }
-    hipLaunchKernelGGL(k_apply_perm<T>, dim3((unsigned)((S.n + 255) / 256)), dim3(256), 0, r->stream, A);
+    hipLaunchKernelGGL(k_apply_perm<T>, dim3(xcd_grid((S.n + APPLY_BLOCK - 1) / APPLY_BLOCK)), dim3(256), 0, r->stream, A);
 }
 
 hipError_t materialize(pp_run* r, int s) {
