@@ -170,6 +170,15 @@ __device__ __forceinline__ void rad_cool(T k, T dt, T ic, const V3<T>& um, V3<T>
 
 __device__ __forceinline__ void atomic_add_f64(double* p, double v) { unsafeAtomicAdd(p, v); }
 
+// A pointer read from a table in device memory, marked as one into device memory.  The compiler
+// takes such a pointer for a generic one, whose (flat) accesses count as LDS accesses too and are
+// waited for with them (24 steps of eight serving runs: 54.1 ms, 52.3 so).  Through an integer: it
+// drops a cast there and back between pointer types.
+template <typename T>
+__device__ __forceinline__ T* gl(T* p) {
+    return (T*)(__attribute__((address_space(1))) T*)(uintptr_t)p;
+}
+
 // Workgroups go round-robin over the 8 XCDs, each with its own L2: this block's number when every
 // XCD takes a contiguous eighth of n blocks (-1: none left), so that neighbours share an L2.  The
 // launch has xcd_grid(n) blocks.

@@ -256,11 +256,11 @@ __device__ __forceinline__ void relax_tile(const FieldDesc& D, int b, int k, dou
     tile_ctx(G, D.zc, b, X);
     g.init(X.i0, X.j0, G.n[0], G.n[1]);
     const int64_t co = (int64_t)X.comp * G.nc;
-    double* out = relax_array(D, k) + co;
-    const double* x = (k == 1 ? D.Bn : relax_array(D, k - 1)) + co;
-    const double* pv = (k <= 2 ? D.Bn : relax_array(D, k - 2)) + co;
-    const double* rhs = D.R + co;
-    const double w = D.omega[k];
+    double* out = gl(relax_array(D, k)) + co;
+    const double* x = gl(k == 1 ? D.Bn : relax_array(D, k - 1)) + co;
+    const double* pv = gl(k <= 2 ? D.Bn : relax_array(D, k - 2)) + co;
+    const double* rhs = gl(D.R) + co;
+    const double w = gl(D.omega)[k];
     const int nxy = X.nxy, own = X.own;
     double q[2 * R + 1], hv[NH];
 #pragma unroll
@@ -328,7 +328,7 @@ struct ZStream {
     double wn;
     // lds: the next free part of the block's LDS
     __device__ __forceinline__ void init(const double* src, const TileCtx& X, const FieldGeom& F, double*& lds) {
-        f = src;
+        f = gl(src);
 #pragma unroll
         for (int t = 0; t < NW; ++t) w[t] = f[X.col + X.nxy * nbw(X.z0, WLO + t, X.n2, X.small)];
         if constexpr (PLANE) {
@@ -397,9 +397,9 @@ __device__ __forceinline__ void rhs_tiled_comp(const FieldDesc& D, const TileCtx
     ZStream<R, R, -R, R> sB;
     DStream<M, d1, 1> sEu, sJu;  // E_d2, J_d2 along d1
     DStream<M, d2, 1> sEv, sJv;  // E_d1, J_d1 along d2
-    double* Bn = D.Bn + C * G.nc;
-    double* x1 = D.sweeps > 1 ? D.Bw + C * G.nc : nullptr;
-    const double w1 = D.omega[1];
+    double* Bn = gl(D.Bn) + C * G.nc;
+    double* x1 = D.sweeps > 1 ? gl(D.Bw) + C * G.nc : nullptr;
+    const double w1 = gl(D.omega)[1];
     sB.init(D.B + C * G.nc, X, G, lds);
     sEu.init(D.E + d2 * G.nc, X, G, lds);
     sEv.init(D.E + d1 * G.nc, X, G, lds);
@@ -434,7 +434,7 @@ __device__ __forceinline__ void rhs_tiled_comp(const FieldDesc& D, const TileCtx
             const double xq = sB.at(0);
             const double rq = xq + D.cab * lp - D.dt * curlE + D.cj * curlJ;
             const int64_t q = X.own + (int64_t)kz * X.nxy;
-            D.R[C * G.nc + q] = rq;
+            gl(D.R)[C * G.nc + q] = rq;
             Bn[q] = xq;
             if (x1) {  // sweep 1
                 const double Ax = xq - D.al2s * lp;
@@ -485,7 +485,7 @@ __device__ __forceinline__ void update_E_tiled_comp(const FieldDesc& D, const Ti
         if (X.valid) {
             const double cn = dtile<M, d1, 0>(sBu, G.a[d1]) - dtile<M, d2, 0>(sBv, G.a[d2]);
             const double co = dtile<M, d1, 0>(sNu, G.a[d1]) - dtile<M, d2, 0>(sNv, G.a[d2]);
-            D.E[C * G.nc + X.own + (int64_t)kz * X.nxy] =
+            gl(D.E)[C * G.nc + X.own + (int64_t)kz * X.nxy] =
                 sE.at(0) + D.c2dt * (D.al * cn + D.be * co - D.mu0 * sJ.at(0));
         }
         if (more) {
@@ -990,7 +990,7 @@ __device__ __forceinline__ void line_body(const LineArgs& A, int64_t b) {
     const int stride[3] = {1, A.G.n[0], A.G.n[0] * A.G.n[1]};
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-        const double* src = A.J2 + (int64_t)c * nc;
+        const double* src = gl(A.J2) + (int64_t)c * nc;
         const int N = A.G.n[c];
         const int rowbase = q - ijk[c] * stride[c];
         double s = 0.0;
@@ -998,10 +998,10 @@ __device__ __forceinline__ void line_body(const LineArgs& A, int64_t b) {
         idx %= N;
         if (idx < 0) idx += N;
         for (int jj = 0; jj < A.len[c]; ++jj) {
-            s += A.coef[c][jj] * src[rowbase + idx * stride[c]];
+            s += gl(A.coef[c])[jj] * src[rowbase + idx * stride[c]];
             if (++idx == N) idx = 0;
         }
-        A.J[(int64_t)c * nc + q] = s;
+        gl(A.J)[(int64_t)c * nc + q] = s;
     }
 }
 
@@ -1076,7 +1076,7 @@ __device__ __forceinline__ void line_lds_body(const LineArgs& A, int64_t b, doub
     const int N = arg3(G.n, c), W = arg3(A.W, c), len = arg3(A.len, c), off = arg3(A.off, c);
     const int ext = N + len - 1;
     const int64_t nc = G.nc;
-    double* dst = A.J + (int64_t)c * nc;
+    double* dst = gl(A.J) + (int64_t)c * nc;
     // first line of the block and the line count / axis stride
     int64_t base0;
     int stride, nlines;

@@ -6,6 +6,7 @@
 #include <cstdint>
 
 #include "../../include/pp.h"
+#include "pp_device.hpp"
 
 struct pp_run;
 
@@ -24,7 +25,7 @@ FixedScale gpd32_scale(const pp_run* r);
 __device__ __forceinline__ double fixed_scale(const FixedScale& F) {
     long long nb = 0;
 #pragma unroll
-    for (int s = 0; s < PP_MAX_SPECIES; ++s) nb += F.tile_max[s];
+    for (int s = 0; s < PP_MAX_SPECIES; ++s) nb += gl(F.tile_max)[s];
     const int e = __builtin_amdgcn_readfirstlane(F.e0 - (nb > 1 ? 64 - __clzll(nb - 1) : 0));  // uniform
     if (e >= -1022 && e <= 1023) return __longlong_as_double((long long)(e + 1023) << 52);
     return ldexp(1.0, e);

@@ -283,7 +283,7 @@ __device__ __forceinline__ int32_t dest_rank(const Gpd32Args& A, const Sp32& S, 
         if (r < (1 << 20)) return (sl << 20) | r;
         atomicSub(&slots[sl], 1);  // past the word's range: counted below instead
     }
-    return (int32_t)(0x80000000u | (uint32_t)atomicAdd(&S.cnt[gcell], 1));
+    return (int32_t)(0x80000000u | (uint32_t)atomicAdd(gl(S.cnt) + gcell, 1));
 }
 
 // What the charge-conserving deposit of one particle needs, kept in registers between its step
@@ -354,25 +354,25 @@ __device__ __forceinline__ void step_particle(const Gpd32Args& A, const Sp32& S,
                                               int32_t q, Win<O>& W, int& bad_all) {
     W.dep = false;
     const int n0 = A.n[0], n1 = A.n[1], n2 = A.n[2];
-    const int32_t p = S.perm ? S.perm[q] : q;
+    const int32_t p = S.perm ? gl(S.perm)[q] : q;
     if (p < 0) {  // an empty slot (counts made inconsistent by flagged particles)
-        S.rank[q] = -1;
+        gl(S.rank)[q] = -1;
         return;
     }
-    const int32_t cell = S.cell[p];
-    float f[3] = {S.pos[0][p], S.pos[1][p], S.pos[2][p]};
-    V3<float> u{S.u[0][p], S.u[1][p], S.u[2][p]};
-    if (S.id) S.id_o[q] = S.id[p];
+    const int32_t cell = gl(S.cell)[p];
+    float f[3] = {gl(S.pos[0])[p], gl(S.pos[1])[p], gl(S.pos[2])[p]};
+    V3<float> u{gl(S.u[0])[p], gl(S.u[1])[p], gl(S.u[2])[p]};
+    if (S.id) gl(S.id_o)[q] = gl(S.id)[p];
     // a particle left as it is still moves to its slot when the kernel reorders
     auto keep = [&](const V3<float>& uk) {
         if (!S.perm) return;
-        S.cell_o[q] = cell;
-        S.pos_o[0][q] = f[0];
-        S.pos_o[1][q] = f[1];
-        S.pos_o[2][q] = f[2];
-        S.u_o[0][q] = uk.x;
-        S.u_o[1][q] = uk.y;
-        S.u_o[2][q] = uk.z;
+        gl(S.cell_o)[q] = cell;
+        gl(S.pos_o[0])[q] = f[0];
+        gl(S.pos_o[1])[q] = f[1];
+        gl(S.pos_o[2])[q] = f[2];
+        gl(S.u_o[0])[q] = uk.x;
+        gl(S.u_o[1])[q] = uk.y;
+        gl(S.u_o[2])[q] = uk.z;
     };
     // position inside the tile: rel = li + n0 lj + n0 n1 lk with l < t, found by
     // comparisons (no division)
@@ -397,13 +397,13 @@ __device__ __forceinline__ void step_particle(const Gpd32Args& A, const Sp32& S,
     if (!inside) {  // not this tile's particle: left out of the next sort
         bad_all |= PP_FLAG_OUT_OF_TILE;
         keep(u);
-        S.rank[q] = -1;
+        gl(S.rank)[q] = -1;
         return;
     }
     if (!offset_ok<O>(f[0]) || !offset_ok<O>(f[1]) || !offset_ok<O>(f[2])) {  // left as it is
         bad_all |= PP_FLAG_OUT_OF_TILE;
         keep(u);
-        S.rank[q] = dest_rank(A, S, C.slots, loc, cell);
+        gl(S.rank)[q] = dest_rank(A, S, C.slots, loc, cell);
         return;
     }
 
@@ -451,7 +451,7 @@ __device__ __forceinline__ void step_particle(const Gpd32Args& A, const Sp32& S,
     if (bad) {  // left as it was before the push
         bad_all |= bad;
         keep(um);
-        S.rank[q] = dest_rank(A, S, C.slots, loc, cell);
+        gl(S.rank)[q] = dest_rank(A, S, C.slots, loc, cell);
         return;
     }
 
@@ -533,15 +533,15 @@ __device__ __forceinline__ void step_particle(const Gpd32Args& A, const Sp32& S,
         nc3[d] = wrap_near(gc[d] + (int)sh, A.n[d]);
     }
     const int32_t newcell = nc3[0] + n0 * (nc3[1] + n1 * nc3[2]);
-    S.cell_o[q] = newcell;
-    S.pos_o[0][q] = fn[0];
-    S.pos_o[1][q] = fn[1];
-    S.pos_o[2][q] = fn[2];
-    S.u_o[0][q] = u.x;
-    S.u_o[1][q] = u.y;
-    S.u_o[2][q] = u.z;
+    gl(S.cell_o)[q] = newcell;
+    gl(S.pos_o[0])[q] = fn[0];
+    gl(S.pos_o[1])[q] = fn[1];
+    gl(S.pos_o[2])[q] = fn[2];
+    gl(S.u_o[0])[q] = u.x;
+    gl(S.u_o[1])[q] = u.y;
+    gl(S.u_o[2])[q] = u.z;
     const int dst[3] = {li + shv[0], lj + shv[1], lk + shv[2]};
-    S.rank[q] = dest_rank(A, S, C.slots, dst, newcell);
+    gl(S.rank)[q] = dest_rank(A, S, C.slots, dst, newcell);
 }
 
 // Charge-conserving current of one particle (W1), or of two particles whose windows start at
@@ -673,7 +673,7 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, int
             const int gk = wrap_near(org[2] - L.floz + c, n2);
             const int64_t gq = (int64_t)gi + (int64_t)n0 * (gj + (int64_t)n1 * gk);
             const double* src = comp < 3 ? A.E + comp * A.nc : A.B + (comp - 3) * A.nc;
-            v[k] = src[gq];
+            v[k] = gl(src)[gq];
         }
 #pragma unroll
         for (int k = 0; k < STAGE_BATCH; ++k)
@@ -699,8 +699,8 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, int
 
     for (int s = s0; s < s1; ++s) {
         const Sp32& S = A.sp[s];
-        const int32_t start = S.start[tile];
-        const int32_t end = S.start[tile + 1];
+        const int32_t start = gl(S.start)[tile];
+        const int32_t end = gl(S.start)[tile + 1];
         if (threadIdx.x < 4) facq[threadIdx.x] = (threadIdx.x < 3 ? S.fac[threadIdx.x] : S.qw) * qs;
         __syncthreads();
         if constexpr (!TL::pairs) {
@@ -755,13 +755,13 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, int
                 const int gx = A.sext[0] == 1 ? 0 : wrap_near(org[0] + x - DEST_HALO, n0);
                 const int gy = A.sext[1] == 1 ? 0 : wrap_near(org[1] + y - DEST_HALO, n1);
                 const int gz = A.sext[2] == 1 ? 0 : wrap_near(org[2] + z - DEST_HALO, n2);
-                first = atomicAdd(&S.cnt[gx + n0 * (gy + n1 * gz)], c);
+                first = atomicAdd(gl(S.cnt) + (gx + n0 * (gy + n1 * gz)), c);
             }
-            S.base[tile * A.nslots + q] = first;
+            gl(S.base)[tile * A.nslots + q] = first;
         }
         __syncthreads();
     }
-    if (bad_all) atomic_or_flag(A.flags, bad_all);
+    if (bad_all) atomic_or_flag(gl(A.flags), bad_all);
 
     // 3. flush the current block (integer adds commute: the sum is order-independent); each
     // thread reads STAGE_BATCH entries before it waits for the first
@@ -787,7 +787,7 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, int
             const int gi = wrap_near(org[0] - L.clox + a, n0);
             const int gj = wrap_near(org[1] - L.cloy + bb, n1);
             const int gk = wrap_near(org[2] - L.cloz + c, n2);
-            atomicAdd(A.Jq + comp * A.nc + (int64_t)gi + (int64_t)n0 * (gj + (int64_t)n1 * gk),
+            atomicAdd(gl(A.Jq) + comp * A.nc + (int64_t)gi + (int64_t)n0 * (gj + (int64_t)n1 * gk),
                       (unsigned long long)v);
         }
     }
@@ -832,8 +832,8 @@ struct FixedDesc {
 
 __device__ __forceinline__ void fixed_body(const FixedDesc& D, int64_t q, double inv) {
     if (q >= D.n3) return;
-    D.J[q] = (double)(long long)D.Jq[q] * inv;
-    D.Jq[q] = 0ull;
+    gl(D.J)[q] = (double)(long long)gl(D.Jq)[q] * inv;
+    gl(D.Jq)[q] = 0ull;
 }
 
 __global__ void __launch_bounds__(256) k_fixed(FixedDesc D) {

@@ -435,16 +435,16 @@ struct RankedArgs {
 __device__ __forceinline__ void bin_prefix_tile(const RankedArgs& A, int64_t t) {
     const int lane = threadIdx.x & 63;
     if (t >= A.G.ntiles) return;
-    const int32_t c = A.cnt[t * TILE_CELLS + lane];
-    A.cnt[t * TILE_CELLS + lane] = 0;
+    const int32_t c = gl(A.cnt)[t * TILE_CELLS + lane];
+    gl(A.cnt)[t * TILE_CELLS + lane] = 0;
     int32_t incl = c;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
         const int32_t y = __shfl_up(incl, o, 64);
         if (lane >= o) incl += y;
     }
-    A.pre[t * TILE_CELLS + lane] = incl - c;
-    if (lane == 63) A.tot[t] = incl;
+    gl(A.pre)[t * TILE_CELLS + lane] = incl - c;
+    if (lane == 63) gl(A.tot)[t] = incl;
 }
 
 // one wavefront per tile: lane = local cell
@@ -458,8 +458,8 @@ __device__ __forceinline__ void round_table_tile(const RankedArgs& A, int64_t t)
     int c = 0;
     if (lk < G.t[2] && i < G.n[0] && j < G.n[1] && k < G.n[2]) {
         const int64_t g = (int64_t)i + (int64_t)G.n[0] * (j + (int64_t)G.n[1] * k);
-        c = A.cnt[g];
-        A.cnt[g] = 0;
+        c = gl(A.cnt)[g];
+        gl(A.cnt)[g] = 0;
     }
     int tot = c, mx = c;
 #pragma unroll
@@ -471,12 +471,12 @@ __device__ __forceinline__ void round_table_tile(const RankedArgs& A, int64_t t)
     const int rmax = mx < SORT_RCAP ? mx : SORT_RCAP;
     const int kc = c < SORT_RCAP ? c : SORT_RCAP;
     int32_t nchunk, intable;
-    pair_table(kc, rmax, [&](int r, const RoundEntry& e) { A.rounds[t * SORT_RCAP + r] = e; }, nchunk, intable);
+    pair_table(kc, rmax, [&](int r, const RoundEntry& e) { gl(A.rounds)[t * SORT_RCAP + r] = e; }, nchunk, intable);
     if (lane == 0) {
-        A.tot[t] = tot;
-        A.rtot[t] = intable;
-        A.nchunk[t] = nchunk;
-        A.ovf[t] = 0;
+        gl(A.tot)[t] = tot;
+        gl(A.rtot)[t] = intable;
+        gl(A.nchunk)[t] = nchunk;
+        gl(A.ovf)[t] = 0;
     }
 }
 
@@ -546,12 +546,12 @@ __device__ __forceinline__ void scan_workgroup(int32_t* data, int64_t n, int32_t
 // the slots past it (particles left out) hold no particle.
 __device__ __forceinline__ void ranked_scan(const RankedArgs& A) {
     int32_t total, largest;
-    scan_workgroup(A.tot, A.G.ntiles, total, largest);
+    scan_workgroup(gl(A.tot), A.G.ntiles, total, largest);
     if (threadIdx.x == 0) {
-        A.tot[A.G.ntiles] = total;
-        if (A.tile_max) *A.tile_max = largest;
+        gl(A.tot)[A.G.ntiles] = total;
+        if (A.tile_max) *gl(A.tile_max) = largest;
     }
-    for (int64_t q = total + (int64_t)threadIdx.x; q < A.n; q += SCAN1_BS) A.perm[q] = -1;
+    for (int64_t q = total + (int64_t)threadIdx.x; q < A.n; q += SCAN1_BS) gl(A.perm)[q] = -1;
 }
 
 // What a particle bound for one destination cell needs: the cell's tile and place in it, the
@@ -570,10 +570,10 @@ __device__ __forceinline__ DestCell dest_cell(const RankedArgs& A, int gx, int g
     const int lc = (gx & (G.t[0] - 1)) + ((gy & (G.t[1] - 1)) << A.tsh[0]) + ((gz & (G.t[2] - 1)) << (A.tsh[0] + A.tsh[1]));
     DestCell c;
     c.tile_lc = (t << 6) | lc;
-    c.d0 = A.tot[t];
-    c.nd = A.tot[t + 1] - c.d0;
-    c.nchunk = A.nchunk[t];
-    c.rtot = A.rtot[t];
+    c.d0 = gl(A.tot)[t];
+    c.nd = gl(A.tot)[t + 1] - c.d0;
+    c.nchunk = gl(A.nchunk)[t];
+    c.rtot = gl(A.rtot)[t];
     c.base = base;
     return c;
 }
@@ -594,8 +594,8 @@ constexpr int PERM_IMG = 4096;
 __device__ __forceinline__ void ranked_perm_tile(const RankedArgs& A, int64_t T, int32_t* lds) {
     const Geom& G = A.G;
     if (T >= G.ntiles) return;
-    const int32_t ss = A.start[T], se = A.start[T + 1];
-    const int32_t d0 = A.tot[T], nd = A.tot[T + 1] - d0;
+    const int32_t ss = gl(A.start)[T], se = gl(A.start)[T + 1];
+    const int32_t d0 = gl(A.tot)[T], nd = gl(A.tot)[T + 1] - d0;
     const bool staged = nd <= PERM_IMG;
     int32_t* img = lds;
     DestCell* dest = (DestCell*)(lds + PERM_IMG);
@@ -609,7 +609,7 @@ __device__ __forceinline__ void ranked_perm_tile(const RankedArgs& A, int64_t T,
             const int z = q / (e0 * e1), r = q - z * e0 * e1, y = r / e0, x = r - y * e0;
             dest[q] = dest_cell(A, e0 == 1 ? 0 : wrap_near(ox + x - DEST_HALO, G.n[0]),
                                 e1 == 1 ? 0 : wrap_near(oy + y - DEST_HALO, G.n[1]),
-                                G.n[2] == 1 ? 0 : wrap_near(oz + z - DEST_HALO, G.n[2]), A.base[T * slots + q]);
+                                G.n[2] == 1 ? 0 : wrap_near(oz + z - DEST_HALO, G.n[2]), gl(A.base)[T * slots + q]);
         }
     __syncthreads();
     const int lane = threadIdx.x & 63;
@@ -620,14 +620,14 @@ __device__ __forceinline__ void ranked_perm_tile(const RankedArgs& A, int64_t T,
 #pragma unroll
         for (int k = 0; k < PERM_PER; ++k) {
             const int64_t p = b + threadIdx.x + k * 256;
-            w[k] = p < se ? A.rank[p] : -1;
+            w[k] = p < se ? gl(A.rank)[p] : -1;
         }
 #pragma unroll
         for (int k = 0; k < PERM_PER; ++k) {
             c[k] = dest[w[k] >= 0 ? w[k] >> 20 : 0];
             r[k] = w[k] >= 0 ? c[k].base + (w[k] & 0xFFFFF) : -1;
             if (w[k] < -1) {  // its rank itself, in a cell that may lie anywhere
-                const int32_t g = A.cell[b + threadIdx.x + k * 256];
+                const int32_t g = gl(A.cell)[b + threadIdx.x + k * 256];
                 const bool in = g >= 0 && g < G.ncell;
                 const int gx = in ? g % G.n[0] : 0, gr = in ? g / G.n[0] : 0;
                 c[k] = dest_cell(A, gx, gr % G.n[1], gr / G.n[1], 0);
@@ -636,7 +636,7 @@ __device__ __forceinline__ void ranked_perm_tile(const RankedArgs& A, int64_t T,
         }
 #pragma unroll
         for (int k = 0; k < PERM_PER; ++k)
-            e[k] = A.rounds[(int64_t)(c[k].tile_lc >> 6) * SORT_RCAP + (r[k] >= 0 && r[k] < SORT_RCAP ? r[k] : 0)];
+            e[k] = gl(A.rounds)[(int64_t)(c[k].tile_lc >> 6) * SORT_RCAP + (r[k] >= 0 && r[k] < SORT_RCAP ? r[k] : 0)];
         int32_t pos[PERM_PER];
 #pragma unroll
         for (int k = 0; k < PERM_PER; ++k) {
@@ -655,7 +655,7 @@ __device__ __forceinline__ void ranked_perm_tile(const RankedArgs& A, int64_t T,
                 const int32_t lt = __shfl(t, leader, 64);
                 const uint64_t grp = __ballot(over && t == lt) & todo;
                 int32_t first = 0;
-                if (lane == leader) first = atomicAdd(&A.ovf[lt], (int32_t)__popcll(grp));
+                if (lane == leader) first = atomicAdd(gl(A.ovf) + lt, (int32_t)__popcll(grp));
                 first = __shfl(first, leader, 64);
                 if (over && t == lt) pos[k] += first + (int32_t)__popcll(grp & ((1ull << lane) - 1ull));
                 todo &= ~grp;
@@ -668,14 +668,14 @@ __device__ __forceinline__ void ranked_perm_tile(const RankedArgs& A, int64_t T,
             if (staged && (c[k].tile_lc >> 6) == (int32_t)T)
                 img[pos[k]] = p;
             else
-                A.perm[c[k].d0 + pos[k]] = p;
+                gl(A.perm)[c[k].d0 + pos[k]] = p;
         }
     }
     __syncthreads();
     if (staged)
         for (int32_t q = threadIdx.x; q < nd; q += blockDim.x) {
             const int32_t v = img[q];
-            if (v >= 0) A.perm[d0 + q] = v;
+            if (v >= 0) gl(A.perm)[d0 + q] = v;
         }
 }
 
@@ -685,21 +685,21 @@ __device__ __forceinline__ void ranked_perm_tile(const RankedArgs& A, int64_t T,
 __device__ __forceinline__ void bin_perm_tile(const RankedArgs& A, int64_t T, int32_t* lds) {
     const Geom& G = A.G;
     if (T >= G.ntiles) return;
-    const int32_t ss = A.start[T * TILE_CELLS], se = A.start[(T + 1) * TILE_CELLS];
-    const int32_t d0 = A.tot[T], nd = A.tot[T + 1] - d0;
+    const int32_t ss = gl(A.start)[T * TILE_CELLS], se = gl(A.start)[(T + 1) * TILE_CELLS];
+    const int32_t d0 = gl(A.tot)[T], nd = gl(A.tot)[T + 1] - d0;
     const bool staged = nd <= PERM_IMG;
     int32_t* img = lds;
     int32_t* first = lds + PERM_IMG;  // first slot of each destination cell
     if (threadIdx.x < TILE_CELLS) {
-        A.next_bins[T * TILE_CELLS + threadIdx.x] = d0 + A.pre[T * TILE_CELLS + threadIdx.x];
-        if (T == G.ntiles - 1 && threadIdx.x == 0) A.next_bins[G.nbins] = A.tot[G.ntiles];
+        gl(A.next_bins)[T * TILE_CELLS + threadIdx.x] = d0 + gl(A.pre)[T * TILE_CELLS + threadIdx.x];
+        if (T == G.ntiles - 1 && threadIdx.x == 0) gl(A.next_bins)[G.nbins] = gl(A.tot)[G.ntiles];
     }
     if (staged)
         for (int32_t q = threadIdx.x; q < nd; q += blockDim.x) img[q] = -1;
     auto cell_first = [&](int gx, int gy, int gz) {
         const int32_t t = (gx >> A.tsh[0]) + G.nt[0] * ((gy >> A.tsh[1]) + G.nt[1] * (gz >> A.tsh[2]));
         const int lc = (gx & (G.t[0] - 1)) + ((gy & (G.t[1] - 1)) << A.tsh[0]) + ((gz & (G.t[2] - 1)) << (A.tsh[0] + A.tsh[1]));
-        return A.tot[t] + A.pre[t * TILE_CELLS + lc];
+        return gl(A.tot)[t] + gl(A.pre)[t * TILE_CELLS + lc];
     };
     const int e0 = G.dest_ext(0), e1 = G.dest_ext(1), slots = e0 * e1 * G.dest_ext(2);
     const int ox = (int)(T % G.nt[0]) * G.t[0], oy = (int)((T / G.nt[0]) % G.nt[1]) * G.t[1],
@@ -717,7 +717,7 @@ __device__ __forceinline__ void bin_perm_tile(const RankedArgs& A, int64_t T, in
 #pragma unroll
         for (int k = 0; k < PERM_PER; ++k) {
             const int64_t p = b + threadIdx.x + k * 256;
-            w[k] = p < se ? A.rank[p] : 0;
+            w[k] = p < se ? gl(A.rank)[p] : 0;
         }
 #pragma unroll
         for (int k = 0; k < PERM_PER; ++k) {
@@ -727,19 +727,19 @@ __device__ __forceinline__ void bin_perm_tile(const RankedArgs& A, int64_t T, in
             if (w[k] >= 0)
                 q = first[w[k] >> 20] + (w[k] & 0xFFFFF);
             else
-                q = cell_first(nearest_cell(A.pos[0][p], G.n[0]), nearest_cell(A.pos[1][p], G.n[1]),
-                               nearest_cell(A.pos[2][p], G.n[2])) + (w[k] & 0x7FFFFFFF);
+                q = cell_first(nearest_cell(gl(A.pos[0])[p], G.n[0]), nearest_cell(gl(A.pos[1])[p], G.n[1]),
+                               nearest_cell(gl(A.pos[2])[p], G.n[2])) + (w[k] & 0x7FFFFFFF);
             if (staged && q >= d0 && q < d0 + nd)
                 img[q - d0] = (int32_t)p;
             else
-                A.perm[q] = (int32_t)p;
+                gl(A.perm)[q] = (int32_t)p;
         }
     }
     __syncthreads();
     if (staged)
         for (int32_t q = threadIdx.x; q < nd; q += blockDim.x) {
             const int32_t v = img[q];
-            if (v >= 0) A.perm[d0 + q] = v;
+            if (v >= 0) gl(A.perm)[d0 + q] = v;
         }
 }
 
