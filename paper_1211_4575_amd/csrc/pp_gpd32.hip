@@ -86,12 +86,11 @@ struct Gpd32Args {
     int32_t* flags;
     int per_xcd;
     int sext[3];  // destination-cell window per axis (tile and DEST_HALO around it; 1 if collapsed)
-    int nslots;   // sext[0] * sext[1] * sext[2]
     int direct;   // PP_CURRENT_DIRECT: eq. "jj2" instead of the Esirkepov current
 };
 
 constexpr int GPD32_BS = 256;
-constexpr int STAGE_BATCH = 8;  // field loads / current reads a thread issues before the first wait
+constexpr int STAGE_NODES = 3;  // nodes whose fields a thread loads before the first wait
 constexpr double ROUND_MAGIC = 6755399441055744.0;  // 1.5 * 2^52
 constexpr unsigned long long LOW51 = (1ull << 51) - 1ull;
 constexpr long long BIT50 = 1ll << 50;
@@ -121,6 +120,7 @@ constexpr int fld_plane_444(int O) { return O == 3 ? 90 : (O + 6) * (O + 6); }
 // The current block is indexed x + crow*y + cplane*z (padding entries stay zero).
 template <int O, int TX, int TY, int TZ, bool CZ>
 struct TileCT {
+    static constexpr bool fixed_shape = true;
     static constexpr int tx = TX, ty = TY, tz = TZ;
     static constexpr int flox = FLD_LO, floy = FLD_LO, floz = CZ ? 0 : FLD_LO;
     static constexpr int clox = cur_lo(O), cloy = cur_lo(O), cloz = CZ ? 0 : cur_lo(O);
@@ -128,6 +128,8 @@ struct TileCT {
     static constexpr int fez = CZ ? 1 : TZ + FLD_LO + fld_hi(O);
     static constexpr int cex = TX + cur_lo(O) + cur_hi(O), cey = TY + cur_lo(O) + cur_hi(O);
     static constexpr int cez = CZ ? 1 : TZ + cur_lo(O) + cur_hi(O);
+    // destination cells: the tile and DEST_HALO around it
+    static constexpr int dex = TX + 2 * DEST_HALO, dey = TY + 2 * DEST_HALO, dez = CZ ? 1 : TZ + 2 * DEST_HALO;
     static constexpr bool f444 = TX == 4 && TY == 4 && TZ == 4 && !CZ;
     static constexpr int frow = f444 ? fld_row_444(O) : fex;
     static constexpr int fplane = f444 ? fld_plane_444(O) : frow * fey;
@@ -149,11 +151,12 @@ struct TileCT {
 };
 
 struct TileRT {
+    static constexpr bool fixed_shape = false;
     static constexpr bool pairs = false;
     static constexpr bool flat = false;
     int tx, ty, tz;
     int flox, floy, floz, clox, cloy, cloz;
-    int fex, fey, fez, cex, cey, cez;
+    int fex, fey, fez, cex, cey, cez, dex, dey, dez;
     int fsx, fsy, fsz, csx, csy, csz;
     int crow, cplane, frow, fplane;
     int fvol, cvol;
@@ -173,6 +176,9 @@ struct TileRT {
         cex = A.ce[0];
         cey = A.ce[1];
         cez = A.ce[2];
+        dex = A.sext[0];
+        dey = A.sext[1];
+        dez = A.sext[2];
         fsx = A.n[0] > 1 ? 1 : 0;
         frow = fex;
         fplane = fex * fey;
@@ -266,19 +272,12 @@ __device__ __forceinline__ float gather_comp(const float* __restrict__ F, const 
 // relative to the tile origin (unwrapped), gcell = its linear index.  Inside the tile's
 // window the rank comes from the LDS counter of that cell (slot << 20 | rank in the tile; the
 // sort adds the cell's range start); otherwise from the global count directly (bit 31 set).
-__device__ __forceinline__ int32_t dest_rank(const Gpd32Args& A, const Sp32& S, int32_t* slots, const int rel[3],
-                                             int32_t gcell) {
-    int sl = 0, mul = 1;
-    bool win = true;
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const int e = A.sext[d];
-        const int x = e == 1 ? 0 : rel[d] + DEST_HALO;
-        win = win && x >= 0 && x < e;
-        sl += x * mul;
-        mul *= e;
-    }
-    if (win) {
+template <class TL>
+__device__ __forceinline__ int32_t dest_rank(const Sp32& S, const TL& L, int32_t* slots, const int rel[3], int32_t gcell) {
+    const int x = L.dex == 1 ? 0 : rel[0] + DEST_HALO, y = L.dey == 1 ? 0 : rel[1] + DEST_HALO;
+    const int z = L.dez == 1 ? 0 : rel[2] + DEST_HALO;
+    if ((unsigned)x < (unsigned)L.dex && (unsigned)y < (unsigned)L.dey && (unsigned)z < (unsigned)L.dez) {
+        const int sl = x + L.dex * (y + L.dey * z);
         const int32_t r = atomicAdd(&slots[sl], 1);
         if (r < (1 << 20)) return (sl << 20) | r;
         atomicSub(&slots[sl], 1);  // past the word's range: counted below instead
@@ -337,8 +336,7 @@ __device__ __forceinline__ int window_start(const TL& L, const Win<O>& W, int d)
 // What the particle step of one tile and species needs besides the arguments.
 struct TileCtx {
     int org[3];
-    int64_t base_cell;
-    int nxy;
+    uint32_t base_cell, nxy;  // of 32 bits as the particles' cell indices are
     const float* fld;
     unsigned long long* cur;
     int32_t* slots;
@@ -376,24 +374,30 @@ __device__ __forceinline__ void step_particle(const Gpd32Args& A, const Sp32& S,
     };
     // position inside the tile: rel = li + n0 lj + n0 n1 lk with l < t, found by
     // comparisons (no division)
-    int64_t rel = (int64_t)cell - C.base_cell;
+    uint32_t rel = (uint32_t)cell - C.base_cell;
     int lk = 0, lj = 0;
-    while (lk < L.tz - 1 && rel >= (int64_t)C.nxy) {
-        rel -= C.nxy;
-        ++lk;
-    }
-    while (lj < L.ty - 1 && rel >= (int64_t)n0) {
-        rel -= n0;
-        ++lj;
+    if constexpr (TL::fixed_shape) {
+#pragma unroll
+        for (int k = 1; k < TL::tz; ++k) lk += rel >= k * C.nxy ? 1 : 0;
+        rel -= lk * C.nxy;
+#pragma unroll
+        for (int k = 1; k < TL::ty; ++k) lj += rel >= (uint32_t)(k * n0) ? 1 : 0;
+        rel -= lj * n0;
+    } else {
+        while (lk < L.tz - 1 && rel >= C.nxy) {
+            rel -= C.nxy;
+            ++lk;
+        }
+        while (lj < L.ty - 1 && rel >= (uint32_t)n0) {
+            rel -= n0;
+            ++lj;
+        }
     }
     const int li = (int)rel;
     const int loc[3] = {li, lj, lk};
     const int* org = C.org;
-    // the particle must lie in this tile: local indices in range and the cell index
-    // rebuilt from them equal to the stored one
-    const bool inside = rel >= 0 && li < L.tx && org[0] + li < n0 && org[1] + lj < n1 && org[2] + lk < n2 &&
-                        (int64_t)(org[0] + li) + (int64_t)n0 * ((org[1] + lj) + (int64_t)n1 * (org[2] + lk)) ==
-                            (int64_t)cell;
+    // the particle must lie in this tile (the cell index rebuilt from li, lj and lk is the stored one)
+    const bool inside = rel < (uint32_t)L.tx && org[0] + li < n0 && org[1] + lj < n1 && org[2] + lk < n2;
     if (!inside) {  // not this tile's particle: left out of the next sort
         bad_all |= PP_FLAG_OUT_OF_TILE;
         keep(u);
@@ -403,7 +407,7 @@ __device__ __forceinline__ void step_particle(const Gpd32Args& A, const Sp32& S,
     if (!offset_ok<O>(f[0]) || !offset_ok<O>(f[1]) || !offset_ok<O>(f[2])) {  // left as it is
         bad_all |= PP_FLAG_OUT_OF_TILE;
         keep(u);
-        gl(S.rank)[q] = dest_rank(A, S, C.slots, loc, cell);
+        gl(S.rank)[q] = dest_rank<TL>(S, L, C.slots, loc, cell);
         return;
     }
 
@@ -451,7 +455,7 @@ __device__ __forceinline__ void step_particle(const Gpd32Args& A, const Sp32& S,
     if (bad) {  // left as it was before the push
         bad_all |= bad;
         keep(um);
-        gl(S.rank)[q] = dest_rank(A, S, C.slots, loc, cell);
+        gl(S.rank)[q] = dest_rank<TL>(S, L, C.slots, loc, cell);
         return;
     }
 
@@ -541,7 +545,7 @@ __device__ __forceinline__ void step_particle(const Gpd32Args& A, const Sp32& S,
     gl(S.u_o[1])[q] = u.y;
     gl(S.u_o[2])[q] = u.z;
     const int dst[3] = {li + shv[0], lj + shv[1], lk + shv[2]};
-    gl(S.rank)[q] = dest_rank(A, S, C.slots, dst, newcell);
+    gl(S.rank)[q] = dest_rank<TL>(S, L, C.slots, dst, newcell);
 }
 
 // Charge-conserving current of one particle (W1), or of two particles whose windows start at
@@ -639,9 +643,10 @@ __device__ __forceinline__ void deposit_cc(const TL& L, unsigned long long* cur,
 template <int O, class TL>
 __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, int s0, int s1, unsigned char* lds_raw) {
     const TL L(A);
-    const int ti = (int)(tile % A.nt[0]);
-    const int tj = (int)((tile / A.nt[0]) % A.nt[1]);
-    const int tk = (int)(tile / ((int64_t)A.nt[0] * A.nt[1]));
+    const uint32_t tile32 = (uint32_t)tile, row = tile32 / (uint32_t)A.nt[0];  // tiles are numbered in 32 bits
+    const int ti = (int)(tile32 - row * (uint32_t)A.nt[0]);
+    const int tk = (int)(row / (uint32_t)A.nt[1]);
+    const int tj = (int)(row - (uint32_t)tk * (uint32_t)A.nt[1]);
     const int org[3] = {ti * L.tx, tj * L.ty, tk * L.tz};
     const int n0 = A.n[0], n1 = A.n[1], n2 = A.n[2];
     const double qs = fixed_scale(A.scale);
@@ -650,45 +655,70 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, int
     float* fld = (float*)lds_raw;  // 6 * fvol
     unsigned long long* cur = (unsigned long long*)(lds_raw + ((6 * L.fvol * sizeof(float) + 15) & ~(size_t)15));
 
-    // 1. stage fields (each thread has STAGE_BATCH loads in flight before it waits for the
-    // first), clear the current block
-    for (int q0 = threadIdx.x; q0 < 6 * L.fvol; q0 += STAGE_BATCH * GPD32_BS) {
-        double v[STAGE_BATCH];
-        int dst[STAGE_BATCH];  // LDS entry, or -1 (past the end, or padding)
+    double* facq = (double*)(cur + 3 * L.cvol);
+    int32_t* slots = (int32_t*)(facq + 4);  // destination-cell counters
+    const int nslots = L.dex * L.dey * L.dez;
+    // Mesh offsets of the tile's nodes along each axis, counted from the lower end of the halo (the
+    // same for the fields, the current and the destination cells): for the compile-time shapes a
+    // table, one wrap per node of an axis instead of one per node in each of the three loops below
+    // (with a wrap and a division chain per node and component these loops took a tenth of the
+    // kernel's instructions at 32 particles per cell: 690 us against 636 for 128x32x32, two
+    // species; 40 against 32 for 16^3, quadratic; 11.60 ms against 11.21 for 128^3, 64 per cell).
+    // A runtime shape has no room for it in LDS where its tile was chosen to fill that.
+    int32_t* ox = slots + nslots;
+    if constexpr (TL::fixed_shape) {
+        for (int q = threadIdx.x; q < L.cex + L.cey + L.cez; q += GPD32_BS) {
+            const int y = q - L.cex, z = y - L.cey;
+            ox[q] = y < 0   ? wrap_near(org[0] - L.clox + q, n0)
+                    : z < 0 ? n0 * wrap_near(org[1] - L.cloy + y, n1)
+                            : n0 * n1 * wrap_near(org[2] - L.cloz + z, n2);
+        }
+        __syncthreads();
+    }
+    auto mesh = [&](int a, int b, int c) {
+        if constexpr (TL::fixed_shape)
+            return ox[a] + ox[L.cex + b] + ox[L.cex + L.cey + c];
+        else
+            return wrap_near(org[0] - L.clox + a, n0) +
+                   n0 * (wrap_near(org[1] - L.cloy + b, n1) + n1 * wrap_near(org[2] - L.cloz + c, n2));
+    };
+
+    // 1. stage fields, a thread per node and STAGE_NODES nodes' loads in flight before it waits for
+    // the first; clear the current block and the counters
+    const int fnodes = L.fex * L.fey * L.fez;
+    for (int q0 = threadIdx.x; q0 < fnodes; q0 += STAGE_NODES * GPD32_BS) {
+        double v[STAGE_NODES][6];
+        int dst[STAGE_NODES];  // LDS entry, or -1 (past the end)
 #pragma unroll
-        for (int k = 0; k < STAGE_BATCH; ++k) {
-            // every lane loads (an entry past the end or in the padding reads a node of the
-            // tile instead and writes nothing), so that no load waits at a branch
+        for (int k = 0; k < STAGE_NODES; ++k) {
+            // every lane loads (past the end: the first node, which it doesn't write), so that no
+            // load waits at a branch
             const int q = q0 + k * GPD32_BS;
-            const int qc = q < 6 * L.fvol ? q : 0;
-            const int comp = qc / L.fvol;
-            const int r = qc - comp * L.fvol;
-            const int c = r / L.fplane;
-            const int rr = r - c * L.fplane;
-            const int bb = rr / L.frow;
-            const int a = rr - bb * L.frow;
-            dst[k] = (q < 6 * L.fvol && a < L.fex && bb < L.fey) ? q : -1;
-            const int gi = wrap_near(org[0] - L.flox + (a < L.fex ? a : 0), n0);
-            const int gj = wrap_near(org[1] - L.floy + (bb < L.fey ? bb : 0), n1);
-            const int gk = wrap_near(org[2] - L.floz + c, n2);
-            const int64_t gq = (int64_t)gi + (int64_t)n0 * (gj + (int64_t)n1 * gk);
-            const double* src = comp < 3 ? A.E + comp * A.nc : A.B + (comp - 3) * A.nc;
-            v[k] = gl(src)[gq];
+            const int qc = q < fnodes ? q : 0;
+            const int row = qc / L.fex, a = qc - row * L.fex, c = row / L.fey, bb = row - c * L.fey;
+            dst[k] = q < fnodes ? a + L.frow * bb + L.fplane * c : -1;
+            const int g = mesh(a, bb, c);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) {
+                v[k][d] = gl(A.E)[d * A.nc + g];
+                v[k][3 + d] = gl(A.B)[d * A.nc + g];
+            }
         }
 #pragma unroll
-        for (int k = 0; k < STAGE_BATCH; ++k)
-            if (dst[k] >= 0) fld[dst[k]] = (float)v[k];
+        for (int k = 0; k < STAGE_NODES; ++k)
+            if (dst[k] >= 0) {
+#pragma unroll
+                for (int comp = 0; comp < 6; ++comp) fld[comp * L.fvol + dst[k]] = (float)v[k][comp];
+            }
     }
     for (int q = threadIdx.x; q < 3 * L.cvol; q += GPD32_BS) cur[q] = 0ull;
-    double* facq = (double*)(cur + 3 * L.cvol);
-    int32_t* slots = (int32_t*)(facq + 4);  // A.nslots destination-cell counters
-    for (int q = threadIdx.x; q < A.nslots; q += GPD32_BS) slots[q] = 0;
+    for (int q = threadIdx.x; q < nslots; q += GPD32_BS) slots[q] = 0;
     __syncthreads();
 
     TileCtx C;
     for (int d = 0; d < 3; ++d) C.org[d] = org[d];
-    C.base_cell = (int64_t)org[0] + (int64_t)n0 * (org[1] + (int64_t)n1 * org[2]);
-    C.nxy = n0 * n1;
+    C.nxy = (uint32_t)n0 * (uint32_t)n1;
+    C.base_cell = (uint32_t)org[0] + (uint32_t)n0 * (uint32_t)org[1] + C.nxy * (uint32_t)org[2];
     C.fld = fld;
     C.cur = cur;
     C.slots = slots;
@@ -746,49 +776,32 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, int
         // reserve the tile's range in each destination cell's count; the sort adds its start to
         // the particles' ranks
         __syncthreads();
-        for (int q = threadIdx.x; q < A.nslots; q += GPD32_BS) {
+        for (int q = threadIdx.x; q < nslots; q += GPD32_BS) {
             const int c = slots[q];
             slots[q] = 0;
             int first = 0;
             if (c != 0) {
-                const int x = q % A.sext[0], y = (q / A.sext[0]) % A.sext[1], z = q / (A.sext[0] * A.sext[1]);
-                const int gx = A.sext[0] == 1 ? 0 : wrap_near(org[0] + x - DEST_HALO, n0);
-                const int gy = A.sext[1] == 1 ? 0 : wrap_near(org[1] + y - DEST_HALO, n1);
-                const int gz = A.sext[2] == 1 ? 0 : wrap_near(org[2] + z - DEST_HALO, n2);
-                first = atomicAdd(gl(S.cnt) + (gx + n0 * (gy + n1 * gz)), c);
+                const int row = q / L.dex, x = q - row * L.dex, z = row / L.dey, y = row - z * L.dey;
+                first = atomicAdd(gl(S.cnt) + mesh(x, y, z), c);
             }
-            gl(S.base)[tile * A.nslots + q] = first;
+            gl(S.base)[tile * nslots + q] = first;
         }
         __syncthreads();
     }
     if (bad_all) atomic_or_flag(gl(A.flags), bad_all);
 
-    // 3. flush the current block (integer adds commute: the sum is order-independent); each
-    // thread reads STAGE_BATCH entries before it waits for the first
-    for (int q0 = threadIdx.x; q0 < 3 * L.cvol; q0 += STAGE_BATCH * GPD32_BS) {
-        unsigned long long raw[STAGE_BATCH];
+    // 3. flush the current block (integer adds commute: the sum is order-independent)
+    const int cnodes = L.cex * L.cey * L.cez;
+    for (int q = threadIdx.x; q < cnodes; q += GPD32_BS) {
+        const int row = q / L.cex, a = q - row * L.cex, c = row / L.cey, bb = row - c * L.cey;
+        const int l = a + L.crow * bb + L.cplane * c, g = mesh(a, bb, c);
+        unsigned long long raw[3];
 #pragma unroll
-        for (int k = 0; k < STAGE_BATCH; ++k) {
-            const int q = q0 + k * GPD32_BS;
-            raw[k] = q < 3 * L.cvol ? cur[q] : 0ull;
-        }
+        for (int comp = 0; comp < 3; ++comp) raw[comp] = cur[comp * L.cvol + l];
 #pragma unroll
-        for (int k = 0; k < STAGE_BATCH; ++k) {
-            const int q = q0 + k * GPD32_BS;
-            const long long v = fixed_sum(raw[k]);
-            if (v == 0) continue;  // also every entry past the end
-            const int comp = q / L.cvol;
-            const int r = q - comp * L.cvol;
-            const int c = r / L.cplane;
-            const int rr = r - c * L.cplane;
-            const int bb = rr / L.crow;
-            const int a = rr - bb * L.crow;
-            if (bb >= L.cey) continue;  // padding
-            const int gi = wrap_near(org[0] - L.clox + a, n0);
-            const int gj = wrap_near(org[1] - L.cloy + bb, n1);
-            const int gk = wrap_near(org[2] - L.cloz + c, n2);
-            atomicAdd(gl(A.Jq) + comp * A.nc + (int64_t)gi + (int64_t)n0 * (gj + (int64_t)n1 * gk),
-                      (unsigned long long)v);
+        for (int comp = 0; comp < 3; ++comp) {
+            const long long v = fixed_sum(raw[comp]);
+            if (v != 0) atomicAdd(gl(A.Jq) + comp * A.nc + g, (unsigned long long)v);
         }
     }
 }
@@ -880,7 +893,8 @@ size_t gpd32_lds_bytes(const pp_run* r) {
                       : kind == TILE_881_FLAT ? (size_t)cur_row_881 * ce[1]
                                               : (size_t)ce[0] * ce[1] * ce[2];
     const size_t slots = r->g.dest_slots();
-    return ((6 * fv * sizeof(float) + 15) & ~(size_t)15) + 3 * cv * sizeof(unsigned long long) + 4 * sizeof(double) + slots * sizeof(int32_t);
+    return ((6 * fv * sizeof(float) + 15) & ~(size_t)15) + 3 * cv * sizeof(unsigned long long) + 4 * sizeof(double) +
+           (slots + (kind == TILE_RT ? 0 : ce[0] + ce[1] + ce[2])) * sizeof(int32_t);
 }
 
 // Host part of the fixed-point exponent: e0 = 50 - ceil(log2(max |fac|)), every contribution
@@ -959,7 +973,6 @@ void gpd32_fill_args(const pp_run* r, Gpd32Args* Ap) {
     A.per_xcd = (int)((r->g.ntiles + 7) / 8);
     A.direct = r->p.current_scheme == PP_CURRENT_DIRECT ? 1 : 0;
     for (int d = 0; d < 3; ++d) A.sext[d] = r->g.dest_ext(d);
-    A.nslots = r->g.dest_slots();
 }
 
 FixedScale gpd32_scale(const pp_run* r) { return FixedScale{r->tile_max, gpd32_scale_e0(r)}; }
