@@ -110,10 +110,15 @@ __device__ __forceinline__ long long fixed_sum(unsigned long long v) {
 constexpr int cur_row_444 = 12;
 constexpr int cur_plane_444(int O) { return O == 2 ? 112 : 128; }
 constexpr int cur_row_881 = 24;
-// Row and plane strides (floats) of the field tile of a 4x4x4 tile (cubic weights: padded
-// from 9 and 81, which measured a few per cent faster).
-constexpr int fld_row_444(int O) { return O == 3 ? 10 : O + 6; }
-constexpr int fld_plane_444(int O) { return O == 3 ? 90 : (O + 6) * (O + 6); }
+// Row and plane strides (floats) of the field tile of a 4x4x4 tile.  The gather reads two
+// neighbouring floats per lane, half a wavefront at a time: the windows of 32 particles, one per
+// cell of two z layers and each up to a node off its cell, over 64 banks.  A row of 10 and planes
+// one short of nine (eight) such rows collide least of the strides near the extents 9 and 81 (8
+// and 64): 1.3 accesses a read for random offsets, against 1.6 with planes of 90 and 2.3 with 8
+// and 64.  Quadratic, 50x42x37: 471 -> 446 us; cubic, 128^3: 11.31 -> 11.25 ms.  A plane's last row
+// is not padded.
+constexpr int fld_row_444 = 10;
+constexpr int fld_plane_444(int O) { return O == 3 ? 89 : 79; }
 
 // LDS layout of a tile: compile-time for the common shapes, runtime otherwise.  A
 // single-cell axis is collapsed (extent 1, stride 0): every node offset maps to plane 0.
@@ -131,7 +136,7 @@ struct TileCT {
     // destination cells: the tile and DEST_HALO around it
     static constexpr int dex = TX + 2 * DEST_HALO, dey = TY + 2 * DEST_HALO, dez = CZ ? 1 : TZ + 2 * DEST_HALO;
     static constexpr bool f444 = TX == 4 && TY == 4 && TZ == 4 && !CZ;
-    static constexpr int frow = f444 ? fld_row_444(O) : fex;
+    static constexpr int frow = f444 ? fld_row_444 : fex;
     static constexpr int fplane = f444 ? fld_plane_444(O) : frow * fey;
     static constexpr int fsx = 1, fsy = frow, fsz = CZ ? 0 : fplane;
     static constexpr bool t444 = TX == 4 && TY == 4 && TZ == 4 && !CZ;
@@ -141,7 +146,7 @@ struct TileCT {
     static_assert(crow >= cex, "current row padding");
     static_assert(cplane >= crow * cey, "current plane padding");
     static constexpr int csx = 1, csy = crow, csz = CZ ? 0 : cplane;
-    static_assert(frow >= fex && fplane >= frow * fey, "field tile padding");
+    static_assert(frow >= fex && fplane >= frow * (fey - 1) + fex, "field tile padding");
     static constexpr int fvol = fplane * fez, cvol = cplane * cez;
     // two particles per lane (the paired deposit) on cubic tiles; flat tiles keep one per
     // lane, whose smaller register set leaves room for more resident wavefronts
