@@ -89,7 +89,7 @@ struct Gpd32Args {
     int direct;   // PP_CURRENT_DIRECT: eq. "jj2" instead of the Esirkepov current
 };
 
-constexpr int GPD32_BS = 256;
+constexpr int GPD32_BS = 256;  // threads of a workgroup (small boxes take more, see launch_tiles32)
 constexpr int STAGE_NODES = 3;  // nodes whose fields a thread loads before the first wait
 constexpr double ROUND_MAGIC = 6755399441055744.0;  // 1.5 * 2^52
 constexpr unsigned long long LOW51 = (1ull << 51) - 1ull;
@@ -123,7 +123,7 @@ constexpr int fld_plane_444(int O) { return O == 3 ? 89 : 79; }
 // LDS layout of a tile: compile-time for the common shapes, runtime otherwise.  A
 // single-cell axis is collapsed (extent 1, stride 0): every node offset maps to plane 0.
 // The current block is indexed x + crow*y + cplane*z (padding entries stay zero).
-template <int O, int TX, int TY, int TZ, bool CZ>
+template <int O, int TX, int TY, int TZ, bool CZ, bool PAIRS>
 struct TileCT {
     static constexpr bool fixed_shape = true;
     static constexpr int tx = TX, ty = TY, tz = TZ;
@@ -150,10 +150,15 @@ struct TileCT {
     static constexpr int fvol = fplane * fez, cvol = cplane * cez;
     // two particles per lane (the paired deposit) on cubic tiles; flat tiles keep one per
     // lane, whose smaller register set leaves room for more resident wavefronts
-    static constexpr bool pairs = t444;
+    static constexpr bool pairs = PAIRS;
     static constexpr bool flat = CZ;  // one field plane: the gather's z taps read the same nodes
     __device__ TileCT(const Gpd32Args&) {}
 };
+
+template <int O, bool PAIRS>
+using Tile444 = TileCT<O, 4, 4, 4, false, PAIRS>;
+template <int O>
+using Tile881 = TileCT<O, 8, 8, 1, true, false>;
 
 struct TileRT {
     static constexpr bool fixed_shape = false;
@@ -643,9 +648,9 @@ __device__ __forceinline__ void deposit_cc(const TL& L, unsigned long long* cur,
 // not expect; such pairs deposit together with one atomic per node for both.  Where some
 // lane's pair does not share a window, that lane's second particle deposits alone in a second
 // pass; where no lane's does (the single particles after the chunks), each particle deposits
-// alone.  Flat (8x8x1) and runtime-shaped tiles take one particle per lane and slot (64
-// consecutive slots per wavefront).
-template <int O, class TL>
+// alone.  Flat (8x8x1) and runtime-shaped tiles and small boxes take one particle per lane and slot
+// (64 consecutive slots per wavefront).
+template <int O, class TL, int BS>
 __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, int s0, int s1, unsigned char* lds_raw) {
     const TL L(A);
     const uint32_t tile32 = (uint32_t)tile, row = tile32 / (uint32_t)A.nt[0];  // tiles are numbered in 32 bits
@@ -668,11 +673,11 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, int
     // table, one wrap per node of an axis instead of one per node in each of the three loops below
     // (with a wrap and a division chain per node and component these loops took a tenth of the
     // kernel's instructions at 32 particles per cell: 690 us against 636 for 128x32x32, two
-    // species; 40 against 32 for 16^3, quadratic; 11.60 ms against 11.21 for 128^3, 64 per cell).
+    // species; 40 against 32 for 16^3, quadratic, in 256 threads; 11.60 ms against 11.21 for 128^3, 64 per cell).
     // A runtime shape has no room for it in LDS where its tile was chosen to fill that.
     int32_t* ox = slots + nslots;
     if constexpr (TL::fixed_shape) {
-        for (int q = threadIdx.x; q < L.cex + L.cey + L.cez; q += GPD32_BS) {
+        for (int q = threadIdx.x; q < L.cex + L.cey + L.cez; q += BS) {
             const int y = q - L.cex, z = y - L.cey;
             ox[q] = y < 0   ? wrap_near(org[0] - L.clox + q, n0)
                     : z < 0 ? n0 * wrap_near(org[1] - L.cloy + y, n1)
@@ -691,14 +696,14 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, int
     // 1. stage fields, a thread per node and STAGE_NODES nodes' loads in flight before it waits for
     // the first; clear the current block and the counters
     const int fnodes = L.fex * L.fey * L.fez;
-    for (int q0 = threadIdx.x; q0 < fnodes; q0 += STAGE_NODES * GPD32_BS) {
+    for (int q0 = threadIdx.x; q0 < fnodes; q0 += STAGE_NODES * BS) {
         double v[STAGE_NODES][6];
         int dst[STAGE_NODES];  // LDS entry, or -1 (past the end)
 #pragma unroll
         for (int k = 0; k < STAGE_NODES; ++k) {
             // every lane loads (past the end: the first node, which it doesn't write), so that no
             // load waits at a branch
-            const int q = q0 + k * GPD32_BS;
+            const int q = q0 + k * BS;
             const int qc = q < fnodes ? q : 0;
             const int row = qc / L.fex, a = qc - row * L.fex, c = row / L.fey, bb = row - c * L.fey;
             dst[k] = q < fnodes ? a + L.frow * bb + L.fplane * c : -1;
@@ -716,8 +721,8 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, int
                 for (int comp = 0; comp < 6; ++comp) fld[comp * L.fvol + dst[k]] = (float)v[k][comp];
             }
     }
-    for (int q = threadIdx.x; q < 3 * L.cvol; q += GPD32_BS) cur[q] = 0ull;
-    for (int q = threadIdx.x; q < nslots; q += GPD32_BS) slots[q] = 0;
+    for (int q = threadIdx.x; q < 3 * L.cvol; q += BS) cur[q] = 0ull;
+    for (int q = threadIdx.x; q < nslots; q += BS) slots[q] = 0;
     __syncthreads();
 
     TileCtx C;
@@ -739,13 +744,13 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, int
         if (threadIdx.x < 4) facq[threadIdx.x] = (threadIdx.x < 3 ? S.fac[threadIdx.x] : S.qw) * qs;
         __syncthreads();
         if constexpr (!TL::pairs) {
-            for (int32_t q = start + threadIdx.x; q < end; q += GPD32_BS) {
+            for (int32_t q = start + threadIdx.x; q < end; q += BS) {
                 Win<O> W;
                 step_particle<O, TL>(A, S, L, C, q, W, bad_all);
                 if (W.dep) deposit_cc<O, TL, false>(L, cur, W, C.facq, W, C.facq, 0.0f);
             }
         } else {
-            for (int32_t b = start + 128 * wave; b < end; b += 4 * 128) {
+            for (int32_t b = start + 128 * wave; b < end; b += BS * 2) {
                 Win<O> W1, W2;
                 const int32_t q1 = b + lane, q2 = b + 64 + lane;
                 W1.dep = W2.dep = false;
@@ -781,7 +786,7 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, int
         // reserve the tile's range in each destination cell's count; the sort adds its start to
         // the particles' ranks
         __syncthreads();
-        for (int q = threadIdx.x; q < nslots; q += GPD32_BS) {
+        for (int q = threadIdx.x; q < nslots; q += BS) {
             const int c = slots[q];
             slots[q] = 0;
             int first = 0;
@@ -797,7 +802,7 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, int
 
     // 3. flush the current block (integer adds commute: the sum is order-independent)
     const int cnodes = L.cex * L.cey * L.cez;
-    for (int q = threadIdx.x; q < cnodes; q += GPD32_BS) {
+    for (int q = threadIdx.x; q < cnodes; q += BS) {
         const int row = q / L.cex, a = q - row * L.cex, c = row / L.cey, bb = row - c * L.cey;
         const int l = a + L.crow * bb + L.cplane * c, g = mesh(a, bb, c);
         unsigned long long raw[3];
@@ -811,8 +816,8 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, int
     }
 }
 
-template <int O, class TL>
-__global__ void __launch_bounds__(GPD32_BS, TL::pairs ? 3 : 1) k_gpd32(Gpd32Args A) {
+template <int O, class TL, int BS>
+__global__ void __launch_bounds__(BS, TL::pairs ? 3 : 1) k_gpd32(Gpd32Args A) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     // XCD-aware tile order: consecutive workgroups go round-robin over the 8 XCDs, so give
     // each XCD a contiguous run of tiles (neighbouring tiles share halos in that XCD's L2).
@@ -821,7 +826,7 @@ __global__ void __launch_bounds__(GPD32_BS, TL::pairs ? 3 : 1) k_gpd32(Gpd32Args
     if (tile >= A.ntiles) return;
     // a small box has a workgroup per tile and species (the current's integer sum is the same)
     const int s0 = gridDim.y > 1 ? (int)blockIdx.y : 0, s1 = gridDim.y > 1 ? s0 + 1 : A.nsp;
-    gpd32_tile<O, TL>(A, tile, s0, s1, lds_raw);
+    gpd32_tile<O, TL, BS>(A, tile, s0, s1, lds_raw);
 }
 
 // Batched: block b of the launch belongs to run r with prefix[r] <= b (prefix = running block counts).
@@ -836,7 +841,7 @@ __global__ void __launch_bounds__(GPD32_BS, TL::pairs ? 3 : 1) k_gpd32_batch(con
     // eights, so the XCD is the same b & 7)
     const int64_t lb = b - prefix[r], tile = (lb & 7) * (int64_t)table[r].per_xcd + (lb >> 3);
     if (tile >= table[r].ntiles) return;
-    gpd32_tile<O, TL>(table[r], tile, 0, table[r].nsp, lds_raw);
+    gpd32_tile<O, TL, GPD32_BS>(table[r], tile, 0, table[r].nsp, lds_raw);
 }
 
 // Fixed-point current of a run to FP64, clearing the accumulator for the next step (runs without
@@ -1003,31 +1008,39 @@ static unsigned fixed_grid(int64_t n3) {
     return (unsigned)(g < 1 ? 1 : g);
 }
 
+// With three workgroups a CU (of 256), a species of its own each halves the time of two species as
+// long as all are resident at once (768); beyond that it only stages the fields twice.
+// A box of fewer workgroups than that leaves wavefronts' places idle, and its time is the chain one
+// wavefront goes through: staging, its particles, flushing.  Larger workgroups that give a lane one
+// particle at a time (no pairs, 100 registers) shorten each part of it, with twice the atomics, which
+// the idle LDS has room for: 1024 threads up to a workgroup a CU, 512 up to two.  Two species,
+// time of pairs in 256 threads -> this: 16^3, 8 per cell, quadratic 33 -> 22.5 us, cubic 46 -> 32;
+// 16^3, 32 per cell 109 -> 72 (512 threads: 74); 24^3 (432 workgroups), 32 per cell 136 -> 129;
+// 28^3 (686) would take 201 us in 512 threads against 181, which keeps it with the pairs.
+template <int O>
+static void launch_tiles32(int kind, const Gpd32Args& A, size_t lds, hipStream_t st) {
+    const int64_t wgs = A.ntiles * A.nsp;
+    const dim3 grid((unsigned)(8 * (int64_t)A.per_xcd), wgs <= 768 && A.nsp > 0 ? (unsigned)A.nsp : 1u);
+    if (kind == TILE_444 && wgs <= 256)
+        hipLaunchKernelGGL((k_gpd32<O, Tile444<O, false>, 1024>), grid, dim3(1024), lds, st, A);
+    else if (kind == TILE_444 && wgs <= 512)
+        hipLaunchKernelGGL((k_gpd32<O, Tile444<O, false>, 512>), grid, dim3(512), lds, st, A);
+    else if (kind == TILE_444)
+        hipLaunchKernelGGL((k_gpd32<O, Tile444<O, true>, GPD32_BS>), grid, dim3(GPD32_BS), lds, st, A);
+    else if (kind == TILE_881_FLAT)
+        hipLaunchKernelGGL((k_gpd32<O, Tile881<O>, GPD32_BS>), grid, dim3(GPD32_BS), lds, st, A);
+    else
+        hipLaunchKernelGGL((k_gpd32<O, TileRT, GPD32_BS>), grid, dim3(GPD32_BS), lds, st, A);
+}
+
 hipError_t launch_gpd32(pp_run* r) {
     Gpd32Args A;
     gpd32_fill_args(r, &A);
     const size_t lds = gpd32_lds_bytes(r);
-    // with three workgroups a CU (of 256), a species of its own each halves the time of two
-    // species as long as all are resident at once (16^3, quadratic, 2 x 3.3e4 particles: 36 us
-    // against 58); beyond that it only stages the fields twice
-    const unsigned split = A.ntiles * A.nsp <= 768 ? (unsigned)(A.nsp > 0 ? A.nsp : 1) : 1u;
-    const dim3 grid((unsigned)(8 * (int64_t)A.per_xcd), split);
-    const int kind = tile_kind(r);
-    if (r->p.shape_order == 2) {
-        if (kind == TILE_444)
-            hipLaunchKernelGGL((k_gpd32<2, TileCT<2, 4, 4, 4, false>>), grid, dim3(GPD32_BS), lds, r->stream, A);
-        else if (kind == TILE_881_FLAT)
-            hipLaunchKernelGGL((k_gpd32<2, TileCT<2, 8, 8, 1, true>>), grid, dim3(GPD32_BS), lds, r->stream, A);
-        else
-            hipLaunchKernelGGL((k_gpd32<2, TileRT>), grid, dim3(GPD32_BS), lds, r->stream, A);
-    } else {
-        if (kind == TILE_444)
-            hipLaunchKernelGGL((k_gpd32<3, TileCT<3, 4, 4, 4, false>>), grid, dim3(GPD32_BS), lds, r->stream, A);
-        else if (kind == TILE_881_FLAT)
-            hipLaunchKernelGGL((k_gpd32<3, TileCT<3, 8, 8, 1, true>>), grid, dim3(GPD32_BS), lds, r->stream, A);
-        else
-            hipLaunchKernelGGL((k_gpd32<3, TileRT>), grid, dim3(GPD32_BS), lds, r->stream, A);
-    }
+    if (r->p.shape_order == 2)
+        launch_tiles32<2>(tile_kind(r), A, lds, r->stream);
+    else
+        launch_tiles32<3>(tile_kind(r), A, lds, r->stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (!line_reads_fixed(r)) {
@@ -1046,10 +1059,10 @@ hipError_t launch_gpd32_batch(const void* args_table, const int64_t* tile_prefix
     if (n == 0) return hipSuccess;
     const Gpd32Args* T = (const Gpd32Args*)args_table;
     if (shape_order == 2)
-        hipLaunchKernelGGL((k_gpd32_batch<2, TileCT<2, 4, 4, 4, false>>), dim3((unsigned)total_blocks), dim3(GPD32_BS),
+        hipLaunchKernelGGL((k_gpd32_batch<2, Tile444<2, true>>), dim3((unsigned)total_blocks), dim3(GPD32_BS),
                            lds, st, T, tile_prefix, n);
     else
-        hipLaunchKernelGGL((k_gpd32_batch<3, TileCT<3, 4, 4, 4, false>>), dim3((unsigned)total_blocks), dim3(GPD32_BS),
+        hipLaunchKernelGGL((k_gpd32_batch<3, Tile444<3, true>>), dim3((unsigned)total_blocks), dim3(GPD32_BS),
                            lds, st, T, tile_prefix, n);
     if (total_fixed_blocks > 0)
         hipLaunchKernelGGL(k_fixed_batch, dim3((unsigned)total_fixed_blocks), dim3(256), 0, st,

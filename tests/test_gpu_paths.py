@@ -156,3 +156,40 @@ def test_fp64_sort_orders(ppm, orc, n, O):
             assert np.max(np.abs(periodic_diff(a["pos"], b["pos"], n))) < 1e-12
             assert np.array_equal(np.isnan(a["u"]), np.isnan(b["u"]))
             assert np.nanmax(np.abs(a["u"] - b["u"])) < 1e-12
+
+
+@pytest.mark.parametrize("n,O", [((9, 10, 7), 3), ((13, 4, 16), 2), ((24, 23, 24), 3), ((22, 24, 21), 2), ((28, 26, 27), 3)])
+def test_split_push_for_every_box_size_equals_batched(ppm, orc, n, O):
+    """Boxes of up to 256, 512 and 768 tiles and species take workgroups of different sizes, a batch
+    always the paired ones: the same particles and exact sums, so bit for bit the same."""
+    import torch
+    from paper_1211_4575_amd import inputs as I
+    species, E, B = random_state(orc, n, 3, seed=12, uth=0.4)
+    many = 0.4 * np.array(n)[:, None] + np.random.default_rng(1).uniform(0, 0.3, (3, 1300))
+    split = []
+    for s in species:
+        cell, off = I.to_split(np.concatenate([s["pos"], many], 1), n, origin=I.split_origin(O))
+        u = np.concatenate([s["u"], np.full((3, 1300), 0.1)], 1).astype(np.float32)
+        split.append(dict(q=s["q"], m=s["m"], w=s["w"], cell=cell, off=off, u=u))
+    kw = dict(n=n, dt=0.35, shape_order=O, field_order=4, relax_max_iter=100, precision=ppm.PP_PREC_FP32_SPLIT)
+    out = []
+    for batched in (False, True):
+        run = ppm.Run(ppm.make_params(**kw), split, E=E, B=B)
+        if batched:
+            batch = ppm.pp_batch_create(1, torch.cuda.current_stream().cuda_stream)
+            ppm.pp_batch_add(batch, run.handle)
+            for _ in range(4):
+                ppm.pp_batch_step(batch)
+            ppm.pp_batch_remove(batch, run.handle)
+            ppm.pp_batch_destroy(batch)
+        else:
+            for _ in range(4):
+                run.step()
+        assert run.diagnostics().flags == 0
+        out.append((run.fields(), [_by_id(run.particles(s)) for s in range(2)]))
+        run.close()
+    (f1, p1), (f2, p2) = out
+    for a, b in zip(f1, f2):
+        assert np.array_equal(a, b)
+    for a, b in zip(p1, p2):
+        assert all(np.array_equal(a[k], b[k]) for k in a)
