@@ -252,7 +252,8 @@ struct Gpd64TileArgs {
     int t[3], tsh[3], nt[3];  // sides (powers of two) and their logarithms, tiles
     int64_t ntiles;
     int per_xcd;
-    int parts;  // workgroups sharing a tile's particles
+    int parts;  // workgroups sharing a tile's particles of a species
+    int split;  // nsp: a workgroup per species; 1: all of them in one
     int sext[3];  // destination-cell window per axis
     int nsp;
     const int32_t* bins[PP_MAX_SPECIES];  // cell-bin starts of the sort (64 per tile)
@@ -517,8 +518,9 @@ __global__ void __launch_bounds__(GPD64_BS, 3) k_gpd64_tile(Gpd64TileArgs A) {
     for (int s = s0; s < s1; ++s) any |= A.bins[s][(tile + 1) * TILE_CELLS] - A.bins[s][tile * TILE_CELLS];
     if (any == 0) return;
     const Gpd64Args& G = A.sp[0];
-    const int org[3] = {(int)(tile % A.nt[0]) * A.t[0], (int)((tile / A.nt[0]) % A.nt[1]) * A.t[1],
-                        (int)(tile / ((int64_t)A.nt[0] * A.nt[1])) * A.t[2]};
+    const uint32_t row = (uint32_t)tile / (uint32_t)A.nt[0], layer = row / (uint32_t)A.nt[1];  // numbered in 32 bits
+    const int org[3] = {(int)((uint32_t)tile - row * (uint32_t)A.nt[0]) * A.t[0],
+                        (int)(row - layer * (uint32_t)A.nt[1]) * A.t[1], (int)layer * A.t[2]};
     double* fld = lds64;
     double* cur = lds64 + 6 * L.fvol;
     const int se[3] = {A.sext[0], A.sext[1], A.sext[2]};
@@ -602,15 +604,17 @@ __global__ void __launch_bounds__(GPD64_BS, 3) k_gpd64_tile(Gpd64TileArgs A) {
         for (int q = threadIdx.x; q < nslots; q += GPD64_BS) *L.slot(cur, q) = 0;
         __syncthreads();
     }
-    for (int q = threadIdx.x; q < 3 * L.cvol; q += GPD64_BS) {
-        const int comp = q / L.cvol, r0 = q - comp * L.cvol;
-        const int c = r0 / L.cplane, r = r0 - c * L.cplane, b = r / L.crow, a = r - b * L.crow;
-        const double v = cur[q];
-        if (a >= L.cex || v == 0.0) continue;  // padding, or nothing
+    for (int q = threadIdx.x; q < L.cvol; q += GPD64_BS) {  // by node: its place in the mesh serves three components
+        const int c = q / L.cplane, r = q - c * L.cplane, b = r / L.crow, a = r - b * L.crow;
+        if (a >= L.cex) continue;  // padding
+        const double v[3] = {cur[q], cur[L.cvol + q], cur[2 * L.cvol + q]};
         const int i = G.n[0] == 1 ? 0 : wrap_near(org[0] - F64_LO - 1 + a, G.n[0]);
         const int j = G.n[1] == 1 ? 0 : wrap_near(org[1] - F64_LO - 1 + b, G.n[1]);
         const int k = G.n[2] == 1 ? 0 : wrap_near(org[2] - F64_LO - 1 + c, G.n[2]);
-        atomic_add_f64(G.J + comp * G.ncell + (int64_t)i + (int64_t)G.n[0] * (j + (int64_t)G.n[1] * k), v);
+        double* J = G.J + (int64_t)i + (int64_t)G.n[0] * (j + (int64_t)G.n[1] * k);
+#pragma unroll
+        for (int comp = 0; comp < 3; ++comp)
+            if (v[comp] != 0.0) atomic_add_f64(J + comp * G.ncell, v[comp]);
     }
 }
 
@@ -662,9 +666,8 @@ hipError_t launch_gpd64(pp_run* r, int s, double* J) {
 
 template <int O, class TL>
 static void launch_tile(const Gpd64TileArgs& A, size_t lds, hipStream_t st) {
-    const unsigned split = A.ntiles * A.parts * A.nsp <= 768 ? (unsigned)A.nsp : 1u;  // all resident at once: 31 us against 50 (16^3)
-    hipLaunchKernelGGL((k_gpd64_tile<O, TL>), dim3((unsigned)(8 * A.per_xcd), (unsigned)A.parts, split), dim3(GPD64_BS),
-                       lds, st, A);
+    hipLaunchKernelGGL((k_gpd64_tile<O, TL>), dim3((unsigned)(8 * A.per_xcd), (unsigned)A.parts, (unsigned)A.split),
+                       dim3(GPD64_BS), lds, st, A);
 }
 
 // LDS bytes of a tile of the runtime-shaped kernel.
@@ -694,6 +697,28 @@ static hipError_t launch_tiles(pp_run* r, const Gpd64TileArgs& A) {
     return hipGetLastError();
 }
 
+// How the particles of np are shared out.  256 CUs hold three workgroups each.
+// Few tiles: a workgroup per tile, species and part of its particles, as many parts as are resident
+// at once (768 workgroups; two parts also a little beyond it) with a wavefront's worth of particles
+// each.  Two species, cubic, time with parts of at least 256 particles and, past 768, no split by
+// species -> this: 8^3, 8 per cell 47 -> 34 us; 16^3, 8 per cell 47 -> 43; 64x64 flat, 20 per cell
+// 39 -> 32; 24^3, 16 per cell 194 -> 163.
+// Many tiles: all species of a tile in one workgroup, which stages the fields once, unless that
+// leaves the last round of workgroups mostly empty: 45x38x29 (960 tiles, 768 and 192) 393 -> 352 us
+// with a workgroup per species, but 32^3 (512, two a CU) 184 -> 202.
+static void plan_workgroups(Gpd64TileArgs& A, int64_t np) {
+    const int64_t units = A.ntiles * A.nsp;
+    A.parts = 1;
+    A.split = A.nsp;
+    if (units <= 512) {
+        A.parts = units > 384 ? 2 : (int)(768 / units < 8 ? 768 / units : 8);
+        while (A.parts > 1 && np < units * A.parts * 64) --A.parts;
+        return;
+    }
+    const int64_t slots = A.ntiles <= 768 ? 256 : 768, filled = (A.ntiles + slots - 1) / slots * slots;
+    if (A.ntiles > 2 * 768 || 10 * A.ntiles >= 9 * filled) A.split = 1;
+}
+
 // All species whose particles lie as the sort left them, in one launch; *done has a bit for each
 // (the others take launch_gpd64).
 hipError_t launch_gpd64_tiles(pp_run* r, double* J, unsigned* done) {
@@ -719,10 +744,7 @@ hipError_t launch_gpd64_tiles(pp_run* r, double* J, unsigned* done) {
     }
     A.ntiles = r->g.ntiles;
     A.per_xcd = (int)((A.ntiles + 7) / 8);
-    // few tiles leave most of the 256 CUs idle: share a tile's particles among workgroups, as
-    // long as each of its wavefronts has particles of its own
-    A.parts = 1;
-    while (A.parts < 8 && A.ntiles * A.parts < 512 && np > A.ntiles * A.parts * 2 * GPD64_BS) A.parts *= 2;
+    plan_workgroups(A, np);
     return r->p.shape_order == 2 ? launch_tiles<2>(r, A) : launch_tiles<3>(r, A);
 }
 
