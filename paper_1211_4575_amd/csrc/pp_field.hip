@@ -166,8 +166,8 @@ __global__ void __launch_bounds__(FIELD_BS) k_field(FieldDesc D, int phase) {
 // cannot do without) and by latency in small ones, where short marches (D.zc, down to one plane
 // with every load in flight at once) spread it over the GPU.  Tiles of 64x8, 32x16, 64x4 and 64x16
 // took 0 to 14 % longer.  Whole field step, us, with each tap of the boxes below 1024 columns read
-// through the caches and now: 256^3 5750 and 4890, 128^3 1520 and 629, 128x32x32 260 and 99,
-// 512x256x1 243 and 108, 64x32x32 222 and 70.
+// through the caches and now: 256^3 5750 and 4800, 128^3 1520 and 608, 128x32x32 260 and 98,
+// 512x256x1 243 and 107, 64x32x32 222 and 70.
 constexpr int RX_TX = 32, RX_TY = 8, RX_ZC = 32;
 constexpr int RX_BS = RX_TX * RX_TY;  // one thread per column of the tile
 
@@ -537,12 +537,28 @@ __device__ __forceinline__ void field_tile(const FieldDesc& D, int b, int k, dou
     }
 }
 
+// The launch order of a phase's blocks.  A sweep's blocks side by side on an XCD share the planes
+// around them in its L2 (128^3: 47 us against 59).  In the other two phases a field is read for two
+// components: in boxes large enough for marches (zc > 1) a tile's three blocks are launched one
+// after the other on an XCD, which takes the tiles of a contiguous eighth of the box (E update
+// 256^3 603 -> 503 us, 128^3 72 -> 64; right-hand side 128^3 107 -> 103 and 256^3 the same; the
+// contiguous eighths without a tile's components together take 256^3 from 0.97 to 1.07 ms).
+// Smaller boxes gain nothing from it (128x32x32: 97.5 us a step, 98.7 with it).
+__host__ __device__ __forceinline__ bool components_together(int kind, int zc) { return kind != FK_RELAX && zc > 1; }
+
+// Four workgroups a CU for the right-hand side, at 125 registers instead of 137 and three (256^3:
+// 797 -> 779 us, 128^3 107 -> 103).
 template <int M, int KIND>
-__global__ void __launch_bounds__(RX_BS) k_field_tiles(FieldDesc D, int k, int blocks) {
+__global__ void __launch_bounds__(RX_BS, KIND == FK_RHS ? 4 : 1) k_field_tiles(FieldDesc D, int k, int blocks) {
     __shared__ double lds[field_lds<M>(KIND)];
-    // a sweep's blocks side by side on an XCD share the planes around them in its L2 (128^3: 47 us
-    // against 59); the other two phases are slower that way in large boxes (256^3: 1.07 against 0.97)
-    const int b = KIND == FK_RELAX ? (int)xcd_block(blockIdx.x, blocks) : (int)blockIdx.x;
+    int b = (int)blockIdx.x;
+    if (KIND == FK_RELAX) {
+        b = (int)xcd_block(blockIdx.x, blocks);
+    } else if (components_together(KIND, D.zc)) {
+        const int tiles = blocks / 3, comp = (b >> 3) % 3;
+        const int t = (int)xcd_block((b & 7) + 8 * (int64_t)(b / 24), tiles);
+        b = t >= 0 ? comp * tiles + t : -1;
+    }
     if (b >= 0) field_tile<M, KIND>(D, b, k, lds);
 }
 
@@ -634,12 +650,15 @@ static void launch_relax_small(const FieldDesc& D, hipStream_t st) {
 
 template <int KIND>
 static void launch_field_tiles(const FieldDesc& D, unsigned blocks, int k, hipStream_t st) {
+    const dim3 grid(KIND == FK_RELAX                      ? xcd_grid(blocks)
+                    : components_together(KIND, D.zc) ? 3 * xcd_grid(blocks / 3)
+                                                          : blocks);
     if (D.G.M == 3)
-        hipLaunchKernelGGL((k_field_tiles<3, KIND>), dim3(KIND == FK_RELAX ? xcd_grid(blocks) : blocks), dim3(RX_BS), 0, st, D, k, (int)blocks);
+        hipLaunchKernelGGL((k_field_tiles<3, KIND>), grid, dim3(RX_BS), 0, st, D, k, (int)blocks);
     else if (D.G.M == 2)
-        hipLaunchKernelGGL((k_field_tiles<2, KIND>), dim3(KIND == FK_RELAX ? xcd_grid(blocks) : blocks), dim3(RX_BS), 0, st, D, k, (int)blocks);
+        hipLaunchKernelGGL((k_field_tiles<2, KIND>), grid, dim3(RX_BS), 0, st, D, k, (int)blocks);
     else
-        hipLaunchKernelGGL((k_field_tiles<1, KIND>), dim3(KIND == FK_RELAX ? xcd_grid(blocks) : blocks), dim3(RX_BS), 0, st, D, k, (int)blocks);
+        hipLaunchKernelGGL((k_field_tiles<1, KIND>), grid, dim3(RX_BS), 0, st, D, k, (int)blocks);
 }
 
 // Planes per block: as many as leave the launch about 8 blocks per CU (its share of them in a

@@ -193,3 +193,19 @@ def test_split_push_for_every_box_size_equals_batched(ppm, orc, n, O):
         assert np.array_equal(a, b)
     for a, b in zip(p1, p2):
         assert all(np.array_equal(a[k], b[k]) for k in a)
+
+
+@pytest.mark.parametrize("n,order", [((33, 9, 350), 6), ((70, 17, 180), 4), ((32, 8, 1400), 2)])
+def test_field_step_of_boxes_marched_in_planes(ppm, orc, n, order):
+    """The field step where a block takes several planes, with numbers of tiles that the XCDs do not
+    divide evenly.  Both sides relax to 1e-14, in FP64: 1e-12 of the largest value."""
+    _, E, B = random_state(orc, n, 1, seed=19)
+    kw = dict(n=n, dt=0.3, shape_order=3, field_order=order, relax_tol=1e-14, relax_max_iter=200)
+    ref = orc.Run(orc.make_params(**kw), [], E=E, B=B)
+    run = ppm.Run(ppm.make_params(precision=ppm.PP_PREC_FP64, **kw), [], E=E, B=B)
+    for _ in range(2):
+        ref.step()
+        run.field_step()
+    Eg, Bg, _ = run.fields()
+    assert rel_inf(Eg, ref.E) < 1e-12 and rel_inf(Bg, ref.B) < 1e-12
+    run.close()
