@@ -405,8 +405,8 @@ __global__ void __launch_bounds__(256) k_tile_reorder(ReorderArgs<T> A) {
 // permutation's bytes: a rank word read and an entry written per particle, the entries of
 // particles that change tile one by one into partial lines.  us per step, before (five to seven
 // launches a species, cell and completed rank read back, a cleared permutation) and now: 2 x
-// 4.2e6 particles in 128x32x32, 170 and 68; 2 x 6.7e7 in 128^3, 1120 and 790; 2 x 3.3e4 in 16^3,
-// 46 and 16.
+// 4.2e6 particles in 128x32x32, 170 and 55; 2 x 6.7e7 in 128^3, 1120 and 700; 2 x 3.3e4 in 16^3,
+// 46 and 15.
 
 struct RankedArgs {
     Geom G;
@@ -559,7 +559,7 @@ __device__ __forceinline__ void ranked_scan(const RankedArgs& A) {
 struct DestCell {
     int32_t tile_lc;  // tile << 6 | local cell
     int32_t d0, nd;
-    int32_t nchunk, rtot;
+    int32_t nchunk;
     int32_t base;
 };
 
@@ -573,7 +573,6 @@ __device__ __forceinline__ DestCell dest_cell(const RankedArgs& A, int gx, int g
     c.d0 = gl(A.tot)[t];
     c.nd = gl(A.tot)[t + 1] - c.d0;
     c.nchunk = gl(A.nchunk)[t];
-    c.rtot = gl(A.rtot)[t];
     c.base = base;
     return c;
 }
@@ -587,26 +586,44 @@ __device__ __forceinline__ DestCell dest_cell(const RankedArgs& A, int gx, int g
 // written directly.  Each thread issues the loads of PERM_PER particles before it uses any.
 // Ranks past the round table take slots at the end of their tile with one atomic per wavefront
 // and tile, lanes in lane order (bunched plasmas put hundreds of particles in one cell).
+// Bound by the latency of its loads, so by the workgroups a CU holds: seven, at 19 KB with the
+// image in 16 bits (a particle's place in its tile) and 20 bytes a cell; four waves of 70 registers
+// each, no fewer (64 spill).  The first rank words are loaded before the cells are looked up, the
+// next ones a block ahead.  128^3, 2 x 6.7e7: 716 us with 29 KB and the loads in turn, 582 now;
+// 128x32x32, 2 x 4.2e6: 48 and 39; eight serving runs: 109 and 82.
 constexpr int PERM_PER = 4;
 constexpr int PERM_BLOCK = 256 * PERM_PER;
-constexpr int PERM_IMG = 4096;
+constexpr int PERM_IMG = 4608, IMG_NONE = 0xFFFF;
 
 __device__ __forceinline__ void ranked_perm_tile(const RankedArgs& A, int64_t T, int32_t* lds) {
     const Geom& G = A.G;
     if (T >= G.ntiles) return;
     const int32_t ss = gl(A.start)[T], se = gl(A.start)[T + 1];
     const int32_t d0 = gl(A.tot)[T], nd = gl(A.tot)[T + 1] - d0;
-    const bool staged = nd <= PERM_IMG;
-    int32_t* img = lds;
-    DestCell* dest = (DestCell*)(lds + PERM_IMG);
+    const bool staged = nd <= PERM_IMG && se - ss < IMG_NONE;
+    uint16_t* img = (uint16_t*)lds;  // particle - ss, IMG_NONE: not one of this tile's
+    DestCell* dest = (DestCell*)(lds + PERM_IMG / 2);
     if (staged)
-        for (int32_t q = threadIdx.x; q < nd; q += blockDim.x) img[q] = -1;
+        for (int32_t q = threadIdx.x; q < nd; q += blockDim.x) img[q] = IMG_NONE;
+    // the first rank words are on their way while the cells are looked up
+    int32_t wn[PERM_PER];
+    auto load_ranks = [&](int64_t b) {
+#pragma unroll
+        for (int k = 0; k < PERM_PER; ++k) {
+            const int64_t p = b + threadIdx.x + k * 256;
+            wn[k] = p < se ? gl(A.rank)[p] : -1;
+        }
+    };
+    load_ranks(ss);
     const int e0 = G.dest_ext(0), e1 = G.dest_ext(1), slots = e0 * e1 * G.dest_ext(2);
-    const int ox = (int)(T % G.nt[0]) * G.t[0], oy = (int)((T / G.nt[0]) % G.nt[1]) * G.t[1],
-              oz = (int)(T / ((int64_t)G.nt[0] * G.nt[1])) * G.t[2];
+    const uint32_t row = (uint32_t)T / (uint32_t)G.nt[0], layer = row / (uint32_t)G.nt[1];  // numbered in 32 bits
+    const int ox = (int)((uint32_t)T - row * (uint32_t)G.nt[0]) * G.t[0],
+              oy = (int)(row - layer * (uint32_t)G.nt[1]) * G.t[1], oz = (int)layer * G.t[2];
+    const bool eight = e0 == 8 && e1 == 8;  // 4x4x4 tiles: no divisions
     if (se > ss)
         for (int q = threadIdx.x; q < slots; q += blockDim.x) {
-            const int z = q / (e0 * e1), r = q - z * e0 * e1, y = r / e0, x = r - y * e0;
+            const int z = eight ? q >> 6 : q / (e0 * e1), r = q - z * e0 * e1;
+            const int y = eight ? r >> 3 : r / e0, x = r - y * e0;
             dest[q] = dest_cell(A, e0 == 1 ? 0 : wrap_near(ox + x - DEST_HALO, G.n[0]),
                                 e1 == 1 ? 0 : wrap_near(oy + y - DEST_HALO, G.n[1]),
                                 G.n[2] == 1 ? 0 : wrap_near(oz + z - DEST_HALO, G.n[2]), gl(A.base)[T * slots + q]);
@@ -618,10 +635,8 @@ __device__ __forceinline__ void ranked_perm_tile(const RankedArgs& A, int64_t T,
         DestCell c[PERM_PER];
         RoundEntry e[PERM_PER];
 #pragma unroll
-        for (int k = 0; k < PERM_PER; ++k) {
-            const int64_t p = b + threadIdx.x + k * 256;
-            w[k] = p < se ? gl(A.rank)[p] : -1;
-        }
+        for (int k = 0; k < PERM_PER; ++k) w[k] = wn[k];
+        load_ranks(b + PERM_BLOCK);
 #pragma unroll
         for (int k = 0; k < PERM_PER; ++k) {
             c[k] = dest[w[k] >= 0 ? w[k] >> 20 : 0];
@@ -643,7 +658,7 @@ __device__ __forceinline__ void ranked_perm_tile(const RankedArgs& A, int64_t T,
             // computed for every particle and selected (no branch the table reads could sink into)
             const bool in_table = r[k] >= 0 && r[k] < SORT_RCAP;
             const int32_t ps = pair_slot(e[k], c[k].nchunk, in_table ? r[k] : 0, c[k].tile_lc & 63);
-            pos[k] = in_table ? ps : c[k].rtot;
+            pos[k] = in_table ? ps : 0;
         }
 #pragma unroll
         for (int k = 0; k < PERM_PER; ++k) {
@@ -655,7 +670,7 @@ __device__ __forceinline__ void ranked_perm_tile(const RankedArgs& A, int64_t T,
                 const int32_t lt = __shfl(t, leader, 64);
                 const uint64_t grp = __ballot(over && t == lt) & todo;
                 int32_t first = 0;
-                if (lane == leader) first = atomicAdd(gl(A.ovf) + lt, (int32_t)__popcll(grp));
+                if (lane == leader) first = gl(A.rtot)[lt] + atomicAdd(gl(A.ovf) + lt, (int32_t)__popcll(grp));
                 first = __shfl(first, leader, 64);
                 if (over && t == lt) pos[k] += first + (int32_t)__popcll(grp & ((1ull << lane) - 1ull));
                 todo &= ~grp;
@@ -666,7 +681,7 @@ __device__ __forceinline__ void ranked_perm_tile(const RankedArgs& A, int64_t T,
             if (r[k] < 0 || pos[k] >= c[k].nd) continue;
             const int32_t p = (int32_t)(b + threadIdx.x + k * 256);
             if (staged && (c[k].tile_lc >> 6) == (int32_t)T)
-                img[pos[k]] = p;
+                img[pos[k]] = (uint16_t)(p - ss);
             else
                 gl(A.perm)[c[k].d0 + pos[k]] = p;
         }
@@ -675,7 +690,7 @@ __device__ __forceinline__ void ranked_perm_tile(const RankedArgs& A, int64_t T,
     if (staged)
         for (int32_t q = threadIdx.x; q < nd; q += blockDim.x) {
             const int32_t v = img[q];
-            if (v >= 0) gl(A.perm)[d0 + q] = v;
+            if (v != IMG_NONE) gl(A.perm)[d0 + q] = ss + v;
         }
 }
 
@@ -687,15 +702,15 @@ __device__ __forceinline__ void bin_perm_tile(const RankedArgs& A, int64_t T, in
     if (T >= G.ntiles) return;
     const int32_t ss = gl(A.start)[T * TILE_CELLS], se = gl(A.start)[(T + 1) * TILE_CELLS];
     const int32_t d0 = gl(A.tot)[T], nd = gl(A.tot)[T + 1] - d0;
-    const bool staged = nd <= PERM_IMG;
-    int32_t* img = lds;
-    int32_t* first = lds + PERM_IMG;  // first slot of each destination cell
+    const bool staged = nd <= PERM_IMG && se - ss < IMG_NONE;
+    uint16_t* img = (uint16_t*)lds;
+    int32_t* first = lds + PERM_IMG / 2;  // first slot of each destination cell
     if (threadIdx.x < TILE_CELLS) {
         gl(A.next_bins)[T * TILE_CELLS + threadIdx.x] = d0 + gl(A.pre)[T * TILE_CELLS + threadIdx.x];
         if (T == G.ntiles - 1 && threadIdx.x == 0) gl(A.next_bins)[G.nbins] = gl(A.tot)[G.ntiles];
     }
     if (staged)
-        for (int32_t q = threadIdx.x; q < nd; q += blockDim.x) img[q] = -1;
+        for (int32_t q = threadIdx.x; q < nd; q += blockDim.x) img[q] = IMG_NONE;
     auto cell_first = [&](int gx, int gy, int gz) {
         const int32_t t = (gx >> A.tsh[0]) + G.nt[0] * ((gy >> A.tsh[1]) + G.nt[1] * (gz >> A.tsh[2]));
         const int lc = (gx & (G.t[0] - 1)) + ((gy & (G.t[1] - 1)) << A.tsh[0]) + ((gz & (G.t[2] - 1)) << (A.tsh[0] + A.tsh[1]));
@@ -730,7 +745,7 @@ __device__ __forceinline__ void bin_perm_tile(const RankedArgs& A, int64_t T, in
                 q = cell_first(nearest_cell(gl(A.pos[0])[p], G.n[0]), nearest_cell(gl(A.pos[1])[p], G.n[1]),
                                nearest_cell(gl(A.pos[2])[p], G.n[2])) + (w[k] & 0x7FFFFFFF);
             if (staged && q >= d0 && q < d0 + nd)
-                img[q - d0] = (int32_t)p;
+                img[q - d0] = (uint16_t)(p - ss);
             else
                 gl(A.perm)[q] = (int32_t)p;
         }
@@ -739,12 +754,12 @@ __device__ __forceinline__ void bin_perm_tile(const RankedArgs& A, int64_t T, in
     if (staged)
         for (int32_t q = threadIdx.x; q < nd; q += blockDim.x) {
             const int32_t v = img[q];
-            if (v >= 0) gl(A.perm)[d0 + q] = v;
+            if (v != IMG_NONE) gl(A.perm)[d0 + q] = ss + v;
         }
 }
 
 size_t sort_perm_lds(const pp_run* r) {
-    return PERM_IMG * sizeof(int32_t) + (size_t)r->g.dest_slots() * sizeof(DestCell);
+    return PERM_IMG * sizeof(uint16_t) + (size_t)r->g.dest_slots() * sizeof(DestCell);
 }
 
 // ---- exclusive scan of int32, in place ------------------------------------------------
@@ -1078,7 +1093,7 @@ static hipError_t sort_ranked(pp_run* r, unsigned mask) {
     if (r->p.precision == PP_PREC_FP32_SPLIT)
         launch_ranked<SF_SPLIT>(r, A, ns, any, sort_perm_lds(r));
     else
-        launch_ranked<SF_FP64>(r, A, ns, any, (PERM_IMG + (size_t)r->g.dest_slots()) * sizeof(int32_t));
+        launch_ranked<SF_FP64>(r, A, ns, any, PERM_IMG * sizeof(uint16_t) + (size_t)r->g.dest_slots() * sizeof(int32_t));
     hipError_t e = hipGetLastError();
     for (int s = 0; s < PP_MAX_SPECIES; ++s)
         if (mask & (1u << s)) sort_enqueued(r, s);

@@ -209,3 +209,36 @@ def test_field_step_of_boxes_marched_in_planes(ppm, orc, n, order):
     Eg, Bg, _ = run.fields()
     assert rel_inf(Eg, ref.E) < 1e-12 and rel_inf(Bg, ref.B) < 1e-12
     run.close()
+
+
+@pytest.mark.parametrize("precision", ["split", "fp64"])
+@pytest.mark.parametrize("count", [4608, 4609, 65534, 65536])
+def test_sort_of_a_tile_at_the_sizes_of_its_lds_image(ppm, orc, precision, count):
+    """A box of one tile: the sort loses no particle, and the next current is the same for the
+    particles in another order (the split form; bit for bit, in fixed point) or left unsorted (FP64
+    may be; 1e-12 of the largest value for sums in another order)."""
+    from paper_1211_4575_amd import inputs as I
+    n = (4, 4, 4)
+    rng = np.random.default_rng(2)
+    _, E, B = random_state(orc, n, 1, seed=5)
+    s = dict(q=-1.0, m=1.0, w=1.0 / count, pos=rng.uniform(0, 4, (3, count)), u=rng.normal(0, 0.3, (3, count)))
+    split = precision == "split"
+    if split:
+        cell, off = I.to_split(s["pos"], n, origin=I.split_origin(3))
+        s = dict(q=-1.0, m=1.0, w=1.0 / count, cell=cell, off=off, u=s["u"].astype(np.float32))
+    kw = dict(n=n, dt=0.35, shape_order=3, field_order=2, relax_max_iter=100,
+              precision=ppm.PP_PREC_FP32_SPLIT if split else ppm.PP_PREC_FP64)
+    out = []
+    for first in (True, False):
+        if split and not first:
+            s = dict(s, **{k: np.ascontiguousarray(s[k][..., ::-1]) for k in ("cell", "off", "u")})
+        run = ppm.Run(ppm.make_params(**kw), [s], E=E, B=B)
+        run.gather_push_deposit()
+        if split or first:
+            run.sort()
+        run.gather_push_deposit()
+        assert run.diagnostics().flags == 0
+        assert np.array_equal(np.sort(run.particles(0)["id"]), np.arange(count))
+        out.append(run.fields()[2])
+        run.close()
+    assert np.array_equal(*out) if split else rel_inf(*out) < 1e-12
