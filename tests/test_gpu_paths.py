@@ -242,3 +242,28 @@ def test_sort_of_a_tile_at_the_sizes_of_its_lds_image(ppm, orc, precision, count
         out.append(run.fields()[2])
         run.close()
     assert np.array_equal(*out) if split else rel_inf(*out) < 1e-12
+
+
+@pytest.mark.parametrize("current", [0, 1])
+@pytest.mark.parametrize("n,O", [((24, 16, 1), 3), ((9, 17, 1), 2), ((13, 11, 1), 3)])
+def test_flat_tiles_match_oracle(ppm, orc, n, O, current):
+    """The current of 8x8x1 tiles, whose z nodes share their additions, over three steps of particles
+    that cross faces along z too.  FP32 weights and offsets: 1e-5 in the L2 norm."""
+    from paper_1211_4575_amd import inputs as I
+    species, E, B = random_state(orc, n, 5, seed=23, uth=0.7)
+    split, ref_species = [], []
+    for s in species:
+        cell, off = I.to_split(s["pos"], n, origin=I.split_origin(O))
+        u = s["u"].astype(np.float32)
+        split.append(dict(q=s["q"], m=s["m"], w=s["w"], cell=cell, off=off, u=u))
+        ref_species.append(dict(s, pos=I.from_split(cell, off, n), u=u.astype(np.float64)))
+    kw = dict(n=n, dt=0.45, shape_order=O, field_order=4, relax_tol=1e-14, relax_max_iter=200)
+    ref = orc.Run(orc.make_params(current_scheme=current, **kw), ref_species, E=E, B=B)
+    run = ppm.Run(ppm.make_params(precision=ppm.PP_PREC_FP32_SPLIT, current_scheme=current, **kw), split, E=E, B=B)
+    for _ in range(3):
+        ref.step()
+        run.step()
+        J = run.fields()[2]
+        assert np.linalg.norm(J - ref.J) < 1e-5 * np.linalg.norm(ref.J)
+    assert run.diagnostics().flags == 0
+    run.close()
