@@ -249,86 +249,162 @@ __global__ void k_rho_scale(const int32_t* __restrict__ tile_max, unsigned mask,
     *scale = ldexp(1.0, e0 - lg - margin);
 }
 
+// What a particle deposits: its weights and the first node of its support in the block; ok false:
+// nothing there.
 template <int O>
+struct RhoWin {
+    double w[3][O + 1];
+    int base;
+    bool ok;
+};
+
+// The block's strides.  Compile-time for the 4x4x4 tile (CUBE): rows of 12 words put the 16 cells of a
+// plane, 16 lanes of a round, on different banks.  A single-cell axis has stride 0.
+template <int O, bool CUBE>
+struct RhoBlk {
+    static constexpr int E = 4 + 2 * RHO_HALO + O + 1;
+    static constexpr int sx = 1, sy = 12, sz = 12 * E, words = 12 * E * E;
+    static_assert(E <= 12, "row padding");
+    __device__ RhoBlk(const Rho32Args&) {}
+};
+
+template <int O>
+struct RhoBlk<O, false> {
+    int sx, sy, sz;
+    __device__ RhoBlk(const Rho32Args& A) {
+        sx = A.ext[0] == 1 ? 0 : 1;
+        sy = A.ext[1] == 1 ? 0 : A.ext[0];
+        sz = A.ext[2] == 1 ? 0 : A.ext[0] * A.ext[1];
+    }
+};
+
+template <int O, class BL>
+__device__ __forceinline__ void rho_window(const Rho32Args& A, const Rho32Sp& S, const BL& L, const int org[3], int32_t p,
+                                           double v, RhoWin<O>& W) {
+    const int32_t cell = S.cell[p];
+    if (cell < 0 || (int64_t)cell >= A.nc) return;  // reported by the error flags
+    // exact: (cell + 1/2) / n is at least 1/(2n) from an integer, and below 2^30
+    const int row = (int)(((double)cell + 0.5) * A.inv_n0), gz = (int)(((double)row + 0.5) * A.inv_n1);
+    const int g[3] = {cell - row * A.n[0], row - gz * A.n[1], gz};
+    const float f[3] = {S.pos[0][p], S.pos[1][p], S.pos[2][p]};
+    const float flo = O == 2 ? -0.5f : 0.0f;
+    bool finite = true, in_block = true;
+    int ll[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+        finite = finite && fabsf(f[d]) <= 1048576.0f;  // false for NaN and Inf as well
+        int l = g[d] - org[d];  // cell relative to the tile, nearest periodic image
+        if (l >= A.t[d] + A.halo[d])
+            l -= A.n[d];
+        else if (l < -A.halo[d])
+            l += A.n[d];
+        ll[d] = l;
+        in_block = in_block && l >= -A.halo[d] && l < A.t[d] + A.halo[d] && f[d] >= flo && f[d] < flo + 2.0f;
+    }
+    if (!finite) return;  // reported by the error flags
+    int i0[3];
+    if (in_block) {
+        // support inside the block: nodes of cells -halo .. t + halo - 1 around the tile,
+        // i.e. block indices 0 .. t + 2 halo + O
+#pragma unroll
+        for (int d = 0; d < 3; ++d) i0[d] = weights_abs<O>((double)(ll[d] + A.lo[d]) + (double)f[d], W.w[d]);
+        W.base = i0[0] * L.sx + i0[1] * L.sy + i0[2] * L.sz;
+        W.ok = true;
+        return;
+    }
+    double w[3][O + 1];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) i0[d] = weights_abs<O>((double)g[d] + (double)f[d], w[d]);
+#pragma unroll
+    for (int c = 0; c <= O; ++c) {
+        const int k = wrap(i0[2] + c, A.n[2]);
+#pragma unroll
+        for (int b = 0; b <= O; ++b) {
+            const int j = wrap(i0[1] + b, A.n[1]);
+            const double vzy = v * w[2][c] * w[1][b];
+#pragma unroll
+            for (int a = 0; a <= O; ++a) {
+                const int i = wrap(i0[0] + a, A.n[0]);
+                const long long x = rho_fixed_sum(rho_pattern(vzy, w[0][a]));
+                atomicAdd(A.acc + (int64_t)i + (int64_t)A.n[0] * (j + (int64_t)A.n[1] * k), (unsigned long long)x);
+            }
+        }
+    }
+}
+
+// Charge of one particle, or of two on the same nodes (PAIR; v2 = 0: of the first alone): each
+// contribution's pattern is rounded on its own, so that two of them summed before the atomic give
+// the same exact sum as two atomics.
+template <int O, class BL, bool PAIR>
+__device__ __forceinline__ void rho_deposit(unsigned long long* blk, const BL& L, const RhoWin<O>& W1, const RhoWin<O>& W2,
+                                            double v1, double v2) {
+#pragma unroll
+    for (int c = 0; c <= O; ++c)
+#pragma unroll
+        for (int b = 0; b <= O; ++b) {
+            const double vzy1 = v1 * W1.w[2][c] * W1.w[1][b];
+            const double vzy2 = PAIR ? v2 * W2.w[2][c] * W2.w[1][b] : 0.0;
+            unsigned long long* row = blk + W1.base + c * L.sz + b * L.sy;
+#pragma unroll
+            for (int a = 0; a <= O; ++a) {
+                unsigned long long bits = rho_pattern(vzy1, W1.w[0][a]);
+                if (PAIR) bits += rho_pattern(vzy2, W2.w[0][a]);
+                atomicAdd(row + a * L.sx, bits);
+            }
+        }
+}
+
+// Bound by the LDS atomics, 64 a cubic particle.  In the 4x4x4 tiles' storage order (chunks of 64
+// pairs, see pp_sort.hip) lane l takes slots l and 64 + l of a chunk, two particles of a cell, whose
+// supports are the same unless one of them has since left it: one atomic a node for both.  70x46x50,
+// 1.03e7 particles, cubic: 169 us one by one with the strides read from the arguments, 128 now;
+// 50x42x37, quadratic, after a push: 85 and 75.
+template <int O, bool CUBE>
 __global__ void __launch_bounds__(256) k_rho32(Rho32Args A) {
     extern __shared__ unsigned long long rho_blk[];
-    const int64_t tile = blockIdx.x;
-    const int ti = (int)(tile % A.nt[0]);
-    const int tj = (int)((tile / A.nt[0]) % A.nt[1]);
-    const int tk = (int)(tile / ((int64_t)A.nt[0] * A.nt[1]));
-    const int org[3] = {ti * A.t[0], tj * A.t[1], tk * A.t[2]};
-    const int vol = A.ext[0] * A.ext[1] * A.ext[2];
+    const RhoBlk<O, CUBE> L(A);
+    const uint32_t tile = blockIdx.x, trow = tile / (uint32_t)A.nt[0], layer = trow / (uint32_t)A.nt[1];
+    const int org[3] = {(int)(tile - trow * (uint32_t)A.nt[0]) * A.t[0], (int)(trow - layer * (uint32_t)A.nt[1]) * A.t[1],
+                        (int)layer * A.t[2]};
+    int vol;
+    if constexpr (CUBE)
+        vol = L.words;
+    else
+        vol = A.ext[0] * A.ext[1] * A.ext[2];
     for (int q = threadIdx.x; q < vol; q += blockDim.x) rho_blk[q] = 0ull;
     __syncthreads();
     const double sc = *A.scale;
-    const float flo = O == 2 ? -0.5f : 0.0f;
     for (int s = 0; s < A.nsp; ++s) {
         const Rho32Sp& S = A.sp[s];
         const double v = S.qw * sc;
-        const int32_t end = S.start[tile + 1];
-        for (int32_t p = S.start[tile] + threadIdx.x; p < end; p += blockDim.x) {
-            const int32_t cell = S.cell[p];
-            if (cell < 0 || (int64_t)cell >= A.nc) continue;  // reported by the error flags
-            // exact: (cell + 1/2) / n is at least 1/(2n) from an integer, and below 2^30
-            const int row = (int)(((double)cell + 0.5) * A.inv_n0), gz = (int)(((double)row + 0.5) * A.inv_n1);
-            const int g[3] = {cell - row * A.n[0], row - gz * A.n[1], gz};
-            const float f[3] = {S.pos[0][p], S.pos[1][p], S.pos[2][p]};
-            bool finite = true, in_block = true;
-            int ll[3];
-#pragma unroll
-            for (int d = 0; d < 3; ++d) {
-                finite = finite && fabsf(f[d]) <= 1048576.0f;  // false for NaN and Inf as well
-                int l = g[d] - org[d];  // cell relative to the tile, nearest periodic image
-                if (l >= A.t[d] + A.halo[d])
-                    l -= A.n[d];
-                else if (l < -A.halo[d])
-                    l += A.n[d];
-                ll[d] = l;
-                in_block = in_block && l >= -A.halo[d] && l < A.t[d] + A.halo[d] && f[d] >= flo && f[d] < flo + 2.0f;
-            }
-            if (!finite) continue;  // reported by the error flags
-            double w[3][O + 1];
-            int i0[3];
-            if (in_block) {
-                // support inside the block: nodes of cells -halo .. t + halo - 1 around the tile,
-                // i.e. block indices 0 .. t + 2 halo + O
+        const int32_t start = S.start[tile], end = S.start[tile + 1];
+        if constexpr (CUBE) {
+            const int lane = threadIdx.x & 63;
+            for (int32_t b = start + 128 * (int)(threadIdx.x >> 6); b < end; b += 128 * 4) {
+                RhoWin<O> W1, W2;
+                W1.ok = W2.ok = false;
+                W1.base = W2.base = 0;
 #pragma unroll
                 for (int d = 0; d < 3; ++d)
-                    i0[d] = weights_abs<O>((double)(ll[d] + A.lo[d]) + (double)f[d], w[d]);
 #pragma unroll
-                for (int c = 0; c <= O; ++c) {
-                    const int zc = A.ext[2] == 1 ? 0 : i0[2] + c;
-#pragma unroll
-                    for (int b = 0; b <= O; ++b) {
-                        const int yb = A.ext[1] == 1 ? 0 : i0[1] + b;
-                        const double vzy = v * w[2][c] * w[1][b];
-                        const int row = A.ext[0] * (yb + A.ext[1] * zc);
-#pragma unroll
-                        for (int a = 0; a <= O; ++a) {
-                            const int xa = A.ext[0] == 1 ? 0 : i0[0] + a;
-                            atomicAdd(&rho_blk[row + xa], rho_pattern(vzy, w[0][a]));
-                        }
-                    }
+                    for (int a = 0; a <= O; ++a) W2.w[d][a] = 0.0;  // finite where v2 = 0 leaves it out
+                const int32_t p1 = b + lane, p2 = p1 + 64;
+                if (p1 < end) rho_window<O>(A, S, L, org, p1, v, W1);
+                if (p2 < end) rho_window<O>(A, S, L, org, p2, v, W2);
+                const bool same = W1.ok && W2.ok && W1.base == W2.base;
+                if (__any(same)) {
+                    if (W1.ok) rho_deposit<O, RhoBlk<O, CUBE>, true>(rho_blk, L, W1, W2, v, same ? v : 0.0);
+                } else if (W1.ok) {
+                    rho_deposit<O, RhoBlk<O, CUBE>, false>(rho_blk, L, W1, W1, v, 0.0);
                 }
-            } else {
-#pragma unroll
-                for (int d = 0; d < 3; ++d) i0[d] = weights_abs<O>((double)g[d] + (double)f[d], w[d]);
-#pragma unroll
-                for (int c = 0; c <= O; ++c) {
-                    const int k = wrap(i0[2] + c, A.n[2]);
-#pragma unroll
-                    for (int b = 0; b <= O; ++b) {
-                        const int j = wrap(i0[1] + b, A.n[1]);
-                        const double vzy = v * w[2][c] * w[1][b];
-#pragma unroll
-                        for (int a = 0; a <= O; ++a) {
-                            const int i = wrap(i0[0] + a, A.n[0]);
-                            const long long x = rho_fixed_sum(rho_pattern(vzy, w[0][a]));
-                            atomicAdd(A.acc + (int64_t)i + (int64_t)A.n[0] * (j + (int64_t)A.n[1] * k),
-                                      (unsigned long long)x);
-                        }
-                    }
-                }
+                if (W2.ok && !same) rho_deposit<O, RhoBlk<O, CUBE>, false>(rho_blk, L, W2, W2, v, 0.0);
+            }
+        } else {
+            for (int32_t p = start + threadIdx.x; p < end; p += blockDim.x) {
+                RhoWin<O> W;
+                W.ok = false;
+                rho_window<O>(A, S, L, org, p, v, W);
+                if (W.ok) rho_deposit<O, RhoBlk<O, CUBE>, false>(rho_blk, L, W, W, v, 0.0);
             }
         }
     }
@@ -336,12 +412,19 @@ __global__ void __launch_bounds__(256) k_rho32(Rho32Args A) {
     for (int q = threadIdx.x; q < vol; q += blockDim.x) {
         const long long x = rho_fixed_sum(rho_blk[q]);
         if (x == 0) continue;
-        const int a = q % A.ext[0];
-        const int b = (q / A.ext[0]) % A.ext[1];
-        const int c = q / (A.ext[0] * A.ext[1]);
-        const int i = wrap(org[0] - A.lo[0] + a, A.n[0]);
-        const int j = wrap(org[1] - A.lo[1] + b, A.n[1]);
-        const int k = wrap(org[2] - A.lo[2] + c, A.n[2]);
+        int a, b, c;
+        if constexpr (CUBE) {  // the rows' padding holds nothing
+            c = q / L.sz;
+            b = (q - c * L.sz) / L.sy;
+            a = q - c * L.sz - b * L.sy;
+        } else {
+            a = q % A.ext[0];
+            b = (q / A.ext[0]) % A.ext[1];
+            c = q / (A.ext[0] * A.ext[1]);
+        }
+        const int i = wrap_near(org[0] - A.lo[0] + a, A.n[0]);
+        const int j = wrap_near(org[1] - A.lo[1] + b, A.n[1]);
+        const int k = wrap_near(org[2] - A.lo[2] + c, A.n[2]);
         atomicAdd(A.acc + (int64_t)i + (int64_t)A.n[0] * (j + (int64_t)A.n[1] * k), (unsigned long long)x);
     }
 }
@@ -493,11 +576,18 @@ static hipError_t launch_rho32(pp_run* r, unsigned mask) {
     if (e0 > 1000) e0 = 1000;
     hipLaunchKernelGGL(k_rho_scale, dim3(1), dim3(64), 0, r->stream, (const int32_t*)r->tile_max, mask, e0,
                        pending ? 1 : 0, r->dacc + ACC_RHO_SCALE);
+    const bool cube = A.t[0] == 4 && A.t[1] == 4 && A.t[2] == 4 && A.ext[0] > 1 && A.ext[1] > 1 && A.ext[2] > 1;
+    if (cube) vol = O == 2 ? RhoBlk<2, true>::words : RhoBlk<3, true>::words;
     const size_t lds = (size_t)vol * sizeof(unsigned long long);
-    if (O == 2)
-        hipLaunchKernelGGL(k_rho32<2>, dim3((unsigned)r->g.ntiles), dim3(256), lds, r->stream, A);
+    const dim3 grid((unsigned)r->g.ntiles);
+    if (O == 2 && cube)
+        hipLaunchKernelGGL((k_rho32<2, true>), grid, dim3(256), lds, r->stream, A);
+    else if (O == 2)
+        hipLaunchKernelGGL((k_rho32<2, false>), grid, dim3(256), lds, r->stream, A);
+    else if (cube)
+        hipLaunchKernelGGL((k_rho32<3, true>), grid, dim3(256), lds, r->stream, A);
     else
-        hipLaunchKernelGGL(k_rho32<3>, dim3((unsigned)r->g.ntiles), dim3(256), lds, r->stream, A);
+        hipLaunchKernelGGL((k_rho32<3, false>), grid, dim3(256), lds, r->stream, A);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     int64_t g = (A.nc + 255) / 256;
