@@ -913,7 +913,7 @@ __device__ __forceinline__ void gpd32_tile(const Gpd32Args& A, int64_t tile, int
 }
 
 // Wavefronts a SIMD: three with pairs (168 registers; 128 spill, 128^3 11.3 -> 13.5 ms), five in flat
-// tiles (96, a spilled pair of them; 106 and four take 1 % longer).
+// tiles (96, ten of them spilled; 106 and four take 1 % longer).
 template <int O, class TL, int BS>
 __global__ void __launch_bounds__(BS, TL::pairs ? 3 : TL::flat ? 5 : 1) k_gpd32(Gpd32Args A) {
     extern __shared__ __align__(16) unsigned char lds_raw[];
@@ -1106,8 +1106,11 @@ static unsigned fixed_grid(int64_t n3) {
     return (unsigned)(g < 1 ? 1 : g);
 }
 
-// With three workgroups a CU (of 256), a species of its own each halves the time of two species as
-// long as all are resident at once (768); beyond that it only stages the fields twice.
+// A workgroup takes one species up to 4096 tiles, which are few rounds of the 768 workgroups that are
+// resident at once (three a CU): the last round is shorter.  Two species, cubic, all species of a
+// tile in a workgroup -> one each: 900 tiles 255 -> 216 us, 64x32x32 (1024) at 16 per cell 287 -> 254,
+// 56x48x40 (1680) 411 -> 387, 64x64x48 (3072) 648 -> 638; 80x80x64 (6400) 1276 -> 1267, and in 128^3
+// (32768) staging the fields twice costs more, 11.15 -> 11.28 ms.
 // A box of fewer workgroups than that leaves wavefronts' places idle, and its time is the chain one
 // wavefront goes through: staging, its particles, flushing.  Larger workgroups that give a lane one
 // particle at a time (no pairs, 100 registers) shorten each part of it, with twice the atomics, which
@@ -1118,7 +1121,7 @@ static unsigned fixed_grid(int64_t n3) {
 template <int O>
 static void launch_tiles32(int kind, const Gpd32Args& A, size_t lds, hipStream_t st) {
     const int64_t wgs = A.ntiles * A.nsp;
-    const dim3 grid((unsigned)(8 * (int64_t)A.per_xcd), wgs <= 768 && A.nsp > 0 ? (unsigned)A.nsp : 1u);
+    const dim3 grid((unsigned)(8 * (int64_t)A.per_xcd), A.ntiles <= 4096 && A.nsp > 0 ? (unsigned)A.nsp : 1u);
     if (kind == TILE_444 && wgs <= 256)
         hipLaunchKernelGGL((k_gpd32<O, Tile444<O, false>, 1024>), grid, dim3(1024), lds, st, A);
     else if (kind == TILE_444 && wgs <= 512)
