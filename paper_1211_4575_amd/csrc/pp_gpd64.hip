@@ -698,11 +698,12 @@ static hipError_t launch_tiles(pp_run* r, const Gpd64TileArgs& A) {
 }
 
 // How the particles of np are shared out.  256 CUs hold three workgroups each.
-// Few tiles: a workgroup per tile, species and part of its particles, as many parts as are resident
-// at once (768 workgroups; two parts also a little beyond it) with a wavefront's worth of particles
-// each.  Two species, cubic, time with parts of at least 256 particles and, past 768, no split by
-// species -> this: 8^3, 8 per cell 47 -> 34 us; 16^3, 8 per cell 47 -> 43; 64x64 flat, 20 per cell
-// 39 -> 32; 24^3, 16 per cell 194 -> 163.
+// Few tiles: a workgroup per tile, species and part of its particles, or, past 384 tiles and species,
+// per tile and part, as many parts as are resident at once (768 workgroups) with a wavefront's worth
+// of particles each.  Two species, cubic, time with parts of at least 256 particles and in powers of
+// two -> this: 8^3, 8 per cell 47 -> 34 us; 16^3, 8 per cell 47 -> 43; 64x64 flat, 20 per cell 39 -> 32;
+// 24^3, 16 per cell 194 -> 168.  64x16x16 (256 tiles), four steps of a bunched two-stream plasma: 2.50 ms
+// with three parts, 2.51 with two, 2.69 with two parts of a species each.
 // Many tiles: all species of a tile in one workgroup, which stages the fields once, unless that
 // leaves the last round of workgroups mostly empty: 45x38x29 (960 tiles, 768 and 192) 393 -> 352 us
 // with a workgroup per species, but 32^3 (512, two a CU) 184 -> 202.
@@ -711,7 +712,9 @@ static void plan_workgroups(Gpd64TileArgs& A, int64_t np) {
     A.parts = 1;
     A.split = A.nsp;
     if (units <= 512) {
-        A.parts = units > 384 ? 2 : (int)(768 / units < 8 ? 768 / units : 8);
+        if (units > 384) A.split = 1;
+        const int64_t n = units > 384 ? A.ntiles : units;
+        A.parts = (int)(768 / n < 2 ? 2 : (768 / n > 8 ? 8 : 768 / n));
         while (A.parts > 1 && np < units * A.parts * 64) --A.parts;
         return;
     }
