@@ -340,7 +340,7 @@ def counter_summary(dirs, out, particles, cmds):
     per, copy, ew, times = {}, {}, {}, []
     for d in dirs:
         agg, dur = _pmc_rows(d)
-        launches = sorted((k for k in agg if "k_gpd32<3, pp::TileCT<3, 4, 4, 4, false>" in k[0]), key=lambda k: k[1])
+        launches = sorted((k for k in agg if "k_gpd32<3, pp::TileCT<3, 4, 4, 4, false" in k[0]), key=lambda k: k[1])
         for key in launches[1:]:
             for cname, v in agg[key].items():
                 per.setdefault(cname, []).append(v)
@@ -465,7 +465,7 @@ def stats_summary(d, out, particles, cmd):
         lines.append(f"| `{r['Name'][:90]}` | {r['Calls']} | {float(r['AverageNs']) * 1e-6:.3f} | "
                      f"{float(r['MinNs']) * 1e-6:.3f} | {float(r['MaxNs']) * 1e-6:.3f} | {float(r['Percentage']):.2f} |")
     calls = sorted(csv.DictReader(open(tr[0])), key=lambda r: int(r["Start_Timestamp"]))
-    gpd = [i for i, r in enumerate(calls) if "k_gpd32<3, pp::TileCT<3, 4, 4, 4, false>" in r["Kernel_Name"]]
+    gpd = [i for i, r in enumerate(calls) if "k_gpd32<3, pp::TileCT<3, 4, 4, 4, false" in r["Kernel_Name"]]
     per = {}
     for r in calls[gpd[0] + 1:] if gpd else []:
         per.setdefault(r["Kernel_Name"], []).append((int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) * 1e-6)
@@ -1189,8 +1189,8 @@ def main(argv=None):
                                   current_scheme=scheme, gauss_passes=args.gauss_passes, time_order=args.time_order)
         log(f"[bench] FP64 plain: warmup 1, timing {args.fp64_steps} steps")
         wall64, gpd64_ms = time_steps(run, torch, args.fp64_steps, 1)
-        fp64 = dict(form="plain FP64: untiled, one thread per particle, every current contribution a global "
-                         "FP64 atomic (the ratio measures the tiled split design, not the precision alone)",
+        fp64 = dict(form="plain FP64: tiled, fields and current of a tile in LDS, every current contribution "
+                         "an FP64 LDS atomic",
                     value=npart * args.fp64_steps / wall64, ms_per_step=1e3 * wall64 / args.fp64_steps,
                     gpd_updates_per_s=npart / (gpd64_ms * 1e-3), gpd_ms=gpd64_ms)
         # per-step charge conservation and Gauss residual of the FP64 form, outside the timed region

@@ -229,10 +229,10 @@ pp_status pp_field_step(pp_run* run);
 
 /* Counting sort of species s (-1 = all) by tile-major cell key (Sec. III: the
  * particle arrays are sorted by cell between steps 3 and 4).  The order inside a
- * cell is unspecified.  The current and alternate buffers swap roles.  FP32_SPLIT:
- * after a push the sort computes the new order only; the particles are moved into it
- * by the next pp_gather_push_deposit (together with their update) or by
- * pp_get_particles, whichever comes first. */
+ * cell is unspecified.  The current and alternate buffers swap roles.  After a push (in
+ * the FP64 form: one of particles that a sort had put in order) the sort computes the new
+ * order only; the particles are moved into it by the next pp_gather_push_deposit (together
+ * with their update) or by pp_get_particles, whichever comes first. */
 pp_status pp_sort_particles(pp_run* run, int32_t s);
 
 /* One whole time step in the run's time order (Sec. III step list): for time_order 2,

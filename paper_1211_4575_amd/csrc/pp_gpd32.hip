@@ -12,10 +12,10 @@
 // cells of the tile, in a full round all 64 cells in order, so the 64 lanes of a wavefront
 // touch 64 aligned stencils, which the padded LDS layout spreads over all banks.
 //
-// One workgroup (4 wavefronts) per tile of 64 cells:
+// One workgroup (4 wavefronts; more in small boxes) per tile of 64 cells:
 //   1. stage E and B of the tile plus a 2-node halo from the FP64 mesh into LDS as FP32;
-//   2. each wavefront takes 64 consecutive particles at a time (coalesced loads and
-//      stores): gather (LDS) -> push (registers) -> move and renormalise the split
+//   2. each wavefront takes 64 or 128 consecutive particles at a time (coalesced stores,
+//      loads through the pending order): gather (LDS) -> push (registers) -> move and renormalise the split
 //      position -> Esirkepov current (registers) -> LDS accumulation of the tile's current
 //      block (halo of 2 nodes below and O + 1 above);
 //   3. flush the current block to the global accumulator with 64-bit integer atomics.
@@ -32,8 +32,8 @@
 // recovered when the block is flushed; the scale 2^e (from the largest particle count of any
 // tile) keeps every node's sum below 2^50 in magnitude.  The global accumulator adds the
 // recovered integers, so the current is the exact sum of the rounded contributions,
-// independent of summation order (bitwise deterministic).  All species are processed by the
-// same workgroup.
+// independent of summation order (bitwise deterministic).  A workgroup takes all species of its
+// tile or, up to a few thousand tiles, one (see launch_tiles32).
 #include "pp_device.hpp"
 #include "pp_fixed.hpp"
 #include "pp_internal.hpp"
@@ -922,7 +922,7 @@ __global__ void __launch_bounds__(BS, TL::pairs ? 3 : TL::flat ? 5 : 1) k_gpd32(
     const int64_t b = blockIdx.x;
     const int64_t tile = (b & 7) * (int64_t)A.per_xcd + (b >> 3);
     if (tile >= A.ntiles) return;
-    // a small box has a workgroup per tile and species (the current's integer sum is the same)
+    // a workgroup per tile and species, or per tile (the current's integer sum is the same)
     const int s0 = gridDim.y > 1 ? (int)blockIdx.y : 0, s1 = gridDim.y > 1 ? s0 + 1 : A.nsp;
     gpd32_tile<O, TL, BS>(A, tile, s0, s1, lds_raw);
 }

@@ -497,7 +497,7 @@ __device__ __forceinline__ bool gpd64_in_tile(const Gpd64Args& A, const TL& L, c
 // 8 bytes per particle (ds_add_f64 runs at 9 clocks per wavefront where the 64 lanes' addresses
 // differ and at 193 where they coincide), against 300 global FP64 atomics of the untiled kernel.
 // 1.05e6 particles of a 64x16x16 two-stream box, cubic: 0.275 ms against 8.70; 9.9e5 of a 45x38x29
-// pair plasma: 0.383 against 6.67; 6.6e4 of a 16^3 box, quadratic: 0.045 against 0.252.
+// pair plasma: 0.354 against 6.67; 6.6e4 of a 16^3 box, quadratic: 0.031 against 0.252.
 // A workgroup takes the particles of one tile (a part of them where the box has few tiles).
 // They lie in cell order, so lane l of a wavefront walks the l-th 64th of them: the 64 lanes
 // then sit in different cells, mostly one each, and their LDS additions fall on different
