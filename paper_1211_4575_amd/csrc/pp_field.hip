@@ -166,7 +166,7 @@ __global__ void __launch_bounds__(FIELD_BS) k_field(FieldDesc D, int phase) {
 // cannot do without) and by latency in small ones, where short marches (D.zc, down to one plane
 // with every load in flight at once) spread it over the GPU.  Tiles of 64x8, 32x16, 64x4 and 64x16
 // took 0 to 14 % longer.  Whole field step, us, with each tap of the boxes below 1024 columns read
-// through the caches and now: 256^3 5750 and 4800, 128^3 1520 and 608, 128x32x32 260 and 98,
+// through the caches and now: 256^3 5750 and 4510, 128^3 1520 and 608, 128x32x32 260 and 98,
 // 512x256x1 243 and 107, 64x32x32 222 and 70.
 constexpr int RX_TX = 32, RX_TY = 8, RX_ZC = 32;
 constexpr int RX_BS = RX_TX * RX_TY;  // one thread per column of the tile
@@ -244,10 +244,28 @@ __device__ __forceinline__ void tile_ctx(const FieldGeom& G, int zc, int b, Tile
     X.small = G.small;
 }
 
+// STREAM: what a phase touches once passes by the caches, which are left to the stencils' reads (see
+// streams_past_cache).
+template <bool STREAM>
+__device__ __forceinline__ double load_once(const double* p) {
+    if constexpr (STREAM)
+        return __builtin_nontemporal_load(p);
+    else
+        return *p;
+}
+
+template <bool STREAM>
+__device__ __forceinline__ void store_once(double v, double* p) {
+    if constexpr (STREAM)
+        __builtin_nontemporal_store(v, p);
+    else
+        *p = v;
+}
+
 // Sweep k of one block: the loads are unconditional (the last plane reloads its own plane, a lane
 // off the ring or the box reads entry 0), so that none waits at a branch before the plane that is
 // computed meanwhile.
-template <int R>
+template <int R, bool STREAM>
 __device__ __forceinline__ void relax_tile(const FieldDesc& D, int b, int k, double* pl) {
     constexpr int W = Ring<R, R>::W, NH = Ring<R, R>::NH;
     const FieldGeom& G = D.G;
@@ -267,8 +285,8 @@ __device__ __forceinline__ void relax_tile(const FieldDesc& D, int b, int k, dou
     for (int t = 0; t <= 2 * R; ++t) q[t] = x[X.col + nxy * nbw(X.z0, t - R, X.n2, X.small)];
 #pragma unroll
     for (int e = 0; e < NH; ++e) hv[e] = x[g.hg[e] + X.z0 * nxy];
-    double rq = rhs[own + X.z0 * nxy];
-    double pq = pv[own + X.z0 * nxy];
+    double rq = load_once<STREAM>(rhs + own + X.z0 * nxy);
+    double pq = load_once<STREAM>(pv + own + X.z0 * nxy);
     const int c0 = g.own(X.tx, X.ty);
     for (int kz = X.z0; kz < X.z1; ++kz) {
         if (kz > X.z0) __syncthreads();  // the previous plane's LDS reads are done
@@ -284,8 +302,8 @@ __device__ __forceinline__ void relax_tile(const FieldDesc& D, int b, int k, dou
             qn = x[X.col + nxy * nbw(kn, R, X.n2, X.small)];
 #pragma unroll
             for (int e = 0; e < NH; ++e) hv[e] = x[g.hg[e] + kn * nxy];
-            rn = rhs[own + kn * nxy];
-            pn = pv[own + kn * nxy];
+            rn = load_once<STREAM>(rhs + own + kn * nxy);
+            pn = load_once<STREAM>(pv + own + kn * nxy);
         }
         if (X.valid) {
             double sl = 0.0;
@@ -298,7 +316,7 @@ __device__ __forceinline__ void relax_tile(const FieldDesc& D, int b, int k, dou
             const double xq = q[R];
             const double Ax = xq - D.al2s * sl;
             const double y = xq + (rq - Ax) * D.gdiag;
-            out[own + kz * nxy] = pq + w * (y - pq);
+            store_once<STREAM>(pq + w * (y - pq), out + own + kz * nxy);
         }
         if (more) {
 #pragma unroll
@@ -389,7 +407,7 @@ __device__ __forceinline__ double dtile(const DStream<M, AX, UP>& st, const doub
 
 // rhs = B + alpha beta s lap B - dt curl+ E + alpha c^2 mu0 dt^2 curl+ J   (B = B^n), B^n's copy and
 // sweep 1
-template <int M, int C>
+template <int M, int C, bool STREAM>
 __device__ __forceinline__ void rhs_tiled_comp(const FieldDesc& D, const TileCtx& X, double* lds) {
     constexpr int R = 2 * M - 1;
     constexpr int d1 = (C + 1) % 3, d2 = (C + 2) % 3;
@@ -434,12 +452,12 @@ __device__ __forceinline__ void rhs_tiled_comp(const FieldDesc& D, const TileCtx
             const double xq = sB.at(0);
             const double rq = xq + D.cab * lp - D.dt * curlE + D.cj * curlJ;
             const int64_t q = X.own + (int64_t)kz * X.nxy;
-            gl(D.R)[C * G.nc + q] = rq;
-            Bn[q] = xq;
+            store_once<STREAM>(rq, gl(D.R) + C * G.nc + q);
+            store_once<STREAM>(xq, Bn + q);
             if (x1) {  // sweep 1
                 const double Ax = xq - D.al2s * lp;
                 const double y = xq + (rq - Ax) * D.gdiag;
-                x1[q] = xq + w1 * (y - xq);
+                store_once<STREAM>(xq + w1 * (y - xq), x1 + q);
             }
         }
         if (more) {
@@ -453,7 +471,7 @@ __device__ __forceinline__ void rhs_tiled_comp(const FieldDesc& D, const TileCtx
 }
 
 // E += c^2 dt (curl- (alpha B' + beta B) - mu0 J)
-template <int M, int C>
+template <int M, int C, bool STREAM>
 __device__ __forceinline__ void update_E_tiled_comp(const FieldDesc& D, const TileCtx& X, double* lds) {
     constexpr int d1 = (C + 1) % 3, d2 = (C + 2) % 3;
     const FieldGeom& G = D.G;
@@ -485,8 +503,8 @@ __device__ __forceinline__ void update_E_tiled_comp(const FieldDesc& D, const Ti
         if (X.valid) {
             const double cn = dtile<M, d1, 0>(sBu, G.a[d1]) - dtile<M, d2, 0>(sBv, G.a[d2]);
             const double co = dtile<M, d1, 0>(sNu, G.a[d1]) - dtile<M, d2, 0>(sNv, G.a[d2]);
-            gl(D.E)[C * G.nc + X.own + (int64_t)kz * X.nxy] =
-                sE.at(0) + D.c2dt * (D.al * cn + D.be * co - D.mu0 * sJ.at(0));
+            store_once<STREAM>(sE.at(0) + D.c2dt * (D.al * cn + D.be * co - D.mu0 * sJ.at(0)),
+                               gl(D.E) + C * G.nc + X.own + (int64_t)kz * X.nxy);
         }
         if (more) {
             sBu.shift();
@@ -512,27 +530,27 @@ constexpr int field_lds(int kind) {
 }
 
 // block b of a run's launch of one phase (k: the sweep)
-template <int M, int KIND>
+template <int M, int KIND, bool STREAM>
 __device__ __forceinline__ void field_tile(const FieldDesc& D, int b, int k, double* lds) {
     if constexpr (KIND == FK_RELAX) {
-        relax_tile<2 * M - 1>(D, b, k, lds);
+        relax_tile<2 * M - 1, STREAM>(D, b, k, lds);
     } else {
         TileCtx X;
         tile_ctx(D.G, D.zc, b, X);
         if constexpr (KIND == FK_RHS) {
             if (X.comp == 0)
-                rhs_tiled_comp<M, 0>(D, X, lds);
+                rhs_tiled_comp<M, 0, STREAM>(D, X, lds);
             else if (X.comp == 1)
-                rhs_tiled_comp<M, 1>(D, X, lds);
+                rhs_tiled_comp<M, 1, STREAM>(D, X, lds);
             else
-                rhs_tiled_comp<M, 2>(D, X, lds);
+                rhs_tiled_comp<M, 2, STREAM>(D, X, lds);
         } else {
             if (X.comp == 0)
-                update_E_tiled_comp<M, 0>(D, X, lds);
+                update_E_tiled_comp<M, 0, STREAM>(D, X, lds);
             else if (X.comp == 1)
-                update_E_tiled_comp<M, 1>(D, X, lds);
+                update_E_tiled_comp<M, 1, STREAM>(D, X, lds);
             else
-                update_E_tiled_comp<M, 2>(D, X, lds);
+                update_E_tiled_comp<M, 2, STREAM>(D, X, lds);
         }
     }
 }
@@ -548,7 +566,7 @@ __host__ __device__ __forceinline__ bool components_together(int kind, int zc) {
 
 // Four workgroups a CU for the right-hand side, at 125 registers instead of 137 and three (256^3:
 // 797 -> 779 us, 128^3 107 -> 103).
-template <int M, int KIND>
+template <int M, int KIND, bool STREAM>
 __global__ void __launch_bounds__(RX_BS, KIND == FK_RHS ? 4 : 1) k_field_tiles(FieldDesc D, int k, int blocks) {
     __shared__ double lds[field_lds<M>(KIND)];
     int b = (int)blockIdx.x;
@@ -559,7 +577,7 @@ __global__ void __launch_bounds__(RX_BS, KIND == FK_RHS ? 4 : 1) k_field_tiles(F
         const int t = (int)xcd_block((b & 7) + 8 * (int64_t)(b / 24), tiles);
         b = t >= 0 ? comp * tiles + t : -1;
     }
-    if (b >= 0) field_tile<M, KIND>(D, b, k, lds);
+    if (b >= 0) field_tile<M, KIND, STREAM>(D, b, k, lds);
 }
 
 // batched: block b belongs to run r with prefix[r] <= b < prefix[r+1] (prefix in blocks)
@@ -574,11 +592,11 @@ __global__ void __launch_bounds__(RX_BS) k_field_tiles_batch(const FieldDesc* __
     if (KIND == FK_RELAX && (k > D.sweeps || (k == 1 && D.sweeps > 1))) return;
     const int lb = (int)(b - prefix[r]);
     if (D.G.M == 3)
-        field_tile<3, KIND>(D, lb, k, lds);
+        field_tile<3, KIND, false>(D, lb, k, lds);
     else if (D.G.M == 2)
-        field_tile<2, KIND>(D, lb, k, lds);
+        field_tile<2, KIND, false>(D, lb, k, lds);
     else
-        field_tile<1, KIND>(D, lb, k, lds);
+        field_tile<1, KIND, false>(D, lb, k, lds);
 }
 
 // The whole relaxation of a small box, a workgroup per component: the current iterate in LDS
@@ -648,17 +666,32 @@ static void launch_relax_small(const FieldDesc& D, hipStream_t st) {
         hipLaunchKernelGGL(k_relax_small<1>, dim3(3), dim3(RS_BS), 0, st, D);
 }
 
+// Boxes whose four arrays of a sweep are far larger than the 256 MB of the last cache: they come from
+// memory in every pass, and what is touched once only drives out what a neighbouring block reads
+// again.  Field step with all accesses cached -> this, ms: 256^3 (1.6 GB) 4.77 -> 4.51, 192^3 2.07 -> 1.92
+// and at 4th order 2.00 -> 1.79, 160^3 (393 MB) 1.265 -> 1.243.  Smaller boxes find part of the arrays in
+// the cache: 152^3 (337 MB) 1.07 -> 1.23, 128^3 0.60 -> 0.68.
+static bool streams_past_cache(const FieldGeom& G) { return 4 * 3 * G.nc * (int64_t)sizeof(double) > (352ll << 20); }
+
+template <int KIND, bool STREAM>
+static void launch_field_order(const FieldDesc& D, dim3 grid, unsigned blocks, int k, hipStream_t st) {
+    if (D.G.M == 3)
+        hipLaunchKernelGGL((k_field_tiles<3, KIND, STREAM>), grid, dim3(RX_BS), 0, st, D, k, (int)blocks);
+    else if (D.G.M == 2)
+        hipLaunchKernelGGL((k_field_tiles<2, KIND, STREAM>), grid, dim3(RX_BS), 0, st, D, k, (int)blocks);
+    else
+        hipLaunchKernelGGL((k_field_tiles<1, KIND, STREAM>), grid, dim3(RX_BS), 0, st, D, k, (int)blocks);
+}
+
 template <int KIND>
 static void launch_field_tiles(const FieldDesc& D, unsigned blocks, int k, hipStream_t st) {
-    const dim3 grid(KIND == FK_RELAX                      ? xcd_grid(blocks)
+    const dim3 grid(KIND == FK_RELAX                  ? xcd_grid(blocks)
                     : components_together(KIND, D.zc) ? 3 * xcd_grid(blocks / 3)
-                                                          : blocks);
-    if (D.G.M == 3)
-        hipLaunchKernelGGL((k_field_tiles<3, KIND>), grid, dim3(RX_BS), 0, st, D, k, (int)blocks);
-    else if (D.G.M == 2)
-        hipLaunchKernelGGL((k_field_tiles<2, KIND>), grid, dim3(RX_BS), 0, st, D, k, (int)blocks);
+                                                      : blocks);
+    if (streams_past_cache(D.G))
+        launch_field_order<KIND, true>(D, grid, blocks, k, st);
     else
-        hipLaunchKernelGGL((k_field_tiles<1, KIND>), grid, dim3(RX_BS), 0, st, D, k, (int)blocks);
+        launch_field_order<KIND, false>(D, grid, blocks, k, st);
 }
 
 // Planes per block: as many as leave the launch about 8 blocks per CU (its share of them in a

@@ -267,3 +267,37 @@ def test_flat_tiles_match_oracle(ppm, orc, n, O, current):
         assert np.linalg.norm(J - ref.J) < 1e-5 * np.linalg.norm(ref.J)
     assert run.diagnostics().flags == 0
     run.close()
+
+
+@pytest.mark.parametrize("order", [2, 4, 6])
+def test_field_step_of_a_box_past_the_caches_equals_batched(ppm, order):
+    """A box whose arrays stream past the caches when it is stepped alone, not in a batch: bit for bit
+    the same fields."""
+    import torch
+    n = (164, 161, 160)
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    E0, B0 = (torch.randn(3, n[2], n[1], n[0], dtype=torch.float64, device="cuda", generator=gen) for _ in range(2))
+    kw = dict(n=n, dt=0.35, shape_order=2, field_order=order, relax_tol=1e-8, relax_max_iter=100,
+              precision=ppm.PP_PREC_FP32_SPLIT)
+    species = [dict(q=-1.0, m=1.0, w=0.1, cell=np.arange(64, dtype=np.int32), off=np.zeros((3, 64), np.float32),
+                    u=np.full((3, 64), 0.1, np.float32))]
+    out = []
+    for batched in (False, True):
+        run = ppm.Run(ppm.make_params(**kw), species)
+        run.E.copy_(E0)
+        run.B.copy_(B0)
+        if batched:
+            batch = ppm.pp_batch_create(1, torch.cuda.current_stream().cuda_stream)
+            ppm.pp_batch_add(batch, run.handle)
+            for _ in range(2):
+                ppm.pp_batch_step(batch)
+            ppm.pp_batch_remove(batch, run.handle)
+            ppm.pp_batch_destroy(batch)
+        else:
+            for _ in range(2):
+                run.step()
+        torch.cuda.synchronize()
+        out.append((run.E.clone(), run.B.clone()))
+        run.close()
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
