@@ -234,19 +234,19 @@ __device__ __forceinline__ unsigned long long rho_pattern(double a, double b) {
     return (unsigned long long)__double_as_longlong(fma(a, b, RHO_MAGIC));
 }
 
-// 2^e with e = e0 - ceil(log2(N)) - margin, N the sum of the largest tile populations of
-// the deposited species: a contribution is at most 2^(50 - ceil log2 N) and an LDS node sum
-// at most 2^50 in magnitude.  margin = 1 under a pending sort order, whose tile ranges are
-// the previous step's (their populations differ from the new ones by the particles that
-// changed tile).
-__global__ void k_rho_scale(const int32_t* __restrict__ tile_max, unsigned mask, int e0, int margin, double* scale) {
+// 2^e with e = e0 - ceil(log2(N)), N the sum of the largest tile populations of the deposited
+// species: a contribution is at most 2^(50 - ceil log2 N) and an LDS node sum at most 2^50 in
+// magnitude.  The populations are those of the ranges that the particles lie in: under a pending
+// sort order (mask pending) the order's before it (a cluster at a tile's corner that shares itself
+// out among eight tiles leaves an eighth of its old tile's count in each).
+__global__ void k_rho_scale(const int32_t* __restrict__ tile_max, unsigned mask, unsigned pending, int e0, double* scale) {
     if (blockIdx.x != 0 || threadIdx.x != 0) return;
     long long nb = 0;
     for (int s = 0; s < PP_MAX_SPECIES; ++s)
-        if (mask & (1u << s)) nb += tile_max[s];
+        if (mask & (1u << s)) nb += tile_max[pending & (1u << s) ? PP_MAX_SPECIES + s : s];
     int lg = 0;
     while ((1ll << lg) < nb) ++lg;
-    *scale = ldexp(1.0, e0 - lg - margin);
+    *scale = ldexp(1.0, e0 - lg);
 }
 
 // What a particle deposits: its weights and the first node of its support in the block; ok false:
@@ -541,7 +541,7 @@ static hipError_t launch_rho32(pp_run* r, unsigned mask) {
     Rho32Args A;
     const int O = r->p.shape_order;
     double qwmax = 0.0;
-    bool pending = false;
+    unsigned pending = 0;
     A.nsp = 0;
     for (int s = 0; s < PP_MAX_SPECIES; ++s) {
         if (!(mask & (1u << s))) continue;
@@ -549,7 +549,7 @@ static hipError_t launch_rho32(pp_run* r, unsigned mask) {
         Rho32Sp& D = A.sp[A.nsp++];
         // with a sort order pending, the buffers still follow the previous tile starts
         D.start = S.pending ? S.offsets_next : S.offsets;
-        pending = pending || S.pending;
+        pending |= S.pending ? 1u << s : 0u;
         D.cell = (const int32_t*)S.cur.cell;
         for (int d = 0; d < 3; ++d) D.pos[d] = (const float*)S.cur.pos[d];
         D.qw = S.q * S.w;
@@ -574,8 +574,8 @@ static hipError_t launch_rho32(pp_run* r, unsigned mask) {
     // every contribution is at most |q w| (the weights of a node are at most 1)
     int e0 = 50 - (int)ceil(log2(qwmax));
     if (e0 > 1000) e0 = 1000;
-    hipLaunchKernelGGL(k_rho_scale, dim3(1), dim3(64), 0, r->stream, (const int32_t*)r->tile_max, mask, e0,
-                       pending ? 1 : 0, r->dacc + ACC_RHO_SCALE);
+    hipLaunchKernelGGL(k_rho_scale, dim3(1), dim3(64), 0, r->stream, (const int32_t*)r->tile_max, mask, pending, e0,
+                       r->dacc + ACC_RHO_SCALE);
     const bool cube = A.t[0] == 4 && A.t[1] == 4 && A.t[2] == 4 && A.ext[0] > 1 && A.ext[1] > 1 && A.ext[2] > 1;
     if (cube) vol = O == 2 ? RhoBlk<2, true>::words : RhoBlk<3, true>::words;
     const size_t lds = (size_t)vol * sizeof(unsigned long long);

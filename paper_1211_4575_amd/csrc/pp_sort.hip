@@ -427,7 +427,7 @@ struct RankedArgs {
     int32_t* rtot;          // ntiles: particles in the table's rounds
     int32_t* nchunk;        // ntiles: whole chunks of 64 pairs
     int32_t* ovf;           // ntiles: overflow cursors
-    int32_t* tile_max;      // largest tile population
+    int32_t* tile_max;      // largest tile population; PP_MAX_SPECIES entries on, that of the order before
     const int32_t* start;   // current tile starts (source order)
     const int32_t* rank;    // n rank words
     const int32_t* base;    // ntiles * slots
@@ -559,7 +559,10 @@ __device__ __forceinline__ void ranked_scan(const RankedArgs& A) {
     scan_workgroup(gl(A.tot), A.G.ntiles, total, largest);
     if (threadIdx.x == 0) {
         gl(A.tot)[A.G.ntiles] = total;
-        if (A.tile_max) *gl(A.tile_max) = largest;
+        if (A.tile_max) {  // the ranges the particles still lie in until they are moved, and the new ones
+            gl(A.tile_max)[PP_MAX_SPECIES] = *gl(A.tile_max);
+            *gl(A.tile_max) = largest;
+        }
     }
     for (int64_t q = total + (int64_t)threadIdx.x; q < A.n; q += SCAN1_BS) gl(A.perm)[q] = -1;
 }
