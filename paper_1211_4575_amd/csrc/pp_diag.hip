@@ -571,8 +571,9 @@ static hipError_t launch_rho32(pp_run* r, unsigned mask) {
     A.inv_n1 = 1.0 / A.n[1];
     A.acc = (unsigned long long*)r->Jq;  // free and zero between steps, and left so
     A.scale = r->dacc + ACC_RHO_SCALE;
-    // every contribution is at most |q w| (the weights of a node are at most 1)
-    int e0 = 50 - (int)ceil(log2(qwmax));
+    // every contribution is at most |q w| (the weights of a node are at most 1); a box of one cell, whose
+    // node takes whole particles, needs a bit more to keep a sum of 2^50 below the sign
+    int e0 = 50 - (int)ceil(log2(qwmax)) - (A.nc == 1 ? 1 : 0);
     if (e0 > 1000) e0 = 1000;
     hipLaunchKernelGGL(k_rho_scale, dim3(1), dim3(64), 0, r->stream, (const int32_t*)r->tile_max, mask, pending, e0,
                        r->dacc + ACC_RHO_SCALE);

@@ -45,3 +45,20 @@ def test_charge_of_a_cluster_that_splits_over_its_tiles(ppm, orc, n, O, per_tile
     run.close()
     rho = orc.deposit_rho(orc.make_params(**kw), 1.0, 1.0, I.from_split(parts["cell"], parts["pos"], n))
     assert np.max(np.abs(np.array(got) / np.max(rho) - 1.0)) < 1e-10, (got, np.max(rho))
+
+
+@pytest.mark.parametrize("count,q", [(1, 1.0), (64, -0.5), (100, 1.0)])
+def test_charge_of_a_single_cell(ppm, count, q):
+    """A box of one cell, whose only node takes every particle's whole charge: density q w count, to the
+    FP64 rounding of the weights (1e-12)."""
+    rng = np.random.default_rng(4)
+    sp = dict(q=q, m=1.0, w=1.0, cell=np.zeros(count, np.int32), off=rng.uniform(0, 1, (3, count)).astype(np.float32),
+              u=np.zeros((3, count), np.float32))
+    for background in (0.0, -q * count):
+        run = ppm.Run(ppm.make_params((1, 1, 1), dt=0.4, shape_order=3, field_order=2, rho_background=background,
+                                      precision=ppm.PP_PREC_FP32_SPLIT), [sp])
+        for call in (lambda: None, run.gather_push_deposit, run.sort):
+            call()
+            d = run.diagnostics(ppm.PP_DIAG_RHO)
+            assert abs(d.gauss_max - abs(q * count + background)) < 1e-12 * abs(q) * count
+        run.close()
