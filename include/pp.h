@@ -232,7 +232,12 @@ pp_status pp_field_step(pp_run* run);
  * cell is unspecified.  The current and alternate buffers swap roles.  After a push (in
  * the FP64 form: one of particles that a sort had put in order) the sort computes the new
  * order only; the particles are moved into it by the next pp_gather_push_deposit (together
- * with their update) or by pp_get_particles, whichever comes first. */
+ * with their update) or by pp_get_particles, whichever comes first.
+ * That order is the one of the positions the push left.  A caller that writes FP64 positions
+ * between a push and the sort takes the pointers from pp_get_particles after that push: the
+ * sort then counts the positions as they are when it runs (through pointers taken earlier the
+ * particles written to only miss their place in the order until the next sort; no particle is
+ * lost and no result changes).  The split form's cells and offsets are not written there. */
 pp_status pp_sort_particles(pp_run* run, int32_t s);
 
 /* One whole time step in the run's time order (Sec. III step list): for time_order 2,
@@ -251,7 +256,8 @@ pp_status pp_diagnostics(pp_run* run, uint32_t what, pp_diag* out);
 
 /* Current buffer assignment of species s after sorts (host struct), with the particles
  * in sorted order: a new order left pending by pp_sort_particles is applied first
- * (enqueued on the run's stream). */
+ * (enqueued on the run's stream).  In the FP64 form the pointers may be written through: a
+ * sort that follows looks at the positions again (see pp_sort_particles). */
 pp_status pp_get_particles(pp_run* run, int32_t s, pp_particles* out);
 
 /* Time of the gather/push/deposit kernels: when enabled, HIP events bracket every

@@ -141,6 +141,7 @@ static void species_arrays(const pp_params* p, const Geom& g, int64_t n, Species
     } else {
         A.add(&S.bin_pre, nb);
         A.add(&S.tile_tot, nt + 1);
+        A.add(&S.far_bin, (size_t)n);
     }
 }
 
@@ -187,15 +188,16 @@ const char* pp_last_hip_error(void) { return g_err; }
 
 // Device bytes pp_create and pp_init_species allocate for a run at most (the caller-owned mesh
 // and particle arrays not included): the arrays without particles, the rank and permutation of
-// every species' particles and, in the split form, as much again for the largest species (the
-// first sort's scratch, which those two arrays serve as today).
+// every species' particles (in the FP64 form a bin as well) and, in the split form, two words a particle
+// of the largest species again (the first sort's scratch, which those two arrays serve as today).
 static size_t internal_bytes(const pp_params* p, const Geom& g, int64_t nmax, int nsp) {
     pp_run r;
     Arena A, B;
     run_arrays(p, g, &r, A);
     species_arrays(p, g, 0, r.sp[0], B);
     const size_t pair = 2 * (size_t)nmax * sizeof(int32_t);
-    return A.size + (size_t)nsp * (B.size + pair) + (p->precision == PP_PREC_FP32_SPLIT ? pair : 0);
+    const bool split = p->precision == PP_PREC_FP32_SPLIT;
+    return A.size + (size_t)nsp * (B.size + (split ? pair : pair + pair / 2)) + (split ? pair : 0);
 }
 
 static void make_geom_host(const pp_params* p, Geom& g) {
@@ -370,15 +372,15 @@ pp_status pp_gather_push_deposit(pp_run* r) {
             if (!r->sp[s].active) continue;
             Species& S = r->sp[s];
             S.binned = false;  // the particles move: their bins are those of the last sort
-            const bool counts_left = S.ranked;  // by an earlier push that no sort has followed
-            S.ranked = (done & (1u << s)) != 0;
-            if (S.ranked) {
+            const bool by_tiles = (done & (1u << s)) != 0;
+            if (by_tiles) {
                 if (S.pending) swap_buffers(S.cur);  // the kernel wrote the pending order
                 S.pending = false;
+                S.ranked = true;
                 continue;
             }
             if (!ok(materialize(r, s), "materialize")) return PP_E_HIP;
-            if (counts_left && !ok(launch_fill_i32(S.cell_cnt, r->g.nbins, 0, r->stream), "fill")) return PP_E_HIP;
+            if (!ok(drop_ranks(r, s), "fill")) return PP_E_HIP;  // of an earlier push that no sort has followed
             e = launch_gpd64(r, s, target);
             if (!ok(e, "gather_push_deposit")) return PP_E_HIP;
         }
@@ -493,6 +495,8 @@ pp_status pp_get_particles(pp_run* r, int32_t s, pp_particles* out) {
     if (!r || !out || s < 0 || s >= PP_MAX_SPECIES) return PP_E_ARG;
     if (!r->sp[s].active) return PP_E_STATE;
     if (!ok(materialize(r, s), "materialize")) return PP_E_HIP;  // the buffers in sort order
+    // the caller may write the positions it is handed: the next sort looks at them again
+    if (r->p.precision == PP_PREC_FP64 && !ok(drop_ranks(r, s), "fill")) return PP_E_HIP;
     *out = r->sp[s].cur;
     return PP_OK;
 }

@@ -28,9 +28,11 @@ struct Gpd64Args {
     double* u_o[3];
     const int64_t* id;  // tags that move along (nullptr: none, or in place)
     int64_t* id_o;
-    // for the next sort (tiled kernel): particles per new bin, rank word per slot
+    // for the next sort (tiled kernel): particles per new bin, rank word per slot, bin per slot whose
+    // word has no room for it
     int32_t* cnt;
     int32_t* rank;
+    int32_t* far_bin;
     const double* E;
     const double* B;
     double* J;
@@ -348,6 +350,14 @@ __device__ __forceinline__ int32_t bin_of(const Gpd64TileArgs& A, const int c[3]
     return tile * TILE_CELLS + lc;
 }
 
+// cell of entry q of a tile's destination window (se: its extents)
+__device__ __forceinline__ void window_cell(const Gpd64Args& G, const int org[3], const int se[3], int q, int c[3]) {
+    const int z = q / (se[0] * se[1]), r = q - z * se[0] * se[1], y = r / se[0], x = r - y * se[0];
+    c[0] = se[0] == 1 ? 0 : wrap_near(org[0] + x - DEST_HALO, G.n[0]);
+    c[1] = se[1] == 1 ? 0 : wrap_near(org[1] + y - DEST_HALO, G.n[1]);
+    c[2] = se[2] == 1 ? 0 : wrap_near(org[2] + z - DEST_HALO, G.n[2]);
+}
+
 __device__ __forceinline__ void lds_add_f64(double* p, double v) {
     __hip_atomic_fetch_add((__attribute__((address_space(3))) double*)p, v, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -575,7 +585,9 @@ __global__ void __launch_bounds__(GPD64_BS, 3) k_gpd64_tile(Gpd64TileArgs A) {
                 rank |= sl << 20;
             } else {
                 if (win) atomicSub(L.slot(cur, sl), 1);  // past the word's range: counted below instead
-                rank = (int32_t)(0x80000000u | (uint32_t)atomicAdd(&S.cnt[bin_of(A, c)], 1));
+                const int32_t bin = bin_of(A, c);
+                rank = (int32_t)(0x80000000u | (uint32_t)atomicAdd(&S.cnt[bin], 1));
+                S.far_bin[q] = bin;
             }
             S.rank[q] = rank;
         }
@@ -584,10 +596,8 @@ __global__ void __launch_bounds__(GPD64_BS, 3) k_gpd64_tile(Gpd64TileArgs A) {
         for (int q = threadIdx.x; q < nslots; q += GPD64_BS) {
             int32_t* slot = L.slot(cur, q);
             if (*slot == 0) continue;
-            const int z = q / (se[0] * se[1]), r = q - z * se[0] * se[1], y = r / se[0], x = r - y * se[0];
-            const int c[3] = {se[0] == 1 ? 0 : wrap_near(org[0] + x - DEST_HALO, G.n[0]),
-                              se[1] == 1 ? 0 : wrap_near(org[1] + y - DEST_HALO, G.n[1]),
-                              se[2] == 1 ? 0 : wrap_near(org[2] + z - DEST_HALO, G.n[2])};
+            int c[3];
+            window_cell(G, org, se, q, c);
             *slot = atomicAdd(&S.cnt[bin_of(A, c)], *slot);
         }
         __syncthreads();
@@ -596,9 +606,16 @@ __global__ void __launch_bounds__(GPD64_BS, 3) k_gpd64_tile(Gpd64TileArgs A) {
             if (q >= end) continue;
             const int32_t w = S.rank[q];
             if (w < 0) continue;
-            const int32_t rank = *L.slot(cur, w >> 20) + (w & 0xFFFFF);
-            // a rank past the word's range leaves its cell to the position
-            S.rank[q] = rank < (1 << 20) ? ((w >> 20) << 20) | rank : (int32_t)(0x80000000u | (uint32_t)rank);
+            const int sl = w >> 20;
+            const int32_t rank = *L.slot(cur, sl) + (w & 0xFFFFF);
+            if (rank < (1 << 20)) {
+                S.rank[q] = (sl << 20) | rank;
+            } else {  // past the word's range
+                int c[3];
+                window_cell(G, org, se, sl, c);
+                S.far_bin[q] = bin_of(A, c);
+                S.rank[q] = (int32_t)(0x80000000u | (uint32_t)rank);
+            }
         }
         __syncthreads();
         for (int q = threadIdx.x; q < nslots; q += GPD64_BS) *L.slot(cur, q) = 0;
@@ -640,6 +657,7 @@ static void gpd64_args(const pp_run* r, int s, double* J, Gpd64Args& A) {
     A.id_o = S.pending ? S.cur.id_alt : nullptr;
     A.cnt = S.cell_cnt;
     A.rank = S.rank;
+    A.far_bin = S.far_bin;
     A.E = r->mesh.E;
     A.B = r->mesh.B;
     A.J = J;

@@ -63,9 +63,11 @@ struct Species {
     // tile order of pp_sort.hip (valid when sorted).
     int32_t* offsets = nullptr;
     bool binned = false;  // FP64 form: sorted and not pushed since (offsets are the bins of the positions)
-    // FP64 form: starts of a tile's cells inside the tile (nbins), tile totals and starts (ntiles + 1)
+    // FP64 form: starts of a tile's cells inside the tile (nbins), tile totals and starts (ntiles + 1),
+    // the new bin of each particle whose rank word has no room for its cell (n; other entries unused)
     int32_t* bin_pre = nullptr;
     int32_t* tile_tot = nullptr;
+    int32_t* far_bin = nullptr;
     // filled by the (tiled) particle kernel for the next sort: particles per cell of the
     // new positions (ncell, FP64 form per bin; zero between steps), each particle's rank among the
     // particles of its new cell (n; as pp_sort.hip reads it), per tile and destination cell the
@@ -199,6 +201,9 @@ int64_t field_blocks(const pp_run* r, int nruns);
 // by bucketing and a per-tile rebuild.
 hipError_t launch_sort(pp_run* r, int s);
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st);
+// FP64 form: forget the push's counts and ranks of species s, so that the next sort counts the
+// positions as they are then
+hipError_t drop_ranks(pp_run* r, int s);
 void sort_enqueued(pp_run* r, int s);  // host bookkeeping after a ranked sort was enqueued
 // move the particles of species s (or of every species, s = -1) to a pending sort order
 hipError_t materialize(pp_run* r, int s);

@@ -438,7 +438,7 @@ struct RankedArgs {
     // tile's cells inside it; no round table, rank base or overflow
     int32_t* pre;
     int32_t* next_bins;
-    const double* pos[3];
+    const int32_t* far_bin;
 };
 
 // FP64 form, one wavefront per tile: the cells' starts inside the tile and its total
@@ -709,7 +709,8 @@ __device__ __forceinline__ void ranked_perm_tile(const RankedArgs& A, int64_t T,
 
 // FP64 form: perm[slot] = particle for the particles of source tile T, and T's next bin starts.  A
 // rank word holds the destination cell and the rank in it (slot << 20 | rank, or bit 31 | rank
-// with the cell taken from the position), so a particle's slot is one LDS lookup away.
+// with the cell's bin in far_bin), so a particle's slot is one LDS lookup away.  Positions are not
+// looked at: the slots are a permutation whatever the caller has done to them since the push.
 __device__ __forceinline__ void bin_perm_tile(const RankedArgs& A, int64_t T, int32_t* lds) {
     const Geom& G = A.G;
     if (T >= G.ntiles) return;
@@ -724,10 +725,11 @@ __device__ __forceinline__ void bin_perm_tile(const RankedArgs& A, int64_t T, in
     }
     if (staged)
         for (int32_t q = threadIdx.x; q < nd; q += blockDim.x) img[q] = IMG_NONE;
+    auto bin_first = [&](int32_t bin) { return gl(A.tot)[bin / TILE_CELLS] + gl(A.pre)[bin]; };
     auto cell_first = [&](int gx, int gy, int gz) {
         const int32_t t = (gx >> A.tsh[0]) + G.nt[0] * ((gy >> A.tsh[1]) + G.nt[1] * (gz >> A.tsh[2]));
         const int lc = (gx & (G.t[0] - 1)) + ((gy & (G.t[1] - 1)) << A.tsh[0]) + ((gz & (G.t[2] - 1)) << (A.tsh[0] + A.tsh[1]));
-        return gl(A.tot)[t] + gl(A.pre)[t * TILE_CELLS + lc];
+        return bin_first(t * TILE_CELLS + lc);
     };
     const int e0 = G.dest_ext(0), e1 = G.dest_ext(1), slots = e0 * e1 * G.dest_ext(2);
     const int ox = (int)(T % G.nt[0]) * G.t[0], oy = (int)((T / G.nt[0]) % G.nt[1]) * G.t[1],
@@ -755,8 +757,7 @@ __device__ __forceinline__ void bin_perm_tile(const RankedArgs& A, int64_t T, in
             if (w[k] >= 0)
                 q = first[w[k] >> 20] + (w[k] & 0xFFFFF);
             else
-                q = cell_first(nearest_cell(gl(A.pos[0])[p], G.n[0]), nearest_cell(gl(A.pos[1])[p], G.n[1]),
-                               nearest_cell(gl(A.pos[2])[p], G.n[2])) + (w[k] & 0x7FFFFFFF);
+                q = bin_first(gl(A.far_bin)[p]) + (w[k] & 0x7FFFFFFF);
             if (staged && q >= d0 && q < d0 + nd)
                 img[q - d0] = (uint16_t)(p - ss);
             else
@@ -932,7 +933,7 @@ void sort_desc(const pp_run* r, int s, RankedArgs* A) {
     A->cell = S.cur.cell;
     A->pre = S.bin_pre;
     A->next_bins = S.offsets_next;
-    for (int d = 0; d < 3; ++d) A->pos[d] = split ? nullptr : (const double*)S.cur.pos[d];
+    A->far_bin = S.far_bin;
 }
 
 size_t sort_desc_size() { return sizeof(RankedArgs); }
@@ -1203,6 +1204,13 @@ hipError_t launch_sort(pp_run* r, int s) {
         if (e != hipSuccess) return e;
     }
     return sort_ranked(r, ranked);
+}
+
+hipError_t drop_ranks(pp_run* r, int s) {
+    Species& S = r->sp[s];
+    if (!S.ranked) return hipSuccess;
+    S.ranked = false;
+    return launch_fill_i32(S.cell_cnt, r->g.nbins, 0, r->stream);
 }
 
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st) {

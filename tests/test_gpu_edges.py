@@ -62,3 +62,111 @@ def test_charge_of_a_single_cell(ppm, count, q):
             d = run.diagnostics(ppm.PP_DIAG_RHO)
             assert abs(d.gauss_max - abs(q * count + background)) < 1e-12 * abs(q) * count
         run.close()
+
+
+def _tile(n):
+    """Sides of a tile: powers of two, 64 cells where the box allows."""
+    t = [1, 1, 1]
+    while np.prod(t) < 64 and any(t[d] < n[d] for d in range(3)):
+        t[min((d for d in range(3) if t[d] < n[d]), key=lambda d: t[d])] *= 2
+    return t
+
+
+def _in_cell_order(pos, n):
+    """The FP64 form's particles lie cell by cell, the cells tile by tile."""
+    t, N = _tile(n), np.array(n)[:, None]
+    nt = [-(-n[d] // t[d]) for d in range(3)]
+    c = np.floor(pos + 0.5).astype(int)
+    c = np.where(c >= N, c - N, c)
+    tile = c[0] // t[0] + nt[0] * (c[1] // t[1] + nt[1] * (c[2] // t[2]))
+    key = tile * 64 + c[0] % t[0] + t[0] * (c[1] % t[1] + t[1] * (c[2] % t[2]))
+    return bool(np.all(np.diff(key) >= 0))
+
+
+def _by_id(parts):
+    order = np.argsort(parts["id"])
+    return {k: v[..., order] for k, v in parts.items()}
+
+
+@pytest.mark.parametrize("views", ["taken after each push", "held from the start"])
+@pytest.mark.parametrize("n,O", [((16, 12, 9), 3), ((24, 17, 1), 2), ((70, 1, 1), 3)])
+def test_fp64_positions_written_between_push_and_sort(ppm, orc, n, O, views):
+    """A caller that moves particles to other cells between a push and its sort, twice in a row, so that
+    the second time they lie far from the tile they were pushed in: no particle is lost, the current is
+    that of the same particles pushed unsorted (FP64 sums in another order, 1e-12 of the largest
+    value), and with the pointers taken after the push the sort orders them by the cells they are in."""
+    import torch
+    species, E, B = random_state(orc, n, 40, seed=6, uth=0.4, nspecies=1)
+    count = species[0]["u"].shape[1]
+    rng = np.random.default_rng(9)
+    places = [torch.as_tensor(rng.uniform(0, 1, (3, count)) * (np.array(n, float)[:, None] - 1e-9)).cuda() for _ in range(2)]
+    kw = dict(n=n, dt=0.35, shape_order=O, field_order=2, relax_max_iter=100, precision=ppm.PP_PREC_FP64)
+    out = []
+    for sort in (True, False):
+        run = ppm.Run(ppm.make_params(**kw), species, E=E, B=B)
+        held = run.particle_tensors(0)
+        own = run.bufs[0]
+        other = own["alt"] if held["id"].data_ptr() == own["id"].data_ptr() else own
+        for i, where in enumerate(places):
+            run.gather_push_deposit()
+            if views == "taken after each push":
+                T = run.particle_tensors(0)
+            else:  # the first push works in place, one that finds an order pending in the other buffers
+                T = other if i and sort else held
+            sel = (T["id"] % 3 == 0).nonzero()[:, 0]
+            for d in range(3):
+                T["pos"][d][sel] = where[d][T["id"][sel]]
+            if sort:
+                run.sort()
+                if views == "taken after each push":
+                    assert _in_cell_order(run.particles(0)["pos"], n)
+        run.gather_push_deposit()
+        parts = _by_id(run.particles(0))
+        assert np.array_equal(parts["id"], np.arange(count))
+        assert run.diagnostics().flags == 0
+        out.append((run.fields()[2], parts))
+        run.close()
+    (J1, p1), (J2, p2) = out
+    assert rel_inf(J1, J2) < 1e-12
+    assert np.max(np.abs(periodic_diff(p1["pos"], p2["pos"], n))) < 1e-12
+    assert rel_inf(p1["u"], p2["u"]) < 1e-12
+
+
+@pytest.mark.parametrize("precision", ["split", "fp64"])
+def test_sort_of_more_particles_in_a_cell_than_a_rank_word_counts(ppm, orc, precision):
+    """1.2e6 particles of a tile bound for one cell, whose rank words count to 2^20: the sort loses none
+    and keeps the cell order, and the next current is the same for the particles in another order
+    (split form, bit for bit) or left unsorted (FP64, 1e-12 of the largest value)."""
+    from paper_1211_4575_amd import inputs as I
+    n, heavy, rest = (8, 8, 8), 1_200_000, 3000
+    count = heavy + rest
+    rng = np.random.default_rng(3)
+    pos = np.concatenate([np.array([2.3, 5.2, 1.4])[:, None] + rng.uniform(-0.1, 0.1, (3, heavy)),
+                          rng.uniform(0, 8, (3, rest))], 1)
+    u = np.concatenate([np.full((3, heavy), 0.01), rng.normal(0, 0.3, (3, rest))], 1)
+    split = precision == "split"
+    s = dict(q=-1.0, m=1.0, w=1.0 / count, u=u)
+    if split:
+        cell, off = I.to_split(pos, n, origin=I.split_origin(2))
+        s.update(cell=cell, off=off, u=u.astype(np.float32))
+    else:
+        s.update(pos=pos)
+    kw = dict(n=n, dt=0.35, shape_order=2, field_order=2, relax_max_iter=100,
+              precision=ppm.PP_PREC_FP32_SPLIT if split else ppm.PP_PREC_FP64)
+    out = []
+    for first in (True, False):
+        if split and not first:
+            s = dict(s, **{k: np.ascontiguousarray(s[k][..., ::-1]) for k in ("cell", "off", "u")})
+        run = ppm.Run(ppm.make_params(**kw), [s])
+        for _ in range(2):
+            run.gather_push_deposit()
+            if split or first:
+                run.sort()
+        parts = run.particles(0)
+        assert np.array_equal(np.sort(parts["id"]), np.arange(count))
+        assert split or not first or _in_cell_order(parts["pos"], n)
+        run.gather_push_deposit()
+        assert run.diagnostics().flags == 0
+        out.append(run.fields()[2])
+        run.close()
+    assert np.array_equal(*out) if split else rel_inf(*out) < 1e-12
