@@ -27,6 +27,9 @@
  *   - Streams: all work is enqueued asynchronously on the HIP stream given to
  *     pp_create; a call returns once its kernels are enqueued, except
  *     pp_diagnostics, which synchronises the stream before it returns.
+ *   - Capture: the calls of a step may be captured into a HIP graph (after pp_timing_enable(0)).
+ *     Species buffers swap roles from step to step, so a graph that is replayed holds an even
+ *     number of steps; the run's host state counts only the captured ones.
  *   - Errors: calls return a pp_status; host-side validation happens before
  *     anything is enqueued, and a failing call enqueues nothing.  Device-side
  *     faults of the data (a particle moving a cell or more in a step, non-finite

@@ -360,7 +360,9 @@ pp_status pp_gather_push_deposit(pp_run* r) {
         if (!ok(e, "gather_push_deposit")) return PP_E_HIP;
         for (int s = 0; s < PP_MAX_SPECIES; ++s) {  // the kernel wrote the pending order
             Species& S = r->sp[s];
-            if (!S.active || !S.pending) continue;
+            if (!S.active) continue;
+            S.moved = S.pending;
+            if (!S.pending) continue;
             swap_buffers(S.cur);
             S.pending = false;
         }
@@ -374,6 +376,7 @@ pp_status pp_gather_push_deposit(pp_run* r) {
             S.binned = false;  // the particles move: their bins are those of the last sort
             const bool by_tiles = (done & (1u << s)) != 0;
             if (by_tiles) {
+                S.moved = S.pending;
                 if (S.pending) swap_buffers(S.cur);  // the kernel wrote the pending order
                 S.pending = false;
                 S.ranked = true;

@@ -84,6 +84,7 @@ struct Species {
     // moves the particles
     int32_t* perm = nullptr;
     bool pending = false;
+    bool moved = false;  // the last push wrote a pending order (it worked in place otherwise)
 };
 
 // Line-solve stencil of one axis: out[i] = sum_j coef[j] * in[(i + off + j) mod n].

@@ -1093,6 +1093,11 @@ static void launch_ranked(pp_run* r, const SortArgs& A, unsigned ns, bool any, s
                            r->stream, A);
 }
 
+static bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+    return st && hipStreamIsCapturing(st, &c) == hipSuccess && c == hipStreamCaptureStatusActive;
+}
+
 // The ranked sort of the species in mask, together.
 static hipError_t sort_ranked(pp_run* r, unsigned mask) {
     SortArgs A;
@@ -1109,8 +1114,19 @@ static hipError_t sort_ranked(pp_run* r, unsigned mask) {
     else
         launch_ranked<SF_FP64>(r, A, ns, any, PERM_IMG * sizeof(uint16_t) + (size_t)r->g.dest_slots() * sizeof(int32_t));
     hipError_t e = hipGetLastError();
+    bool in_place = false;
     for (int s = 0; s < PP_MAX_SPECIES; ++s)
-        if (mask & (1u << s)) sort_enqueued(r, s);
+        if (mask & (1u << s)) {
+            sort_enqueued(r, s);
+            in_place = in_place || !r->sp[s].moved;
+        }
+    // Captured steps are replayed on the buffers they were captured with, so an even number of them
+    // has to end as it began.  With every push writing the order pending before it, it does; where the
+    // push before this sort found none (the first after pp_init_species or pp_get_particles), it does
+    // if the order is applied at once, as in the buffers' first sort.
+    if (e != hipSuccess || !in_place || !capturing(r->stream)) return e;
+    for (int s = 0; s < PP_MAX_SPECIES && e == hipSuccess; ++s)
+        if ((mask & (1u << s)) && !r->sp[s].moved) e = materialize(r, s);
     return e;
 }
 

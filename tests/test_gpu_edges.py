@@ -170,3 +170,56 @@ def test_sort_of_more_particles_in_a_cell_than_a_rank_word_counts(ppm, orc, prec
         out.append(run.fields()[2])
         run.close()
     assert np.array_equal(*out) if split else rel_inf(*out) < 1e-12
+
+
+@pytest.mark.parametrize("warmup", [0, 1])
+@pytest.mark.parametrize("precision,n", [("fp64", (12, 9, 8)), ("split", (12, 9, 8)), ("split", (24, 16, 1))])
+def test_captured_steps_replay(ppm, orc, precision, n, warmup):
+    """A pair of steps captured into a graph, right after the run's creation and after a step, replayed
+    with other work in between: the run stepped eagerly, in the split form bit for bit (FP64 sums in
+    another order, 1e-11 after eight steps)."""
+    import torch
+    from paper_1211_4575_amd import inputs as I
+    species, E, B = random_state(orc, n, 6, seed=14, uth=0.4)
+    split = precision == "split"
+    if split:
+        parts = [I.to_split(s["pos"], n, origin=I.split_origin(3)) for s in species]
+        species = [dict(q=s["q"], m=s["m"], w=s["w"], cell=c, off=o, u=s["u"].astype(np.float32))
+                   for s, (c, o) in zip(species, parts)]
+    kw = dict(n=n, dt=0.3, shape_order=3, field_order=4, relax_max_iter=100,
+              precision=ppm.PP_PREC_FP32_SPLIT if split else ppm.PP_PREC_FP64)
+    stream = torch.cuda.Stream()
+    out = []
+    for captured in (True, False):
+        with torch.cuda.stream(stream):
+            run = ppm.Run(ppm.make_params(**kw), species, E=E, B=B)
+            for _ in range(warmup):
+                run.step()
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            if captured:
+                with torch.cuda.graph(graph, stream=stream):
+                    run.step()
+                    run.step()
+            fields = []
+            for _ in range(3):
+                if captured:
+                    graph.replay()
+                else:
+                    run.step()
+                    run.step()
+                torch.cuda.synchronize()
+                torch.ones(1 << 16, device="cuda").cumsum(0)
+                fields.append(run.fields())
+            run.step()  # eagerly after the replays, on the buffers they left
+            fields.append(run.fields())
+            assert run.diagnostics().flags == 0
+            out.append((fields, [_by_id(run.particles(s)) for s in range(2)]))
+            del graph
+            run.close()
+    for f, g in zip(out[0][0], out[1][0]):
+        for a, b in zip(f, g):
+            assert np.array_equal(a, b) if split else rel_inf(a, b) < 1e-11
+    for p, q in zip(out[0][1], out[1][1]):
+        for k in p:
+            assert np.array_equal(p[k], q[k]) if split else np.max(np.abs(p[k] - q[k])) < 1e-11
