@@ -27,7 +27,7 @@ void field_setup(pp_run* r, double* consts);  // consts: host copy of the run's 
 int line_setup_axis(int order, int N, double* coef_host, int* off);
 int64_t scan_tmp_size(int64_t n);
 int diag_acc_count();
-int64_t diag_buffer_count();
+int64_t diag_buffer_count(int64_t ncell);
 size_t gpd32_lds_bytes(const pp_run* r);
 
 static bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
@@ -119,7 +119,7 @@ static void run_arrays(const pp_params* p, const Geom& g, pp_run* r, Arena& A) {
     A.add(&r->rho_prev, nc);
     A.add(&r->sort_cursor, (size_t)g.nbins);
     A.add(&r->scan_tmp, (size_t)scan_tmp_size(g.nbins + 1));
-    A.add(&r->dacc, (size_t)diag_buffer_count());
+    A.add(&r->dacc, (size_t)diag_buffer_count(g.ncell));
     A.add(&r->consts, 3 * omega_count(p) + 3 * 127);
     // cleared at the start, together: the flag word, the largest tiles, the fixed-point current
     A.add(&r->flags, 1);

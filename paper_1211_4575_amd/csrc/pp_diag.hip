@@ -54,7 +54,11 @@ hipError_t launch_fill(double* p, int64_t n, double v, hipStream_t st) {
 // Sums and maxima over particles or cells: each workgroup writes its value of every row to the
 // row's partials, and k_finish combines them in a fixed order (atomics on one address are served
 // one after another, about 13 ns each: 5.2e6 particles' moments took 2 x 160 us that way).
-constexpr int PART_MAX = 512;  // partials of a row: workgroups of a launch
+// Partials of a row, the workgroups that a launch can have: 512 (two a CU) are enough where the caches
+// hold the box, and cost a small run little memory; a large box needs the 4096 to wait for memory in
+// enough places at once.  256^3, 64 particles per cell: residuals and moments 684 and 3180 us with 512,
+// 340 and 2564 with 2048, 329 and 2500 with 4096.
+static int part_max(int64_t ncell) { return (int)(ncell < 512 * 128 ? 512 : (ncell > 4096 * 128 ? 4096 : ncell / 128)); }
 enum { ROW_SPECIES = 0, ROW_FIELD = 4 * PP_MAX_SPECIES, ROW_RESID = ROW_FIELD + 3, ROW_COUNT = ROW_RESID + 3 };
 
 template <bool MAX>
@@ -63,7 +67,7 @@ __device__ __forceinline__ double join(double a, double b) {
 }
 
 template <int NV, bool MAX>
-__device__ __forceinline__ void write_partials(double v[NV], double* part) {
+__device__ __forceinline__ void write_partials(double v[NV], double* part, int row) {
     __shared__ double sh[NV][4];
 #pragma unroll
     for (int a = 0; a < NV; ++a)
@@ -75,16 +79,18 @@ __device__ __forceinline__ void write_partials(double v[NV], double* part) {
     if (threadIdx.x == 0)
 #pragma unroll
         for (int a = 0; a < NV; ++a)
-            part[(int64_t)a * PART_MAX + blockIdx.x] =
+            part[(int64_t)a * row + blockIdx.x] =
                 join<MAX>(join<MAX>(sh[a][0], sh[a][1]), join<MAX>(sh[a][2], sh[a][3]));
 }
 
 constexpr int DIAG_UNROLL = 4;
 
-// workgroups of 256 threads for a sum over n entries: each has a few rounds of work
-static unsigned sum_grid(int64_t n) {
-    const int64_t g = (n + 256 * DIAG_UNROLL - 1) / (256 * DIAG_UNROLL);
-    return (unsigned)(g < 1 ? 1 : (g > PART_MAX ? PART_MAX : g));
+// workgroups of 256 threads for a sum over n entries: up to 1024 with a round of work each, and more if
+// each has 64 rounds (128^3, 64 particles per cell: moments 323 us with 1024, 382 with 4096)
+static unsigned sum_grid(int64_t n, int most) {
+    const int64_t round = 256 * DIAG_UNROLL, rounds = (n + round - 1) / round;
+    const int64_t g = rounds <= 1024 ? rounds : (rounds / 64 > 1024 ? rounds / 64 : 1024);
+    return (unsigned)(g < 1 ? 1 : (g > most ? most : g));
 }
 
 // kinetic energy w V m u^2/(gamma + 1) (= w V m c^2 (gamma - 1)) and momentum w V m u of every
@@ -96,6 +102,7 @@ struct MomentArgs {
     int slot[PP_MAX_SPECIES];
     double ic;
     double* part;
+    int row;  // entries of a row of partials
 };
 
 template <typename T>
@@ -131,11 +138,12 @@ __global__ void __launch_bounds__(256) k_moments(MomentArgs A) {
     }
 #pragma unroll
     for (int a = 0; a < 4; ++a) v[a] *= A.wVm[s];
-    write_partials<4, false>(v, A.part + (int64_t)(ROW_SPECIES + 4 * A.slot[s]) * PART_MAX);
+    write_partials<4, false>(v, A.part + (int64_t)(ROW_SPECIES + 4 * A.slot[s]) * A.row, A.row);
 }
 
 __global__ void __launch_bounds__(256) k_field_energy(const double* __restrict__ E, const double* __restrict__ B,
-                                                      int64_t nc, double hV_eps0, double hV_imu0, double* part) {
+                                                      int64_t nc, double hV_eps0, double hV_imu0, double* part,
+                                                      int row) {
     double v[3] = {0, 0, 0};
 #pragma unroll 2
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < nc; q += (int64_t)gridDim.x * blockDim.x) {
@@ -148,7 +156,7 @@ __global__ void __launch_bounds__(256) k_field_energy(const double* __restrict__
     v[0] *= hV_eps0;
     v[1] *= hV_imu0;
     v[2] *= hV_eps0;
-    write_partials<3, false>(v, part + (int64_t)ROW_FIELD * PART_MAX);
+    write_partials<3, false>(v, part + (int64_t)ROW_FIELD * row, row);
 }
 
 // rho(node) += q w W(X - node), FP64, for either particle form
@@ -491,7 +499,8 @@ __device__ __forceinline__ double div_up(const DivGeom& G, const double* F, int 
 __global__ void __launch_bounds__(256) k_residuals(DivGeom G, const double* __restrict__ E, const double* __restrict__ J,
                                                    const double* __restrict__ B, const double* __restrict__ rho,
                                                    const double* __restrict__ rho_prev, double rho_bg, double ieps0,
-                                                   double dt, int want_rho, int have_prev, int want_divb, double* part) {
+                                                   double dt, int want_rho, int have_prev, int want_divb, double* part,
+                                                   int part_row) {
     double g = 0.0, cc = 0.0, db = 0.0;
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < G.nc; q += (int64_t)gridDim.x * blockDim.x) {
         const int row = (int)(((double)q + 0.5) * G.inv_n0), k = (int)(((double)row + 0.5) * G.inv_n1);
@@ -503,7 +512,7 @@ __global__ void __launch_bounds__(256) k_residuals(DivGeom G, const double* __re
         if (want_divb) db = fmax(db, fabs(div_up(G, B, i, j, k)));
     }
     double v[3] = {g, cc, db};
-    write_partials<3, true>(v, part + (int64_t)ROW_RESID * PART_MAX);
+    write_partials<3, true>(v, part + (int64_t)ROW_RESID * part_row, part_row);
 }
 
 static void fd_coeffs(int order, double a[3]) {
@@ -630,30 +639,32 @@ struct FinishArgs {
     const double* part;
     double* dacc;
     int32_t* flags;
+    int stride;            // entries of a row of partials
     int count[ROW_COUNT];  // partials of each row
 };
 
-__global__ void __launch_bounds__(1024) k_finish(FinishArgs A) {
-    const int lane = threadIdx.x & 63;
-    for (int row = threadIdx.x >> 6; row < ROW_COUNT; row += 16) {
-        const bool mx = row >= ROW_RESID;
-        double v = 0.0;
-        for (int i = lane; i < A.count[row]; i += 64) {
-            const double x = A.part[(int64_t)row * PART_MAX + i];
-            v = mx ? fmax(v, x) : v + x;
-        }
-        for (int o = 32; o > 0; o >>= 1) {
-            const double x = __shfl_xor(v, o, 64);
-            v = mx ? fmax(v, x) : v + x;
-        }
-        int to;
-        if (row < ROW_FIELD)
-            to = row % 4 == 0 ? ACC_KIN + row / 4 : ACC_MOM + 3 * (row / 4) + row % 4 - 1;
-        else
-            to = row < ROW_RESID ? ACC_UE + row - ROW_FIELD : ACC_GAUSS + row - ROW_RESID;
-        if (lane == 0) A.dacc[to] = v;
-    }
-    if (threadIdx.x == 0) {
+constexpr int FINISH_BS = 256;
+
+// a workgroup per row
+__global__ void __launch_bounds__(FINISH_BS) k_finish(FinishArgs A) {
+    __shared__ double sh[FINISH_BS / 64];
+    const int row = blockIdx.x;
+    const bool mx = row >= ROW_RESID;
+    auto joined = [&](double a, double b) { return mx ? fmax(a, b) : a + b; };
+    double v = 0.0;
+    for (int i = threadIdx.x; i < A.count[row]; i += FINISH_BS) v = joined(v, A.part[(int64_t)row * A.stride + i]);
+    for (int o = 32; o > 0; o >>= 1) v = joined(v, __shfl_xor(v, o, 64));
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < FINISH_BS / 64; ++w) v = joined(v, sh[w]);
+    int to;
+    if (row < ROW_FIELD)
+        to = row % 4 == 0 ? ACC_KIN + row / 4 : ACC_MOM + 3 * (row / 4) + row % 4 - 1;
+    else
+        to = row < ROW_RESID ? ACC_UE + row - ROW_FIELD : ACC_GAUSS + row - ROW_RESID;
+    A.dacc[to] = v;
+    if (row == 0) {
         A.dacc[ACC_FLAGS] = (double)*A.flags;
         *A.flags = 0;
     }
@@ -671,6 +682,8 @@ hipError_t launch_diag(pp_run* r, uint32_t what, double* host_out) {
     F.dacc = r->dacc;
     F.flags = r->flags;
     double* part = r->dacc + ACC_PART;
+    const int most = part_max(nc);
+    F.stride = most;
     const bool split = r->p.precision == PP_PREC_FP32_SPLIT;
     const double V = r->p.d[0] * r->p.d[1] * r->p.d[2];
     const double ic = 1.0 / r->p.c;
@@ -690,8 +703,9 @@ hipError_t launch_diag(pp_run* r, uint32_t what, double* host_out) {
         }
         A.ic = ic;
         A.part = part;
+        A.row = most;
         if (ns > 0) {
-            const dim3 grid(sum_grid(nmax), ns);
+            const dim3 grid(sum_grid(nmax, most), ns);
             for (unsigned k = 0; k < ns; ++k)
                 for (int a = 0; a < 4; ++a) F.count[ROW_SPECIES + 4 * A.slot[k] + a] = (int)grid.x;
             if (split)
@@ -702,9 +716,9 @@ hipError_t launch_diag(pp_run* r, uint32_t what, double* host_out) {
     }
     if (what & PP_DIAG_FIELDS) {
         const double mu0 = 1.0 / (r->p.eps0 * r->p.c * r->p.c);
-        hipLaunchKernelGGL(k_field_energy, dim3(sum_grid(nc)), dim3(bs), 0, r->stream, (const double*)r->mesh.E,
-                           (const double*)r->mesh.B, nc, 0.5 * r->p.eps0 * V, 0.5 * V / mu0, part);
-        for (int a = 0; a < 3; ++a) F.count[ROW_FIELD + a] = (int)sum_grid(nc);
+        hipLaunchKernelGGL(k_field_energy, dim3(sum_grid(nc, most)), dim3(bs), 0, r->stream, (const double*)r->mesh.E,
+                           (const double*)r->mesh.B, nc, 0.5 * r->p.eps0 * V, 0.5 * V / mu0, part, most);
+        for (int a = 0; a < 3; ++a) F.count[ROW_FIELD + a] = (int)sum_grid(nc, most);
     }
     const bool want_rho = (what & PP_DIAG_RHO) != 0;
     const bool want_divb = (what & PP_DIAG_DIVB) != 0;
@@ -726,12 +740,12 @@ hipError_t launch_diag(pp_run* r, uint32_t what, double* host_out) {
         for (int d = 0; d < 3; ++d)
             for (int m = 0; m < 3; ++m) G.a[d][m] = a[m] / r->p.d[d];
         int64_t g = (nc + bs - 1) / bs;
-        if (g > PART_MAX) g = PART_MAX;
+        if (g > most) g = most;
         for (int a = 0; a < 3; ++a) F.count[ROW_RESID + a] = (int)g;
         hipLaunchKernelGGL(k_residuals, dim3((unsigned)g), dim3(bs), 0, r->stream, G, (const double*)r->mesh.E,
                            (const double*)r->mesh.J, (const double*)r->mesh.B, (const double*)r->rho,
                            (const double*)r->rho_prev, r->p.rho_background, 1.0 / r->p.eps0, r->dt_drift, want_rho ? 1 : 0,
-                           have_prev ? 1 : 0, want_divb ? 1 : 0, part);
+                           have_prev ? 1 : 0, want_divb ? 1 : 0, part, most);
     }
     const bool want_relax = (what & PP_DIAG_RELAX) != 0 && r->rhs_valid;
     if (want_relax) {
@@ -742,7 +756,7 @@ hipError_t launch_diag(pp_run* r, uint32_t what, double* host_out) {
     }
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_finish, dim3(1), dim3(1024), 0, r->stream, F);
+    hipLaunchKernelGGL(k_finish, dim3(ROW_COUNT), dim3(FINISH_BS), 0, r->stream, F);
     e = hipMemcpyAsync(host_out, r->dacc, (ACC_COUNT + 1) * sizeof(double), hipMemcpyDeviceToHost, r->stream);
     if (e != hipSuccess) return e;
     e = hipStreamSynchronize(r->stream);
@@ -759,6 +773,6 @@ hipError_t launch_diag(pp_run* r, uint32_t what, double* host_out) {
 }
 
 int diag_acc_count() { return ACC_COUNT; }
-int64_t diag_buffer_count() { return ACC_PART + (int64_t)ROW_COUNT * PART_MAX; }
+int64_t diag_buffer_count(int64_t ncell) { return ACC_PART + (int64_t)ROW_COUNT * part_max(ncell); }
 
 }  // namespace pp

@@ -223,3 +223,28 @@ def test_captured_steps_replay(ppm, orc, precision, n, warmup):
     for p, q in zip(out[0][1], out[1][1]):
         for k in p:
             assert np.array_equal(p[k], q[k]) if split else np.max(np.abs(p[k] - q[k])) < 1e-11
+
+
+@pytest.mark.parametrize("n,ppc", [((96, 83, 100), 2), ((64, 41, 26), 24), ((700, 300, 1), 6)])
+def test_sums_of_diagnostics_over_many_rounds(ppm, orc, n, ppc):
+    """Boxes and particle counts past the largest launch of the sums, whose workgroups take several
+    rounds: energies, momenta and the largest divergences and residuals against the oracle, which sums
+    the same FP64 values in another order (1e-11)."""
+    species, E, B = random_state(orc, n, ppc, seed=2, uth=0.5)
+    E[1, 0, 2, 3] = 90.0  # the largest residual, and the one of div B, in a known place
+    B[0, 0, 1, 5] = 70.0
+    kw = dict(n=n, dt=0.3, shape_order=3, field_order=4, relax_max_iter=100)
+    run = ppm.Run(ppm.make_params(precision=ppm.PP_PREC_FP64, **kw), species, E=E, B=B)
+    d = run.diagnostics()
+    run.close()
+    P = orc.make_params(**kw)
+    rho = np.zeros((n[2], n[1], n[0]))
+    for s, sp in enumerate(species):
+        kin, mom = orc.species_moments(P, sp["m"], sp["w"], sp["u"])
+        scale = sp["m"] * sp["w"] * np.sum(np.abs(sp["u"]))  # of the sums the momentum is left over from
+        assert abs(d.kinetic[s] / kin - 1.0) < 1e-11
+        assert np.max(np.abs(np.array(d.momentum[s]) - mom)) < 1e-11 * scale
+        orc.deposit_rho(P, sp["q"], sp["w"], sp["pos"], rho)
+    assert np.max(np.abs(np.array([d.field_E, d.field_B, d.field_Ex]) / orc.field_energy(P, E, B) - 1.0)) < 1e-11
+    assert abs(d.gauss_max / np.max(np.abs(orc.div_down(P, E) - rho)) - 1.0) < 1e-11
+    assert abs(d.divB_max / np.max(np.abs(orc.div_up(P, B))) - 1.0) < 1e-11
