@@ -248,3 +248,46 @@ def test_sums_of_diagnostics_over_many_rounds(ppm, orc, n, ppc):
     assert np.max(np.abs(np.array([d.field_E, d.field_B, d.field_Ex]) / orc.field_energy(P, E, B) - 1.0)) < 1e-11
     assert abs(d.gauss_max / np.max(np.abs(orc.div_down(P, E) - rho)) - 1.0) < 1e-11
     assert abs(d.divB_max / np.max(np.abs(orc.div_up(P, B))) - 1.0) < 1e-11
+
+
+@pytest.mark.parametrize("n", [(100, 101, 104), (128, 128, 64), (132, 128, 64)])
+def test_sort_of_boxes_around_the_largest_one_workgroup_scan(ppm, orc, n):
+    """Boxes of 16384 tiles and of a few more, two species of few particles and one heavy tile at the
+    box's end, and an empty species: no particle is lost, the FP64 form is in cell order, and the split
+    form's current, whose scale comes from the largest tile, agrees with it (FP32 offsets: 1e-5 in the
+    L2 norm) and is bit for bit the same for particles loaded in reverse."""
+    from paper_1211_4575_amd import inputs as I
+    rng = np.random.default_rng(12)
+    N = np.array(n, float)[:, None]
+    species = []
+    for s in range(2):
+        pos = np.concatenate([rng.uniform(0, 1, (3, 50000)) * (N - 1e-6), N - 3.5 + rng.uniform(0, 2, (3, 9000))], 1)
+        species.append(dict(q=(-1.0) ** s, m=1.0 + s, w=0.5, pos=pos, u=rng.normal(0, 0.4, pos.shape)))
+    empty = dict(q=1.0, m=1.0, w=1.0, pos=np.zeros((3, 0)), u=np.zeros((3, 0)))
+    kw = dict(n=n, dt=0.35, shape_order=3, field_order=2, relax_max_iter=100)
+    out = []
+    for form in ("split", "split, reversed", "fp64"):
+        sp = []
+        for s in species + [empty]:
+            cell, off = I.to_split(s["pos"], n, origin=I.split_origin(3))
+            u = s["u"].astype(np.float32)
+            if form == "fp64":
+                sp.append(dict(s, pos=I.from_split(cell, off, n), u=u.astype(np.float64)))
+                continue
+            k = slice(None, None, -1 if "reversed" in form else 1)
+            sp.append({**{x: s[x] for x in "qmw"}, "cell": np.ascontiguousarray(cell[k]),
+                       "off": np.ascontiguousarray(off[:, k]), "u": np.ascontiguousarray(u[:, k])})
+        run = ppm.Run(ppm.make_params(precision=ppm.PP_PREC_FP64 if form == "fp64" else ppm.PP_PREC_FP32_SPLIT, **kw), sp)
+        for _ in range(2):
+            run.gather_push_deposit()
+            run.sort()
+        for s in range(3):
+            parts = run.particles(s)
+            assert np.array_equal(np.sort(parts["id"]), np.arange(sp[s]["u"].shape[1]))
+            assert form != "fp64" or _in_cell_order(parts["pos"], n)
+        run.gather_push_deposit()
+        assert run.diagnostics(ppm.PP_DIAG_MOMENTS).flags == 0
+        out.append(run.fields()[2])
+        run.close()
+    assert np.array_equal(out[0], out[1])
+    assert np.linalg.norm(out[0] - out[2]) < 1e-5 * np.linalg.norm(out[2])
