@@ -132,7 +132,7 @@ static void species_arrays(const pp_params* p, const Geom& g, int64_t n, Species
     const size_t nt = (size_t)g.ntiles, nb = (size_t)g.nbins;
     A.add(&S.offsets, nb + 1);
     A.add(&S.offsets_next, (split ? nt : nb) + 1);
-    A.add(&S.cell_cnt, split ? (size_t)g.ncell : nb);
+    A.add(&S.cell_cnt, split ? (size_t)g.ncell : 2 * nb);
     A.add(&S.rank, (size_t)n);
     A.add(&S.perm, (size_t)n);
     if (split) {
@@ -141,7 +141,6 @@ static void species_arrays(const pp_params* p, const Geom& g, int64_t n, Species
     } else {
         A.add(&S.bin_pre, nb);
         A.add(&S.tile_tot, nt + 1);
-        A.add(&S.far_bin, (size_t)n);
     }
 }
 
@@ -188,16 +187,15 @@ const char* pp_last_hip_error(void) { return g_err; }
 
 // Device bytes pp_create and pp_init_species allocate for a run at most (the caller-owned mesh
 // and particle arrays not included): the arrays without particles, the rank and permutation of
-// every species' particles (in the FP64 form a bin as well) and, in the split form, two words a particle
-// of the largest species again (the first sort's scratch, which those two arrays serve as today).
+// every species' particles and, in the split form, as much again for the largest species (the
+// first sort's scratch, which those two arrays serve as today).
 static size_t internal_bytes(const pp_params* p, const Geom& g, int64_t nmax, int nsp) {
     pp_run r;
     Arena A, B;
     run_arrays(p, g, &r, A);
     species_arrays(p, g, 0, r.sp[0], B);
     const size_t pair = 2 * (size_t)nmax * sizeof(int32_t);
-    const bool split = p->precision == PP_PREC_FP32_SPLIT;
-    return A.size + (size_t)nsp * (B.size + (split ? pair : pair + pair / 2)) + (split ? pair : 0);
+    return A.size + (size_t)nsp * (B.size + pair) + (p->precision == PP_PREC_FP32_SPLIT ? pair : 0);
 }
 
 static void make_geom_host(const pp_params* p, Geom& g) {
@@ -320,7 +318,7 @@ pp_status pp_init_species(pp_run* r, int32_t s, double q, double m, double w, co
         if (!A.allocate(&S.arena)) return PP_E_HIP;
         S.arena_n = parts->n;
     }
-    if (!ok(launch_fill_i32(S.cell_cnt, split ? r->g.ncell : r->g.nbins, 0, r->stream), "fill")) return PP_E_HIP;
+    if (!ok(launch_fill_i32(S.cell_cnt, split ? r->g.ncell : 2 * r->g.nbins, 0, r->stream), "fill")) return PP_E_HIP;
     S.pending = false;
     S.active = true;
     S.q = q;

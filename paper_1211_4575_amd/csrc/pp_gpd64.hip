@@ -28,11 +28,11 @@ struct Gpd64Args {
     double* u_o[3];
     const int64_t* id;  // tags that move along (nullptr: none, or in place)
     int64_t* id_o;
-    // for the next sort (tiled kernel): particles per new bin, rank word per slot, bin per slot whose
-    // word has no room for it
+    // for the next sort (tiled kernel): particles per new bin whose words hold a rank, those whose words
+    // hold the bin alone, rank word per slot
     int32_t* cnt;
+    int32_t* named;
     int32_t* rank;
-    int32_t* far_bin;
     const double* E;
     const double* B;
     double* J;
@@ -350,6 +350,12 @@ __device__ __forceinline__ int32_t bin_of(const Gpd64TileArgs& A, const int c[3]
     return tile * TILE_CELLS + lc;
 }
 
+// rank word of a particle that only names its bin
+__device__ __forceinline__ int32_t name_bin(const Gpd64Args& S, int32_t bin) {
+    atomicAdd(&S.named[bin], 1);
+    return (int32_t)(0x80000000u | (uint32_t)bin);
+}
+
 // cell of entry q of a tile's destination window (se: its extents)
 __device__ __forceinline__ void window_cell(const Gpd64Args& G, const int org[3], const int se[3], int q, int c[3]) {
     const int z = q / (se[0] * se[1]), r = q - z * se[0] * se[1], y = r / se[0], x = r - y * se[0];
@@ -581,13 +587,11 @@ __global__ void __launch_bounds__(GPD64_BS, 3) k_gpd64_tile(Gpd64TileArgs A) {
             }
             int32_t rank = -1;
             if (win) rank = atomicAdd(L.slot(cur, sl), 1);
-            if (win && rank < (1 << 20)) {
+            if (win && rank < F64_RANKS) {
                 rank |= sl << 20;
             } else {
                 if (win) atomicSub(L.slot(cur, sl), 1);  // past the word's range: counted below instead
-                const int32_t bin = bin_of(A, c);
-                rank = (int32_t)(0x80000000u | (uint32_t)atomicAdd(&S.cnt[bin], 1));
-                S.far_bin[q] = bin;
+                rank = name_bin(S, bin_of(A, c));
             }
             S.rank[q] = rank;
         }
@@ -608,13 +612,12 @@ __global__ void __launch_bounds__(GPD64_BS, 3) k_gpd64_tile(Gpd64TileArgs A) {
             if (w < 0) continue;
             const int sl = w >> 20;
             const int32_t rank = *L.slot(cur, sl) + (w & 0xFFFFF);
-            if (rank < (1 << 20)) {
+            if (rank < F64_RANKS) {
                 S.rank[q] = (sl << 20) | rank;
-            } else {  // past the word's range
+            } else {  // past the word's range (the sort takes F64_RANKS of the cell's count for ranked)
                 int c[3];
                 window_cell(G, org, se, sl, c);
-                S.far_bin[q] = bin_of(A, c);
-                S.rank[q] = (int32_t)(0x80000000u | (uint32_t)rank);
+                S.rank[q] = name_bin(S, bin_of(A, c));
             }
         }
         __syncthreads();
@@ -656,8 +659,8 @@ static void gpd64_args(const pp_run* r, int s, double* J, Gpd64Args& A) {
     A.id = S.pending ? S.cur.id : nullptr;
     A.id_o = S.pending ? S.cur.id_alt : nullptr;
     A.cnt = S.cell_cnt;
+    A.named = S.cell_cnt + r->g.nbins;
     A.rank = S.rank;
-    A.far_bin = S.far_bin;
     A.E = r->mesh.E;
     A.B = r->mesh.B;
     A.J = J;

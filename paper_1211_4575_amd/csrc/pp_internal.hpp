@@ -24,6 +24,7 @@ constexpr int cur_lo(int) { return 2; }
 constexpr int cur_hi(int O) { return O + 1; }
 
 constexpr int DEST_HALO = 2;
+constexpr int F64_RANKS = 1 << 20;  // FP64 form: ranks in a cell that a rank word can hold
 
 struct Geom {
     int n[3];       // cells
@@ -63,13 +64,12 @@ struct Species {
     // tile order of pp_sort.hip (valid when sorted).
     int32_t* offsets = nullptr;
     bool binned = false;  // FP64 form: sorted and not pushed since (offsets are the bins of the positions)
-    // FP64 form: starts of a tile's cells inside the tile (nbins), tile totals and starts (ntiles + 1),
-    // the new bin of each particle whose rank word has no room for its cell (n; other entries unused)
+    // FP64 form: starts of a tile's cells inside the tile (nbins), tile totals and starts (ntiles + 1)
     int32_t* bin_pre = nullptr;
     int32_t* tile_tot = nullptr;
-    int32_t* far_bin = nullptr;
     // filled by the (tiled) particle kernel for the next sort: particles per cell of the
-    // new positions (ncell, FP64 form per bin; zero between steps), each particle's rank among the
+    // new positions (ncell; FP64 form per bin, 2 * nbins: those ranked, then those that only name their
+    // bin; zero between steps), each particle's rank among the
     // particles of its new cell (n; as pp_sort.hip reads it), per tile and destination cell the
     // ranks its particles start from (split form: ntiles * dest_slots), the next tile starts
     // (FP64 form: bin starts); the sort's round tables (split form: ntiles * SORT_RCAP)

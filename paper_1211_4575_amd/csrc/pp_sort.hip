@@ -438,14 +438,14 @@ struct RankedArgs {
     // tile's cells inside it; no round table, rank base or overflow
     int32_t* pre;
     int32_t* next_bins;
-    const int32_t* far_bin;
 };
 
 // FP64 form, one wavefront per tile: the cells' starts inside the tile and its total
 __device__ __forceinline__ void bin_prefix_tile(const RankedArgs& A, int64_t t) {
     const int lane = threadIdx.x & 63;
     if (t >= A.G.ntiles) return;
-    const int32_t c = gl(A.cnt)[t * TILE_CELLS + lane];
+    const int32_t ranked = gl(A.cnt)[t * TILE_CELLS + lane], named = gl(A.cnt)[A.G.nbins + t * TILE_CELLS + lane];
+    const int32_t c = (ranked < F64_RANKS ? ranked : F64_RANKS) + named;
     gl(A.cnt)[t * TILE_CELLS + lane] = 0;
     int32_t incl = c;
 #pragma unroll
@@ -777,9 +777,10 @@ __device__ __forceinline__ void ranked_perm_tile(const RankedArgs& A, int64_t T,
 }
 
 // FP64 form: perm[slot] = particle for the particles of source tile T, and T's next bin starts.  A
-// rank word holds the destination cell and the rank in it (slot << 20 | rank, or bit 31 | rank
-// with the cell's bin in far_bin), so a particle's slot is one LDS lookup away.  Positions are not
-// looked at: the slots are a permutation whatever the caller has done to them since the push.
+// rank word holds the destination cell and the rank in it (slot << 20 | rank), so a particle's slot is
+// one LDS lookup away, or the cell's bin alone (bit 31 | bin: far from its tile, or past F64_RANKS in
+// the cell); those fill the cell's range from its end, counting their number down to zero.  Positions
+// are not looked at: the slots are a permutation whatever has become of them since the push.
 __device__ __forceinline__ void bin_perm_tile(const RankedArgs& A, int64_t T, int32_t* lds) {
     const Geom& G = A.G;
     if (T >= G.ntiles) return;
@@ -823,10 +824,13 @@ __device__ __forceinline__ void bin_perm_tile(const RankedArgs& A, int64_t T, in
             const int64_t p = b + threadIdx.x + k * 256;
             if (p >= se) continue;
             int32_t q;
-            if (w[k] >= 0)
+            if (w[k] >= 0) {
                 q = first[w[k] >> 20] + (w[k] & 0xFFFFF);
-            else
-                q = bin_first(gl(A.far_bin)[p]) + (w[k] & 0x7FFFFFFF);
+            } else {
+                const int32_t bin = w[k] & 0x7FFFFFFF, t = bin / TILE_CELLS;
+                const int32_t end = bin % TILE_CELLS == TILE_CELLS - 1 ? gl(A.tot)[t + 1] : bin_first(bin + 1);
+                q = end - atomicSub(gl(A.cnt) + G.nbins + bin, 1);
+            }
             if (staged && q >= d0 && q < d0 + nd)
                 img[q - d0] = (uint16_t)(p - ss);
             else
@@ -1011,7 +1015,6 @@ void sort_desc(const pp_run* r, int s, RankedArgs* A) {
     A->cell = S.cur.cell;
     A->pre = S.bin_pre;
     A->next_bins = S.offsets_next;
-    A->far_bin = S.far_bin;
 }
 
 size_t sort_desc_size() { return sizeof(RankedArgs); }
@@ -1311,7 +1314,7 @@ hipError_t drop_ranks(pp_run* r, int s) {
     Species& S = r->sp[s];
     if (!S.ranked) return hipSuccess;
     S.ranked = false;
-    return launch_fill_i32(S.cell_cnt, r->g.nbins, 0, r->stream);
+    return launch_fill_i32(S.cell_cnt, 2 * r->g.nbins, 0, r->stream);
 }
 
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st) {

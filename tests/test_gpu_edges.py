@@ -133,16 +133,17 @@ def test_fp64_positions_written_between_push_and_sort(ppm, orc, n, O, views):
 
 
 @pytest.mark.parametrize("precision", ["split", "fp64"])
-def test_sort_of_more_particles_in_a_cell_than_a_rank_word_counts(ppm, orc, precision):
+@pytest.mark.parametrize("n", [(8, 8, 8), (32, 32, 36)], ids=["tile shared by workgroups", "a workgroup per tile"])
+def test_sort_of_more_particles_in_a_cell_than_a_rank_word_counts(ppm, orc, precision, n):
     """1.2e6 particles of a tile bound for one cell, whose rank words count to 2^20: the sort loses none
     and keeps the cell order, and the next current is the same for the particles in another order
     (split form, bit for bit) or left unsorted (FP64, 1e-12 of the largest value)."""
     from paper_1211_4575_amd import inputs as I
-    n, heavy, rest = (8, 8, 8), 1_200_000, 3000
+    heavy, rest = 1_200_000, 3000
     count = heavy + rest
     rng = np.random.default_rng(3)
     pos = np.concatenate([np.array([2.3, 5.2, 1.4])[:, None] + rng.uniform(-0.1, 0.1, (3, heavy)),
-                          rng.uniform(0, 8, (3, rest))], 1)
+                          rng.uniform(0, 1, (3, rest)) * np.array(n)[:, None]], 1)
     u = np.concatenate([np.full((3, heavy), 0.01), rng.normal(0, 0.3, (3, rest))], 1)
     split = precision == "split"
     s = dict(q=-1.0, m=1.0, w=1.0 / count, u=u)
