@@ -196,7 +196,9 @@ typedef struct pp_run pp_run;
  * scratch, per-species offsets), for nspecies species of at most
  * max_particles particles each; the caller-owned mesh and particle arrays are
  * not included.  For admission by memory footprint (several runs sharing one
- * GPU).  Validates params like pp_create; no device call. */
+ * GPU).  Besides bytes per cell and per particle, a split species takes about
+ * 4.5 KB per 64 cells for its sort however few particles it has.  Validates
+ * params like pp_create; no device call. */
 pp_status pp_workspace_size(const pp_params* params, int64_t max_particles, int32_t nspecies, size_t* bytes);
 
 /* Create a run: validates params, records the mesh views and the stream

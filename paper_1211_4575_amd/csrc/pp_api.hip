@@ -187,8 +187,12 @@ const char* pp_last_hip_error(void) { return g_err; }
 
 // Device bytes pp_create and pp_init_species allocate for a run at most (the caller-owned mesh
 // and particle arrays not included): the arrays without particles, the rank and permutation of
-// every species' particles and, in the split form, as much again for the largest species (the
-// first sort's scratch, which those two arrays serve as today).
+// every species' particles and, in the split form, as much again for the largest species (room that
+// the first sort no longer takes, in an upper bound that budgets are set by).  Per tile of 64 cells and
+// split species 2304 bytes are the sort's round table and, for 4x4x4 tiles, 2048 the ranks that the
+// tile's particles start from in each cell around it: each species has its own, so that one launch sorts
+// them all, and with few particles per cell they are most of a run's memory (256^3, eight species of one
+// particle per cell: 13.6 GB, of which 9.1; 64x32x32, two of 32: 69 MB, 8.9).
 static size_t internal_bytes(const pp_params* p, const Geom& g, int64_t nmax, int nsp) {
     pp_run r;
     Arena A, B;
