@@ -192,7 +192,7 @@ const char* pp_last_hip_error(void) { return g_err; }
 // split species 2304 bytes are the sort's round table and, for 4x4x4 tiles, 2048 the ranks that the
 // tile's particles start from in each cell around it: each species has its own, so that one launch sorts
 // them all, and with few particles per cell they are most of a run's memory (256^3, eight species of one
-// particle per cell: 13.6 GB, of which 9.1; 64x32x32, two of 32: 69 MB, 8.9).
+// particle per cell: 13.8 GB, of which 9.1; 64x32x32, two of 32: 69 MB, 8.9).
 static size_t internal_bytes(const pp_params* p, const Geom& g, int64_t nmax, int nsp) {
     pp_run r;
     Arena A, B;

@@ -13,19 +13,22 @@ namespace pp {
 // (a row of nx cells, padded to a power of two, several rows per block) or, for nx > 256, a
 // 256-cell chunk of one row; the remaining indices j, k come from the row number.  All
 // indices are 32-bit (a box has at most 2^30 cells).
-struct FieldGeom {
+struct CellGeom {
     int n[3];
-    int64_t nc;
-    int M;           // half-width of the first-derivative stencil (order / 2)
-    double a[3][3];  // a[axis][m-1] / d[axis]: first-derivative coefficients
-    int R;           // Laplacian half-width 2M - 1
-    double L[3][11]; // Laplacian stencil per axis, offsets -R..R
     int xchunks;     // 256-cell chunks per row (nx > 256), else 1
+    int64_t nc;
     int xbits;       // log2 of the padded row length inside a block (<= 8)
     int rows;        // ny * nz
     int rpb;         // rows per block
-    double inv_ny;   // 1 / ny (row -> j, k)
     int small;       // an axis shorter than the stencil reach: general wrap
+    double inv_ny;   // 1 / ny (row -> j, k)
+};
+
+struct FieldGeom : CellGeom {
+    int M;           // half-width of the first-derivative stencil (order / 2)
+    int R;           // Laplacian half-width 2M - 1
+    double a[3][3];  // a[axis][m-1] / d[axis]: first-derivative coefficients
+    double L[3][11]; // Laplacian stencil per axis, offsets -R..R
 };
 
 constexpr int FIELD_BS = 256;
@@ -41,7 +44,7 @@ __device__ __forceinline__ int nbw(int i, int o, int n, int small) {
 }
 
 // cell of thread t in block b of a run's launch; false for padding threads
-__device__ __forceinline__ bool field_cell(const FieldGeom& G, int64_t b, int t, int& i, int& j, int& k) {
+__device__ __forceinline__ bool field_cell(const CellGeom& G, int64_t b, int t, int& i, int& j, int& k) {
     const int xc = (int)(b % G.xchunks);
     const int64_t rb = b / G.xchunks;
     i = xc * FIELD_BS + (t & ((1 << G.xbits) - 1));
@@ -59,7 +62,7 @@ __device__ __forceinline__ bool field_cell(const FieldGeom& G, int64_t b, int t,
     return true;
 }
 
-__device__ __forceinline__ int lin(const FieldGeom& G, int i, int j, int k) { return i + G.n[0] * (j + G.n[1] * k); }
+__device__ __forceinline__ int lin(const CellGeom& G, int i, int j, int k) { return i + G.n[0] * (j + G.n[1] * k); }
 
 // up-shifted derivative along axis ax of f (values on integer nodes along ax) at cell (i,j,k):
 // sum_m a_m (f[i+m] - f[i-m+1]) / d
@@ -756,7 +759,7 @@ static FieldGeom make_geom(const pp_run* r) {
     return G;
 }
 
-static int64_t blocks_of(const FieldGeom& G) { return (int64_t)G.xchunks * ((G.rows + G.rpb - 1) / G.rpb); }
+static int64_t blocks_of(const CellGeom& G) { return (int64_t)G.xchunks * ((G.rows + G.rpb - 1) / G.rpb); }
 
 // Host set-up of the field-step constants: the composed Laplacian stencil (d- after d+,
 // identical as a stencil to d+ after d-), the true diagonal of A = 1 - alpha^2 s lap on this
@@ -1017,7 +1020,7 @@ hipError_t launch_field_step_batch(const void* table, const int64_t* prefix, int
 // coefficients; it is applied as a convolution along each component's own axis.
 // ---------------------------------------------------------------------------------------
 struct LineArgs {
-    FieldGeom G;
+    CellGeom G;
     const double* coef[3];
     int len[3], off[3];
     // LDS form: W[c] lines of component c per block (a power of two, at most 64) and the
@@ -1113,7 +1116,7 @@ __device__ __forceinline__ T arg3(const T a[3], int c) {
 }
 
 __device__ __forceinline__ void line_lds_body(const LineArgs& A, int64_t b, double* e) {
-    const FieldGeom& G = A.G;
+    const CellGeom& G = A.G;
     int c = 0;
     if (b >= A.nb[0]) {
         b -= A.nb[0];

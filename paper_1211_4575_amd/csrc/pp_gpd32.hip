@@ -69,8 +69,6 @@ struct Gpd32Args {
     int nt[3];
     int64_t ntiles;
     int64_t nc;
-    int fe[3], ce[3];  // LDS extents (runtime-shape kernel)
-    int flo[3], clo[3];
     float dt;   // drift: positions and current
     float dtk;  // kick: momentum update (radiative cooling included)
     float pred; // next drift / this drift: the next displacement expected from this one
@@ -85,7 +83,6 @@ struct Gpd32Args {
     FixedScale scale;
     int32_t* flags;
     int per_xcd;
-    int sext[3];  // destination-cell window per axis (tile and DEST_HALO around it; 1 if collapsed)
     int direct;   // PP_CURRENT_DIRECT: eq. "jj2" instead of the Esirkepov current
 };
 
@@ -160,6 +157,7 @@ using Tile444 = TileCT<O, 4, 4, 4, false, PAIRS>;
 template <int O>
 using Tile881 = TileCT<O, 8, 8, 1, true, false>;
 
+template <int O>
 struct TileRT {
     static constexpr bool fixed_shape = false;
     static constexpr bool pairs = false;
@@ -174,21 +172,23 @@ struct TileRT {
         tx = A.t[0];
         ty = A.t[1];
         tz = A.t[2];
-        flox = A.flo[0];
-        floy = A.flo[1];
-        floz = A.flo[2];
-        clox = A.clo[0];
-        cloy = A.clo[1];
-        cloz = A.clo[2];
-        fex = A.fe[0];
-        fey = A.fe[1];
-        fez = A.fe[2];
-        cex = A.ce[0];
-        cey = A.ce[1];
-        cez = A.ce[2];
-        dex = A.sext[0];
-        dey = A.sext[1];
-        dez = A.sext[2];
+        const bool one[3] = {A.n[0] == 1, A.n[1] == 1, A.n[2] == 1};
+        constexpr int fgrow = FLD_LO + fld_hi(O), cgrow = cur_lo(O) + cur_hi(O), dgrow = 2 * DEST_HALO;
+        flox = one[0] ? 0 : FLD_LO;
+        floy = one[1] ? 0 : FLD_LO;
+        floz = one[2] ? 0 : FLD_LO;
+        clox = one[0] ? 0 : cur_lo(O);
+        cloy = one[1] ? 0 : cur_lo(O);
+        cloz = one[2] ? 0 : cur_lo(O);
+        fex = one[0] ? 1 : tx + fgrow;
+        fey = one[1] ? 1 : ty + fgrow;
+        fez = one[2] ? 1 : tz + fgrow;
+        cex = one[0] ? 1 : tx + cgrow;
+        cey = one[1] ? 1 : ty + cgrow;
+        cez = one[2] ? 1 : tz + cgrow;
+        dex = one[0] ? 1 : tx + dgrow;
+        dey = one[1] ? 1 : ty + dgrow;
+        dez = one[2] ? 1 : tz + dgrow;
         fsx = A.n[0] > 1 ? 1 : 0;
         frow = fex;
         fplane = fex * fey;
@@ -981,19 +981,17 @@ static int tile_kind(const pp_run* r) {
     return TILE_RT;
 }
 
-static void lds_extents(const pp_run* r, int fe[3], int ce[3], int flo[3], int clo[3]) {
+static void lds_extents(const pp_run* r, int fe[3], int ce[3]) {
     for (int d = 0; d < 3; ++d) {
         const bool single = r->p.n[d] == 1;
         fe[d] = single ? 1 : r->g.t[d] + FLD_LO + fld_hi(r->p.shape_order);
         ce[d] = single ? 1 : r->g.t[d] + cur_lo(r->p.shape_order) + cur_hi(r->p.shape_order);
-        flo[d] = single ? 0 : FLD_LO;
-        clo[d] = single ? 0 : cur_lo(r->p.shape_order);
     }
 }
 
 size_t gpd32_lds_bytes(const pp_run* r) {
-    int fe[3], ce[3], flo[3], clo[3];
-    lds_extents(r, fe, ce, flo, clo);
+    int fe[3], ce[3];
+    lds_extents(r, fe, ce);
     const size_t fv = tile_kind(r) == TILE_444 ? (size_t)fld_plane_444(r->p.shape_order) * fe[2]
                                                 : (size_t)fe[0] * fe[1] * fe[2];
     const int kind = tile_kind(r);
@@ -1029,16 +1027,10 @@ int gpd32_scale_e0(const pp_run* r) {
 // Kernel arguments of one run (also the batched table entries).
 void gpd32_fill_args(const pp_run* r, Gpd32Args* Ap) {
     Gpd32Args& A = *Ap;
-    int fe[3], ce[3], flo[3], clo[3];
-    lds_extents(r, fe, ce, flo, clo);
     for (int d = 0; d < 3; ++d) {
         A.n[d] = r->p.n[d];
         A.t[d] = r->g.t[d];
         A.nt[d] = r->g.nt[d];
-        A.fe[d] = fe[d];
-        A.ce[d] = ce[d];
-        A.flo[d] = flo[d];
-        A.clo[d] = clo[d];
         A.inv_d[d] = (float)(1.0 / r->p.d[d]);
     }
     A.ntiles = r->g.ntiles;
@@ -1080,7 +1072,6 @@ void gpd32_fill_args(const pp_run* r, Gpd32Args* Ap) {
     A.flags = r->flags;
     A.per_xcd = (int)((r->g.ntiles + 7) / 8);
     A.direct = r->p.current_scheme == PP_CURRENT_DIRECT ? 1 : 0;
-    for (int d = 0; d < 3; ++d) A.sext[d] = r->g.dest_ext(d);
 }
 
 FixedScale gpd32_scale(const pp_run* r) { return FixedScale{r->tile_max, gpd32_scale_e0(r)}; }
@@ -1131,7 +1122,7 @@ static void launch_tiles32(int kind, const Gpd32Args& A, size_t lds, hipStream_t
     else if (kind == TILE_881_FLAT)
         hipLaunchKernelGGL((k_gpd32<O, Tile881<O>, GPD32_BS>), grid, dim3(GPD32_BS), lds, st, A);
     else
-        hipLaunchKernelGGL((k_gpd32<O, TileRT, GPD32_BS>), grid, dim3(GPD32_BS), lds, st, A);
+        hipLaunchKernelGGL((k_gpd32<O, TileRT<O>, GPD32_BS>), grid, dim3(GPD32_BS), lds, st, A);
 }
 
 hipError_t launch_gpd32(pp_run* r) {

@@ -292,3 +292,24 @@ def test_sort_of_boxes_around_the_largest_one_workgroup_scan(ppm, orc, n):
         run.close()
     assert np.array_equal(out[0], out[1])
     assert np.linalg.norm(out[0] - out[2]) < 1e-5 * np.linalg.norm(out[2])
+
+
+def test_static_tables_hold_637_runs(ppm):
+    """pp_batch_step_noalloc takes 637 members of one species with the line solve, 3290 bytes of its
+    2 MiB table array each."""
+    import torch
+    P = ppm.make_params(n=(4, 4, 4), shape_order=3, field_order=6, precision=ppm.PP_PREC_FP32_SPLIT, relax_tol=1e-6)
+    sp = dict(q=-1.0, m=1.0, w=1.0, cell=np.arange(8, dtype=np.int32), off=np.full((3, 8), 0.5, np.float32),
+              u=np.full((3, 8), 0.05, np.float32))
+    batch = ppm.pp_batch_create(1024, torch.cuda.current_stream().cuda_stream)
+    runs = []
+    try:
+        for _ in range(637):
+            runs.append(ppm.Run(P, [sp], with_id=False))
+            ppm.pp_batch_add(batch, runs[-1].handle)
+        ppm.pp_batch_step_noalloc(batch)
+        assert all(r.diagnostics(ppm.PP_DIAG_MOMENTS).step == 1 for r in (runs[0], runs[-1]))
+    finally:
+        ppm.pp_batch_destroy(batch)
+        for r in runs:
+            r.close()
