@@ -719,12 +719,16 @@ static hipError_t launch_tiles(pp_run* r, const Gpd64TileArgs& A) {
 }
 
 // How the particles of np are shared out.  256 CUs hold three workgroups each.
-// Few tiles: a workgroup per tile, species and part of its particles, or, past 384 tiles and species,
-// per tile and part, as many parts as are resident at once (768 workgroups) with a wavefront's worth
-// of particles each.  Two species, cubic, time with parts of at least 256 particles and in powers of
-// two -> this: 8^3, 8 per cell 47 -> 34 us; 16^3, 8 per cell 47 -> 43; 64x64 flat, 20 per cell 39 -> 32;
-// 24^3, 16 per cell 194 -> 168.  64x16x16 (256 tiles), four steps of a bunched two-stream plasma: 2.50 ms
-// with three parts, 2.51 with two, 2.69 with two parts of a species each.
+// Few tiles: a workgroup per tile, species and part of its particles, with as many parts (two to eight) as
+// make the workgroups resident at once, 768, where each has a wavefront's worth of particles.  Two
+// species, cubic, time with parts of at least 256 particles and in powers of two -> this: 8^3, 8 per cell
+// 47 -> 34 us; 16^3, 8 per cell 47 -> 43; 64x64 flat, 20 per cell 39 -> 32; 24^3, 16 per cell 194 -> 168.
+// Past 384 tiles and species two parts of each would be more than one round.  Up to three species are then
+// taken together by a workgroup, in parts of the tile's that make one: 64x16x16 (256 tiles, two species),
+// four steps of a bunched two-stream plasma 2.69 -> 2.50 ms, at 8 and 32 per cell without bunches 101 -> 91 us
+// and 281 -> 287; 168 tiles of three 181 -> 177; 196 of two 147 -> 152; one species the same.  With more of them
+// walking through the species costs more than the second round: 100 tiles of four, 8 and 32 per cell, 85
+// and 271 us -> 103 and 271, 60 tiles of eight 105 and 288 -> 177 and 331.
 // Many tiles: all species of a tile in one workgroup, which stages the fields once, unless that
 // leaves the last round of workgroups mostly empty: 45x38x29 (960 tiles, 768 and 192) 393 -> 352 us
 // with a workgroup per species, but 32^3 (512, two a CU) 184 -> 202.
@@ -733,8 +737,8 @@ static void plan_workgroups(Gpd64TileArgs& A, int64_t np) {
     A.parts = 1;
     A.split = A.nsp;
     if (units <= 512) {
-        if (units > 384) A.split = 1;
-        const int64_t n = units > 384 ? A.ntiles : units;
+        if (units > 384 && A.nsp <= 3) A.split = 1;
+        const int64_t n = A.split == 1 ? A.ntiles : units;
         A.parts = (int)(768 / n < 2 ? 2 : (768 / n > 8 ? 8 : 768 / n));
         while (A.parts > 1 && np < units * A.parts * 64) --A.parts;
         return;

@@ -313,3 +313,71 @@ def test_static_tables_hold_637_runs(ppm):
         ppm.pp_batch_destroy(batch)
         for r in runs:
             r.close()
+
+
+@pytest.mark.parametrize("precision", ["split", "fp64"])
+@pytest.mark.parametrize("leaving", [65000, 66000])
+def test_sort_of_a_large_tile_that_nearly_empties(ppm, orc, precision, leaving):
+    """A tile of about 2^16 particles near its upper x face, all but 300 of which leave in one push: its
+    next range fits the permutation's LDS image, whose 16-bit entries the particles' places do not.  No
+    particle is lost, and the next current is the same for the particles loaded in reverse (split form,
+    bit for bit) or left unsorted (FP64, 1e-12 of the largest value)."""
+    from paper_1211_4575_amd import inputs as I
+    n = (16, 8, 8)
+    split = precision == "split"
+    rng = np.random.default_rng(8)
+    face = 8.0 if split else 7.5  # upper end of the tile's cells: floor (cubic) or nearest
+    pos = np.concatenate([np.stack([face - rng.uniform(0.02, 0.15, leaving), *rng.uniform(0, 3.4, (2, leaving))]),
+                          rng.uniform(4.2, 5.2, (3, 300)) - np.array([0, 4, 4])[:, None]], 1)
+    u = np.concatenate([np.stack([np.full(leaving, 0.8), *np.zeros((2, leaving))]), rng.normal(0, 0.01, (3, 300))], 1)
+    count = leaving + 300
+    s = dict(q=-1.0, m=1.0, w=1.0 / count, pos=pos, u=u)
+    if split:
+        cell, off = I.to_split(pos, n, origin=I.split_origin(3))
+        s = dict(q=-1.0, m=1.0, w=1.0 / count, cell=cell, off=off, u=u.astype(np.float32))
+    kw = dict(n=n, dt=0.45, shape_order=3, field_order=2, relax_max_iter=100,
+              precision=ppm.PP_PREC_FP32_SPLIT if split else ppm.PP_PREC_FP64)
+    out = []
+    for first in (True, False):
+        if split and not first:
+            s = dict(s, **{k: np.ascontiguousarray(s[k][..., ::-1]) for k in ("cell", "off", "u")})
+        run = ppm.Run(ppm.make_params(**kw), [s])
+        run.gather_push_deposit()
+        if split or first:
+            run.sort()
+        run.gather_push_deposit()
+        parts = run.particles(0)
+        assert run.diagnostics().flags == 0
+        assert np.array_equal(np.sort(parts["id"]), np.arange(count))
+        x = parts["cell"] % n[0] if split else np.floor(parts["pos"][0] + 0.5)
+        assert np.sum(x >= 8) == leaving
+        out.append(run.fields()[2])
+        run.close()
+    assert np.array_equal(*out) if split else rel_inf(*out) < 1e-12
+
+
+@pytest.mark.parametrize("n,nspecies", [((20, 12, 16), 8), ((40, 40, 16), 1), ((28, 24, 20), 2), ((40, 40, 32), 1),
+                                        ((40, 40, 32), 3), ((48, 48, 44), 2)])
+def test_fp64_workgroup_plans(ppm, orc, n, nspecies):
+    """Numbers of tiles and species whose particles are shared out differently among workgroups (60 x 8,
+    400 x 1, 210 x 2, 800 x 1, 800 x 3 and 1584 x 2): a push of sorted particles against one of the same
+    particles left unsorted.  FP64 sums in another order, 1e-12 of the largest value."""
+    species, E, B = random_state(orc, n, 3, seed=21, uth=0.4)
+    species = [dict(species[s % 2], q=(-1.0) ** s, m=1.0 + s) for s in range(nspecies)]
+    kw = dict(n=n, dt=0.35, shape_order=3, field_order=2, relax_max_iter=100, precision=ppm.PP_PREC_FP64)
+    out = []
+    for sort in (True, False):
+        run = ppm.Run(ppm.make_params(**kw), species, E=E, B=B)
+        run.gather_push_deposit()
+        if sort:
+            run.sort()
+        run.gather_push_deposit()
+        assert run.diagnostics(ppm.PP_DIAG_MOMENTS).flags == 0
+        out.append((run.fields()[2], [_by_id(run.particles(s)) for s in range(nspecies)]))
+        run.close()
+    (J1, p1), (J2, p2) = out
+    assert rel_inf(J1, J2) < 1e-12
+    for a, b in zip(p1, p2):
+        assert np.array_equal(a["id"], b["id"])
+        assert np.max(np.abs(periodic_diff(a["pos"], b["pos"], n))) < 1e-12
+        assert rel_inf(a["u"], b["u"]) < 1e-12
