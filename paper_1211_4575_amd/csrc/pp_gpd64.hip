@@ -257,8 +257,12 @@ struct Gpd64TileArgs {
     int parts;  // workgroups sharing a tile's particles of a species
     int split;  // nsp: a workgroup per species; 1: all of them in one
     int sext[3];  // destination-cell window per axis
+    int heavy;    // rounds of 64 particles that a workgroup takes of a tile and species at most
+    int helpers;  // blocks past the tiles' own: a chunk of a heavy tile's other rounds each
+    int chunk;    // rounds of a chunk
     int nsp;
     const int32_t* bins[PP_MAX_SPECIES];  // cell-bin starts of the sort (64 per tile)
+    const int32_t* tile_max[PP_MAX_SPECIES];  // an upper bound of a tile's particles, from the sort
     Gpd64Args sp[PP_MAX_SPECIES];
 };
 
@@ -509,6 +513,53 @@ __device__ __forceinline__ bool gpd64_in_tile(const Gpd64Args& A, const TL& L, c
     return true;
 }
 
+// Rounds first .. last - 1 (a wavefront takes every step-th, from first + its number) of the particles
+// of species s0 .. s1 - 1 in a tile.
+struct TileWork {
+    int64_t tile;
+    int s0, s1;
+    int32_t first, last, step;
+};
+
+__device__ __forceinline__ int32_t tile_rounds(const Gpd64TileArgs& A, int s, int64_t tile) {
+    return (A.bins[s][(tile + 1) * TILE_CELLS] - A.bins[s][tile * TILE_CELLS] + 63) / 64;
+}
+
+// What the tiles' own workgroups leave of tiles past A.heavy rounds a part, in chunks of A.chunk rounds
+// numbered through species and tiles: finds the given one (the same in every lane).  A chunk is ranked
+// like a workgroup of its own: its counts are reserved in the destination cells as theirs are.
+__device__ __forceinline__ bool heavy_chunk(const Gpd64TileArgs& A, int number, double* lds, TileWork& W) {
+    uint64_t* words = (uint64_t*)lds;
+    const int32_t own = A.heavy * A.parts;
+    for (int s = 0; s < A.nsp; ++s) {
+        if (*A.tile_max[s] <= 64 * (int64_t)own) continue;
+        for (int64_t base = 0; base < A.ntiles; base += GPD64_BS) {
+            const int64_t t = base + threadIdx.x;
+            const uint64_t heavy = __ballot(t < A.ntiles && tile_rounds(A, s, t < A.ntiles ? t : 0) > own);
+            if ((threadIdx.x & 63) == 0) words[threadIdx.x >> 6] = heavy;
+            __syncthreads();
+            for (int w = 0; w < GPD64_BS / 64; ++w) {
+                uint64_t left = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)words[w]) |
+                                (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(words[w] >> 32)) << 32;
+                for (; left != 0; left &= left - 1) {
+                    const int64_t tile = base + 64 * w + __ffsll((unsigned long long)left) - 1;
+                    const int32_t rounds = tile_rounds(A, s, tile);
+                    const int n = (rounds - own + A.chunk - 1) / A.chunk;
+                    if (number < n) {
+                        const int32_t first = own + number * A.chunk;
+                        W = TileWork{tile, s, s + 1, first, first + A.chunk, 4};
+                        __syncthreads();
+                        return true;
+                    }
+                    number -= n;
+                }
+            }
+            __syncthreads();
+        }
+    }
+    return false;
+}
+
 // What bounds it: the LDS, 384 reads of 8 bytes for the cubic gather and up to 300 additions of
 // 8 bytes per particle (ds_add_f64 runs at 9 clocks per wavefront where the 64 lanes' addresses
 // differ and at 193 where they coincide), against 300 global FP64 atomics of the untiled kernel.
@@ -525,11 +576,25 @@ template <int O, class TL>
 __global__ void __launch_bounds__(GPD64_BS, 3) k_gpd64_tile(Gpd64TileArgs A) {
     extern __shared__ __align__(16) double lds64[];
     const TL L(A);
-    const int64_t tile = (blockIdx.x & 7) * (int64_t)A.per_xcd + (blockIdx.x >> 3);
+    // blocks by tile, then by part, then by species (in a small box), and the helpers last
+    const uint32_t row_blocks = 8 * (uint32_t)A.per_xcd;
+    const int brow = __builtin_amdgcn_readfirstlane((int)(blockIdx.x / row_blocks));
+    const int bspecies = __builtin_amdgcn_readfirstlane(brow / A.parts);
+    const uint32_t b = blockIdx.x - (uint32_t)brow * row_blocks;
+    int64_t tile = (b & 7) * (int64_t)A.per_xcd + (b >> 3);
+    int s0 = A.split > 1 ? bspecies : 0, s1 = A.split > 1 ? s0 + 1 : A.nsp;
+    int first = 4 * (brow - bspecies * A.parts), most = A.heavy * A.parts, step = 4 * A.parts;
+    if (bspecies >= A.split) {
+        TileWork W;
+        if (!heavy_chunk(A, (int)(blockIdx.x - row_blocks * (uint32_t)(A.parts * A.split)), lds64, W)) return;
+        tile = __builtin_amdgcn_readfirstlane((int)W.tile);
+        s0 = __builtin_amdgcn_readfirstlane(W.s0);
+        s1 = s0 + 1;
+        first = __builtin_amdgcn_readfirstlane(W.first);
+        most = __builtin_amdgcn_readfirstlane(W.last);
+        step = 4;
+    }
     if (tile >= A.ntiles) return;
-    const int part = blockIdx.y;
-    // a small box has a workgroup per tile, part and species
-    const int s0 = gridDim.z > 1 ? (int)blockIdx.z : 0, s1 = gridDim.z > 1 ? s0 + 1 : A.nsp;
     int any = 0;
     for (int s = s0; s < s1; ++s) any |= A.bins[s][(tile + 1) * TILE_CELLS] - A.bins[s][tile * TILE_CELLS];
     if (any == 0) return;
@@ -563,8 +628,8 @@ __global__ void __launch_bounds__(GPD64_BS, 3) k_gpd64_tile(Gpd64TileArgs A) {
     for (int s = s0; s < s1; ++s) {
         const Gpd64Args& S = A.sp[s];
         const int32_t start = A.bins[s][tile * TILE_CELLS], end = A.bins[s][(tile + 1) * TILE_CELLS];
-        const int32_t per = (end - start + 63) / 64;
-        for (int32_t r = 4 * part + wave; r < per; r += 4 * A.parts) {
+        const int32_t per = (end - start + 63) / 64, last = per < most ? per : most;
+        for (int32_t r = first + wave; r < last; r += step) {
             const int64_t q = start + (int64_t)lane * per + r;
             if (q >= end) continue;
             const int64_t p = S.perm ? S.perm[q] : q;
@@ -605,7 +670,7 @@ __global__ void __launch_bounds__(GPD64_BS, 3) k_gpd64_tile(Gpd64TileArgs A) {
             *slot = atomicAdd(&S.cnt[bin_of(A, c)], *slot);
         }
         __syncthreads();
-        for (int32_t r = 4 * part + wave; r < per; r += 4 * A.parts) {
+        for (int32_t r = first + wave; r < last; r += step) {
             const int64_t q = start + (int64_t)lane * per + r;
             if (q >= end) continue;
             const int32_t w = S.rank[q];
@@ -687,8 +752,8 @@ hipError_t launch_gpd64(pp_run* r, int s, double* J) {
 
 template <int O, class TL>
 static void launch_tile(const Gpd64TileArgs& A, size_t lds, hipStream_t st) {
-    hipLaunchKernelGGL((k_gpd64_tile<O, TL>), dim3((unsigned)(8 * A.per_xcd), (unsigned)A.parts, (unsigned)A.split),
-                       dim3(GPD64_BS), lds, st, A);
+    hipLaunchKernelGGL((k_gpd64_tile<O, TL>), dim3((unsigned)(8 * A.per_xcd * A.parts * A.split + A.helpers)), dim3(GPD64_BS),
+                       lds, st, A);
 }
 
 // LDS bytes of a tile of the runtime-shaped kernel.
@@ -747,6 +812,20 @@ static void plan_workgroups(Gpd64TileArgs& A, int64_t np) {
     if (A.ntiles > 2 * 768 || 10 * A.ntiles >= 9 * filled) A.split = 1;
 }
 
+// A tile that holds a good part of all particles (a bunch, a point source of tracers) would keep one
+// workgroup busy while the rest of the GPU is done.  What a workgroup would have to take of it past
+// A.heavy rounds -- 64, or four times the mean -- goes to workgroups of their own, a chunk of rounds each;
+// there are as many as np particles can make chunks, and where the sort found no tile that heavy they
+// end after one load.  1e6 particles in one cell of a 64^3 box, cubic: 191 ms -> 1.6 (53 with the untiled
+// kernel); in eight tiles 12.3 -> 0.93; spread evenly 0.31 either way.  Chunks of 256 rounds: 3.4 ms and 2.0.
+static void plan_helpers(Gpd64TileArgs& A, int64_t np) {
+    const int64_t mean = np / (64 * A.ntiles * A.nsp * A.parts), chunk = np / (64 * 256);
+    A.chunk = (int)(chunk > 64 ? chunk : 64);
+    A.heavy = (int)(4 * mean > A.chunk ? 4 * mean : A.chunk);
+    // a tile of c particles, past heavy >= chunk rounds, has fewer than c / 64 / chunk chunks to share
+    A.helpers = np < 64 * (int64_t)A.heavy ? 0 : (int)(np / (64 * (int64_t)A.chunk)) + 1;
+}
+
 // All species whose particles lie as the sort left them, in one launch; *done has a bit for each
 // (the others take launch_gpd64).
 hipError_t launch_gpd64_tiles(pp_run* r, double* J, unsigned* done) {
@@ -758,6 +837,7 @@ hipError_t launch_gpd64_tiles(pp_run* r, double* J, unsigned* done) {
         const Species& S = r->sp[s];
         if (!S.active || !S.binned || S.n == 0) continue;
         A.bins[A.nsp] = S.offsets;
+        A.tile_max[A.nsp] = r->tile_max + s;
         gpd64_args(r, s, J, A.sp[A.nsp++]);
         *done |= 1u << s;
         np += S.n;
@@ -773,6 +853,7 @@ hipError_t launch_gpd64_tiles(pp_run* r, double* J, unsigned* done) {
     A.ntiles = r->g.ntiles;
     A.per_xcd = (int)((A.ntiles + 7) / 8);
     plan_workgroups(A, np);
+    plan_helpers(A, np);
     return r->p.shape_order == 2 ? launch_tiles<2>(r, A) : launch_tiles<3>(r, A);
 }
 

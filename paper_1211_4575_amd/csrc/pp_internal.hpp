@@ -115,8 +115,9 @@ struct pp_run {
     int32_t* scan_tmp = nullptr;      // block sums of the scan
     long long* Jq = nullptr;          // split form: current in 64-bit fixed point (3*ncell), zero
                                       // between calls
-    int32_t* tile_max = nullptr;      // split form: largest particle count of a tile, per species, and
-                                      // after them those of the order before the last sort after a push
+    int32_t* tile_max = nullptr;      // largest particle count of a tile, per species (FP64 form: at
+                                      // most that), and after them those of the order before the last
+                                      // sort after a push
     int32_t* flags = nullptr;        // device error flags
     double* dacc = nullptr;          // device accumulators for diagnostics
     pp::LineStencil line[3];

@@ -557,10 +557,9 @@ __device__ __forceinline__ void scan_workgroup(int32_t* data, int64_t n, int32_t
 __device__ __forceinline__ void scan_results(const RankedArgs& A, int32_t total, int32_t largest) {
     if (threadIdx.x == 0) {
         gl(A.tot)[A.G.ntiles] = total;
-        if (A.tile_max) {  // the ranges the particles still lie in until they are moved, and the new ones
-            gl(A.tile_max)[PP_MAX_SPECIES] = *gl(A.tile_max);
-            *gl(A.tile_max) = largest;
-        }
+        // the ranges the particles still lie in until they are moved, and the new ones
+        gl(A.tile_max)[PP_MAX_SPECIES] = *gl(A.tile_max);
+        *gl(A.tile_max) = largest;
     }
     for (int64_t q = total + (int64_t)threadIdx.x; q < A.n; q += SCAN1_BS) gl(A.perm)[q] = -1;
 }
@@ -1006,7 +1005,7 @@ void sort_desc(const pp_run* r, int s, RankedArgs* A) {
     A->rtot = r->sort_cursor + 3 * nt * s;  // 64 entries per tile, 3 used by each of 8 species
     A->ovf = A->rtot + nt;
     A->nchunk = A->rtot + 2 * nt;
-    A->tile_max = split ? r->tile_max + s : nullptr;
+    A->tile_max = r->tile_max + s;
     A->start = S.offsets;
     A->rank = S.rank;
     A->base = S.rank_base;
@@ -1238,8 +1237,9 @@ static hipError_t sort_species(pp_run* r, int s) {
                                (const double*)S.cur.pos[1], (const double*)S.cur.pos[2], S.n, S.offsets);
     }
     scan_inplace(S.offsets, nkeys + 1, r->scan_tmp, r->stream);
+    // FP64 form: an upper bound will do (it looks for heavy tiles itself)
+    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(1), 0, r->stream, r->tile_max + s, (int64_t)1, split ? 0 : (int32_t)S.n);
     if (split) {
-        hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(1), 0, r->stream, r->tile_max + s, (int64_t)1, 0);
         hipLaunchKernelGGL(k_tile_max, dim3(grid_for(ntiles, bs, 1024)), dim3(bs), 0, r->stream,
                            (const int32_t*)S.offsets, ntiles, r->tile_max + s);
     }

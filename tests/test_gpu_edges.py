@@ -381,3 +381,71 @@ def test_fp64_workgroup_plans(ppm, orc, n, nspecies):
         assert np.array_equal(a["id"], b["id"])
         assert np.max(np.abs(periodic_diff(a["pos"], b["pos"], n))) < 1e-12
         assert rel_inf(a["u"], b["u"]) < 1e-12
+
+
+@pytest.mark.parametrize("n,O", [((40, 40, 32), 3), ((20, 12, 16), 2), ((200, 70, 1), 3), ((700, 3, 1), 2), ((64, 9, 36), 3)])
+def test_fp64_bunches_shared_by_workgroups(ppm, orc, n, O):
+    """A few tiles of two species that hold most of the particles, in numbers at the edges of what one
+    workgroup takes (256 rounds of 64 particles a part): pushes of sorted particles against one of the
+    same particles left unsorted, and the order of the sort that follows.  FP64 sums in another order,
+    1e-12 of the largest value."""
+    rng = np.random.default_rng(5)
+    N = np.array(n, float)[:, None]
+    _, E, B = random_state(orc, n, 1, seed=13)
+    species = []
+    for s, bunches in enumerate(((16384, 16385, 70000), (300, 131072 + 65))):
+        pos = [rng.uniform(0, 1, (3, 20000)) * (N - 1e-9)]
+        for i, k in enumerate(bunches):
+            at = np.floor(N * (0.2 + 0.3 * i) / 8) * 8 * (N > 1)  # a tile's first cell
+            pos.append((at + rng.uniform(0, 1.4, (3, k)) * (N > 1)) % N)
+        pos = np.concatenate(pos, 1)
+        species.append(dict(q=(-1.0) ** s, m=1.0 + s, w=1e-4, pos=pos, u=rng.normal(0, 0.3, pos.shape)))
+    kw = dict(n=n, dt=0.35, shape_order=O, field_order=2, relax_max_iter=100, precision=ppm.PP_PREC_FP64)
+    out = []
+    for sort in (True, False):
+        run = ppm.Run(ppm.make_params(**kw), species, E=E, B=B)
+        run.gather_push_deposit()
+        if sort:
+            run.sort()
+        run.gather_push_deposit()
+        J = run.fields()[2]
+        if sort:
+            run.sort()
+            assert all(_in_cell_order(run.particles(s)["pos"], n) for s in range(2))
+        assert run.diagnostics(ppm.PP_DIAG_MOMENTS).flags == 0
+        out.append((J, [_by_id(run.particles(s)) for s in range(2)]))
+        run.close()
+    (J1, p1), (J2, p2) = out
+    assert rel_inf(J1, J2) < 1e-12
+    for a, b in zip(p1, p2):
+        assert np.array_equal(a["id"], b["id"])
+        assert np.max(np.abs(periodic_diff(a["pos"], b["pos"], n))) < 1e-12
+        assert rel_inf(a["u"], b["u"]) < 1e-12
+
+
+def test_fp64_rank_counters_past_their_word(ppm):
+    """A box of one tile whose 9e6 particles all lie in a cell: each of the eight workgroups that share it
+    counts more of them than a rank word holds.  None is lost, and the current of the next push is that
+    of the particles left unsorted (the sums of 9e6 equal terms in another order: 1e-10)."""
+    import torch
+    count = 9_000_000
+    gen = torch.Generator(device="cuda").manual_seed(1)
+    out = []
+    for sort in (True, False):
+        gen.manual_seed(1)
+        pos = 1.9 + 0.2 * torch.rand((3, count), dtype=torch.float64, device="cuda", generator=gen)
+        u = 0.01 + 0.001 * torch.rand((3, count), dtype=torch.float64, device="cuda", generator=gen)
+        run = ppm.Run(ppm.make_params((4, 4, 4), dt=0.35, shape_order=2, field_order=2, precision=ppm.PP_PREC_FP64),
+                      [dict(q=-1.0, m=1.0, w=1.0 / count, pos=pos, u=u)])
+        run.gather_push_deposit()
+        if sort:
+            run.sort()
+        run.gather_push_deposit()
+        assert run.diagnostics(ppm.PP_DIAG_MOMENTS).flags == 0
+        ids = run.particle_tensors(0)["id"]
+        assert int(torch.bincount(ids, minlength=count).max()) == 1 and ids.numel() == count
+        out.append(run.fields()[2])
+        run.close()
+        del pos, u, ids, run
+        torch.cuda.empty_cache()
+    assert rel_inf(*out) < 1e-10
