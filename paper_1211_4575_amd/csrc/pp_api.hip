@@ -338,6 +338,7 @@ pp_status pp_init_species(pp_run* r, int32_t s, double q, double m, double w, co
     S.sorted = false;
     S.ranked = false;
     S.binned = false;
+    S.handed_out = false;
     // initial sort: the split form needs it before its first push
     hipError_t e = launch_sort(r, s);
     if (!ok(e, "sort")) return PP_E_HIP;
@@ -382,6 +383,7 @@ pp_status pp_gather_push_deposit(pp_run* r) {
                 if (S.pending) swap_buffers(S.cur);  // the kernel wrote the pending order
                 S.pending = false;
                 S.ranked = true;
+                S.handed_out = false;
                 continue;
             }
             if (!ok(materialize(r, s), "materialize")) return PP_E_HIP;
@@ -502,6 +504,7 @@ pp_status pp_get_particles(pp_run* r, int32_t s, pp_particles* out) {
     if (!ok(materialize(r, s), "materialize")) return PP_E_HIP;  // the buffers in sort order
     // the caller may write the positions it is handed: the next sort looks at them again
     if (r->p.precision == PP_PREC_FP64 && !ok(drop_ranks(r, s), "fill")) return PP_E_HIP;
+    r->sp[s].handed_out = true;
     *out = r->sp[s].cur;
     return PP_OK;
 }

@@ -22,6 +22,7 @@ struct Gpd64Args {
     // particle p of pos and u goes to slot q of pos_o and u_o: the same arrays and p = q, or, with
     // a sort order pending, the other buffers and p = perm[q]
     const int32_t* perm;
+    int defer;  // particles out of their tile are left to k_gpd64_deferred
     const double* pos[3];
     const double* u[3];
     double* pos_o[3];
@@ -249,6 +250,7 @@ __global__ void __launch_bounds__(256) k_gpd64(Gpd64Args A) {
 constexpr int F64_LO = 2;
 constexpr int f64_hi(int O) { return O - 1; }
 constexpr int GPD64_BS = 256;
+constexpr int32_t RANK_DEFERRED = -1;  // no bin has that number
 
 struct Gpd64TileArgs {
     int t[3], tsh[3], nt[3];  // sides (powers of two) and their logarithms, tiles
@@ -635,7 +637,13 @@ __global__ void __launch_bounds__(GPD64_BS, 3) k_gpd64_tile(Gpd64TileArgs A) {
             const int64_t p = S.perm ? S.perm[q] : q;
             double Xn[3];
             if (S.id) S.id_o[q] = S.id[p];
-            if (!gpd64_in_tile<O, TL>(S, L, org, A.t, fld, cur, p, q, Xn)) gpd64_particle<O, 1>(S, p, q, Xn);
+            if (!gpd64_in_tile<O, TL>(S, L, org, A.t, fld, cur, p, q, Xn)) {
+                if (S.defer) {
+                    S.rank[q] = RANK_DEFERRED;
+                    continue;
+                }
+                gpd64_particle<O, 1>(S, p, q, Xn);
+            }
             // rank among the particles bound for the new cell: in the tile's neighbourhood counted
             // in LDS, else in the cell's count itself
             int c[3], sl = 0, mul = 1;
@@ -674,7 +682,7 @@ __global__ void __launch_bounds__(GPD64_BS, 3) k_gpd64_tile(Gpd64TileArgs A) {
             const int64_t q = start + (int64_t)lane * per + r;
             if (q >= end) continue;
             const int32_t w = S.rank[q];
-            if (w < 0) continue;
+            if (w < 0) continue;  // names its bin, or deferred
             const int sl = w >> 20;
             const int32_t rank = *L.slot(cur, sl) + (w & 0xFFFFF);
             if (rank < F64_RANKS) {
@@ -703,6 +711,42 @@ __global__ void __launch_bounds__(GPD64_BS, 3) k_gpd64_tile(Gpd64TileArgs A) {
     }
 }
 
+// Steps 1-3 of the particles that the tile kernel left out, as k_gpd64, and the bins they go to: those
+// that do not lie in their tile where pp_get_particles has handed out the positions since the sort, so
+// that there may be many.  (The tile kernel takes a stray one itself, with its loops over nodes rolled
+// up, which holds up a wavefront for 0.3 ms.)  A workgroup packs what it finds in DEFER_BLOCK slots.
+// 64x16x16, 5e5 particles, cubic, 1 % of them moved elsewhere by the caller: 1.56 ms -> 0.31 for both
+// kernels, 4.0 by k_gpd64 for all; 16^3, 3e4: 0.35 -> 0.15 and 0.28.  All of them moved: 4.3, 4.2 by k_gpd64.
+constexpr int DEFER_BLOCK = 256;
+
+template <int O>
+__global__ void __launch_bounds__(256) k_gpd64_deferred(Gpd64Args A, int t0, int t1, int t2) {
+    __shared__ int32_t slot[DEFER_BLOCK];
+    __shared__ int32_t count;
+    if (threadIdx.x == 0) count = 0;
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * DEFER_BLOCK;
+    for (int i = threadIdx.x; i < DEFER_BLOCK && base + i < A.np; i += 256)
+        if (A.rank[base + i] == RANK_DEFERRED) slot[atomicAdd(&count, 1)] = (int32_t)(base + i);
+    __syncthreads();
+    const int t[3] = {t0, t1, t2};
+    for (int i = threadIdx.x; i < count; i += 256) {
+        const int32_t q = slot[i];
+        double Xn[3];
+        gpd64_particle<O, O + 2>(A, A.perm ? A.perm[q] : q, q, Xn);
+        int tile = 0, lc = 0, mul = 1, tmul = 1;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const int c = nearest_cell(Xn[d], A.n[d]), ti = c / t[d];
+            tile += ti * tmul;
+            lc += (c - ti * t[d]) * mul;
+            mul *= t[d];
+            tmul *= (A.n[d] + t[d] - 1) / t[d];
+        }
+        A.rank[q] = name_bin(A, tile * TILE_CELLS + lc);
+    }
+}
+
 static void gpd64_args(const pp_run* r, int s, double* J, Gpd64Args& A) {
     const Species& S = r->sp[s];
     for (int d = 0; d < 3; ++d) {
@@ -721,6 +765,7 @@ static void gpd64_args(const pp_run* r, int s, double* J, Gpd64Args& A) {
     A.krad = r->p.rad_tau * S.q * S.q / S.m;
     A.np = S.n;
     A.perm = S.pending ? S.perm : nullptr;
+    A.defer = S.handed_out ? 1 : 0;
     A.id = S.pending ? S.cur.id : nullptr;
     A.id_o = S.pending ? S.cur.id_alt : nullptr;
     A.cnt = S.cell_cnt;
@@ -854,7 +899,17 @@ hipError_t launch_gpd64_tiles(pp_run* r, double* J, unsigned* done) {
     A.per_xcd = (int)((A.ntiles + 7) / 8);
     plan_workgroups(A, np);
     plan_helpers(A, np);
-    return r->p.shape_order == 2 ? launch_tiles<2>(r, A) : launch_tiles<3>(r, A);
+    hipError_t e = r->p.shape_order == 2 ? launch_tiles<2>(r, A) : launch_tiles<3>(r, A);
+    for (int k = 0; k < A.nsp && e == hipSuccess; ++k) {
+        if (!A.sp[k].defer) continue;
+        const dim3 grid((unsigned)((A.sp[k].np + DEFER_BLOCK - 1) / DEFER_BLOCK));
+        if (r->p.shape_order == 2)
+            hipLaunchKernelGGL(k_gpd64_deferred<2>, grid, dim3(256), 0, r->stream, A.sp[k], A.t[0], A.t[1], A.t[2]);
+        else
+            hipLaunchKernelGGL(k_gpd64_deferred<3>, grid, dim3(256), 0, r->stream, A.sp[k], A.t[0], A.t[1], A.t[2]);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 }  // namespace pp

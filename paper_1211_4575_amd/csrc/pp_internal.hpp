@@ -64,6 +64,7 @@ struct Species {
     // tile order of pp_sort.hip (valid when sorted).
     int32_t* offsets = nullptr;
     bool binned = false;  // FP64 form: sorted and not pushed since (offsets are the bins of the positions)
+    bool handed_out = false;  // FP64 form: pp_get_particles since then (positions may have been written)
     // FP64 form: starts of a tile's cells inside the tile (nbins), tile totals and starts (ntiles + 1)
     int32_t* bin_pre = nullptr;
     int32_t* tile_tot = nullptr;

@@ -1290,6 +1290,7 @@ static hipError_t sort_species(pp_run* r, int s) {
     S.sorted = true;
     S.ranked = false;
     S.binned = !split;
+    S.handed_out = false;
     return hipGetLastError();
 }
 

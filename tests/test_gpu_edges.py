@@ -449,3 +449,45 @@ def test_fp64_rank_counters_past_their_word(ppm):
         del pos, u, ids, run
         torch.cuda.empty_cache()
     assert rel_inf(*out) < 1e-10
+
+
+@pytest.mark.parametrize("share", [0.002, 0.3, 1.0])
+@pytest.mark.parametrize("n,O", [((16, 12, 9), 3), ((24, 17, 1), 2), ((70, 1, 1), 3), ((40, 41, 30), 2)])
+def test_fp64_positions_written_between_sort_and_push(ppm, orc, n, O, share):
+    """A caller that moves particles to other cells between a sort and the push (a source, a boundary of
+    its own), twice: the current and the particles are those of the same state pushed unsorted (1e-12 of
+    the largest value), and the sort after the push has them all in cell order."""
+    import torch
+    species, E, B = random_state(orc, n, 8, seed=16, uth=0.4)
+    count = species[0]["u"].shape[1]
+    rng = np.random.default_rng(10)
+    places = [torch.as_tensor(rng.uniform(0, 1, (3, count)) * (np.array(n, float)[:, None] - 1e-9)).cuda() for _ in range(2)]
+    sel_of = torch.as_tensor(rng.uniform(0, 1, count) < share).cuda()
+    kw = dict(n=n, dt=0.35, shape_order=O, field_order=2, relax_max_iter=100, precision=ppm.PP_PREC_FP64)
+    out = []
+    for sort in (True, False):
+        run = ppm.Run(ppm.make_params(**kw), species, E=E, B=B)
+        if not sort:
+            run.gather_push_deposit()  # unsorted from here on
+        else:
+            run.gather_push_deposit()
+            run.sort()
+        for where in places:
+            T = run.particle_tensors(0)
+            sel = sel_of[T["id"]].nonzero()[:, 0]
+            for d in range(3):
+                T["pos"][d][sel] = where[d][T["id"][sel]]
+            run.gather_push_deposit()
+            J = run.fields()[2]
+            if sort:
+                run.sort()
+                assert all(_in_cell_order(run.particles(s)["pos"], n) for s in range(2))
+        assert run.diagnostics(ppm.PP_DIAG_MOMENTS).flags == 0
+        out.append((J, [_by_id(run.particles(s)) for s in range(2)]))
+        run.close()
+    (J1, p1), (J2, p2) = out
+    assert rel_inf(J1, J2) < 1e-12
+    for a, b in zip(p1, p2):
+        assert np.array_equal(a["id"], np.arange(count)) and np.array_equal(b["id"], a["id"])
+        assert np.max(np.abs(periodic_diff(a["pos"], b["pos"], n))) < 1e-12
+        assert rel_inf(a["u"], b["u"]) < 1e-12
