@@ -491,3 +491,46 @@ def test_fp64_positions_written_between_sort_and_push(ppm, orc, n, O, share):
         assert np.array_equal(a["id"], np.arange(count)) and np.array_equal(b["id"], a["id"])
         assert np.max(np.abs(periodic_diff(a["pos"], b["pos"], n))) < 1e-12
         assert rel_inf(a["u"], b["u"]) < 1e-12
+
+
+@pytest.mark.parametrize("current", [0, 1])
+@pytest.mark.parametrize("n,O", [((16, 12, 9), 3), ((16, 12, 9), 2), ((24, 23, 24), 3), ((24, 23, 24), 2)])
+def test_split_crowds_in_small_boxes_equal_batched(ppm, orc, n, O, current):
+    """Crowds of particles in a cell or at the faces between cells, in boxes of up to 256 and 512 tiles and
+    species: where the lanes of a wavefront share their nodes by fours their contributions are summed
+    before they are added, always exactly.  A batch takes pairs: bit for bit the same."""
+    import torch
+    from paper_1211_4575_amd import inputs as I
+    species, E, B = random_state(orc, n, 2, seed=27, uth=0.4)
+    rng = np.random.default_rng(2)
+    split = []
+    for i, s in enumerate(species):
+        at = np.array([4.3, 5.3, 2.3])[:, None]
+        crowd = np.concatenate([at + rng.uniform(0, 0.1, (3, 3001)), at + 1.7 + rng.uniform(-0.01, 0.01, (3, 2000)),
+                                np.array(n)[:, None] - 1.4 + 0.0 * rng.uniform(0, 1, (3, 257))], 1)
+        cell, off = I.to_split(np.concatenate([s["pos"], crowd], 1), n, origin=I.split_origin(O))
+        u = np.concatenate([s["u"], rng.normal(0, 0.02, crowd.shape)], 1).astype(np.float32)
+        split.append(dict(q=s["q"], m=s["m"], w=s["w"], cell=cell, off=off, u=u))
+    kw = dict(n=n, dt=0.35, shape_order=O, field_order=2, relax_max_iter=100, current_scheme=current,
+              precision=ppm.PP_PREC_FP32_SPLIT)
+    out = []
+    for batched in (False, True):
+        run = ppm.Run(ppm.make_params(**kw), split, E=E, B=B)
+        if batched:
+            batch = ppm.pp_batch_create(1, torch.cuda.current_stream().cuda_stream)
+            ppm.pp_batch_add(batch, run.handle)
+            for _ in range(3):
+                ppm.pp_batch_step(batch)
+            ppm.pp_batch_remove(batch, run.handle)
+            ppm.pp_batch_destroy(batch)
+        else:
+            for _ in range(3):
+                run.step()
+        assert run.diagnostics().flags == 0
+        out.append((run.fields(), [_by_id(run.particles(s)) for s in range(2)]))
+        run.close()
+    (f1, p1), (f2, p2) = out
+    for a, b in zip(f1, f2):
+        assert np.array_equal(a, b)
+    for a, b in zip(p1, p2):
+        assert all(np.array_equal(a[k], b[k]) for k in a)
