@@ -121,8 +121,9 @@ static void run_arrays(const pp_params* p, const Geom& g, pp_run* r, Arena& A) {
     A.add(&r->scan_tmp, (size_t)scan_tmp_size(g.nbins + 1));
     A.add(&r->dacc, (size_t)diag_buffer_count(g.ncell));
     A.add(&r->consts, 3 * omega_count(p) + 3 * 127);
-    // cleared at the start, together: the flag word, the largest tiles, the fixed-point current
+    // cleared at the start, together: the flag word, a counter, the largest tiles, the fixed-point current
     A.add(&r->flags, 1);
+    A.add(&r->tile_count, 2);
     A.add(&r->tile_max, 2 * PP_MAX_SPECIES);
     A.add(&r->Jq, p->precision == PP_PREC_FP32_SPLIT ? n3 : 0);
 }

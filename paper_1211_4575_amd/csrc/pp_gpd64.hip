@@ -262,6 +262,10 @@ struct Gpd64TileArgs {
     int heavy;    // rounds of 64 particles that a workgroup takes of a tile and species at most
     int helpers;  // blocks past the tiles' own: a chunk of a heavy tile's other rounds each
     int chunk;    // rounds of a chunk
+    // a sparse box: the tiles to be taken, as found by k_gpd64_sparse (nullptr: all of them)
+    int32_t* list;
+    int32_t* list_count;  // and, beside it, the next push's
+    int few;              // particles of a tile that is not worth a place in the list
     int nsp;
     const int32_t* bins[PP_MAX_SPECIES];  // cell-bin starts of the sort (64 per tile)
     const int32_t* tile_max[PP_MAX_SPECIES];  // an upper bound of a tile's particles, from the sort
@@ -533,18 +537,20 @@ __device__ __forceinline__ int32_t tile_rounds(const Gpd64TileArgs& A, int s, in
 __device__ __forceinline__ bool heavy_chunk(const Gpd64TileArgs& A, int number, double* lds, TileWork& W) {
     uint64_t* words = (uint64_t*)lds;
     const int32_t own = A.heavy * A.parts;
+    const int64_t ntiles = A.list ? *A.list_count : A.ntiles;
+    auto tile_at = [&](int64_t i) { return A.list ? (int64_t)A.list[i] : i; };
     for (int s = 0; s < A.nsp; ++s) {
         if (*A.tile_max[s] <= 64 * (int64_t)own) continue;
-        for (int64_t base = 0; base < A.ntiles; base += GPD64_BS) {
+        for (int64_t base = 0; base < ntiles; base += GPD64_BS) {
             const int64_t t = base + threadIdx.x;
-            const uint64_t heavy = __ballot(t < A.ntiles && tile_rounds(A, s, t < A.ntiles ? t : 0) > own);
+            const uint64_t heavy = __ballot(t < ntiles && tile_rounds(A, s, tile_at(t < ntiles ? t : 0)) > own);
             if ((threadIdx.x & 63) == 0) words[threadIdx.x >> 6] = heavy;
             __syncthreads();
             for (int w = 0; w < GPD64_BS / 64; ++w) {
                 uint64_t left = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)words[w]) |
                                 (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(words[w] >> 32)) << 32;
                 for (; left != 0; left &= left - 1) {
-                    const int64_t tile = base + 64 * w + __ffsll((unsigned long long)left) - 1;
+                    const int64_t tile = tile_at(base + 64 * w + __ffsll((unsigned long long)left) - 1);
                     const int32_t rounds = tile_rounds(A, s, tile);
                     const int n = (rounds - own + A.chunk - 1) / A.chunk;
                     if (number < n) {
@@ -595,6 +601,9 @@ __global__ void __launch_bounds__(GPD64_BS, 3) k_gpd64_tile(Gpd64TileArgs A) {
         first = __builtin_amdgcn_readfirstlane(W.first);
         most = __builtin_amdgcn_readfirstlane(W.last);
         step = 4;
+    } else if (A.list) {
+        if ((int)b >= *A.list_count) return;
+        tile = __builtin_amdgcn_readfirstlane(A.list[b]);
     }
     if (tile >= A.ntiles) return;
     int any = 0;
@@ -711,9 +720,34 @@ __global__ void __launch_bounds__(GPD64_BS, 3) k_gpd64_tile(Gpd64TileArgs A) {
     }
 }
 
+// A sparse box, before the tile kernel: tiles of more than A.few particles go to its list, the particles
+// of the others are left to k_gpd64_deferred.
+__global__ void __launch_bounds__(256) k_gpd64_sparse(Gpd64TileArgs A, int32_t* next_count) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *next_count = 0;
+    const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    int32_t n = 0;
+    if (t < A.ntiles)
+        for (int s = 0; s < A.nsp; ++s) n += A.bins[s][(t + 1) * TILE_CELLS] - A.bins[s][t * TILE_CELLS];
+    const uint64_t dense = __ballot(n > A.few);
+    const int lane = threadIdx.x & 63;
+    int32_t first = 0;
+    if (lane == 0 && dense != 0) first = atomicAdd(A.list_count, (int32_t)__popcll(dense));
+    first = __shfl(first, 0, 64);
+    if (dense >> lane & 1) {
+        A.list[first + (int32_t)__popcll(dense & ((1ull << lane) - 1ull))] = (int32_t)t;
+        return;
+    }
+    if (n == 0) return;
+    for (int s = 0; s < A.nsp; ++s)
+        for (int32_t q = A.bins[s][t * TILE_CELLS]; q < A.bins[s][(t + 1) * TILE_CELLS]; ++q) {
+            A.sp[s].rank[q] = RANK_DEFERRED;
+            if (A.sp[s].id) A.sp[s].id_o[q] = A.sp[s].id[A.sp[s].perm ? A.sp[s].perm[q] : q];
+        }
+}
+
 // Steps 1-3 of the particles that the tile kernel left out, as k_gpd64, and the bins they go to: those
 // that do not lie in their tile where pp_get_particles has handed out the positions since the sort, so
-// that there may be many.  (The tile kernel takes a stray one itself, with its loops over nodes rolled
+// that there may be many, and those of a sparse box's tiles of a few particles.  (The tile kernel takes a stray one itself, with its loops over nodes rolled
 // up, which holds up a wavefront for 0.3 ms.)  A workgroup packs what it finds in DEFER_BLOCK slots.
 // 64x16x16, 5e5 particles, cubic, 1 % of them moved elsewhere by the caller: 1.56 ms -> 0.31 for both
 // kernels, 4.0 by k_gpd64 for all; 16^3, 3e4: 0.35 -> 0.15 and 0.28.  All of them moved: 4.3, 4.2 by k_gpd64.
@@ -899,6 +933,23 @@ hipError_t launch_gpd64_tiles(pp_run* r, double* J, unsigned* done) {
     A.per_xcd = (int)((A.ntiles + 7) / 8);
     plan_workgroups(A, np);
     plan_helpers(A, np);
+    // A sparse box.  A tile takes a workgroup about 25 ns of the whole GPU's time (15 if flat) and 10 more a
+    // further species, and a launch over all tiles 0.8 each; a particle by itself takes 7 ns, but 0.15 ms at
+    // least.  So the tiles are listed first, those of a few particles only where all particles together
+    // are few.  Push and sort, us, a workgroup per tile -> this, and the untiled kernel with a counting sort:
+    // 200^3, 1000 particles 394 -> 202 (370); 2e4 877 -> 541 (524); 1e5 2122 -> 1160 (1200); 128^3, 2e4 485 ->
+    // 326 (316).  Up to 16384 tiles and from 3 particles per tile of one species on it gains nothing.
+    if (sparse_box(A.ntiles, np, A.nsp)) {
+        A.list = r->sort_cursor;  // the counting sort's, which runs elsewhere
+        A.list_count = r->tile_count + r->tile_count_turn;
+        r->tile_count_turn ^= 1;
+        A.few = np > 8192 ? (r->p.n[2] == 1 ? 1 + A.nsp : 2 + 3 * A.nsp / 2) : 0;
+        hipLaunchKernelGGL(k_gpd64_sparse, dim3((unsigned)((A.ntiles + 255) / 256)), dim3(256), 0, r->stream, A,
+                           r->tile_count + r->tile_count_turn);
+        const int64_t most = np / (A.few + 1);  // entries of the list
+        A.per_xcd = (int)(((most < A.ntiles ? most : A.ntiles) + 7) / 8);
+        for (int k = 0; k < A.nsp && A.few > 0; ++k) A.sp[k].defer = 1;
+    }
     hipError_t e = r->p.shape_order == 2 ? launch_tiles<2>(r, A) : launch_tiles<3>(r, A);
     for (int k = 0; k < A.nsp && e == hipSuccess; ++k) {
         if (!A.sp[k].defer) continue;

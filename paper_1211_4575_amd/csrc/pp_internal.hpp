@@ -120,6 +120,8 @@ struct pp_run {
                                       // most that), and after them those of the order before the last
                                       // sort after a push
     int32_t* flags = nullptr;        // device error flags
+    int32_t* tile_count = nullptr;   // FP64 form: entries of a sparse box's tile list, by turns (2)
+    int tile_count_turn = 0;
     double* dacc = nullptr;          // device accumulators for diagnostics
     pp::LineStencil line[3];
 
@@ -190,6 +192,9 @@ inline bool ok(hipError_t e, const char* where) {
 
 // kernels launchers (defined in the kernel translation units)
 hipError_t launch_gpd64(pp_run* r, int s, double* J);  // particles of one species in any order
+// FP64 form: so few particles of nsp species (np in all) for a box of ntiles tiles that most tiles hold
+// less than a workgroup of their own is worth (see pp_gpd64.hip)
+inline bool sparse_box(int64_t ntiles, int64_t np, int nsp) { return ntiles > 16384 && np < (1 + 2 * (int64_t)nsp) * ntiles; }
 // every species whose particles lie binned by cell, by tiles; *done has a bit for each of them
 hipError_t launch_gpd64_tiles(pp_run* r, double* J, unsigned* done);
 hipError_t launch_gpd32(pp_run* r);       // J (or J2, or Jq where line_reads_fixed) of all species

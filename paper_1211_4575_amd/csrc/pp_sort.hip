@@ -775,6 +775,26 @@ __device__ __forceinline__ void ranked_perm_tile(const RankedArgs& A, int64_t T,
         }
 }
 
+// FP64 form: first slot of a bin, bin of a cell, cell of a destination window's entry along an axis, slot
+// of a particle that only names its bin (see bin_perm_tile)
+__device__ __forceinline__ int32_t bin_first(const RankedArgs& A, int32_t bin) {
+    return gl(A.tot)[bin / TILE_CELLS] + gl(A.pre)[bin];
+}
+
+__device__ __forceinline__ int32_t bin_of_cell(const RankedArgs& A, int gx, int gy, int gz) {
+    const Geom& G = A.G;
+    const int32_t t = (gx >> A.tsh[0]) + G.nt[0] * ((gy >> A.tsh[1]) + G.nt[1] * (gz >> A.tsh[2]));
+    return t * TILE_CELLS + (gx & (G.t[0] - 1)) + ((gy & (G.t[1] - 1)) << A.tsh[0]) +
+           ((gz & (G.t[2] - 1)) << (A.tsh[0] + A.tsh[1]));
+}
+
+__device__ __forceinline__ int window_node(int org, int x, int n) { return n == 1 ? 0 : wrap_near(org + x - DEST_HALO, n); }
+
+__device__ __forceinline__ int32_t named_slot(const RankedArgs& A, int32_t bin) {
+    const int32_t end = bin % TILE_CELLS == TILE_CELLS - 1 ? gl(A.tot)[bin / TILE_CELLS + 1] : bin_first(A, bin + 1);
+    return end - atomicSub(gl(A.cnt) + A.G.nbins + bin, 1);
+}
+
 // FP64 form: perm[slot] = particle for the particles of source tile T, and T's next bin starts.  A
 // rank word holds the destination cell and the rank in it (slot << 20 | rank), so a particle's slot is
 // one LDS lookup away, or the cell's bin alone (bit 31 | bin: far from its tile, or past F64_RANKS in
@@ -794,21 +814,14 @@ __device__ __forceinline__ void bin_perm_tile(const RankedArgs& A, int64_t T, in
     }
     if (staged)
         for (int32_t q = threadIdx.x; q < nd; q += blockDim.x) img[q] = IMG_NONE;
-    auto bin_first = [&](int32_t bin) { return gl(A.tot)[bin / TILE_CELLS] + gl(A.pre)[bin]; };
-    auto cell_first = [&](int gx, int gy, int gz) {
-        const int32_t t = (gx >> A.tsh[0]) + G.nt[0] * ((gy >> A.tsh[1]) + G.nt[1] * (gz >> A.tsh[2]));
-        const int lc = (gx & (G.t[0] - 1)) + ((gy & (G.t[1] - 1)) << A.tsh[0]) + ((gz & (G.t[2] - 1)) << (A.tsh[0] + A.tsh[1]));
-        return bin_first(t * TILE_CELLS + lc);
-    };
     const int e0 = G.dest_ext(0), e1 = G.dest_ext(1), slots = e0 * e1 * G.dest_ext(2);
     const int ox = (int)(T % G.nt[0]) * G.t[0], oy = (int)((T / G.nt[0]) % G.nt[1]) * G.t[1],
               oz = (int)(T / ((int64_t)G.nt[0] * G.nt[1])) * G.t[2];
     if (se > ss)
         for (int q = threadIdx.x; q < slots; q += blockDim.x) {
             const int z = q / (e0 * e1), r = q - z * e0 * e1, y = r / e0, x = r - y * e0;
-            first[q] = cell_first(e0 == 1 ? 0 : wrap_near(ox + x - DEST_HALO, G.n[0]),
-                                  e1 == 1 ? 0 : wrap_near(oy + y - DEST_HALO, G.n[1]),
-                                  G.n[2] == 1 ? 0 : wrap_near(oz + z - DEST_HALO, G.n[2]));
+            first[q] = bin_first(A, bin_of_cell(A, window_node(ox, x, G.n[0]), window_node(oy, y, G.n[1]),
+                                                window_node(oz, z, G.n[2])));
         }
     __syncthreads();
     for (int64_t b = ss; b < se; b += PERM_BLOCK) {
@@ -826,9 +839,7 @@ __device__ __forceinline__ void bin_perm_tile(const RankedArgs& A, int64_t T, in
             if (w[k] >= 0) {
                 q = first[w[k] >> 20] + (w[k] & 0xFFFFF);
             } else {
-                const int32_t bin = w[k] & 0x7FFFFFFF, t = bin / TILE_CELLS;
-                const int32_t end = bin % TILE_CELLS == TILE_CELLS - 1 ? gl(A.tot)[t + 1] : bin_first(bin + 1);
-                q = end - atomicSub(gl(A.cnt) + G.nbins + bin, 1);
+                q = named_slot(A, w[k] & 0x7FFFFFFF);
             }
             if (staged && q >= d0 && q < d0 + nd)
                 img[q - d0] = (uint16_t)(p - ss);
@@ -842,6 +853,43 @@ __device__ __forceinline__ void bin_perm_tile(const RankedArgs& A, int64_t T, in
             const int32_t v = img[q];
             if (v != IMG_NONE) gl(A.perm)[d0 + q] = ss + v;
         }
+}
+
+// The same for four tiles of a sparse box, a wavefront each: the few particles of a tile look their cells
+// up one by one.  Tiles of more than SPARSE_MAX particles are left to the whole workgroup.
+constexpr int SPARSE_MAX = 128;
+
+__device__ __forceinline__ void bin_perm_sparse(const RankedArgs& A, int64_t blk, int32_t* lds) {
+    const Geom& G = A.G;
+    const int64_t T = 4 * blk + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (T < G.ntiles) {
+        const int32_t ss = gl(A.start)[T * TILE_CELLS], se = gl(A.start)[(T + 1) * TILE_CELLS];
+        gl(A.next_bins)[T * TILE_CELLS + lane] = gl(A.tot)[T] + gl(A.pre)[T * TILE_CELLS + lane];
+        if (T == G.ntiles - 1 && lane == 0) gl(A.next_bins)[G.nbins] = gl(A.tot)[G.ntiles];
+        const uint32_t row = (uint32_t)T / (uint32_t)G.nt[0], layer = row / (uint32_t)G.nt[1];
+        const int ox = (int)((uint32_t)T - row * (uint32_t)G.nt[0]) * G.t[0],
+                  oy = (int)(row - layer * (uint32_t)G.nt[1]) * G.t[1], oz = (int)layer * G.t[2];
+        const int e0 = G.dest_ext(0), e1 = G.dest_ext(1);
+        if (se - ss <= SPARSE_MAX)
+            for (int32_t p = ss + lane; p < se; p += 64) {
+                const int32_t w = gl(A.rank)[p];
+                if (w < 0) {
+                    gl(A.perm)[named_slot(A, w & 0x7FFFFFFF)] = p;
+                    continue;
+                }
+                const int sl = w >> 20, z = sl / (e0 * e1), r = sl - z * e0 * e1, y = r / e0, x = r - y * e0;
+                gl(A.perm)[bin_first(A, bin_of_cell(A, window_node(ox, x, G.n[0]), window_node(oy, y, G.n[1]),
+                                                    window_node(oz, z, G.n[2]))) +
+                           (w & 0xFFFFF)] = p;
+            }
+    }
+    for (int k = 0; k < 4; ++k) {
+        const int64_t H = 4 * blk + k;
+        if (H >= G.ntiles || gl(A.start)[(H + 1) * TILE_CELLS] - gl(A.start)[H * TILE_CELLS] <= SPARSE_MAX) continue;
+        __syncthreads();
+        bin_perm_tile(A, H, lds);
+    }
 }
 
 size_t sort_perm_lds(const pp_run* r) {
@@ -940,7 +988,7 @@ static KeyGeom key_geom(const pp_run* r) {
 // ---- launches of the ranked sort: all species of a run, or of all runs of a batch ----------
 enum SortPhase { SP_TABLES = 0, SP_SCAN = 1, SP_PERM = 2 };
 
-enum SortForm { SF_SPLIT = 0, SF_FP64 = 1 };
+enum SortForm { SF_SPLIT = 0, SF_FP64 = 1, SF_FP64_SPARSE = 2 };
 
 template <int PHASE, int FORM>
 __device__ __forceinline__ void sort_phase(const RankedArgs& A, int64_t blk, int32_t* lds) {
@@ -954,8 +1002,10 @@ __device__ __forceinline__ void sort_phase(const RankedArgs& A, int64_t blk, int
         ranked_scan(A);
     } else if constexpr (FORM == SF_SPLIT) {
         ranked_perm_tile(A, blk, lds);
-    } else {
+    } else if constexpr (FORM == SF_FP64) {
         bin_perm_tile(A, blk, lds);
+    } else {
+        bin_perm_sparse(A, blk, lds);
     }
 }
 
@@ -1164,11 +1214,12 @@ hipError_t materialize(pp_run* r, int s) {
 
 template <int FORM>
 static void launch_ranked(pp_run* r, const SortArgs& A, unsigned ns, bool any, size_t perm_lds) {
+    constexpr int TABLES = FORM == SF_SPLIT ? SF_SPLIT : SF_FP64;
     const int64_t nt = r->g.ntiles;
-    hipLaunchKernelGGL((k_sort<SP_TABLES, FORM>), dim3((unsigned)((nt + 3) / 4), ns), dim3(sort_threads(SP_TABLES)), 0,
+    hipLaunchKernelGGL((k_sort<SP_TABLES, TABLES>), dim3((unsigned)((nt + 3) / 4), ns), dim3(sort_threads(SP_TABLES)), 0,
                        r->stream, A);
     if (nt <= SORT_SCAN_ONE) {
-        hipLaunchKernelGGL((k_sort<SP_SCAN, FORM>), dim3(1, ns), dim3(sort_threads(SP_SCAN)), 0, r->stream, A);
+        hipLaunchKernelGGL((k_sort<SP_SCAN, TABLES>), dim3(1, ns), dim3(sort_threads(SP_SCAN)), 0, r->stream, A);
     } else {  // scan_tmp has room for a chunk sum and a maximum of eight species many times over
         const int nchunks = (int)((nt + SORT_CHUNK - 1) / SORT_CHUNK);
         const dim3 grid((unsigned)nchunks, ns);
@@ -1176,7 +1227,7 @@ static void launch_ranked(pp_run* r, const SortArgs& A, unsigned ns, bool any, s
         hipLaunchKernelGGL((k_sort_chunks<true>), grid, dim3(SCAN1_BS), 0, r->stream, A, r->scan_tmp, nchunks);
     }
     if (any)
-        hipLaunchKernelGGL((k_sort<SP_PERM, FORM>), dim3((unsigned)nt, ns), dim3(sort_threads(SP_PERM)), perm_lds,
+        hipLaunchKernelGGL((k_sort<SP_PERM, FORM>), dim3((unsigned)(FORM == SF_FP64_SPARSE ? (nt + 3) / 4 : nt), ns), dim3(sort_threads(SP_PERM)), perm_lds,
                            r->stream, A);
 }
 
@@ -1190,16 +1241,23 @@ static hipError_t sort_ranked(pp_run* r, unsigned mask) {
     SortArgs A;
     unsigned ns = 0;
     bool any = false;
+    int64_t np = 0;
     for (int s = 0; s < PP_MAX_SPECIES; ++s) {
         if (!(mask & (1u << s))) continue;
         sort_desc(r, s, &A.sp[ns++]);
+        np += r->sp[s].n;
         any = any || r->sp[s].n > 0;
     }
     if (ns == 0) return hipSuccess;
-    if (r->p.precision == PP_PREC_FP32_SPLIT)
+    if (r->p.precision == PP_PREC_FP32_SPLIT) {
         launch_ranked<SF_SPLIT>(r, A, ns, any, sort_perm_lds(r));
-    else
-        launch_ranked<SF_FP64>(r, A, ns, any, PERM_IMG * sizeof(uint16_t) + (size_t)r->g.dest_slots() * sizeof(int32_t));
+    } else {
+        const size_t lds = PERM_IMG * sizeof(uint16_t) + (size_t)r->g.dest_slots() * sizeof(int32_t);
+        if (sparse_box(r->g.ntiles, np, (int)ns))
+            launch_ranked<SF_FP64_SPARSE>(r, A, ns, any, lds);
+        else
+            launch_ranked<SF_FP64>(r, A, ns, any, lds);
+    }
     hipError_t e = hipGetLastError();
     bool in_place = false;
     for (int s = 0; s < PP_MAX_SPECIES; ++s)

@@ -174,14 +174,16 @@ def test_sort_of_more_particles_in_a_cell_than_a_rank_word_counts(ppm, orc, prec
 
 
 @pytest.mark.parametrize("warmup", [0, 1])
-@pytest.mark.parametrize("precision,n", [("fp64", (12, 9, 8)), ("split", (12, 9, 8)), ("split", (24, 16, 1))])
+@pytest.mark.parametrize("precision,n", [("fp64", (12, 9, 8)), ("fp64", (128, 128, 68)), ("split", (12, 9, 8)),
+                                         ("split", (24, 16, 1))])
 def test_captured_steps_replay(ppm, orc, precision, n, warmup):
     """A pair of steps captured into a graph, right after the run's creation and after a step, replayed
     with other work in between: the run stepped eagerly, in the split form bit for bit (FP64 sums in
     another order, 1e-11 after eight steps)."""
     import torch
     from paper_1211_4575_amd import inputs as I
-    species, E, B = random_state(orc, n, 6, seed=14, uth=0.4)
+    species, E, B = random_state(orc, n, 6 if max(n) < 100 else 1, seed=14, uth=0.4)
+    species = [dict(s, pos=s["pos"][:, :12000].copy(), u=s["u"][:, :12000].copy()) for s in species]  # sparse in the large box
     split = precision == "split"
     if split:
         parts = [I.to_split(s["pos"], n, origin=I.split_origin(3)) for s in species]
@@ -534,3 +536,45 @@ def test_split_crowds_in_small_boxes_equal_batched(ppm, orc, n, O, current):
         assert np.array_equal(a, b)
     for a, b in zip(p1, p2):
         assert all(np.array_equal(a[k], b[k]) for k in a)
+
+
+@pytest.mark.parametrize("nspecies", [1, 3])
+@pytest.mark.parametrize("count", [7, 5000, 30000])
+@pytest.mark.parametrize("n,O", [((100, 101, 104), 3), ((800, 808, 1), 2), ((600000, 1, 1), 3)])
+def test_fp64_sparse_boxes(ppm, orc, n, O, count, nspecies):
+    """Boxes with far more tiles than particles, some of them in bunches: tiles of a few particles are not
+    taken by workgroups of their own, those of a bunch are, and a bunch of 9000 is shared by several.
+    Three pushes of sorted particles against the same of particles left unsorted (FP64 sums in another
+    order, 1e-12 of the largest value), in cell order after each sort, with tags."""
+    rng = np.random.default_rng(17)
+    N = np.array(n, float)[:, None]
+    species = []
+    for s in range(nspecies):
+        pos = [rng.uniform(0, 1, (3, count)) * (N - 1e-9)]
+        for at, k in ((0.31, 9000 if s == 0 else 4), (0.62, 150), (0.77, 3 + s)):
+            pos.append((np.floor(at * N) + rng.uniform(0, 1.3, (3, k)) * (N > 1)) % N)
+        pos = np.concatenate(pos, 1)
+        species.append(dict(q=(-1.0) ** s, m=1.0 + s, w=0.1, pos=pos, u=rng.normal(0, 0.4, pos.shape)))
+    kw = dict(n=n, dt=0.35, shape_order=O, field_order=2, relax_max_iter=4, precision=ppm.PP_PREC_FP64)
+    E, B = (rng.normal(0, 0.1, (3, n[2], n[1], n[0])) for _ in range(2))
+    out = []
+    for sort in (True, False):
+        run = ppm.Run(ppm.make_params(**kw), species, E=E, B=B)
+        Js = []
+        for _ in range(3):
+            run.gather_push_deposit()
+            Js.append(run.fields()[2])
+            if sort:
+                run.sort()
+        parts = [run.particles(s) for s in range(nspecies)]
+        assert run.diagnostics(ppm.PP_DIAG_MOMENTS).flags == 0
+        assert not sort or all(_in_cell_order(p["pos"], n) for p in parts)
+        out.append((Js, [_by_id(p) for p in parts]))
+        run.close()
+    (J1, p1), (J2, p2) = out
+    for a, b in zip(J1, J2):
+        assert rel_inf(a, b) < 1e-12
+    for a, b, s in zip(p1, p2, species):
+        assert np.array_equal(a["id"], np.arange(s["u"].shape[1])) and np.array_equal(b["id"], a["id"])
+        assert np.max(np.abs(periodic_diff(a["pos"], b["pos"], n))) < 1e-9
+        assert rel_inf(a["u"], b["u"]) < 1e-12
