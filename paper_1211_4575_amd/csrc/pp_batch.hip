@@ -176,7 +176,7 @@ pp_status batch_step(pp_batch* b, TableTarget target) {
     int64_t* fpre = (int64_t*)(H + o_fpre);
     int64_t* cpre = (int64_t*)(H + o_cpre);
     tpre[0] = fpre[0] = cpre[0] = 0;
-    int max_sweeps = 0, min_sweeps = 0;
+    int max_sweeps = 0, min_sweeps = 0, nthin = 0;
     for (int i = 0; i < n; ++i) {
         pp_run* r = b->runs[i];
         gpd32_fill_args(r, (Gpd32Args*)(H + o_gpd + i * gpd32_args_size()));
@@ -191,6 +191,7 @@ pp_status batch_step(pp_batch* b, TableTarget target) {
         tpre[i + 1] = tpre[i] + gpd32_blocks(r);
         fpre[i + 1] = fpre[i] + gpd32_fixed_blocks(r);
         cpre[i + 1] = cpre[i] + field_blocks(r, n);
+        nthin += field_by_cells(r) ? 1 : 0;
         max_sweeps = r->jac_sweeps > max_sweeps ? r->jac_sweeps : max_sweeps;
         min_sweeps = i == 0 || r->jac_sweeps < min_sweeps ? r->jac_sweeps : min_sweeps;
     }
@@ -236,7 +237,8 @@ pp_status batch_step(pp_batch* b, TableTarget target) {
     }
     e = launch_sort_batch(D + o_sort, pre, stot, ns, perm_lds, b->stream);
     if (!ok(e, "batch sort")) return PP_E_HIP;
-    e = launch_field_step_batch(D + o_field, (const int64_t*)(D + o_cpre), n, cpre[n], min_sweeps, max_sweeps, b->stream);
+    e = launch_field_step_batch(D + o_field, (const int64_t*)(D + o_cpre), n, nthin, cpre[n], min_sweeps, max_sweeps,
+                                b->stream);
     if (!ok(e, "batch field_step")) return PP_E_HIP;
 
     // ---- host bookkeeping (tile starts and pending orders after the sort) ------------------

@@ -124,7 +124,7 @@ struct FieldDesc {
     double al2s, gdiag;         // alpha^2 s, gamma / diagonal
     double al, be, c2dt, mu0;   // alpha, beta, c^2 dt, mu0
     int sweeps;
-    int zc;                     // planes a block of the tiled kernels marches over
+    int zc;                     // planes a block of the tiled kernels marches over; 0: a thread per cell
 };
 
 // Gauss-law filter pass, first half: r = div- E - (rho + rho_bg)/eps0 into R
@@ -532,6 +532,81 @@ constexpr int field_lds(int kind) {
     return kind == FK_RELAX ? lap : (kind == FK_RHS ? lap : 0) + 2 * (dx + dy);
 }
 
+// ---- the field step, a thread per cell and component ------------------------------------
+// For boxes that the columns fit badly (see thin_box): every tap read through the caches, the
+// sums in the tiled kernels' order.
+template <int M, int UP>
+__device__ __forceinline__ double dcell(const FieldGeom& G, const double* f, int ax, int i, int j, int k) {
+    const int c[3] = {i, j, k};
+    const int stride = ax == 0 ? 1 : (ax == 1 ? G.n[0] : G.n[0] * G.n[1]);
+    const double* line = f + (lin(G, i, j, k) - c[ax] * stride);
+    double s = 0.0;
+#pragma unroll
+    for (int m = 1; m <= M; ++m)
+        s += G.a[ax][m - 1] * (line[nbw(c[ax], m - 1 + UP, G.n[ax], G.small) * stride] -
+                               line[nbw(c[ax], -m + UP, G.n[ax], G.small) * stride]);
+    return s;
+}
+
+template <int R>
+__device__ __forceinline__ double lap_cell(const FieldGeom& G, const double* f, int i, int j, int k) {
+    const int nx = G.n[0], nxy = G.n[0] * G.n[1];
+    const double *fx = f + nx * (j + G.n[1] * k), *fy = f + (i + nxy * k), *fz = f + (i + nx * j);
+    double s = 0.0;
+#pragma unroll
+    for (int o = -R; o <= R; ++o) {
+        s += G.L[0][o + R] * fx[nbw(i, o, nx, G.small)];
+        s += G.L[1][o + R] * fy[nx * nbw(j, o, G.n[1], G.small)];
+        s += G.L[2][o + R] * fz[nxy * nbw(k, o, G.n[2], G.small)];
+    }
+    return s;
+}
+
+template <int M, int KIND>
+__device__ __forceinline__ void field_cells(const FieldDesc& D, int b, int k) {
+    constexpr int R = 2 * M - 1;
+    const FieldGeom& G = D.G;
+    const int blocks = G.xchunks * ((G.rows + G.rpb - 1) / G.rpb);
+    const int C = b / blocks, d1 = C == 2 ? 0 : C + 1, d2 = C == 0 ? 2 : C - 1;
+    int i, j, z;
+    if (!field_cell(G, b - C * blocks, threadIdx.x, i, j, z)) return;
+    const int64_t co = C * G.nc, q = co + lin(G, i, j, z);
+    if constexpr (KIND == FK_RELAX) {
+        const double* x = gl(k == 1 ? D.Bn : relax_array(D, k - 1)) + co;
+        const double pq = gl(k <= 2 ? D.Bn : relax_array(D, k - 2))[q], xq = x[q - co], w = gl(D.omega)[k];
+        const double Ax = xq - D.al2s * lap_cell<R>(G, x, i, j, z);
+        const double y = xq + (gl(D.R)[q] - Ax) * D.gdiag;
+        gl(relax_array(D, k))[q] = pq + w * (y - pq);
+    } else if constexpr (KIND == FK_RHS) {
+        const double *E1 = gl(D.E) + d1 * G.nc, *E2 = gl(D.E) + d2 * G.nc;
+        const double *J1 = gl(D.J) + d1 * G.nc, *J2 = gl(D.J) + d2 * G.nc;
+        const double* x = gl(D.B) + co;
+        const double lp = lap_cell<R>(G, x, i, j, z);
+        const double curlE = dcell<M, 1>(G, E2, d1, i, j, z) - dcell<M, 1>(G, E1, d2, i, j, z);
+        const double curlJ = dcell<M, 1>(G, J2, d1, i, j, z) - dcell<M, 1>(G, J1, d2, i, j, z);
+        const double xq = x[q - co];
+        const double rq = xq + D.cab * lp - D.dt * curlE + D.cj * curlJ;
+        gl(D.R)[q] = rq;
+        gl(D.Bn)[q] = xq;
+        if (D.sweeps > 1) {  // sweep 1
+            const double Ax = xq - D.al2s * lp;
+            const double y = xq + (rq - Ax) * D.gdiag;
+            gl(D.Bw)[q] = xq + gl(D.omega)[1] * (y - xq);
+        }
+    } else {
+        const double *B1 = gl(D.B) + d1 * G.nc, *B2 = gl(D.B) + d2 * G.nc;
+        const double *N1 = gl(D.Bn) + d1 * G.nc, *N2 = gl(D.Bn) + d2 * G.nc;
+        const double cn = dcell<M, 0>(G, B2, d1, i, j, z) - dcell<M, 0>(G, B1, d2, i, j, z);
+        const double co_ = dcell<M, 0>(G, N2, d1, i, j, z) - dcell<M, 0>(G, N1, d2, i, j, z);
+        gl(D.E)[q] = gl(D.E)[q] + D.c2dt * (D.al * cn + D.be * co_ - D.mu0 * gl(D.J)[q]);
+    }
+}
+
+template <int M, int KIND>
+__global__ void __launch_bounds__(FIELD_BS) k_field_cells(FieldDesc D, int k) {
+    field_cells<M, KIND>(D, (int)blockIdx.x, k);
+}
+
 // block b of a run's launch of one phase (k: the sweep)
 template <int M, int KIND, bool STREAM>
 __device__ __forceinline__ void field_tile(const FieldDesc& D, int b, int k, double* lds) {
@@ -594,12 +669,41 @@ __global__ void __launch_bounds__(RX_BS) k_field_tiles_batch(const FieldDesc* __
     const FieldDesc& D = T[r];
     if (KIND == FK_RELAX && (k > D.sweeps || (k == 1 && D.sweeps > 1))) return;
     const int lb = (int)(b - prefix[r]);
+    if (D.zc == 0) return;  // k_field_cells_batch
     if (D.G.M == 3)
         field_tile<3, KIND, false>(D, lb, k, lds);
     else if (D.G.M == 2)
         field_tile<2, KIND, false>(D, lb, k, lds);
     else
         field_tile<1, KIND, false>(D, lb, k, lds);
+}
+
+// the same launch for the members with a thread per cell
+template <int KIND>
+__global__ void __launch_bounds__(FIELD_BS) k_field_cells_batch(const FieldDesc* __restrict__ T,
+                                                                const int64_t* __restrict__ prefix, int nruns, int k) {
+    const int64_t b = blockIdx.x;
+    const int r = find_segment(prefix, nruns, b);
+    if (r < 0) return;
+    const FieldDesc& D = T[r];
+    if (D.zc != 0 || (KIND == FK_RELAX && (k > D.sweeps || (k == 1 && D.sweeps > 1)))) return;
+    const int lb = (int)(b - prefix[r]);
+    if (D.G.M == 3)
+        field_cells<3, KIND>(D, lb, k);
+    else if (D.G.M == 2)
+        field_cells<2, KIND>(D, lb, k);
+    else
+        field_cells<1, KIND>(D, lb, k);
+}
+
+// One phase of a batch, nthin of whose n members take a thread per cell.
+template <int KIND>
+static void launch_field_batch(const FieldDesc* T, const int64_t* prefix, int n, int nthin, unsigned blocks, int k,
+                               hipStream_t st) {
+    if (nthin < n)
+        hipLaunchKernelGGL(k_field_tiles_batch<KIND>, dim3(blocks), dim3(RX_BS), 0, st, T, prefix, n, k);
+    if (nthin > 0)
+        hipLaunchKernelGGL(k_field_cells_batch<KIND>, dim3(blocks), dim3(FIELD_BS), 0, st, T, prefix, n, k);
 }
 
 // The whole relaxation of a small box, a workgroup per component: the current iterate in LDS
@@ -688,6 +792,15 @@ static void launch_field_order(const FieldDesc& D, dim3 grid, unsigned blocks, i
 
 template <int KIND>
 static void launch_field_tiles(const FieldDesc& D, unsigned blocks, int k, hipStream_t st) {
+    if (D.zc == 0) {
+        if (D.G.M == 3)
+            hipLaunchKernelGGL((k_field_cells<3, KIND>), dim3(blocks), dim3(FIELD_BS), 0, st, D, k);
+        else if (D.G.M == 2)
+            hipLaunchKernelGGL((k_field_cells<2, KIND>), dim3(blocks), dim3(FIELD_BS), 0, st, D, k);
+        else
+            hipLaunchKernelGGL((k_field_cells<1, KIND>), dim3(blocks), dim3(FIELD_BS), 0, st, D, k);
+        return;
+    }
     const dim3 grid(KIND == FK_RELAX                  ? xcd_grid(blocks)
                     : components_together(KIND, D.zc) ? 3 * xcd_grid(blocks / 3)
                                                       : blocks);
@@ -697,20 +810,27 @@ static void launch_field_tiles(const FieldDesc& D, unsigned blocks, int k, hipSt
         launch_field_order<KIND, false>(D, grid, blocks, k, st);
 }
 
+// Boxes that leave most of their columns' threads without a cell, or are only a few cells wide, so that a
+// column's rows are partial lines: a thread per cell (the same in a batch as alone).  Field step, us, 32x8
+// columns -> cells, orders 2 and 6: 2x300x300 387 -> 111 and 595 -> 245; 8x300x300 417 -> 237, 584 -> 500;
+// 512x1x512 236 -> 98, 409 -> 275; 1000000x1x1 1498 -> 213, 3505 -> 788; 10x10x300 88 -> 69, 123 -> 94; on the
+// other side of the line 512x2x512 at 4th and 6th order 374 and 469 against 376 and 529, 12x300x300 478 and 591
+// against 617 and 887, 33x33x33 82 and 87 against 88 and 111.
+static bool thin_box(const int n[3], int order) {
+    const int64_t cells = (int64_t)n[0] * n[1];
+    const int64_t threads = (int64_t)RX_BS * ((n[0] + RX_TX - 1) / RX_TX) * ((n[1] + RX_TY - 1) / RX_TY);
+    return n[0] <= 8 || 5 * cells <= threads || (4 * cells <= threads && (order == 2 || n[2] <= 8));
+}
+
 // Planes per block: as many as leave the launch about 8 blocks per CU (its share of them in a
 // batch of nruns), so that small boxes fill the GPU, and at most RX_ZC, where reading the
-// stencil's planes above and below once per block costs little.
-static int planes_per_block(const int n[3], int nruns) {
+// stencil's planes above and below once per block costs little.  0: a thread per cell.
+static int planes_per_block(const pp_run* r, int nruns) {
+    const int* n = r->p.n;
+    if (thin_box(n, r->p.field_order)) return 0;
     const int64_t cols = 3 * (int64_t)((n[0] + RX_TX - 1) / RX_TX) * ((n[1] + RX_TY - 1) / RX_TY);
     const int64_t zc = cols * n[2] * nruns / 2048;
     return (int)(zc < 1 ? 1 : (zc > RX_ZC ? RX_ZC : zc));
-}
-
-// Blocks of one phase of a run's field step, in a batch of nruns.
-int64_t field_blocks(const pp_run* r, int nruns) {
-    const int* n = r->p.n;
-    const int zc = planes_per_block(n, nruns);
-    return 3 * (int64_t)((n[0] + RX_TX - 1) / RX_TX) * ((n[1] + RX_TY - 1) / RX_TY) * ((n[2] + zc - 1) / zc);
 }
 
 static void fd_coeffs(int order, double a[3]) {
@@ -760,6 +880,16 @@ static FieldGeom make_geom(const pp_run* r) {
 }
 
 static int64_t blocks_of(const CellGeom& G) { return (int64_t)G.xchunks * ((G.rows + G.rpb - 1) / G.rpb); }
+
+bool field_by_cells(const pp_run* r) { return thin_box(r->p.n, r->p.field_order); }
+
+// Blocks of one phase of a run's field step, in a batch of nruns.
+int64_t field_blocks(const pp_run* r, int nruns) {
+    const int* n = r->p.n;
+    const int zc = planes_per_block(r, nruns);
+    if (zc == 0) return 3 * blocks_of(make_geom(r));
+    return 3 * (int64_t)((n[0] + RX_TX - 1) / RX_TX) * ((n[1] + RX_TY - 1) / RX_TY) * ((n[2] + zc - 1) / zc);
+}
 
 // Host set-up of the field-step constants: the composed Laplacian stencil (d- after d+,
 // identical as a stencil to d+ after d-), the true diagonal of A = 1 - alpha^2 s lap on this
@@ -910,7 +1040,7 @@ void field_desc(const pp_run* r, FieldDesc* D, int nruns) {
     D->c2dt = c2 * dt;
     D->mu0 = mu0;
     D->sweeps = r->jac_sweeps;
-    D->zc = planes_per_block(r->p.n, nruns);
+    D->zc = planes_per_block(r, nruns);
 }
 
 size_t field_desc_size() { return sizeof(FieldDesc); }
@@ -1000,15 +1130,15 @@ hipError_t launch_gauss_filter(pp_run* r) {
 }
 
 // Batched field step over n runs: table (device) of FieldDesc, prefix (device) of blocks.
-hipError_t launch_field_step_batch(const void* table, const int64_t* prefix, int n, int64_t total_blocks,
+hipError_t launch_field_step_batch(const void* table, const int64_t* prefix, int n, int nthin, int64_t total_blocks,
                                    int min_sweeps, int max_sweeps, hipStream_t st) {
     if (n == 0 || total_blocks == 0) return hipSuccess;
     const FieldDesc* T = (const FieldDesc*)table;
-    const dim3 grid((unsigned)total_blocks);
-    hipLaunchKernelGGL(k_field_tiles_batch<FK_RHS>, grid, dim3(RX_BS), 0, st, T, prefix, n, 0);
+    const unsigned blocks = (unsigned)total_blocks;
+    launch_field_batch<FK_RHS>(T, prefix, n, nthin, blocks, 0, st);
     for (int k = min_sweeps > 1 ? 2 : 1; k <= max_sweeps; ++k)
-        hipLaunchKernelGGL(k_field_tiles_batch<FK_RELAX>, grid, dim3(RX_BS), 0, st, T, prefix, n, k);
-    hipLaunchKernelGGL(k_field_tiles_batch<FK_UPDATE_E>, grid, dim3(RX_BS), 0, st, T, prefix, n, 0);
+        launch_field_batch<FK_RELAX>(T, prefix, n, nthin, blocks, k, st);
+    launch_field_batch<FK_UPDATE_E>(T, prefix, n, nthin, blocks, 0, st);
     return hipGetLastError();
 }
 

@@ -203,6 +203,7 @@ bool line_reads_fixed(const pp_run* r);   // the line solve takes the fixed-poin
 hipError_t launch_field_step(pp_run* r);
 // blocks of one launch of this run's field step, in a batch of nruns
 int64_t field_blocks(const pp_run* r, int nruns);
+bool field_by_cells(const pp_run* r);  // its field step takes a thread per cell
 // Sort species s (-1: all): FP64 form, counting sort by cell; split form, the tile order (pairs
 // of ranks in chunks of 64) per tile, from the particle kernel's counts and ranks when it has
 // run since the last sort (all such species together), otherwise (first sort, arbitrary order)
@@ -244,7 +245,8 @@ hipError_t launch_gpd32_batch(const void* args_table, const int64_t* tile_prefix
                               int shape_order, size_t lds, hipStream_t st);
 size_t field_desc_size();
 void field_desc(const pp_run* r, FieldDesc* D, int nruns);
-hipError_t launch_field_step_batch(const void* table, const int64_t* prefix, int n, int64_t total_blocks,
+// nthin of the n runs: field_by_cells
+hipError_t launch_field_step_batch(const void* table, const int64_t* prefix, int n, int nthin, int64_t total_blocks,
                                    int min_sweeps, int max_sweeps, hipStream_t st);
 size_t line_desc_size();
 int64_t line_blocks(const pp_run* r, int nruns);  // blocks of this run's line solve in a batch of nruns

@@ -578,3 +578,59 @@ def test_fp64_sparse_boxes(ppm, orc, n, O, count, nspecies):
         assert np.array_equal(a["id"], np.arange(s["u"].shape[1])) and np.array_equal(b["id"], a["id"])
         assert np.max(np.abs(periodic_diff(a["pos"], b["pos"], n))) < 1e-9
         assert rel_inf(a["u"], b["u"]) < 1e-12
+
+
+@pytest.mark.parametrize("n,order", [((2, 300, 40), 4), ((8, 24, 40), 6), ((300, 1, 64), 2), ((300, 1, 64), 6),
+                                     ((1000, 2, 3), 4), ((300, 2, 16), 2), ((1, 1, 5000), 6), ((10, 10, 90), 6),
+                                     ((9, 40, 15), 6), ((64, 2, 33), 4)])
+def test_field_step_of_thin_boxes(ppm, orc, n, order):
+    """Boxes on both sides of the line between columns and a thread per cell, over time steps whose
+    relaxation takes an odd and an even number of sweeps.  Both sides relax to 1e-14, in FP64: 1e-12 of the
+    largest value."""
+    _, E, B = random_state(orc, n, 1, seed=33)
+    odd = set()
+    for dt in (1e-8, 0.1, 0.2, 0.3, 0.4):
+        kw = dict(n=n, dt=dt, shape_order=3, field_order=order, relax_tol=1e-14, relax_max_iter=200)
+        ref = orc.Run(orc.make_params(**kw), [], E=E, B=B)
+        run = ppm.Run(ppm.make_params(precision=ppm.PP_PREC_FP64, **kw), [], E=E, B=B)
+        for _ in range(2):
+            ref.fields_step()
+            run.field_step()
+        Eg, Bg, _ = run.fields()
+        sweeps = run.diagnostics(ppm.PP_DIAG_FIELDS).relax_iters
+        odd.add(1 if sweeps == 1 else 2 + sweeps % 2)
+        assert rel_inf(Eg, ref.E) < 1e-12 and rel_inf(Bg, ref.B) < 1e-12, (dt, sweeps)
+        run.close()
+    assert len(odd) >= 2
+
+
+@pytest.mark.parametrize("order", [2, 4, 6])
+def test_thin_boxes_in_a_batch_equal_alone(ppm, orc, order):
+    """Boxes of both kinds stepped together and alone: bit for bit the same."""
+    import torch
+    from paper_1211_4575_amd import inputs as I
+    boxes = ((4, 4, 4), (8, 40, 36), (33, 9, 12), (10, 10, 96), (40, 4, 44))
+    runs = []
+    for batched in (True, False):
+        runs.append([])
+        for i, n in enumerate(boxes):
+            species, E, B = random_state(orc, n, 3, seed=40 + i, uth=0.3)
+            sp = []
+            for s in species:
+                cell, off = I.to_split(s["pos"], n, origin=I.split_origin(2))
+                sp.append(dict(q=s["q"], m=s["m"], w=s["w"], cell=cell, off=off, u=s["u"].astype(np.float32)))
+            runs[-1].append(ppm.Run(ppm.make_params(n=n, dt=0.3 + 0.02 * i, shape_order=2, field_order=order,
+                                                    relax_max_iter=100, precision=ppm.PP_PREC_FP32_SPLIT), sp, E=E, B=B))
+    batch = ppm.pp_batch_create(8, torch.cuda.current_stream().cuda_stream)
+    for r in runs[0]:
+        ppm.pp_batch_add(batch, r.handle)
+    for _ in range(3):
+        ppm.pp_batch_step(batch)
+        for r in runs[1]:
+            r.step()
+    ppm.pp_batch_destroy(batch)
+    for a, b in zip(*runs):
+        for f, g in zip(a.fields(), b.fields()):
+            assert np.array_equal(f, g)
+        a.close()
+        b.close()
