@@ -65,7 +65,9 @@ __global__ void k_fill_i32(int32_t* p, int64_t n, int32_t v) {
         p[q] = v;
 }
 
-__global__ void k_copy_i32(int32_t* dst, const int32_t* src, int64_t n) {
+// and one entry elsewhere (nullptr: none)
+__global__ void k_copy_i32(int32_t* dst, const int32_t* src, int64_t n, int32_t* one, int32_t value) {
+    if (one && blockIdx.x == 0 && threadIdx.x == 0) *one = value;
     for (int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; q < n; q += (int64_t)gridDim.x * blockDim.x)
         dst[q] = src[q];
 }
@@ -1295,15 +1297,15 @@ static hipError_t sort_species(pp_run* r, int s) {
                                (const double*)S.cur.pos[1], (const double*)S.cur.pos[2], S.n, S.offsets);
     }
     scan_inplace(S.offsets, nkeys + 1, r->scan_tmp, r->stream);
-    // FP64 form: an upper bound will do (it looks for heavy tiles itself)
-    hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(1), 0, r->stream, r->tile_max + s, (int64_t)1, split ? 0 : (int32_t)S.n);
     if (split) {
+        hipLaunchKernelGGL(k_fill_i32, dim3(1), dim3(1), 0, r->stream, r->tile_max + s, (int64_t)1, 0);
         hipLaunchKernelGGL(k_tile_max, dim3(grid_for(ntiles, bs, 1024)), dim3(bs), 0, r->stream,
                            (const int32_t*)S.offsets, ntiles, r->tile_max + s);
     }
     if (S.n > 0) {
+        // FP64 form: an upper bound of the largest tile will do (the push looks for heavy tiles itself)
         hipLaunchKernelGGL(k_copy_i32, dim3(grid_for(nkeys, bs)), dim3(bs), 0, r->stream, r->sort_cursor,
-                           (const int32_t*)S.offsets, nkeys);
+                           (const int32_t*)S.offsets, nkeys, split ? nullptr : r->tile_max + s, (int32_t)S.n);
         ScatterArgs<T> A;
         A.G = G;
         A.n = S.n;
