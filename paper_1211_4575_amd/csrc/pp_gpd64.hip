@@ -754,30 +754,23 @@ __global__ void __launch_bounds__(256) k_gpd64_sparse(Gpd64TileArgs A, int32_t* 
 constexpr int DEFER_BLOCK = 256;
 
 template <int O>
-__global__ void __launch_bounds__(256) k_gpd64_deferred(Gpd64Args A, int t0, int t1, int t2) {
+__global__ void __launch_bounds__(256) k_gpd64_deferred(Gpd64TileArgs T) {
     __shared__ int32_t slot[DEFER_BLOCK];
     __shared__ int32_t count;
+    const Gpd64Args& A = T.sp[blockIdx.y];
+    if (!A.defer) return;
     if (threadIdx.x == 0) count = 0;
     __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * DEFER_BLOCK;
     for (int i = threadIdx.x; i < DEFER_BLOCK && base + i < A.np; i += 256)
         if (A.rank[base + i] == RANK_DEFERRED) slot[atomicAdd(&count, 1)] = (int32_t)(base + i);
     __syncthreads();
-    const int t[3] = {t0, t1, t2};
     for (int i = threadIdx.x; i < count; i += 256) {
         const int32_t q = slot[i];
         double Xn[3];
         gpd64_particle<O, O + 2>(A, A.perm ? A.perm[q] : q, q, Xn);
-        int tile = 0, lc = 0, mul = 1, tmul = 1;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const int c = nearest_cell(Xn[d], A.n[d]), ti = c / t[d];
-            tile += ti * tmul;
-            lc += (c - ti * t[d]) * mul;
-            mul *= t[d];
-            tmul *= (A.n[d] + t[d] - 1) / t[d];
-        }
-        A.rank[q] = name_bin(A, tile * TILE_CELLS + lc);
+        const int c[3] = {nearest_cell(Xn[0], A.n[0]), nearest_cell(Xn[1], A.n[1]), nearest_cell(Xn[2], A.n[2])};
+        A.rank[q] = name_bin(A, bin_of(T, c));
     }
 }
 
@@ -951,16 +944,16 @@ hipError_t launch_gpd64_tiles(pp_run* r, double* J, unsigned* done) {
         for (int k = 0; k < A.nsp && A.few > 0; ++k) A.sp[k].defer = 1;
     }
     hipError_t e = r->p.shape_order == 2 ? launch_tiles<2>(r, A) : launch_tiles<3>(r, A);
-    for (int k = 0; k < A.nsp && e == hipSuccess; ++k) {
-        if (!A.sp[k].defer) continue;
-        const dim3 grid((unsigned)((A.sp[k].np + DEFER_BLOCK - 1) / DEFER_BLOCK));
-        if (r->p.shape_order == 2)
-            hipLaunchKernelGGL(k_gpd64_deferred<2>, grid, dim3(256), 0, r->stream, A.sp[k], A.t[0], A.t[1], A.t[2]);
-        else
-            hipLaunchKernelGGL(k_gpd64_deferred<3>, grid, dim3(256), 0, r->stream, A.sp[k], A.t[0], A.t[1], A.t[2]);
-        e = hipGetLastError();
-    }
-    return e;
+    int64_t longest = 0;
+    for (int k = 0; k < A.nsp; ++k)
+        if (A.sp[k].defer && A.sp[k].np > longest) longest = A.sp[k].np;
+    if (e != hipSuccess || longest == 0) return e;
+    const dim3 grid((unsigned)((longest + DEFER_BLOCK - 1) / DEFER_BLOCK), (unsigned)A.nsp);
+    if (r->p.shape_order == 2)
+        hipLaunchKernelGGL(k_gpd64_deferred<2>, grid, dim3(256), 0, r->stream, A);
+    else
+        hipLaunchKernelGGL(k_gpd64_deferred<3>, grid, dim3(256), 0, r->stream, A);
+    return hipGetLastError();
 }
 
 }  // namespace pp
