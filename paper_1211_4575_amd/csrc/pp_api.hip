@@ -123,7 +123,7 @@ static void run_arrays(const pp_params* p, const Geom& g, pp_run* r, Arena& A) {
     A.add(&r->consts, 3 * omega_count(p) + 3 * 127);
     // cleared at the start, together: the flag word, a counter, the largest tiles, the fixed-point current
     A.add(&r->flags, 1);
-    A.add(&r->tile_count, 2);
+    A.add(&r->tile_count, 1);
     A.add(&r->tile_max, 2 * PP_MAX_SPECIES);
     A.add(&r->Jq, p->precision == PP_PREC_FP32_SPLIT ? n3 : 0);
 }

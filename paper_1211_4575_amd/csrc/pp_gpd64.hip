@@ -264,7 +264,7 @@ struct Gpd64TileArgs {
     int chunk;    // rounds of a chunk
     // a sparse box: the tiles to be taken, as found by k_gpd64_sparse (nullptr: all of them)
     int32_t* list;
-    int32_t* list_count;  // and, beside it, the next push's
+    int32_t* list_count;  // zero before k_gpd64_sparse
     int few;              // particles of a tile that is not worth a place in the list
     int nsp;
     const int32_t* bins[PP_MAX_SPECIES];  // cell-bin starts of the sort (64 per tile)
@@ -722,8 +722,7 @@ __global__ void __launch_bounds__(GPD64_BS, 3) k_gpd64_tile(Gpd64TileArgs A) {
 
 // A sparse box, before the tile kernel: tiles of more than A.few particles go to its list, the particles
 // of the others are left to k_gpd64_deferred.
-__global__ void __launch_bounds__(256) k_gpd64_sparse(Gpd64TileArgs A, int32_t* next_count) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *next_count = 0;
+__global__ void __launch_bounds__(256) k_gpd64_sparse(Gpd64TileArgs A) {
     const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
     int32_t n = 0;
     if (t < A.ntiles)
@@ -934,11 +933,11 @@ hipError_t launch_gpd64_tiles(pp_run* r, double* J, unsigned* done) {
     // 326 (316).  Up to 16384 tiles and from 3 particles per tile of one species on it gains nothing.
     if (sparse_box(A.ntiles, np, A.nsp)) {
         A.list = r->sort_cursor;  // the counting sort's, which runs elsewhere
-        A.list_count = r->tile_count + r->tile_count_turn;
-        r->tile_count_turn ^= 1;
+        A.list_count = r->tile_count;
         A.few = np > 8192 ? (r->p.n[2] == 1 ? 1 + A.nsp : 2 + 3 * A.nsp / 2) : 0;
-        hipLaunchKernelGGL(k_gpd64_sparse, dim3((unsigned)((A.ntiles + 255) / 256)), dim3(256), 0, r->stream, A,
-                           r->tile_count + r->tile_count_turn);
+        const hipError_t e = launch_fill_i32(r->tile_count, 1, 0, r->stream);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_gpd64_sparse, dim3((unsigned)((A.ntiles + 255) / 256)), dim3(256), 0, r->stream, A);
         const int64_t most = np / (A.few + 1);  // entries of the list
         A.per_xcd = (int)(((most < A.ntiles ? most : A.ntiles) + 7) / 8);
         for (int k = 0; k < A.nsp && A.few > 0; ++k) A.sp[k].defer = 1;

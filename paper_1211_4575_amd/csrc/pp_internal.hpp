@@ -120,8 +120,7 @@ struct pp_run {
                                       // most that), and after them those of the order before the last
                                       // sort after a push
     int32_t* flags = nullptr;        // device error flags
-    int32_t* tile_count = nullptr;   // FP64 form: entries of a sparse box's tile list, by turns (2)
-    int tile_count_turn = 0;
+    int32_t* tile_count = nullptr;   // FP64 form: entries of a sparse box's tile list
     double* dacc = nullptr;          // device accumulators for diagnostics
     pp::LineStencil line[3];
 

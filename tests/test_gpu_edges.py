@@ -228,6 +228,48 @@ def test_captured_steps_replay(ppm, orc, precision, n, warmup):
             assert np.array_equal(p[k], q[k]) if split else np.max(np.abs(p[k] - q[k])) < 1e-11
 
 
+def test_captured_steps_with_one_sort_replay(ppm, orc):
+    """A pair of FP64 steps of a sparse box, the first without a sort, so that one of the two pushes is by
+    tiles: replayed with other work in between it is the run stepped eagerly (sums in another order)."""
+    import torch
+    n = (128, 128, 68)
+    species, E, B = random_state(orc, n, 1, seed=23, uth=0.4)
+    species = [dict(s, pos=s["pos"][:, :12000].copy(), u=s["u"][:, :12000].copy()) for s in species]
+    kw = dict(n=n, dt=0.3, shape_order=3, field_order=4, relax_max_iter=100, precision=ppm.PP_PREC_FP64)
+    stream = torch.cuda.Stream()
+    out = []
+    for captured in (True, False):
+        with torch.cuda.stream(stream):
+            run = ppm.Run(ppm.make_params(**kw), species, E=E, B=B)
+            run.step()
+            torch.cuda.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            if captured:
+                with torch.cuda.graph(graph, stream=stream):
+                    run.step(sort=False)
+                    run.step()
+            fields = []
+            for _ in range(3):
+                if captured:
+                    graph.replay()
+                else:
+                    run.step(sort=False)
+                    run.step()
+                torch.cuda.synchronize()
+                torch.ones(1 << 16, device="cuda").cumsum(0)
+                fields.append(run.fields())
+            assert run.diagnostics().flags == 0
+            out.append((fields, [_by_id(run.particles(s)) for s in range(2)]))
+            del graph
+            run.close()
+    for f, g in zip(out[0][0], out[1][0]):
+        for a, b in zip(f, g):
+            assert rel_inf(a, b) < 1e-11
+    for p, q in zip(out[0][1], out[1][1]):
+        for k in p:
+            assert np.max(np.abs(p[k] - q[k])) < 1e-11
+
+
 @pytest.mark.parametrize("n,ppc", [((96, 83, 100), 2), ((64, 41, 26), 24), ((700, 300, 1), 6)])
 def test_sums_of_diagnostics_over_many_rounds(ppm, orc, n, ppc):
     """Boxes and particle counts past the largest launch of the sums, whose workgroups take several
