@@ -165,9 +165,10 @@ __global__ void __launch_bounds__(FIELD_BS) k_field(FieldDesc D, int phase) {
 // in flight while the block works on the current one.  Single and batched runs take the same
 // code, so a batched run gives the same bits as the run alone.
 //
-// A sweep is bound by memory in large boxes (256^3: 0.38 ms, 4.2 TB/s for the four arrays it
+// A sweep is bound by memory in large boxes (256^3: 0.34 ms, 4.7 TB/s for the four arrays it
 // cannot do without) and by latency in small ones, where short marches (D.zc, down to one plane
-// with every load in flight at once) spread it over the GPU.  Tiles of 64x8, 32x16, 64x4 and 64x16
+// with every load in flight at once) spread it over the GPU.  Boxes that leave most of a column's
+// threads idle take a thread per cell instead (thin_box).  Tiles of 64x8, 32x16, 64x4 and 64x16
 // took 0 to 14 % longer.  Whole field step, us, with each tap of the boxes below 1024 columns read
 // through the caches and now: 256^3 5750 and 4510, 128^3 1520 and 608, 128x32x32 260 and 98,
 // 512x256x1 243 and 107, 64x32x32 222 and 70.

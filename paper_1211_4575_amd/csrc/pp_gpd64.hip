@@ -1,10 +1,13 @@
 // FP64 form of steps 1-3 (Sec. III): absolute FP64 positions and momenta.
 //
-// Two kernels.  k_gpd64_tile takes the particles as the sort left them, binned by cell: a
-// workgroup per tile of 64 cells with the tile's fields and current in LDS.  k_gpd64 takes them
-// in any order (pushed again without a sort), one thread per particle, fields read from and
-// current added to global memory; the tile kernel sends it the rare particle that does not lie
-// in its tile.
+// k_gpd64_tile takes the particles as the sort left them, binned by cell: a workgroup per tile of
+// 64 cells with the tile's fields and current in LDS, and more workgroups for the tiles that hold
+// far more particles than the mean.  In large boxes of few particles k_gpd64_sparse first lists the
+// tiles that are worth a workgroup.  A particle that does not lie in its tile (its position written
+// between the sort and the push) is taken by the lane that finds it.  Where a caller has had the
+// arrays, so that there may be many, those are left to k_gpd64_deferred, and so are the particles of
+// the tiles not listed.  k_gpd64 takes particles in any order (pushed again without a sort).  Both
+// have one thread per particle, read the fields from and add the current to global memory.
 #include "pp_device.hpp"
 #include "pp_internal.hpp"
 
@@ -746,8 +749,9 @@ __global__ void __launch_bounds__(256) k_gpd64_sparse(Gpd64TileArgs A) {
 
 // Steps 1-3 of the particles that the tile kernel left out, as k_gpd64, and the bins they go to: those
 // that do not lie in their tile where pp_get_particles has handed out the positions since the sort, so
-// that there may be many, and those of a sparse box's tiles of a few particles.  (The tile kernel takes a stray one itself, with its loops over nodes rolled
-// up, which holds up a wavefront for 0.3 ms.)  A workgroup packs what it finds in DEFER_BLOCK slots.
+// that there may be many, and those of a sparse box's tiles of a few particles.  (The tile kernel takes
+// a stray one itself, with its loops over nodes rolled up, which holds up a wavefront for 0.3 ms.)  All
+// species in one launch; a workgroup packs what it finds in DEFER_BLOCK slots.
 // 64x16x16, 5e5 particles, cubic, 1 % of them moved elsewhere by the caller: 1.56 ms -> 0.31 for both
 // kernels, 4.0 by k_gpd64 for all; 16^3, 3e4: 0.35 -> 0.15 and 0.28.  All of them moved: 4.3, 4.2 by k_gpd64.
 constexpr int DEFER_BLOCK = 256;

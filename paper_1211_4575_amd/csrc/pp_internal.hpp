@@ -203,10 +203,10 @@ hipError_t launch_field_step(pp_run* r);
 // blocks of one launch of this run's field step, in a batch of nruns
 int64_t field_blocks(const pp_run* r, int nruns);
 bool field_by_cells(const pp_run* r);  // its field step takes a thread per cell
-// Sort species s (-1: all): FP64 form, counting sort by cell; split form, the tile order (pairs
-// of ranks in chunks of 64) per tile, from the particle kernel's counts and ranks when it has
-// run since the last sort (all such species together), otherwise (first sort, arbitrary order)
-// by bucketing and a per-tile rebuild.
+// Sort species s (-1: all): FP64 form, by cell; split form, the tile order (pairs of ranks in
+// chunks of 64) per tile.  From the particle kernel's counts and ranks when it has run since the
+// last sort (all such species together), otherwise (first sort, arbitrary order) by a counting sort
+// (FP64 form) or by bucketing and a per-tile rebuild (split form).
 hipError_t launch_sort(pp_run* r, int s);
 hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t st);
 // FP64 form: forget the push's counts and ranks of species s, so that the next sort counts the

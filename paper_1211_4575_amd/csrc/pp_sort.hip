@@ -3,7 +3,8 @@
 //
 // FP64 form: particles in cell order, the cells tile by tile (order inside a cell unspecified).
 // After a push by tiles the particle kernel has counted and ranked the particles of every new
-// cell (ranked sort, as for the split form); otherwise a counting sort by tile-major cell key
+// cell (ranked sort, as for the split form) or, of those far from their tile, named the cell;
+// otherwise a counting sort by tile-major cell key
 // (histogram -> exclusive scan -> scatter with atomic cursors).
 //
 // Split form: particles are laid out tile by tile (64 cells).  Every particle has a rank r
@@ -400,7 +401,7 @@ __global__ void __launch_bounds__(256) k_tile_reorder(ReorderArgs<T> A) {
     tile_reorder_tile(A, blockIdx.x);
 }
 
-// ---- ranked sort (split form, after a push) ---------------------------------------------
+// ---- ranked sort (after a push) ---------------------------------------------------------
 // The particle kernel left, for each species, the number of particles of each cell at the new
 // positions (cnt), and a rank word per particle:
 //   slot << 20 | r   the r-th of its tile's particles bound for destination cell `slot` of the
@@ -411,9 +412,9 @@ __global__ void __launch_bounds__(256) k_tile_reorder(ReorderArgs<T> A) {
 // goes inside its tile is in the tile's round table (pair_slot).  Ranks of SORT_RCAP and beyond
 // go to an overflow tail of the tile (order there unspecified).
 //
-// Three launches over every species: the round tables, a scan of the tile totals (which also
-// finds the largest tile; an atomic maximum per tile on one address had cost 20 us for 2048
-// tiles) and the permutation.  In small boxes their latency counts, in large ones the
+// Three launches over every species (four past SORT_SCAN_ONE tiles): the round tables, a scan of the
+// tile totals (which also finds the largest tile; an atomic maximum per tile on one address had cost
+// 20 us for 2048 tiles) and the permutation.  In small boxes their latency counts, in large ones the
 // permutation's bytes: a rank word read and an entry written per particle, the entries of
 // particles that change tile one by one into partial lines.  us per step, before (five to seven
 // launches a species, cell and completed rank read back, a cleared permutation) and now: 2 x
