@@ -322,7 +322,7 @@ pp_status pp_batch_destroy(pp_batch* batch);
  *    has to start at zero.  Calls that overlap on one GPU (batches stepped from two threads,
  *    or on two streams whose work overlaps) race on it and must be serialised by the caller.
  *  - PP_E_CAPACITY, with nothing enqueued and a message in pp_last_hip_error, when the
- *    members' tables need more than PP_BATCH_NOALLOC_TABLE_BYTES (about 5 KiB per member run
+ *    members' tables need more than PP_BATCH_NOALLOC_TABLE_BYTES (about 3.4 KiB per member run
  *    with two species); PP_E_STATE if the batch's GPU has no static array; otherwise the
  *    statuses of pp_batch_step.
  *  - The batch must be stepped on the GPU that was current at pp_batch_create. */
