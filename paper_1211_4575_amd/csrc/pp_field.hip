@@ -13,10 +13,14 @@ namespace pp {
 // (a row of nx cells, padded to a power of two, several rows per block) or, for nx > 256, a
 // 256-cell chunk of one row; the remaining indices j, k come from the row number.  All
 // indices are 32-bit (a box has at most 2^30 cells).
-struct CellGeom {
+struct FieldGeom {
     int n[3];
-    int xchunks;     // 256-cell chunks per row (nx > 256), else 1
+    int M;           // half-width of the first-derivative stencil (order / 2)
     int64_t nc;
+    double a[3][3];  // a[axis][m-1] / d[axis]: first-derivative coefficients
+    double L[3][11]; // Laplacian stencil per axis, offsets -R..R
+    int R;           // Laplacian half-width 2M - 1
+    int xchunks;     // 256-cell chunks per row (nx > 256), else 1
     int xbits;       // log2 of the padded row length inside a block (<= 8)
     int rows;        // ny * nz
     int rpb;         // rows per block
@@ -24,11 +28,17 @@ struct CellGeom {
     double inv_ny;   // 1 / ny (row -> j, k)
 };
 
-struct FieldGeom : CellGeom {
-    int M;           // half-width of the first-derivative stencil (order / 2)
-    int R;           // Laplacian half-width 2M - 1
-    double a[3][3];  // a[axis][m-1] / d[axis]: first-derivative coefficients
-    double L[3][11]; // Laplacian stencil per axis, offsets -R..R
+// the same without the stencils
+struct CellGeom {
+    int n[3];
+    int small;
+    int64_t nc;
+    int xchunks, xbits, rows, rpb;
+    double inv_ny;
+    CellGeom() = default;
+    explicit CellGeom(const FieldGeom& G)
+        : n{G.n[0], G.n[1], G.n[2]}, small(G.small), nc(G.nc), xchunks(G.xchunks), xbits(G.xbits), rows(G.rows),
+          rpb(G.rpb), inv_ny(G.inv_ny) {}
 };
 
 constexpr int FIELD_BS = 256;
@@ -44,7 +54,8 @@ __device__ __forceinline__ int nbw(int i, int o, int n, int small) {
 }
 
 // cell of thread t in block b of a run's launch; false for padding threads
-__device__ __forceinline__ bool field_cell(const CellGeom& G, int64_t b, int t, int& i, int& j, int& k) {
+template <class GEOM>
+__device__ __forceinline__ bool field_cell(const GEOM& G, int64_t b, int t, int& i, int& j, int& k) {
     const int xc = (int)(b % G.xchunks);
     const int64_t rb = b / G.xchunks;
     i = xc * FIELD_BS + (t & ((1 << G.xbits) - 1));
@@ -62,7 +73,8 @@ __device__ __forceinline__ bool field_cell(const CellGeom& G, int64_t b, int t, 
     return true;
 }
 
-__device__ __forceinline__ int lin(const CellGeom& G, int i, int j, int k) { return i + G.n[0] * (j + G.n[1] * k); }
+template <class GEOM>
+__device__ __forceinline__ int lin(const GEOM& G, int i, int j, int k) { return i + G.n[0] * (j + G.n[1] * k); }
 
 // up-shifted derivative along axis ax of f (values on integer nodes along ax) at cell (i,j,k):
 // sum_m a_m (f[i+m] - f[i-m+1]) / d
@@ -880,7 +892,8 @@ static FieldGeom make_geom(const pp_run* r) {
     return G;
 }
 
-static int64_t blocks_of(const CellGeom& G) { return (int64_t)G.xchunks * ((G.rows + G.rpb - 1) / G.rpb); }
+template <class GEOM>
+static int64_t blocks_of(const GEOM& G) { return (int64_t)G.xchunks * ((G.rows + G.rpb - 1) / G.rpb); }
 
 bool field_by_cells(const pp_run* r) { return thin_box(r->p.n, r->p.field_order); }
 
@@ -1433,7 +1446,7 @@ bool line_reads_fixed(const pp_run* r) {
 }
 
 void line_desc(const pp_run* r, LineArgs* A, int nruns) {
-    A->G = make_geom(r);
+    A->G = CellGeom(make_geom(r));
     for (int d = 0; d < 3; ++d) {
         A->coef[d] = r->line[d].coef;
         A->len[d] = r->line[d].len;
